@@ -443,10 +443,22 @@ int lbm_init(const lbm_config* cfg, const lbm_buffers* bufs, lbm_ctx** out)
     }
     c->geom.stride = sz.cell_stride;
     c->geom.ncell = (uint32_t)sz.ncell;
+    for (int a = 0; a < 2; ++a) {
+        // m = ceil(2^(31 + s) / d) with 2^s >= d, s >= 1 for d > 1: m d exceeds
+        // 2^(31 + s) by less than d <= 2^s, so (n m) >> (31 + s) is n / d for
+        // every n < 2^31, and m < 2^32
+        uint32_t s = 0;
+        while (((uint64_t)1 << s) < (uint64_t)dims[a]) ++s;
+        const uint64_t one = (uint64_t)1 << (31 + s);
+        c->geom.div_m[a] = (uint32_t)((one + (uint64_t)dims[a] - 1) / (uint64_t)dims[a]);
+        c->geom.div_s[a] = 31 + s;
+    }
     Phys& ph = c->phys;
     ph.tau = cfg->tau;
     ph.omega = 1.0 / cfg->tau;
     ph.omegaf = (float)ph.omega;
+    ph.go = cfg->tau - 0.5;
+    ph.gof = (float)ph.go;
     ph.rho0 = cfg->rho0;
     for (int a = 0; a < 3; ++a) {
         ph.F[a] = cfg->body_force[a];

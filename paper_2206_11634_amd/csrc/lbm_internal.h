@@ -121,14 +121,16 @@ struct Geom {
     int per[3];
     int64_t stride;   // elements between population planes
     uint32_t ncell;
+    uint32_t div_m[2], div_s[2];  // n / n[a] = (n * div_m) >> div_s for a = 0, 1, n < 2^31
 };
 
 // Physical constants for one launch.
 struct Phys {
     double tau, omega;     // omega = 1/tau
+    double go;             // 1/omega - 1/2
     double F[3];           // body-force density
     double rho0;
-    float omegaf;
+    float omegaf, gof;
     float Ff[3];
     float scale, inv_scale;  // FP16 deviation scale
     int neq_split;           // VIBB: fneq(x_d) = fneq(x_f) for q > 1/2 (treatment bit 8)

@@ -27,6 +27,10 @@ struct St<LBM_STORE_F64> {
     static constexpr bool dev = false;
     static __device__ __forceinline__ double ld(const double* p, float) { return *p; }
     static __device__ __forceinline__ void st(double* p, double v, float) { *p = v; }
+    // as stored, without the scale of half deviations
+    static __device__ __forceinline__ double raw(const double* p) { return *p; }
+    static __device__ __forceinline__ void put(double* p, double v) { *p = v; }
+    static constexpr bool scaled = false;
     static __device__ __forceinline__ void st_mom(M* p, double d, double x, double y, double z, float)
     {
         *p = Mom64{d, x, y, z};
@@ -46,6 +50,9 @@ struct St<LBM_STORE_F32> {
     static constexpr bool dev = true;
     static __device__ __forceinline__ float ld(const float* p, float) { return *p; }
     static __device__ __forceinline__ void st(float* p, float v, float) { *p = v; }
+    static __device__ __forceinline__ float raw(const float* p) { return *p; }
+    static __device__ __forceinline__ void put(float* p, float v) { *p = v; }
+    static constexpr bool scaled = false;
     static __device__ __forceinline__ void st_mom(M* p, float d, float x, float y, float z, float)
     {
         *p = make_float4(d, x, y, z);
@@ -71,6 +78,9 @@ struct St<LBM_STORE_F16> {
     {
         *p = __float2half_rn(v * sc);
     }
+    static __device__ __forceinline__ float raw(const __half* p) { return __half2float(*p); }
+    static __device__ __forceinline__ void put(__half* p, float v) { *p = __float2half_rn(v); }
+    static constexpr bool scaled = true;
     static __device__ __forceinline__ void st_mom(M* p, float d, float x, float y, float z, float sc)
     {
         Mom16 m;
@@ -137,22 +147,115 @@ __device__ __forceinline__ void moments(const A* v, A shift, const A* F, A& drho
     uz = (jz + shift * F[2]) * ir;
 }
 
+// e_i . (x, y, z) for a direction known at compile time (after unrolling): the
+// zero components take no part, since 0 * x may not be dropped by the compiler.
+template <class A>
+__device__ __forceinline__ A edot(int i, A x, A y, A z)
+{
+    A r = A(0);
+    bool any = false;
+    if (cx(i)) {
+        r = cx(i) > 0 ? x : -x;
+        any = true;
+    }
+    if (cy(i)) {
+        const A t = cy(i) > 0 ? y : -y;
+        r = any ? r + t : t;
+        any = true;
+    }
+    if (cz(i)) {
+        const A t = cz(i) > 0 ? z : -z;
+        r = any ? r + t : t;
+    }
+    return r;
+}
+
 // BGK collision with Guo forcing, in place:
 //   f+ = f + omega (feq - f) + (1 - omega/2) w [3 (e - u) + 9 (e.u) e].F
-template <bool DEV, class A>
-__device__ __forceinline__ void collide(A* v, A omega, const A* F, A& drho, A& ux, A& uy, A& uz)
+//      = f + omega (w X - f)
+// over the opposite pairs (i, i + 1), e_{i+1} = -e_i.  With go = 1/omega - 1/2,
+// g = rho u + go F and h = rho u + 2 go F,
+//   X = drho - 3/2 rho u.u - 3 go u.F + 9/2 (e.u)(e.h) + 3 (e.g)
+// (rho in place of drho for plain populations), of which only the last term
+// changes its sign within a pair: about 145 multiply-adds a node.  (A sum per
+// direction with the products by zero components, which the compiler may not
+// drop, took the FP32 kernel to 687 vector instructions a wave instead of
+// about 200.)  The error of f+ against 64 bits is 1.1e-7 in FP32 deviations
+// where the sum per direction had 1.4e-7.
+// With SCALED the populations come and go multiplied by `scale` (half
+// deviations as stored): the moments are unscaled and the node's few common
+// factors scaled, instead of every population twice.
+template <bool DEV, class A, bool SCALED = false>
+__device__ __forceinline__ void collide(A* v, A omega, A go, const A* F, A& drho, A& ux, A& uy,
+                                        A& uz, A inv = A(1), A scale = A(1))
 {
-    A rho;
-    moments<DEV, A>(v, A(0.5), F, drho, rho, ux, uy, uz);
-    const A uF = ux * F[0] + uy * F[1] + uz * F[2];
-    const A gf = A(1) - A(0.5) * omega;
+    // (directions 1 to 6 are the axes)
+    A s = v[0] + ((v[1] + v[2]) + (v[3] + v[4]) + (v[5] + v[6]));
+    A jx = v[1] - v[2], jy = v[3] - v[4], jz = v[5] - v[6];
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-        const A eu = A(cx(i)) * ux + A(cy(i)) * uy + A(cz(i)) * uz;
-        const A eF = A(cx(i)) * F[0] + A(cy(i)) * F[1] + A(cz(i)) * F[2];
-        const A src = gf * W<A>(i) * (A(3) * (eF - uF) + A(9) * eu * eF);
-        v[i] = v[i] + omega * (eq_i<DEV, A>(i, drho, rho, ux, uy, uz) - v[i]) + src;
+    for (int i = 7; i < kQ; i += 2) {
+        s += v[i] + v[i + 1];
+        const A m = v[i] - v[i + 1];
+        if (cx(i)) jx = cx(i) > 0 ? jx + m : jx - m;
+        if (cy(i)) jy = cy(i) > 0 ? jy + m : jy - m;
+        if (cz(i)) jz = cz(i) > 0 ? jz + m : jz - m;
     }
+    if constexpr (SCALED) {
+        s *= inv;
+        jx *= inv;
+        jy *= inv;
+        jz *= inv;
+    }
+    A rho;
+    if constexpr (DEV) {
+        drho = s;
+        rho = A(1) + s;
+    } else {
+        rho = s;
+        drho = s - A(1);
+    }
+    const A ir = A(1) / rho;
+    ux = (jx + A(0.5) * F[0]) * ir;
+    uy = (jy + A(0.5) * F[1]) * ir;
+    uz = (jz + A(0.5) * F[2]) * ir;
+    const A go2 = go + go;
+    A gx = rho * ux + go * F[0], gy = rho * uy + go * F[1], gz = rho * uz + go * F[2];
+    A hx = rho * ux + go2 * F[0], hy = rho * uy + go2 * F[1], hz = rho * uz + go2 * F[2];
+    const A uu = ux * ux + uy * uy + uz * uz;
+    const A uF = ux * F[0] + uy * F[1] + uz * F[2];
+    A c = (DEV ? drho : rho) - (A(1.5) * rho * uu + A(3) * go * uF);
+    if constexpr (SCALED) {
+        c *= scale;
+        gx *= scale;
+        gy *= scale;
+        gz *= scale;
+        hx *= scale;
+        hy *= scale;
+        hz *= scale;
+    }
+    v[0] += omega * (W<A>(0) * c - v[0]);
+#pragma unroll
+    for (int i = 1; i < kQ; i += 2) {
+        const A eu = edot(i, ux, uy, uz), eg = edot(i, gx, gy, gz), eh = edot(i, hx, hy, hz);
+        const A even = (A(4.5) * eu) * eh + c;
+        v[i] += omega * (W<A>(i) * (A(3) * eg + even) - v[i]);
+        v[i + 1] += omega * (W<A>(i) * (A(-3) * eg + even) - v[i + 1]);
+    }
+}
+
+// Coordinates of a node from its index: division by the invariant nx and ny
+// as a multiplication and a shift (exact for indices below 2^31).
+__device__ __forceinline__ uint32_t fdiv(uint32_t n, uint32_t m, uint32_t sh)
+{
+    return (uint32_t)(((uint64_t)n * m) >> sh);
+}
+__device__ __forceinline__ void node_xyz(uint32_t node, const Geom& g, uint32_t& x, uint32_t& y,
+                                         uint32_t& z)
+{
+    const uint32_t yz = fdiv(node, g.div_m[0], g.div_s[0]);
+    x = node - yz * (uint32_t)g.n[0];
+    z = fdiv(yz, g.div_m[1], g.div_s[1]);
+    y = yz - z * (uint32_t)g.n[1];
 }
 
 // Offsets of (c-1, c, c+1) along one axis and whether each lies in the domain.
@@ -174,6 +277,96 @@ __device__ __forceinline__ void axis3(uint32_t c, uint32_t n, int per, uint32_t 
     } else {
         o[2] = 0;
         v[2] = per != 0;
+    }
+}
+
+// The pre-collision populations of node first + threadIdx.x (first: the
+// workgroup's first node, the same for all its threads), pulled from x - e_i;
+// beyond a wall the node's own opposite population (static halfway
+// bounce-back).  Every thread of a wave calls it; `on`: the node wants them.
+//
+// A wave whose nodes all lie off the y and z faces takes its sources at
+// offsets that are the same for every lane: the plane, the shift by e_y and
+// e_z and the workgroup's first node go into the scalar base address, and
+// three vector offsets (x - 1, x, x + 1, wrapped within the row) serve all
+// directions, so a load costs no vector arithmetic.  Lanes at an x wall load
+// their five (D3Q19) opposite populations again.  Waves that touch a y or z
+// face (3% of them at 128^3, 1% at 512^3) form each lane's address.  Half
+// deviations keep their scale.
+template <int S>
+__device__ __forceinline__ void pull_node(const typename St<S>::T* __restrict__ src, const Geom& g,
+                                          uint32_t first, bool on, typename St<S>::A f[kQ])
+{
+    using T = typename St<S>::T;
+    constexpr uint32_t es = sizeof(T);
+    const uint32_t cell = first + threadIdx.x;
+    const uint32_t nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    uint32_t x, y, z;
+    node_xyz(cell, g, x, y, z);
+    const bool face = y == 0u || y + 1u >= ny || z == 0u || z + 1u >= nz;
+    if (!__any(on && face)) {
+        if (!on) return;
+        const uint32_t t = threadIdx.x;
+        // byte offsets from `nx` nodes before the workgroup's first
+        const uint32_t o0 = (t + nx) * es;
+        const uint32_t om = x > 0u ? o0 - es : (t + 2u * nx - 1u) * es;
+        const uint32_t op = x + 1u < nx ? o0 + es : (t + 1u) * es;
+        const T* b0 = src + ((int64_t)first - (int64_t)nx);
+#pragma unroll
+        for (int i = 0; i < kQ; ++i) {
+            const int64_t shift = (int64_t)cy(i) * nx + (int64_t)cz(i) * ((int64_t)nx * ny);
+            const char* b = reinterpret_cast<const char*>(b0 + ((int64_t)i * g.stride - shift));
+            const uint32_t o = cx(i) > 0 ? om : (cx(i) < 0 ? op : o0);
+            f[i] = St<S>::raw(reinterpret_cast<const T*>(b + o));
+        }
+        if (!g.per[0]) {
+            auto own = [&](int i) {
+                const char* b = reinterpret_cast<const char*>(b0 + (int64_t)opp(i) * g.stride);
+                return St<S>::raw(reinterpret_cast<const T*>(b + o0));
+            };
+            if (x == 0u) {
+#pragma unroll
+                for (int i = 1; i < kQ; ++i)
+                    if (cx(i) > 0) f[i] = own(i);
+            }
+            if (x + 1u == nx) {
+#pragma unroll
+                for (int i = 1; i < kQ; ++i)
+                    if (cx(i) < 0) f[i] = own(i);
+            }
+        }
+        return;
+    }
+    if (!on) return;
+    uint32_t ox[3], oy[3], oz[3];
+    bool vx[3], vy[3], vz[3];
+    axis3(x, nx, g.per[0], 1u, ox, vx);
+    axis3(y, ny, g.per[1], nx, oy, vy);
+    axis3(z, nz, g.per[2], nx * ny, oz, vz);
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) {
+        const int sx = 1 - cx(i), sy = 1 - cy(i), sz = 1 - cz(i);
+        const bool ok = vx[sx] && vy[sy] && vz[sz];
+        const int64_t at = ok ? (int64_t)i * g.stride + (ox[sx] + oy[sy] + oz[sz])
+                              : (int64_t)opp(i) * g.stride + cell;
+        f[i] = St<S>::raw(src + at);
+    }
+}
+
+// The populations of node first + threadIdx.x into every plane of dst (a
+// scalar base address and one vector offset for all planes); half deviations
+// come scaled.
+template <int S>
+__device__ __forceinline__ void store_node(typename St<S>::T* __restrict__ dst, const Geom& g,
+                                           uint32_t first, const typename St<S>::A f[kQ])
+{
+    using T = typename St<S>::T;
+    const uint32_t o = threadIdx.x * (uint32_t)sizeof(T);
+    T* b0 = dst + first;
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) {
+        char* b = reinterpret_cast<char*>(b0 + (int64_t)i * g.stride);
+        St<S>::put(reinterpret_cast<T*>(b + o), f[i]);
     }
 }
 

@@ -43,7 +43,12 @@ __device__ __forceinline__ uint32_t xcd_block()
 }
 
 // ---------------------------------------------------------------------------
-// Bulk: one thread per node, pull f_i(x - e_i), collide, store.
+// Bulk: one thread per node, pull f_i(x - e_i), collide, store.  Bound by HBM:
+// FP32 3.70-3.76 ms on 512^3 (153 + 16 B a node, 6.1 TB/s, the rate of a copy),
+// FP64 7.4 ms, FP32 D3Q15 3.0 ms; small lattices by the latency of the flag and
+// population loads (48x40x44: 4.8 us FP32, 7.2 us FP64).  With an address per
+// lane and direction (687 vector instructions a wave instead of about 200; FP64
+// 112 registers instead of 88) 3.83, 7.5, 3.0-3.3 ms, 5.5 and 7.7 us.
 // ---------------------------------------------------------------------------
 template <int S>
 __global__ __launch_bounds__(256) void k_stream_collide(const typename St<S>::T* __restrict__ src,
@@ -54,157 +59,157 @@ __global__ __launch_bounds__(256) void k_stream_collide(const typename St<S>::T*
 {
     using A = typename St<S>::A;
     constexpr bool DEV = St<S>::dev;
-    const uint32_t cell = xcd_block() * 256u + threadIdx.x;
+    const uint32_t first = xcd_block() * 256u;
+    const uint32_t cell = first + threadIdx.x;
     if (cell >= g.ncell) return;
-    if (flag[cell]) {
-        // A solid node's slots are only ever read as link ghosts, which the
-        // boundary kernel writes before they are pulled.  Storing the rest
-        // state keeps every cache line of the wave fully written (partially
-        // written lines cost far more HBM time than the bytes saved) and keeps
-        // stale values from evolving inside the bodies.
-        const A rest = DEV ? A(0) : A(1);
-#pragma unroll
-        for (int i = 0; i < kQ; ++i)
-            St<S>::st(dst + (int64_t)i * g.stride + cell, DEV ? A(0) : A(wgt(i)) * rest, ph.scale);
-        St<S>::st_mom(mom + cell, A(0), A(0), A(0), A(0), ph.scale);
-        return;
-    }
-    const uint32_t nx = g.n[0], ny = g.n[1];
-    const uint32_t x = cell % nx, yz = cell / nx, y = yz % ny, z = yz / ny;
-    uint32_t ox[3], oy[3], oz[3];
-    bool vx[3], vy[3], vz[3];
-    axis3(x, nx, g.per[0], 1u, ox, vx);
-    axis3(y, ny, g.per[1], nx, oy, vy);
-    axis3(z, g.n[2], g.per[2], nx * ny, oz, vz);
+    const bool fluid = flag[cell] == 0;
+    // A solid node's slots are only ever read as link ghosts, which the
+    // boundary kernel writes before they are pulled.  Storing the rest state
+    // keeps every cache line of the wave fully written (partially written
+    // lines cost far more HBM time than the bytes saved) and keeps stale
+    // values from evolving inside the bodies.  Fluid and solid lanes of a wave
+    // share the stores below.
     A f[kQ];
+    A drho = A(0), ux = A(0), uy = A(0), uz = A(0);
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-        const int sx = 1 - cx(i), sy = 1 - cy(i), sz = 1 - cz(i);
-        const bool ok = vx[sx] && vy[sy] && vz[sz];
-        // a source beyond a wall: static halfway bounce-back, f_i = f+_opp(i)(x)
-        const uint32_t s = ok ? ox[sx] + oy[sy] + oz[sz] : cell;
-        const int64_t plane = ok ? i : opp(i);
-        f[i] = St<S>::ld(src + plane * g.stride + s, ph.inv_scale);
+    for (int i = 0; i < kQ; ++i) f[i] = DEV ? A(0) : W<A>(i);
+    if (__any(fluid)) {
+        pull_node<S>(src, g, first, fluid, f);
+        if (fluid) {
+            A F[3];
+            A om, go;
+            if constexpr (DEV) {
+                F[0] = ph.Ff[0], F[1] = ph.Ff[1], F[2] = ph.Ff[2];
+                om = ph.omegaf, go = ph.gof;
+            } else {
+                F[0] = ph.F[0], F[1] = ph.F[1], F[2] = ph.F[2];
+                om = ph.omega, go = ph.go;
+            }
+            collide<DEV, A, St<S>::scaled>(f, om, go, F, drho, ux, uy, uz, A(ph.inv_scale), A(ph.scale));
+        }
     }
-    A F[3];
-    A om;
-    if constexpr (DEV) {
-        F[0] = ph.Ff[0], F[1] = ph.Ff[1], F[2] = ph.Ff[2];
-        om = ph.omegaf;
-    } else {
-        F[0] = ph.F[0], F[1] = ph.F[1], F[2] = ph.F[2];
-        om = ph.omega;
-    }
-    A drho, ux, uy, uz;
-    collide<DEV, A>(f, om, F, drho, ux, uy, uz);
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) St<S>::st(dst + (int64_t)i * g.stride + cell, f[i], ph.scale);
+    store_node<S>(dst, g, first, f);
     St<S>::st_mom(mom + cell, drho, ux, uy, uz, ph.scale);
 }
 
 // FP16 deviation storage, two x-neighbouring nodes per thread: the stores
 // and the pulls along directions with e_x = 0 move a pair of values per lane
 // (half2) instead of one.  Pulls with e_x != 0 start at an odd node and
-// are loaded per node.  The arithmetic per node is that of k_stream_collide,
-// bit for bit.  Requires an even nx (pairs never straddle a row).
-template <int S>
-struct Pair;
-template <>
-struct Pair<LBM_STORE_F16> {
-    using T = __half;
-    static __device__ __forceinline__ void ld2(const __half* p, float inv, float& a, float& b)
-    {
-        const float2 v = __half22float2(*reinterpret_cast<const __half2*>(p));
-        a = v.x * inv;
-        b = v.y * inv;
-    }
-    static __device__ __forceinline__ void st2(__half* p, float a, float b, float sc)
-    {
-        *reinterpret_cast<__half2*>(p) = __floats2half2_rn(a * sc, b * sc);
-    }
-    static __device__ __forceinline__ void st_mom2(Mom16* p, const float m0[4], const float m1[4],
-                                                   float sc)
-    {
-        struct alignas(16) M2 {
-            Mom16 a, b;
-        } m;
-        m.a.a = __floats2half2_rn(m0[0] * sc, m0[1] * sc);
-        m.a.b = __floats2half2_rn(m0[2] * sc, m0[3] * sc);
-        m.b.a = __floats2half2_rn(m1[0] * sc, m1[1] * sc);
-        m.b.b = __floats2half2_rn(m1[2] * sc, m1[3] * sc);
-        *reinterpret_cast<M2*>(p) = m;
-    }
-};
-// (a bound of six waves per SIMD: 78 registers instead of 96 and five waves,
-// 3% faster on 512^3; dword loads of the shifted pairs at 2-byte aligned
-// addresses instead of two 2-byte loads ran 30% slower and are not used)
-template <int S>
-__global__ __launch_bounds__(256, 6) void k_stream_collide_x2(const typename St<S>::T* __restrict__ src,
-                                                           typename St<S>::T* __restrict__ dst,
-                                                           typename St<S>::M* __restrict__ mom,
-                                                           const uint8_t* __restrict__ flag,
-                                                           Geom g, Phys ph)
+// are loaded per node.  The arithmetic per node is that of k_stream_collide.
+// Requires an even nx (pairs never straddle a row).  Addresses as pull_node's:
+// the wave's common offset in the scalar base, three vector offsets.  Bound by
+// HBM: 2.10 ms on 512^3 (77 + 8 B a node, 5.4 TB/s), 28.5 us on 128^3; with an
+// address per lane and direction and a sum per direction in the collision
+// (1345 vector instructions a wave) 2.31 ms and 35 us.
+__device__ __forceinline__ void pull_pair(const __half* __restrict__ src, const Geom& g,
+                                          uint32_t first, bool on, float f0[kQ], float f1[kQ])
 {
-    using P2 = Pair<S>;
-    const uint32_t pair = xcd_block() * 256u + threadIdx.x;
-    const uint32_t cell = 2u * pair;
-    if (cell >= g.ncell) return;
-    const uint16_t fl = *reinterpret_cast<const uint16_t*>(flag + cell);
-    const bool solid0 = (fl & 0xFFu) != 0, solid1 = (fl >> 8) != 0;
-    const float zero4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (solid0 && solid1) {
+    const uint32_t t2 = 2u * threadIdx.x, cell = first + t2;
+    const uint32_t nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    uint32_t x, y, z;
+    node_xyz(cell, g, x, y, z);
+    const bool face = y == 0u || y + 1u >= ny || z == 0u || z + 1u >= nz;
+    const bool slow = __any(on && face);  // uniform over the wave
+    if (!on) return;
+    auto both = [](const void* p) { return __half22float2(*static_cast<const __half2*>(p)); };
+    auto one = [](const void* p) { return __half2float(*static_cast<const __half*>(p)); };
+    if (!slow) {
+        const uint32_t o0 = (t2 + nx) * 2u;
+        const uint32_t om = x > 0u ? o0 - 2u : (t2 + 2u * nx - 1u) * 2u;
+        const uint32_t op = x + 2u < nx ? o0 + 4u : (t2 + 2u) * 2u;
+        const __half* b0 = src + ((int64_t)first - (int64_t)nx);
+        const bool wall0 = !g.per[0] && x == 0u, wall1 = !g.per[0] && x + 2u == nx;
 #pragma unroll
-        for (int i = 0; i < kQ; ++i) P2::st2(dst + (int64_t)i * g.stride + cell, 0.0f, 0.0f, ph.scale);
-        P2::st_mom2(mom + cell, zero4, zero4, ph.scale);
+        for (int i = 0; i < kQ; ++i) {
+            const int64_t shift = (int64_t)cy(i) * nx + (int64_t)cz(i) * ((int64_t)nx * ny);
+            const char* b = reinterpret_cast<const char*>(b0 + ((int64_t)i * g.stride - shift));
+            if (cx(i) == 0) {
+                const float2 v = both(b + o0);
+                f0[i] = v.x;
+                f1[i] = v.y;
+            } else if (cx(i) > 0) {
+                f0[i] = one(wall0 ? reinterpret_cast<const char*>(b0 + (int64_t)opp(i) * g.stride) + o0
+                                  : b + om);
+                f1[i] = one(b + o0);
+            } else {
+                f0[i] = one(b + o0 + 2);
+                f1[i] = one(wall1 ? reinterpret_cast<const char*>(b0 + (int64_t)opp(i) * g.stride) + o0 + 2
+                                  : b + op);
+            }
+        }
         return;
     }
-    const uint32_t nx = g.n[0], ny = g.n[1];
-    const uint32_t x = cell % nx, yz = cell / nx, y = yz % ny, z = yz / ny;
     uint32_t ox0[3], ox1[3], oy[3], oz[3];
     bool vx0[3], vx1[3], vy[3], vz[3];
     axis3(x, nx, g.per[0], 1u, ox0, vx0);
     axis3(x + 1u, nx, g.per[0], 1u, ox1, vx1);
     axis3(y, ny, g.per[1], nx, oy, vy);
-    axis3(z, g.n[2], g.per[2], nx * ny, oz, vz);
-    float f0[kQ], f1[kQ];
+    axis3(z, nz, g.per[2], nx * ny, oz, vz);
 #pragma unroll
     for (int i = 0; i < kQ; ++i) {
-        const int sy = 1 - cy(i), sz = 1 - cz(i);
+        const int sx = 1 - cx(i), sy = 1 - cy(i), sz = 1 - cz(i);
+        const uint32_t row = oy[sy] + oz[sz];
+        const int64_t pl = (int64_t)i * g.stride, own = (int64_t)opp(i) * g.stride + cell;
         if (cx(i) == 0) {
-            // both sources in one aligned pair: x and x + 1 of the source row,
-            // or, beyond a wall, the nodes' own opposite populations
-            const bool ok = vy[sy] && vz[sz];
-            const uint32_t s = ok ? ox0[1] + oy[sy] + oz[sz] : cell;
-            const int64_t plane = ok ? i : opp(i);
-            P2::ld2(src + plane * g.stride + s, ph.inv_scale, f0[i], f1[i]);
+            const float2 v = both(src + (vy[sy] && vz[sz] ? pl + ox0[1] + row : own));
+            f0[i] = v.x;
+            f1[i] = v.y;
         } else {
-            const int sx = 1 - cx(i);
-            const bool ok0 = vx0[sx] && vy[sy] && vz[sz];
-            const bool ok1 = vx1[sx] && vy[sy] && vz[sz];
-            const uint32_t s0 = ok0 ? ox0[sx] + oy[sy] + oz[sz] : cell;
-            const uint32_t s1 = ok1 ? ox1[sx] + oy[sy] + oz[sz] : cell + 1u;
-            f0[i] = St<S>::ld(src + (int64_t)(ok0 ? i : opp(i)) * g.stride + s0, ph.inv_scale);
-            f1[i] = St<S>::ld(src + (int64_t)(ok1 ? i : opp(i)) * g.stride + s1, ph.inv_scale);
+            f0[i] = one(src + (vx0[sx] && vy[sy] && vz[sz] ? pl + ox0[sx] + row : own));
+            f1[i] = one(src + (vx1[sx] && vy[sy] && vz[sz] ? pl + ox1[sx] + row : own + 1));
         }
     }
-    const float F[3] = {ph.Ff[0], ph.Ff[1], ph.Ff[2]};
-    float m0[4], m1[4];
-    collide<true, float>(f0, ph.omegaf, F, m0[0], m0[1], m0[2], m0[3]);
-    collide<true, float>(f1, ph.omegaf, F, m1[0], m1[1], m1[2], m1[3]);
-    if (solid0) {
-        // rest state, as k_stream_collide stores at solid nodes
+}
+
+__global__ __launch_bounds__(256, 6) void k_stream_collide_x2(const __half* __restrict__ src,
+                                                           __half* __restrict__ dst,
+                                                           Mom16* __restrict__ mom,
+                                                           const uint8_t* __restrict__ flag,
+                                                           Geom g, Phys ph)
+{
+    const uint32_t first = xcd_block() * 512u;
+    const uint32_t cell = first + 2u * threadIdx.x;
+    if (cell >= g.ncell) return;
+    const uint16_t fl = *reinterpret_cast<const uint16_t*>(flag + cell);
+    const bool solid0 = (fl & 0xFFu) != 0, solid1 = (fl >> 8) != 0;
+    float f0[kQ], f1[kQ];
+    float d0 = 0.0f, x0 = 0.0f, y0 = 0.0f, z0 = 0.0f, d1 = 0.0f, x1 = 0.0f, y1 = 0.0f, z1 = 0.0f;
 #pragma unroll
-        for (int i = 0; i < kQ; ++i) f0[i] = 0.0f;
-        m0[0] = m0[1] = m0[2] = m0[3] = 0.0f;
+    for (int i = 0; i < kQ; ++i) f0[i] = f1[i] = 0.0f;
+    const bool on = !(solid0 && solid1);
+    if (__any(on)) {
+        pull_pair(src, g, first, on, f0, f1);
+        const float F[3] = {ph.Ff[0], ph.Ff[1], ph.Ff[2]};
+        // (solid pairs collide the rest state: zeros, or the force's share,
+        // cleared below)
+        collide<true, float, true>(f0, ph.omegaf, ph.gof, F, d0, x0, y0, z0, ph.inv_scale, ph.scale);
+        collide<true, float, true>(f1, ph.omegaf, ph.gof, F, d1, x1, y1, z1, ph.inv_scale, ph.scale);
+        if (solid0) {
+            // rest state, as k_stream_collide stores at solid nodes
+#pragma unroll
+            for (int i = 0; i < kQ; ++i) f0[i] = 0.0f;
+            d0 = x0 = y0 = z0 = 0.0f;
+        }
+        if (solid1) {
+#pragma unroll
+            for (int i = 0; i < kQ; ++i) f1[i] = 0.0f;
+            d1 = x1 = y1 = z1 = 0.0f;
+        }
     }
-    if (solid1) {
+    const uint32_t o = 4u * threadIdx.x;
 #pragma unroll
-        for (int i = 0; i < kQ; ++i) f1[i] = 0.0f;
-        m1[0] = m1[1] = m1[2] = m1[3] = 0.0f;
+    for (int i = 0; i < kQ; ++i) {
+        char* b = reinterpret_cast<char*>(dst + first + (int64_t)i * g.stride);
+        *reinterpret_cast<__half2*>(b + o) = __floats2half2_rn(f0[i], f1[i]);
     }
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) P2::st2(dst + (int64_t)i * g.stride + cell, f0[i], f1[i], ph.scale);
-    P2::st_mom2(mom + cell, m0, m1, ph.scale);
+    struct alignas(16) M2 {
+        Mom16 a, b;
+    } m;
+    m.a.a = __floats2half2_rn(d0 * ph.scale, x0 * ph.scale);
+    m.a.b = __floats2half2_rn(y0 * ph.scale, z0 * ph.scale);
+    m.b.a = __floats2half2_rn(d1 * ph.scale, x1 * ph.scale);
+    m.b.b = __floats2half2_rn(y1 * ph.scale, z1 * ph.scale);
+    *reinterpret_cast<M2*>(mom + cell) = m;
 }
 
 // ---------------------------------------------------------------------------
@@ -472,16 +477,16 @@ __device__ __forceinline__ void refill_node(const typename St<S>::T* __restrict_
         }
     }
     A F[3];
-    A om;
+    A om, go;
     if constexpr (DEV) {
         F[0] = ph.Ff[0], F[1] = ph.Ff[1], F[2] = ph.Ff[2];
-        om = ph.omegaf;
+        om = ph.omegaf, go = ph.gof;
     } else {
         F[0] = ph.F[0], F[1] = ph.F[1], F[2] = ph.F[2];
-        om = ph.omega;
+        om = ph.omega, go = ph.go;
     }
     A drho, ux, uy, uz;
-    collide<DEV, A>(v, om, F, drho, ux, uy, uz);
+    collide<DEV, A>(v, om, go, F, drho, ux, uy, uz);
 #pragma unroll
     for (int i = 0; i < kQ; ++i) St<S>::st(cur + (int64_t)i * g.stride + r.node, v[i], ph.scale);
     St<S>::st_mom(mom + r.node, drho, ux, uy, uz, ph.scale);
@@ -611,7 +616,7 @@ struct RunSC {
             if (c->geom.n[0] % 2 == 0) {
                 uint32_t nb = blocks_for(c->geom.ncell / 2);
                 nb = (nb + 7u) & ~7u;
-                hipLaunchKernelGGL(k_stream_collide_x2<S>, dim3(nb), dim3(256), 0, c->stream,
+                hipLaunchKernelGGL(k_stream_collide_x2, dim3(nb), dim3(256), 0, c->stream,
                                    (const typename St<S>::T*)src, (typename St<S>::T*)dst,
                                    (typename St<S>::M*)c->mom, c->flag, c->geom, c->phys);
                 return hipGetLastError();

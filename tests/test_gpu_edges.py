@@ -1,0 +1,44 @@
+"""Kernels at the sizes where their paths change: edges of waves, rows shorter
+and longer than a wave, single-node axes, walls and periodic faces."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2206_11634_amd import binding as B
+from paper_2206_11634_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+NONE = W.make_particles([], np.zeros((0, 3)), np.zeros((0, 4)), 1.0)
+
+# |f - w| stays below 0.03 and each of the 3 steps rounds about ten times at
+# that size: 3 * 10 * 0.03 * 2^-24 for float, 3 * 0.03 * 2^-11 for half storage
+BULK_TOL = {"f64": 1e-14, "f32": 6e-8, "f16": 5e-5}
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16"])
+@pytest.mark.parametrize("lattice", [19, 15])
+@pytest.mark.parametrize("dims", [(1, 1, 1), (2, 1, 3), (3, 70, 1), (63, 5, 4), (64, 4, 5),
+                                  (65, 3, 7), (62, 6, 5), (130, 4, 6), (256, 3, 4), (20, 20, 4)])
+def test_stream_collide_at_wave_and_row_edges(storage, lattice, dims):
+    """Three steps of random populations against the oracle, for every set of
+    periodic axes (waves off the faces, on them, and mixed; both pulls)."""
+    rng = np.random.default_rng(5)
+    for mask in range(8):
+        per = tuple((mask >> a) & 1 for a in range(3))
+        lat = W.LatticeSpec(*dims, periodic=per, tau=0.62, body_force=(2e-4, -1e-4, 3e-4))
+        gpu, ora = B.Lattice(lat, storage=storage, lattice=lattice), O.Oracle(lat, Q=lattice)
+        parts = B.DeviceParticles(NONE)
+        ora.classify(NONE)
+        _, w, _ = O.stencil(lattice)
+        f = w[:, None] * (1.0 + 0.04 * rng.uniform(-1, 1, (lattice, lat.ncell)))
+        if storage != "f64":   # values the storage holds
+            cut, s = (np.float32, 1.0) if storage == "f32" else (np.float16, 1024.0)
+            f = ((f - w[:, None]) * s).astype(cut).astype(np.float64) / s + w[:, None]
+        gpu.set_populations(f)
+        ora.f[:] = f
+        for _ in range(3):
+            gpu.step(parts)
+            ora.step(NONE)
+        assert np.abs(gpu.populations() - ora.f).max() <= BULK_TOL[storage], per
+        gpu.close()
