@@ -201,13 +201,6 @@ struct GeoArgs {
     double* w_refill = nullptr;     // dJ/domega_p seen by the refill (null: not kept)
 };
 
-__device__ __forceinline__ void dir_of(int d, int e[3])
-{
-    e[0] = cx(d);
-    e[1] = cy(d);
-    e[2] = cz(d);
-}
-
 // Sum n doubles over the block and add them to out[] (one atomic each).
 template <int NV>
 __device__ __forceinline__ void block_add(double (&v)[NV], double* const* out)

@@ -399,6 +399,50 @@ __device__ __forceinline__ uint32_t node_of(const int c[3], const Geom& g)
     return (uint32_t)c[0] + (uint32_t)g.n[0] * ((uint32_t)c[1] + (uint32_t)g.n[1] * (uint32_t)c[2]);
 }
 
+// The equilibrium of a moving direction d known at run time (eu = e_d.u,
+// uu = u.u), in the storage's form as eq_i.
+template <bool DEV, class A>
+__device__ __forceinline__ A eq_moving(A w, A drho, A rho, A eu, A uu)
+{
+    const A poly = A(3) * eu + A(4.5) * eu * eu - A(1.5) * uu;
+    if constexpr (DEV)
+        return w * (drho + rho * poly);
+    else
+        return w * rho * (A(1) + poly);
+}
+
+// Sums of six values over a wave: lane k (k < 6) gets the sum of v[k] over all
+// lanes (lanes 6 and 7 zero).  Each of the first three exchanges halves the number
+// of values a lane carries, so ten exchanges do what 36 would value by value.
+__device__ __forceinline__ double wave_sum6(const double v[6])
+{
+    const int lane = threadIdx.x & 63;
+    double a[4];
+    {
+        // lanes with bit 2 set keep values 4-7
+        const bool up = lane & 4;
+        const double w[8] = {v[0], v[1], v[2], v[3], v[4], v[5], 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double give = up ? w[k] : w[k + 4], keep = up ? w[k + 4] : w[k];
+            a[k] = keep + __shfl_xor(give, 4, 64);
+        }
+    }
+    double b[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const bool up = lane & 2;
+        const double give = up ? a[k] : a[k + 2], keep = up ? a[k + 2] : a[k];
+        b[k] = keep + __shfl_xor(give, 2, 64);
+    }
+    const bool up = lane & 1;
+    double s = (up ? b[1] : b[0]) + __shfl_xor(up ? b[0] : b[1], 1, 64);
+    s += __shfl_xor(s, 8, 64);
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    return s;
+}
+
 __device__ __forceinline__ double dsum_wave(double v)
 {
 #pragma unroll

@@ -18,6 +18,8 @@
 #error "MDLBM_Q must be 19 or 15"
 #endif
 
+#include <cstdint>
+
 namespace mdlbm {
 
 constexpr int kQ = MDLBM_Q;
@@ -75,6 +77,37 @@ __host__ __device__ constexpr float wgtf(int i)
 }
 #endif
 __host__ __device__ constexpr int opp(int i) { return i == 0 ? 0 : ((i & 1) ? i + 1 : i - 1); }
+
+// The components of e_d for a direction known at run time only, from two-bit
+// fields (value + 1): a shift and a mask, where the functions above become a
+// chain of compares.
+struct DirTable {
+    uint64_t x, y, z;
+};
+__host__ __device__ constexpr DirTable dir_table()
+{
+    DirTable t{0, 0, 0};
+    for (int i = 0; i < kQ; ++i) {
+        t.x |= (uint64_t)(cx(i) + 1) << (2 * i);
+        t.y |= (uint64_t)(cy(i) + 1) << (2 * i);
+        t.z |= (uint64_t)(cz(i) + 1) << (2 * i);
+    }
+    return t;
+}
+__host__ __device__ __forceinline__ void dir_of(int d, int e[3])
+{
+    constexpr DirTable t = dir_table();
+    e[0] = (int)((t.x >> (2 * d)) & 3u) - 1;
+    e[1] = (int)((t.y >> (2 * d)) & 3u) - 1;
+    e[2] = (int)((t.z >> (2 * d)) & 3u) - 1;
+}
+// The weight of a moving direction (d >= 1): axes 1-6, then the diagonals.
+template <class A>
+__host__ __device__ __forceinline__ A wgt_moving(int d)
+{
+    return d <= 6 ? A(wgt(1)) : A(wgt(7));
+}
+__host__ __device__ __forceinline__ int opp_moving(int d) { return ((d - 1) ^ 1) + 1; }
 
 // Largest |e_i| of the lattice, rounded up in FP32: sqrt 2 (D3Q19), sqrt 3 (D3Q15).
 constexpr float kMaxSpeedUp = (MDLBM_Q == 19) ? 1.4143f : 1.7321f;

@@ -213,7 +213,13 @@ __global__ __launch_bounds__(256, 6) void k_stream_collide_x2(const __half* __re
 }
 
 // ---------------------------------------------------------------------------
-// Links: one thread per link record of one particle (blockIdx.y).
+// Links: one thread per link record, one workgroup per 256-record chunk.
+// With many bodies bound by the lines its gathers touch (c. 5.7 GB read for
+// 26.4 M links on 512^3: every population line that holds a surface node, once;
+// 1.39 ms whatever the instruction count); with few by one wave's chain of
+// loads and instructions, so directions come from tables and coordinates from
+// multiplications (640 instructions instead of 2450, most of them compares of
+// the run-time direction): 5.6 us for one or two bodies, before 10.
 // ---------------------------------------------------------------------------
 // Exact force sums: a term v becomes the 128-bit two's-complement integer
 // v * 2^80 rounded toward zero (hi: the signed upper word, lo: the lower);
@@ -257,31 +263,35 @@ __global__ __launch_bounds__(256) void k_boundary(typename St<S>::T* __restrict_
     constexpr bool DEV = St<S>::dev;
     // one workgroup per 256-record chunk of the link layout (chunks do not
     // straddle particles)
-    const int p = (int)chunk[blockIdx.x];
     const int64_t g0 = (int64_t)blockIdx.x * 256;
+    // (every record of a chunk is allocated: it loads beside the particle's
+    // index, and counts only if it lies below the particle's link count)
+    const LinkRec r = links[g0 + threadIdx.x];
+    const int p = (int)chunk[blockIdx.x];
     const int64_t cnt = min(loff[p + 1] - loff[p], (int64_t)cursor[(int64_t)p * kCursorPad]);
     if (g0 - loff[p] >= cnt) return;  // uniform over the block
     const int64_t l = g0 - loff[p] + threadIdx.x;
     double acc[6] = {0, 0, 0, 0, 0, 0};
     if (l < cnt) {
-        const LinkRec r = links[g0 + threadIdx.x];
-        const int d = r.d, db = opp(d);
-        const int e[3] = {cx(d), cy(d), cz(d)};
-        const uint32_t nx = g.n[0], ny = g.n[1];
-        const int cs[3] = {(int)(r.node % nx), (int)((r.node / nx) % ny), (int)(r.node / (nx * ny))};
-        int cn[3] = {cs[0] - e[0], cs[1] - e[1], cs[2] - e[2]};
+        const int d = r.d, db = opp_moving(d);
+        int e[3];
+        dir_of(d, e);
+        uint32_t ux, uy, uz;
+        node_xyz(r.node, g, ux, uy, uz);
         const double xp[3] = {P.pos[3 * p], P.pos[3 * p + 1], P.pos[3 * p + 2]};
         const double vp[3] = {P.vel[3 * p], P.vel[3 * p + 1], P.vel[3 * p + 2]};
         const double wp[3] = {P.omega[3 * p], P.omega[3 * p + 1], P.omega[3 * p + 2]};
+        int cn[3] = {(int)ux - e[0], (int)uy - e[1], (int)uz - e[2]};
         wrap3(cn, g);  // for a missing point beyond a wall the node is virtual
-        double Xw[3], rr[3], uw[3];
+        double rr[3], uw[3];
+        const double ed[3] = {(double)e[0], (double)e[1], (double)e[2]};
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             // periodic axes are wrapped by wrap3; a node beyond a wall keeps
             // its raw coordinate (a virtual missing force point)
             const double Xn = image_coord(cn[a], g.n[a], g.per[a], xp[a]);
-            Xw[a] = Xn + r.q * (double)e[a];
-            rr[a] = Xw[a] - xp[a];
+            const double Xw = Xn + r.q * ed[a];
+            rr[a] = Xw - xp[a];
         }
         uw[0] = vp[0] + (wp[1] * rr[2] - wp[2] * rr[1]);
         uw[1] = vp[1] + (wp[2] * rr[0] - wp[0] * rr[2]);
@@ -289,69 +299,77 @@ __global__ __launch_bounds__(256) void k_boundary(typename St<S>::T* __restrict_
         double out, in;
         if (r.kind == LBM_LINK_MISSING) {
             // treatment 2: equilibrium at (rho0, u_w) on both sides
-            out = eq_i<false, double>(d, ph.rho0 - 1.0, ph.rho0, uw[0], uw[1], uw[2]);
-            in = eq_i<false, double>(db, ph.rho0 - 1.0, ph.rho0, uw[0], uw[1], uw[2]);
+            const double w = wgt_moving<double>(d);
+            const double eu = ed[0] * uw[0] + ed[1] * uw[1] + ed[2] * uw[2];
+            const double uu = uw[0] * uw[0] + uw[1] * uw[1] + uw[2] * uw[2];
+            out = eq_moving<false, double>(w, 0.0, ph.rho0, eu, uu);
+            in = eq_moving<false, double>(w, 0.0, ph.rho0, -eu, uu);
         } else {
             // x_f: its outgoing population and moments at time t
+            const A ea[3] = {A(e[0]), A(e[1]), A(e[2])};
+            const A w = wgt_moving<A>(d);
+            const typename St<S>::T* fd = f + (int64_t)d * g.stride;
             const uint32_t xf = node_of(cn, g);
-            const A fdf = St<S>::ld(f + (int64_t)d * g.stride + xf, ph.inv_scale);
+            const A fdf = St<S>::ld(fd + xf, ph.inv_scale);
             A drf, uf[3];
             St<S>::ld_mom(mom + xf, ph.inv_scale, drf, uf[0], uf[1], uf[2]);
             const A rf = A(1) + drf;
             const A uwa[3] = {A(uw[0]), A(uw[1]), A(uw[2])};
-            const A ebu = -(A(e[0]) * uwa[0] + A(e[1]) * uwa[1] + A(e[2]) * uwa[2]);
+            // 6 w rho_f e_{opp d}.u_w
+            const A mw = A(-6) * w * rf * (ea[0] * uwa[0] + ea[1] * uwa[1] + ea[2] * uwa[2]);
             A unk;
             if (r.kind == LBM_LINK_VIBB) {
                 int cf[3] = {cn[0] - e[0], cn[1] - e[1], cn[2] - e[2]};
                 wrap3(cf, g);
                 const uint32_t xff = node_of(cf, g);
-                const A fdff = St<S>::ld(f + (int64_t)d * g.stride + xff, ph.inv_scale);
+                const A fdff = St<S>::ld(fd + xff, ph.inv_scale);
                 A drff, uff[3];
                 St<S>::ld_mom(mom + xff, ph.inv_scale, drff, uff[0], uff[1], uff[2]);
                 const A rff = A(1) + drff;
                 const A q = A(r.q);
+                const bool low = q <= A(0.5);
                 const A tq = A(2) * q, oq = A(1) - A(2) * q;
+                auto eq = [&](A dr, A rh, const A u[3]) {
+                    return eq_moving<DEV, A>(w, dr, rh, ea[0] * u[0] + ea[1] * u[1] + ea[2] * u[2],
+                                             u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+                };
                 // non-equilibrium part extrapolated to x_d (Eq. neqd), or for
                 // q > 1/2 under treatment bit 8 held at its x_f value
-                const bool hold = ph.neq_split && q > A(0.5);
-                const A fneq = (hold ? A(1) : tq) * (fdf - eq_i<DEV, A>(d, drf, rf, uf[0], uf[1], uf[2])) +
-                               (hold ? A(0) : oq) *
-                                   (fdff - eq_i<DEV, A>(d, drff, rff, uff[0], uff[1], uff[2]));
+                const bool hold = ph.neq_split && !low;
+                const A fneq = (hold ? A(1) : tq) * (fdf - eq(drf, rf, uf)) +
+                               (hold ? A(0) : oq) * (fdff - eq(drff, rff, uff));
                 // density at x_d (Eq. rhod)
-                A drd, rd;
-                if (q <= A(0.5)) {
-                    drd = tq * drf + oq * drff;
-                    rd = tq * rf + oq * rff;
-                } else {
-                    drd = drf;
-                    rd = rf;
-                }
+                const A drd = low ? tq * drf + oq * drff : drf;
+                const A rd = low ? tq * rf + oq * rff : rf;
+                // u*_d from x_f and x_ff (q <= 1/2) or the wall, u**_d from
+                // x_ff and the wall
+                const A iq1 = A(1) / (A(1) + q);
+                const A a1 = low ? tq : (A(1) - q) / q, a2 = low ? oq : (tq - A(1)) / q;
+                const A b1 = (A(1) - q) * iq1, b2 = tq * iq1;
                 A ud[3];
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    const A us = (q <= A(0.5)) ? tq * uf[a] + oq * uff[a]
-                                               : (A(1) - q) / q * uf[a] + (tq - A(1)) / q * uwa[a];
-                    const A uss = (A(1) - q) / (A(1) + q) * uff[a] + tq / (A(1) + q) * uwa[a];
-                    ud[a] = us / A(3) + A(2) * uss / A(3);
+                    const A us = a1 * uf[a] + a2 * (low ? uff[a] : uwa[a]);
+                    const A uss = b1 * uff[a] + b2 * uwa[a];
+                    ud[a] = (us + A(2) * uss) * A(1.0 / 3.0);
                 }
-                unk = eq_i<DEV, A>(d, drd, rd, ud[0], ud[1], ud[2]) + fneq +
-                      A(6) * W<A>(d) * rf * ebu;
+                unk = eq(drd, rd, ud) + fneq + mw;
             } else {
                 // treatment 1: halfway bounce-back with the moving-wall term
-                unk = fdf + A(6) * W<A>(d) * rf * ebu;
+                unk = fdf + mw;
             }
             St<S>::st(f + (int64_t)db * g.stride + r.node, unk, ph.scale);
             out = (double)fdf;
             in = (double)unk;
             if constexpr (DEV) {
-                out += wgt(d);
-                in += wgt(db);
+                out += wgt_moving<double>(d);
+                in += wgt_moving<double>(d);
             }
         }
         // Galilean-invariant momentum exchange (Eq. mem)
         double t[3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) t[a] = ((double)e[a] - uw[a]) * out - (-(double)e[a] - uw[a]) * in;
+        for (int a = 0; a < 3; ++a) t[a] = (ed[a] - uw[a]) * out + (ed[a] + uw[a]) * in;
         acc[0] = t[0];
         acc[1] = t[1];
         acc[2] = t[2];
@@ -395,11 +413,8 @@ __global__ __launch_bounds__(256) void k_boundary(typename St<S>::T* __restrict_
         }
     } else {
         __shared__ double red[4][6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const double s = dsum_wave(acc[k]);
-            if (lane == 0) red[wv][k] = s;
-        }
+        const double sum = wave_sum6(acc);
+        if (lane < 6) red[wv][lane] = sum;
         __syncthreads();
         if (threadIdx.x < 6) {
             const double s = (red[0][threadIdx.x] + red[1][threadIdx.x]) +
@@ -426,7 +441,11 @@ __global__ __launch_bounds__(256) void k_fixed_to_f64(const unsigned long long* 
 // strides over the list.  Each node reads only the previous populations and
 // owners and writes only its own populations and moments, so running the
 // kernel again over a longer list (after the list has grown) gives the same
-// values at the nodes of the first run.
+// values at the nodes of the first run.  Bound by the latency of one node's
+// chain: each neighbour's owner and population load once (the bounce-back of
+// direction i reads what the streaming of opp(i) would), all before the first
+// use: 4.3-5.2 us for a few nodes, 10 us for 60 bodies in FP64, where 38
+// populations and 36 owners with wrapped coordinates took 10-15 and 21 us.
 // ---------------------------------------------------------------------------
 template <int S>
 __device__ __forceinline__ void refill_node(const typename St<S>::T* __restrict__ prev,
@@ -439,42 +458,47 @@ __device__ __forceinline__ void refill_node(const typename St<S>::T* __restrict_
     using A = typename St<S>::A;
     constexpr bool DEV = St<S>::dev;
     const int p = r.part;
-    const uint32_t nx = g.n[0], ny = g.n[1];
-    const int c[3] = {(int)(r.node % nx), (int)((r.node / nx) % ny), (int)(r.node / (nx * ny))};
+    // the wrapped neighbours x - e_i, whether each lies in the lattice, its
+    // owner and its f_i; x + e_i and its f_opp(i) are those of opp(i)
+    uint32_t x[3];
+    node_xyz(r.node, g, x[0], x[1], x[2]);
+    uint32_t o[3][3];
+    bool in[3][3];
+    axis3(x[0], g.n[0], g.per[0], 1u, o[0], in[0]);
+    axis3(x[1], g.n[1], g.per[1], g.n[0], o[1], in[1]);
+    axis3(x[2], g.n[2], g.per[2], (uint32_t)g.n[0] * (uint32_t)g.n[1], o[2], in[2]);
+    A a[kQ];
+    uint32_t own[kQ];
+#pragma unroll
+    for (int i = 1; i < kQ; ++i) {
+        const uint32_t n = o[0][1 - cx(i)] + o[1][1 - cy(i)] + o[2][1 - cz(i)];
+        a[i] = St<S>::ld(prev + (int64_t)i * g.stride + n, ph.inv_scale);
+        own[i] = own_prev[n];
+    }
     double rr[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const double xp = P.pos[3 * p + a];
-        rr[a] = image_coord(c[a], g.n[a], g.per[a], xp) - xp;
+    for (int k = 0; k < 3; ++k) {
+        const double xp = P.pos[3 * p + k];
+        rr[k] = image_coord((int)x[k], g.n[k], g.per[k], xp) - xp;
     }
     const double wp[3] = {P.omega[3 * p], P.omega[3 * p + 1], P.omega[3 * p + 2]};
     const A un[3] = {A(P.vel[3 * p] + (wp[1] * rr[2] - wp[2] * rr[1])),
                      A(P.vel[3 * p + 1] + (wp[2] * rr[0] - wp[0] * rr[2])),
                      A(P.vel[3 * p + 2] + (wp[0] * rr[1] - wp[1] * rr[0]))};
     const A r0 = A(ph.rho0), dr0 = A(ph.rho0 - 1.0);
-    A v[kQ];
+    const A uu = un[0] * un[0] + un[1] * un[1] + un[2] * un[2];
+    bool fluid[kQ];
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-        int cu[3] = {c[0] - cx(i), c[1] - cy(i), c[2] - cz(i)};
-        int cd[3] = {c[0] + cx(i), c[1] + cy(i), c[2] + cz(i)};
-        const bool iu = i > 0 && wrap3(cu, g);
-        const bool id = i > 0 && wrap3(cd, g);
-        const uint32_t nu = iu ? node_of(cu, g) : r.node;
-        const uint32_t nd = id ? node_of(cd, g) : r.node;
-        // both candidate populations load beside the owners (both indices
-        // are nodes of the lattice), the owners then pick
-        const A a_up = St<S>::ld(prev + (int64_t)i * g.stride + nu, ph.inv_scale);
-        const A a_dn = St<S>::ld(prev + (int64_t)opp(i) * g.stride + nd, ph.inv_scale);
-        const bool up = iu && own_prev[nu] == kFluid;
-        const bool dn = id && own_prev[nd] == kFluid;
-        if (up) {
-            v[i] = a_up;  // streamed
-        } else if (dn) {
-            const A eu = A(cx(i)) * un[0] + A(cy(i)) * un[1] + A(cz(i)) * un[2];
-            v[i] = a_dn + A(6) * W<A>(i) * r0 * eu;  // bounce-back of the streamed opposite
-        } else {
-            v[i] = eq_i<DEV, A>(i, dr0, r0, un[0], un[1], un[2]);
-        }
+    for (int i = 1; i < kQ; ++i)
+        fluid[i] = in[0][1 - cx(i)] && in[1][1 - cy(i)] && in[2][1 - cz(i)] && own[i] == kFluid;
+    A v[kQ];
+    v[0] = eq_moving<DEV, A>(W<A>(0), dr0, r0, A(0), uu);
+#pragma unroll
+    for (int i = 1; i < kQ; ++i) {
+        const A eu = edot(i, un[0], un[1], un[2]);
+        v[i] = fluid[i]        ? a[i]                                          // streamed
+               : fluid[opp(i)] ? a[opp(i)] + A(6) * W<A>(i) * r0 * eu          // bounced back
+                               : eq_moving<DEV, A>(W<A>(i), dr0, r0, eu, uu);  // equilibrium
     }
     A F[3];
     A om, go;
