@@ -342,7 +342,7 @@ int dem_alloc(lbm_ctx* c)
 // The work space of a dem_step call on the context.
 DemScratch dem_scratch(lbm_ctx* c)
 {
-    DemScratch ws{c->pairs, c->pair_count, c->reach};
+    DemScratch ws{c->pairs, c->pair_count, c->reach, c->reach + std::max(c->cfg.n_particles, 1)};
     if (c->grid) {
         ws.gcount = c->grid;
         ws.gcursor = c->grid + c->grid_cap + 1;
@@ -532,7 +532,7 @@ int lbm_init(const lbm_config* cfg, const lbm_buffers* bufs, lbm_ctx** out)
     if (e == hipSuccess && np && cfg->force_sum == LBM_FORCE_SUM_EXACT)
         e = alloc(&c->FX, (size_t)12 * np);
     if (e == hipSuccess) e = alloc(&c->fc, (size_t)6 * std::max(np, 1));
-    if (e == hipSuccess) e = alloc(&c->reach, (size_t)std::max(np, 1));
+    if (e == hipSuccess) e = alloc(&c->reach, (size_t)2 * std::max(np, 1));
     if (e == hipSuccess)
         e = hipHostMalloc((void**)&c->host_stage,
                           sizeof(uint32_t) * (kStageHead + 2 * (size_t)kCursorPad * np1),

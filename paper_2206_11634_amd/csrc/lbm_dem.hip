@@ -6,11 +6,20 @@
 // contactprop) and metaball-wall contacts by Newton on the in-plane gradient
 // (Eqs. metawall, metawallcp, k, contactprop2).
 //
-// One substep = three launches: half kick + drift + rotation + reset of the
-// contact sums (one thread per particle), contacts (one thread per pair i < j
-// and one per particle-wall pair, FP64 atomics into the sums), second half
-// kick.
-// The work is latency-bound (a few thousand particles at most), not HBM-bound.
+// The work is latency-bound (chains of FP64 operations on a few thousand
+// particles at most), not HBM-bound.  Up to kBlockParticles particles one
+// workgroup runs the whole call: the broad phase and every substep, a thread
+// per particle and kPairLanes lanes per candidate pair, with barriers where
+// more particles take a launch.  Beyond, a substep is two launches: the
+// contacts (2 or kPairLanes lanes per candidate pair, a thread per
+// particle-wall pair, FP64 atomics into the sums), then the second half kick,
+// and the first half of the next substep (a thread per particle).
+// Measured, microseconds a call of ten substeps (before: a thread per pair,
+// per pair test and per particle's cells, 23 launches whatever the count):
+//   1 sphere 32 (83), 2 flat metaballs 60 (153), 64 packed spheres 98 (173),
+//   1000 metaballs of the 512^3 run 275 (535), packed spheres 1000: 145 (226),
+//   2548: 164 (420), 8000: 186 (462), 27 000: 328 (745).
+#include <algorithm>
 #include <mutex>
 
 #include "lbm_internal.h"
@@ -39,7 +48,7 @@ __device__ __forceinline__ double dot3(const double a[3], const double b[3])
     return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
 }
 
-__device__ void rotmat(const double* q, double R[9])
+__device__ __forceinline__ void rotmat(const double q[4], double R[9])
 {
     const double w = q[0], x = q[1], y = q[2], z = q[3];
     R[0] = 1 - 2 * (y * y + z * z);
@@ -53,98 +62,74 @@ __device__ void rotmat(const double* q, double R[9])
     R[8] = 1 - 2 * (x * x + y * y);
 }
 
-// M, grad M and the Hessian of a metaball with n points at X; pts may be
-// shifted by `sh` (a periodic image).
-__device__ void mb_d2(const double* pts, const double* K, int n, const double sh[3],
-                      const double X[3], double& M, double g[3], double H[9])
+// Sum over the G lanes of a pair's group (2 or 4 lanes of a quad, exchanged by
+// quad permutes; the same bits in each of them).
+template <int CTRL>
+__device__ __forceinline__ double quad_perm(double v)
 {
-    M = 0.0;
-    for (int a = 0; a < 3; ++a) g[a] = 0.0;
-    for (int a = 0; a < 9; ++a) H[a] = 0.0;
-    for (int i = 0; i < n; ++i) {
-        double r[3];
-        for (int a = 0; a < 3; ++a) r[a] = X[a] - (pts[3 * i + a] + sh[a]);
-        const double r2 = (r[0] * r[0] + r[1] * r[1]) + r[2] * r[2];
-        const double i2 = 1.0 / r2, i4 = i2 * i2, i6 = i4 * i2;
-        M += K[i] * i2;
-        for (int a = 0; a < 3; ++a) {
-            g[a] += -2.0 * K[i] * r[a] * i4;
-            for (int b = 0; b < 3; ++b)
-                H[3 * a + b] += K[i] * (8.0 * r[a] * r[b] * i6 - (a == b ? 2.0 * i4 : 0.0));
-        }
-    }
+    union {
+        double d;
+        int w[2];
+    } u;
+    u.d = v;
+    u.w[0] = __builtin_amdgcn_mov_dpp(u.w[0], CTRL, 0xf, 0xf, true);
+    u.w[1] = __builtin_amdgcn_mov_dpp(u.w[1], CTRL, 0xf, 0xf, true);
+    return u.d;
+}
+template <int G>
+__device__ __forceinline__ double gsum(double v)
+{
+    static_assert(G == 1 || G == 2 || G == 4, "a group is part of a quad");
+    if constexpr (G >= 2) v += quad_perm<0xB1>(v);  // lanes 1 0 3 2
+    if constexpr (G >= 4) v += quad_perm<0x4E>(v);  // lanes 2 3 0 1
+    return v;
 }
 
-// A body's control points for the Newton iterations: read from global
-// memory each time, or (up to kRegPts points) held in registers, which
-// removes the memory latency from the serial iteration.  Both evaluate
-// exactly the sums of mb_d2 in the same order.
-struct BodyG {
-    const double* pts;
-    const double* K;
-    int n;
-    __device__ void eval(const double sh[3], const double X[3], double& M, double g[3],
-                         double H[9]) const
-    {
-        mb_d2(pts, K, n, sh, X, M, g, H);
-    }
-};
-
-constexpr int kRegPts = 6;
-struct BodyR {
-    double p[kRegPts][3], k[kRegPts];
-    int n;
-    __device__ BodyR(const double* pts, const double* K, int n_) : n(n_)
-    {
-#pragma unroll
-        for (int i = 0; i < kRegPts; ++i) {
-            const bool on = i < n;
-            for (int a = 0; a < 3; ++a) p[i][a] = on ? pts[3 * i + a] : 0.0;
-            k[i] = on ? K[i] : 0.0;
-        }
-    }
-    __device__ __forceinline__ void eval(const double sh[3], const double X[3], double& M,
-                                         double g[3], double H[9]) const
-    {
-        M = 0.0;
-        for (int a = 0; a < 3; ++a) g[a] = 0.0;
-        for (int a = 0; a < 9; ++a) H[a] = 0.0;
-#pragma unroll
-        for (int i = 0; i < kRegPts; ++i) {
-            if (i >= n) break;
-            double r[3];
-            for (int a = 0; a < 3; ++a) r[a] = X[a] - (p[i][a] + sh[a]);
-            const double r2 = (r[0] * r[0] + r[1] * r[1]) + r[2] * r[2];
-            const double i2 = 1.0 / r2, i4 = i2 * i2, i6 = i4 * i2;
-            M += k[i] * i2;
-            for (int a = 0; a < 3; ++a) {
-                g[a] += -2.0 * k[i] * r[a] * i4;
-                for (int b = 0; b < 3; ++b)
-                    H[3 * a + b] += k[i] * (8.0 * r[a] * r[b] * i6 - (a == b ? 2.0 * i4 : 0.0));
-            }
-        }
-    }
-};
-
-__device__ bool solve3(const double H[9], const double g[3], double dx[3])
+// 1/x for a Newton iteration: the hardware's estimate and two Newton steps
+// (an ulp or so; the iteration corrects itself, and the sums that the contact
+// force is built from divide).
+__device__ __forceinline__ double fast_rcp(double x)
 {
-    double c[9];
-    c[0] = H[4] * H[8] - H[5] * H[7];
-    c[1] = H[2] * H[7] - H[1] * H[8];
-    c[2] = H[1] * H[5] - H[2] * H[4];
-    c[3] = H[5] * H[6] - H[3] * H[8];
-    c[4] = H[0] * H[8] - H[2] * H[6];
-    c[5] = H[2] * H[3] - H[0] * H[5];
-    c[6] = H[3] * H[7] - H[4] * H[6];
-    c[7] = H[1] * H[6] - H[0] * H[7];
-    c[8] = H[0] * H[4] - H[1] * H[3];
-    const double det = H[0] * c[0] + H[1] * c[3] + H[2] * c[6];
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+
+// Terms of one control point at distance r: its share of M, grad M (negated:
+// s r with s = 2 K / r^4) and the upper triangle of the Hessian.
+__device__ __forceinline__ void add_point(double K, const double r[3], double i2, double& M,
+                                          double g[3], double H[6])
+{
+    const double t = K * i2, s = 2.0 * t * i2, q = 4.0 * s * i2;
+    M += t;
+    g[0] -= s * r[0];
+    g[1] -= s * r[1];
+    g[2] -= s * r[2];
+    const double q0 = q * r[0], q1 = q * r[1], q2 = q * r[2];
+    H[0] += q0 * r[0] - s;
+    H[1] += q0 * r[1];
+    H[2] += q0 * r[2];
+    H[3] += q1 * r[1] - s;
+    H[4] += q1 * r[2];
+    H[5] += q2 * r[2] - s;
+}
+
+// dx = -H^-1 g for a symmetric H (upper triangle).
+__device__ __forceinline__ bool solve3(const double H[6], const double g[3], double dx[3])
+{
+    const double a = H[0], b = H[1], c = H[2], d = H[3], e = H[4], f = H[5];
+    const double c00 = d * f - e * e, c01 = c * e - b * f, c02 = b * e - c * d;
+    const double c11 = a * f - c * c, c12 = b * c - a * e, c22 = a * d - b * b;
+    const double det = a * c00 + b * c01 + c * c02;
     if (!(fabs(det) > 0.0) || !isfinite(det)) return false;
-    for (int i = 0; i < 3; ++i) dx[i] = -(c[3 * i] * g[0] + c[3 * i + 1] * g[1] + c[3 * i + 2] * g[2]) / det;
+    const double s = -fast_rcp(det);
+    dx[0] = s * (c00 * g[0] + c01 * g[1] + c02 * g[2]);
+    dx[1] = s * (c01 * g[0] + c11 * g[1] + c12 * g[2]);
+    dx[2] = s * (c02 * g[0] + c12 * g[1] + c22 * g[2]);
     return true;
 }
 
-__device__ double reach(const PartDev& P, int p)
+__device__ __forceinline__ double reach(const PartDev& P, int p)
 {
     double sk = 0.0, r = 0.0;
     for (int i = P.off[p]; i < P.off[p + 1]; ++i) {
@@ -156,17 +141,18 @@ __device__ double reach(const PartDev& P, int p)
 }
 
 // Normal spring-dashpot (clamped at zero) and tangential spring with Coulomb
-// limit; updates the spring xi in h[1..3]; returns the force on body i.
-__device__ void contact_force(const DemP& c, double delta, const double n[3], const double vrel[3],
-                              double dt, double* h, double Fi[3])
+// limit; updates the spring xi; returns the force on body i.
+__device__ __forceinline__ void contact_force(const DemP& c, double delta, const double n[3],
+                                              const double vrel[3], double dt, double xi[3],
+                                              double Fi[3])
 {
     const double vn = dot3(vrel, n);
     double Fn = c.kn * delta - c.etan * vn;
     if (Fn < 0.0) Fn = 0.0;
-    double vt[3], xi[3], Ft[3];
+    double vt[3], Ft[3];
     for (int a = 0; a < 3; ++a) vt[a] = vrel[a] - vn * n[a];
-    const double xin = h[1] * n[0] + h[2] * n[1] + h[3] * n[2];
-    for (int a = 0; a < 3; ++a) xi[a] = h[1 + a] - xin * n[a] + vt[a] * dt;
+    const double xin = dot3(xi, n);
+    for (int a = 0; a < 3; ++a) xi[a] = xi[a] - xin * n[a] + vt[a] * dt;
     for (int a = 0; a < 3; ++a) Ft[a] = -c.kt * xi[a] - c.etat * vt[a];
     const double ftn = sqrt(dot3(Ft, Ft));
     if (ftn > c.mu * Fn && ftn > 0.0) {
@@ -176,113 +162,237 @@ __device__ void contact_force(const DemP& c, double delta, const double n[3], co
             xi[a] = -(Ft[a] + c.etat * vt[a]) / c.kt;
         }
     }
-    for (int a = 0; a < 3; ++a) {
-        h[1 + a] = xi[a];
-        Fi[a] = Fn * n[a] + Ft[a];
-    }
+    for (int a = 0; a < 3; ++a) Fi[a] = Fn * n[a] + Ft[a];
 }
 
-__device__ void half_kick(const PartDev& P, int p, const double* FTh, const double* fc,
-                          const DemP& c, double h, bool implicit)
+// A particle's state and constants in registers.
+struct Body {
+    double x[3], q[4], v[3], w[3];  // centre, orientation, velocity, angular velocity
+    double F[3], T[3];              // F^h + relative gravity, T^h
+    double hm, I[3], hI[3];         // half step over the mass and the moments
+    int c0, c1;                     // control points
+};
+
+__device__ __forceinline__ Body load_body(const PartDev& P, int p, const double* FTh, const DemP& c,
+                                          double h)
 {
+    Body b;
     const double m = P.mass[p];
     const double mrel = m - c.rhof * P.volume[p];
+    b.hm = h / m;
+    b.c0 = P.off[p];
+    b.c1 = P.off[p + 1];
+    for (int a = 0; a < 3; ++a) {
+        b.x[a] = P.pos[3 * p + a];
+        b.v[a] = P.vel[3 * p + a];
+        b.w[a] = P.omega[3 * p + a];
+        b.I[a] = P.inertia[3 * p + a];
+        b.hI[a] = h / b.I[a];
+        b.F[a] = FTh[6 * p + a] + mrel * c.g[a];
+        b.T[a] = FTh[6 * p + 3 + a];
+    }
+    for (int a = 0; a < 4; ++a) b.q[a] = P.quat[4 * p + a];
+    return b;
+}
+
+// Half a kick under F, T and the contact sum fc; the rotational part by one
+// explicit or four fixed-point sweeps of Euler's equations.
+__device__ __forceinline__ void half_kick(Body& b, const double fc[6], bool implicit)
+{
     double T[3];
     for (int a = 0; a < 3; ++a) {
-        const double F = FTh[6 * p + a] + mrel * c.g[a] + fc[6 * p + a];
-        P.vel[3 * p + a] += h * F / m;
-        T[a] = FTh[6 * p + 3 + a] + fc[6 * p + 3 + a];
+        b.v[a] += b.hm * (b.F[a] + fc[a]);
+        T[a] = b.T[a] + fc[3 + a];
     }
     double R[9];
-    rotmat(P.quat + 4 * p, R);
+    rotmat(b.q, R);
     double w0[3], Tb[3], wb[3];
-    const double* om = P.omega + 3 * p;
     for (int i = 0; i < 3; ++i) {
-        w0[i] = R[i] * om[0] + R[3 + i] * om[1] + R[6 + i] * om[2];
+        w0[i] = R[i] * b.w[0] + R[3 + i] * b.w[1] + R[6 + i] * b.w[2];
         Tb[i] = R[i] * T[0] + R[3 + i] * T[1] + R[6 + i] * T[2];
         wb[i] = w0[i];
     }
-    const double* I = P.inertia + 3 * p;
     const int iters = implicit ? 4 : 1;
     for (int it = 0; it < iters; ++it) {
-        const double Iw[3] = {I[0] * wb[0], I[1] * wb[1], I[2] * wb[2]};
+        const double Iw[3] = {b.I[0] * wb[0], b.I[1] * wb[1], b.I[2] * wb[2]};
         double cc[3];
         cross3(wb, Iw, cc);
-        double nw[3];
-        for (int a = 0; a < 3; ++a) nw[a] = w0[a] + h * (Tb[a] - cc[a]) / I[a];
-        for (int a = 0; a < 3; ++a) wb[a] = nw[a];
+        for (int a = 0; a < 3; ++a) wb[a] = w0[a] + b.hI[a] * (Tb[a] - cc[a]);
     }
-    for (int i = 0; i < 3; ++i) P.omega[3 * p + i] = R[3 * i] * wb[0] + R[3 * i + 1] * wb[1] + R[3 * i + 2] * wb[2];
+    for (int i = 0; i < 3; ++i)
+        b.w[i] = R[3 * i] * wb[0] + R[3 * i + 1] * wb[1] + R[3 * i + 2] * wb[2];
 }
 
-// First half kick, drift, rotation and world control points of particle p;
-// also its broad-phase reach and the reset of its contact sums.
-__device__ void first_half(const PartDev& P, int p, const double* FTh, double* fc,
-                           double* reach_out, const DemP& c, double dt, const Geom& g)
+// Drift and rotation over dt, and the world control points of the new pose.
+__device__ __forceinline__ void drift(const PartDev& P, Body& b, double dt, const Geom& g)
 {
-    half_kick(P, p, FTh, fc, c, 0.5 * dt, false);
-    for (int k = 0; k < 6; ++k) fc[6 * p + k] = 0.0;
-    reach_out[p] = reach(P, p);
     for (int a = 0; a < 3; ++a) {
-        double x = P.pos[3 * p + a] + dt * P.vel[3 * p + a];
+        double x = b.x[a] + dt * b.v[a];
         if (g.per[a]) {
             if (x >= (double)g.n[a]) x -= g.n[a];
             else if (x < 0.0) x += g.n[a];
         }
-        P.pos[3 * p + a] = x;
+        b.x[a] = x;
     }
-    const double* om = P.omega + 3 * p;
-    const double wn = sqrt(om[0] * om[0] + om[1] * om[1] + om[2] * om[2]);
-    double dq[4];
-    dq[0] = cos(0.5 * wn * dt);
-    const double s = wn > 0.0 ? sin(0.5 * wn * dt) / wn : 0.0;
-    dq[1] = s * om[0];
-    dq[2] = s * om[1];
-    dq[3] = s * om[2];
-    double* q = P.quat + 4 * p;
+    const double wn = sqrt(dot3(b.w, b.w));
+    double dq[4], sn;
+    sincos(0.5 * wn * dt, &sn, &dq[0]);
+    const double s = wn > 0.0 ? sn / wn : 0.0;
+    for (int a = 0; a < 3; ++a) dq[1 + a] = s * b.w[a];
+    const double* q = b.q;
     double qn[4];
     qn[0] = dq[0] * q[0] - dq[1] * q[1] - dq[2] * q[2] - dq[3] * q[3];
     qn[1] = dq[0] * q[1] + dq[1] * q[0] + dq[2] * q[3] - dq[3] * q[2];
     qn[2] = dq[0] * q[2] - dq[1] * q[3] + dq[2] * q[0] + dq[3] * q[1];
     qn[3] = dq[0] * q[3] + dq[1] * q[2] - dq[2] * q[1] + dq[3] * q[0];
     const double nrm = sqrt(qn[0] * qn[0] + qn[1] * qn[1] + qn[2] * qn[2] + qn[3] * qn[3]);
-    for (int a = 0; a < 4; ++a) q[a] = qn[a] / nrm;
+    const double in = 1.0 / nrm;
+    for (int a = 0; a < 4; ++a) b.q[a] = qn[a] * in;
     double R[9];
-    rotmat(q, R);
-    for (int i = P.off[p]; i < P.off[p + 1]; ++i) {
-        const double* b = P.body_pts + 3 * (int64_t)i;
+    rotmat(b.q, R);
+    for (int i = b.c0; i < b.c1; ++i) {
+        const double* bp = P.body_pts + 3 * (int64_t)i;
         for (int a = 0; a < 3; ++a)
-            P.wpts[3 * (int64_t)i + a] = P.pos[3 * p + a] + (R[3 * a] * b[0] + R[3 * a + 1] * b[1] + R[3 * a + 2] * b[2]);
+            P.wpts[3 * (int64_t)i + a] =
+                b.x[a] + (R[3 * a] * bp[0] + R[3 * a + 1] * bp[1] + R[3 * a + 2] * bp[2]);
     }
 }
 
-__global__ void k_first_half(PartDev P, const double* FTh, double* fc, double* reach_out, DemP c,
-                             double dt, Geom g)
+__device__ __forceinline__ void store_body(const PartDev& P, int p, const Body& b, bool pose)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P.n) return;
-    first_half(P, p, FTh, fc, reach_out, c, dt, g);
+    for (int a = 0; a < 3; ++a) {
+        P.vel[3 * p + a] = b.v[a];
+        P.omega[3 * p + a] = b.w[a];
+        if (pose) P.pos[3 * p + a] = b.x[a];
+    }
+    if (pose)
+        for (int a = 0; a < 4; ++a) P.quat[4 * p + a] = b.q[a];
 }
 
-__device__ void wall_contact(const PartDev& P, int t, double* hist, double* fc, const double* rch,
-                             const DemP& c, double dt, const Geom& g);
+// What a contact reads of a particle at the current substep, wherever it is
+// kept: the caller's arrays and the library's reach, or a workgroup's copies.
+struct StateG {
+    const double *pos, *vel, *omega, *rs, *reach;
+    double* fc;
+    const int32_t* off;
+};
 
-// Newton on grad(M_A + M_B) = 0 from x, the contact test and the force of
-// pair (i, j); A and B supply the two bodies' metaball sums.
-template <class BA, class BB>
-__device__ __forceinline__ void pair_contact(const BA& A, const BB& B, double x[3], double* h, const double* xi,
-                             const double* xj, const double sh[3], int i, int j, double rsi,
-                             double rsj, const PartDev& P, const DemP& c, double dt, double* fc)
+__device__ __forceinline__ void clear_record(double* h)
 {
-    const double z3[3] = {0.0, 0.0, 0.0};
-    double MA, MB, gA[3], gB[3], HA[9], HB[9];
+    for (int k = 0; k < kHist; ++k) h[k] = 0.0;
+}
+
+// Contact of pair (i < j), record h of particle i: test on the reach radii,
+// Newton on grad(M_i + M_j) = 0 from the recorded point or the closest pair
+// of control points, the contact test and the force.  The G lanes of a group
+// share a pair: each sums every G-th control point of the two bodies (kept in
+// registers up to 4 a lane), and all follow the same branches on the same bits.
+template <int G>
+__device__ __forceinline__ void pair_item(const PartDev& P, const StateG& S, double* hist,
+                                          const DemP& c, double dt, const Geom& g, int i, int j,
+                                          int slot, int l)
+{
+    double* h = hist + ((int64_t)i * kPairSlots + slot) * kHist;
+    double xi[3], xj[3], sh[3], dv[3];
+    for (int a = 0; a < 3; ++a) {
+        xi[a] = S.pos[3 * i + a];
+        xj[a] = S.pos[3 * j + a];
+        const double d = xj[a] - xi[a];
+        sh[a] = 0.0;
+        if (g.per[a]) {
+            const double L = g.n[a];
+            if (d > 0.5 * L) sh[a] = -L;
+            else if (d < -0.5 * L) sh[a] = L;
+        }
+        dv[a] = d + sh[a];
+    }
+    const double rsi = S.rs[i], rsj = S.rs[j];
+    const double active = h[0];
+    if (sqrt(dot3(dv, dv)) > S.reach[i] + S.reach[j] + rsi + rsj) {
+        // out of reach: forget the pair's contact (read one double instead of
+        // writing eight when the record is zero already)
+        if (active != 0.0 && l == 0) clear_record(h);
+        return;
+    }
+    const int ai = S.off[i], ni = min(S.off[i + 1] - ai, kMaxPts);
+    const int aj = S.off[j], nj = min(S.off[j + 1] - aj, kMaxPts);
+    const double* pi = P.wpts + 3 * (int64_t)ai;
+    const double* pj = P.wpts + 3 * (int64_t)aj;
+    const double* Ki = P.K + ai;
+    const double* Kj = P.K + aj;
+    const int nt = ni + nj;
+    // point u of the pair: body i's, then body j's at their image nearest i
+    auto point = [&](int u, double r[3], double& K) {
+        const bool second = u >= ni;
+        const double* q = second ? pj + 3 * (u - ni) : pi + 3 * u;
+        for (int a = 0; a < 3; ++a) r[a] = q[a] + (second ? sh[a] : 0.0);
+        K = second ? Kj[u - ni] : Ki[u];
+    };
+    constexpr int R = 4;
+    double pr[R][3], kr[R];
+    const bool regs = nt <= G * R;
+    if (regs) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int u = l + G * k;
+            pr[k][0] = pr[k][1] = pr[k][2] = kr[k] = 0.0;
+            if (u < nt) point(u, pr[k], kr[k]);
+        }
+    }
+    double x[3];
+    if (active != 0.0) {
+        for (int a = 0; a < 3; ++a) x[a] = xi[a] + h[4 + a];
+    } else {
+        double best = INFINITY;
+        int at = 0x7fffffff;
+        for (int t = l; t < ni * nj; t += G) {
+            const int u = t / nj, v = t % nj;
+            double d2 = 0.0;
+            for (int a = 0; a < 3; ++a) {
+                const double dd = pi[3 * u + a] - (pj[3 * v + a] + sh[a]);
+                d2 += dd * dd;
+            }
+            if (d2 < best) {
+                best = d2;
+                at = t;
+            }
+        }
+        // the first of the closest
+#pragma unroll
+        for (int m = 1; m < G; m <<= 1) {
+            const double ob = __shfl_xor(best, m, 64);
+            const int oa = __shfl_xor(at, m, 64);
+            if (ob < best || (ob == best && oa < at)) {
+                best = ob;
+                at = oa;
+            }
+        }
+        if (at == 0x7fffffff) at = 0;
+        const int u = at / nj, v = at % nj;
+        for (int a = 0; a < 3; ++a) x[a] = 0.5 * (pi[3 * u + a] + pj[3 * v + a] + sh[a]);
+    }
     bool conv = false;
     for (int it = 0; it < c.niter; ++it) {
-        A.eval(z3, x, MA, gA, HA);
-        B.eval(sh, x, MB, gB, HB);
-        double gg[3], H[9], dx[3];
-        for (int a = 0; a < 3; ++a) gg[a] = gA[a] + gB[a];
-        for (int a = 0; a < 9; ++a) H[a] = HA[a] + HB[a];
+        double M = 0.0, gg[3] = {0, 0, 0}, H[6] = {0, 0, 0, 0, 0, 0}, dx[3];
+        if (regs) {
+#pragma unroll
+            for (int k = 0; k < R; ++k)
+                if (l + G * k < nt) {
+                    const double r[3] = {x[0] - pr[k][0], x[1] - pr[k][1], x[2] - pr[k][2]};
+                    add_point(kr[k], r, fast_rcp(dot3(r, r)), M, gg, H);
+                }
+        } else {
+            for (int u = l; u < nt; u += G) {
+                double r[3], K;
+                point(u, r, K);
+                for (int a = 0; a < 3; ++a) r[a] = x[a] - r[a];
+                add_point(K, r, fast_rcp(dot3(r, r)), M, gg, H);
+            }
+        }
+        if constexpr (G > 1) {
+            for (int a = 0; a < 3; ++a) gg[a] = gsum<G>(gg[a]);
+            for (int a = 0; a < 6; ++a) H[a] = gsum<G>(H[a]);
+        }
         if (!solve3(H, gg, dx)) break;
         for (int a = 0; a < 3; ++a) x[a] += dx[a];
         if (sqrt(dot3(dx, dx)) < c.ntol) {
@@ -291,11 +401,33 @@ __device__ __forceinline__ void pair_contact(const BA& A, const BB& B, double x[
         }
     }
     if (!conv) {
-        for (int k = 0; k < kHist; ++k) h[k] = 0.0;
+        if (l == 0) clear_record(h);
         return;
     }
-    A.eval(z3, x, MA, gA, HA);
-    B.eval(sh, x, MB, gB, HB);
+    // M and grad M of each body at the stationary point
+    double MA = 0.0, MB = 0.0, gA[3] = {0, 0, 0}, gB[3] = {0, 0, 0};
+    for (int u = l; u < nt; u += G) {
+        double r[3], K;
+        point(u, r, K);
+        for (int a = 0; a < 3; ++a) r[a] = x[a] - r[a];
+        const double t = K / dot3(r, r), s = 2.0 * t / dot3(r, r);
+        if (u < ni) {
+            MA += t;
+            for (int a = 0; a < 3; ++a) gA[a] -= s * r[a];
+        } else {
+            MB += t;
+            for (int a = 0; a < 3; ++a) gB[a] -= s * r[a];
+        }
+    }
+    if constexpr (G > 1) {
+        MA = gsum<G>(MA);
+        MB = gsum<G>(MB);
+        for (int a = 0; a < 3; ++a) {
+            gA[a] = gsum<G>(gA[a]);
+            gB[a] = gsum<G>(gB[a]);
+        }
+    }
+    if (l != 0) return;
     // both bodies' fields above ctol at the stationary point (Eq. opt); the
     // separation is signed along the common line of the two projections of
     // Eq. cp, n = (grad M_i - grad M_j)/|.| from body j to body i, so that a
@@ -303,10 +435,7 @@ __device__ __forceinline__ void pair_contact(const BA& A, const BB& B, double x[
     // meeting at an angle) reads as an overlap rather than as no contact;
     // overlaps beyond 2 (R_si + R_sj) are stationary points inside a body,
     // where the projection of Eq. k0 does not hold, and are not contacts
-    if (!(MA > c.ctol && MB > c.ctol)) {
-        for (int k = 0; k < kHist; ++k) h[k] = 0.0;
-        return;
-    }
+    if (!(MA > c.ctol && MB > c.ctol)) return clear_record(h);
     const double qA = (1.0 - MA) / dot3(gA, gA), qB = (1.0 - MB) / dot3(gB, gB);
     double xa[3], dd[3], n[3];
     for (int a = 0; a < 3; ++a) {
@@ -315,16 +444,10 @@ __device__ __forceinline__ void pair_contact(const BA& A, const BB& B, double x[
         n[a] = gA[a] - gB[a];
     }
     const double un = sqrt(dot3(n, n));
-    if (!(un > 0.0)) {
-        for (int k = 0; k < kHist; ++k) h[k] = 0.0;
-        return;
-    }
+    if (!(un > 0.0)) return clear_record(h);
     for (int a = 0; a < 3; ++a) n[a] = n[a] / un;
     const double delta = rsi + rsj - dot3(dd, n);
-    if (!(delta <= 2.0 * (rsi + rsj))) {
-        for (int k = 0; k < kHist; ++k) h[k] = 0.0;
-        return;
-    }
+    if (!(delta <= 2.0 * (rsi + rsj))) return clear_record(h);
     h[0] = 1.0;
     for (int a = 0; a < 3; ++a) h[4 + a] = x[a] - xi[a];
     if (delta <= 0.0) {
@@ -337,89 +460,132 @@ __device__ __forceinline__ void pair_contact(const BA& A, const BB& B, double x[
         ra[a] = xcp[a] - xi[a];
         rb[a] = xcp[a] - (xj[a] + sh[a]);
     }
-    double ca[3], cb[3], vrel[3], Fi[3], tq[3];
-    cross3(P.omega + 3 * i, ra, ca);
-    cross3(P.omega + 3 * j, rb, cb);
-    for (int a = 0; a < 3; ++a) vrel[a] = (P.vel[3 * i + a] + ca[a]) - (P.vel[3 * j + a] + cb[a]);
-    contact_force(c, delta, n, vrel, dt, h, Fi);
+    double ca[3], cb[3], vrel[3], Fi[3], tq[3], spring[3] = {h[1], h[2], h[3]};
+    cross3(S.omega + 3 * i, ra, ca);
+    cross3(S.omega + 3 * j, rb, cb);
+    for (int a = 0; a < 3; ++a) vrel[a] = (S.vel[3 * i + a] + ca[a]) - (S.vel[3 * j + a] + cb[a]);
+    contact_force(c, delta, n, vrel, dt, spring, Fi);
     for (int a = 0; a < 3; ++a) {
-        atomicAdd(fc + 6 * i + a, Fi[a]);
-        atomicAdd(fc + 6 * j + a, -Fi[a]);
+        h[1 + a] = spring[a];
+        atomicAdd(S.fc + 6 * i + a, Fi[a]);
+        atomicAdd(S.fc + 6 * j + a, -Fi[a]);
     }
     cross3(ra, Fi, tq);
-    for (int a = 0; a < 3; ++a) atomicAdd(fc + 6 * i + 3 + a, tq[a]);
+    for (int a = 0; a < 3; ++a) atomicAdd(S.fc + 6 * i + 3 + a, tq[a]);
     cross3(rb, Fi, tq);
-    for (int a = 0; a < 3; ++a) atomicAdd(fc + 6 * j + 3 + a, -tq[a]);
+    for (int a = 0; a < 3; ++a) atomicAdd(S.fc + 6 * j + 3 + a, -tq[a]);
 }
 
-// Contact of pair (i < j): broad-phase test on the reach radii, then the
-// Newton search and force; the pair's history is record `slot` of particle i.
-__device__ __forceinline__ void pair_item(const PartDev& P, double* hist, double* fc,
-                                          const double* rch, const DemP& c, double dt,
-                                          const Geom& g, int i, int j, int slot)
+// Whether particle i can touch wall (ax, side).
+__device__ __forceinline__ bool near_wall(const StateG& S, int i, int ax, int side, const Geom& g)
 {
-    double* h = hist + ((int64_t)i * kPairSlots + slot) * kHist;
-    const double* xi = P.pos + 3 * i;
-    const double* xj = P.pos + 3 * j;
-    double sh[3], dv[3];
-    for (int a = 0; a < 3; ++a) {
-        const double d = xj[a] - xi[a];
-        sh[a] = 0.0;
-        if (g.per[a]) {
-            const double L = g.n[a];
-            if (d > 0.5 * L) sh[a] = -L;
-            else if (d < -0.5 * L) sh[a] = L;
-        }
-        dv[a] = d + sh[a];
-    }
-    const double rsi = P.rs[i], rsj = P.rs[j];
-    if (sqrt(dot3(dv, dv)) > rch[i] + rch[j] + rsi + rsj) {
-        // out of reach: forget the pair's contact (read one double instead of
-        // writing eight when the record is zero already)
-        if (h[0] != 0.0)
-            for (int k = 0; k < kHist; ++k) h[k] = 0.0;
-        return;
-    }
-    const int ai = P.off[i], ni = min(P.off[i + 1] - ai, kMaxPts);
-    const int aj = P.off[j], nj = min(P.off[j + 1] - aj, kMaxPts);
+    const double plane = side ? g.n[ax] - 0.5 : -0.5, sgn = side ? -1.0 : 1.0;
+    return !(sgn * (S.pos[3 * i + ax] - plane) > S.reach[i] + S.rs[i]);
+}
+
+// Contact of particle i with wall (ax, side) near it, record h: in-plane Newton
+// for the point of the wall plane where M is largest, the contact test and the
+// force.
+__device__ __forceinline__ void wall_contact(const PartDev& P, const StateG& S, double* h, int i,
+                                             int ax, int side, const DemP& c, double dt,
+                                             const Geom& g)
+{
+    const double plane = side ? g.n[ax] - 0.5 : -0.5, sgn = side ? -1.0 : 1.0;
+    const double xa = S.pos[3 * i + ax];
+    const double active = h[0];
+    const int ai = S.off[i], ni = min(S.off[i + 1] - ai, kMaxPts);
     const double* pi = P.wpts + 3 * (int64_t)ai;
-    const double* pj = P.wpts + 3 * (int64_t)aj;
-    double x[3];
-    if (h[0] != 0.0) {
-        for (int a = 0; a < 3; ++a) x[a] = xi[a] + h[4 + a];
+    const double* Ki = P.K + ai;
+    const int t1 = (ax + 1) % 3, t2 = (ax + 2) % 3;
+    // coordinates along (ax, t1, t2)
+    double y1, y2;
+    if (active != 0.0) {
+        y1 = S.pos[3 * i + t1] + h[4 + t1];
+        y2 = S.pos[3 * i + t2] + h[4 + t2];
     } else {
         double best = INFINITY;
-        for (int u = 0; u < ni; ++u)
-            for (int v = 0; v < nj; ++v) {
-                double d2 = 0.0;
-                for (int a = 0; a < 3; ++a) {
-                    const double dd = pi[3 * u + a] - (pj[3 * v + a] + sh[a]);
-                    d2 += dd * dd;
-                }
-                if (d2 < best) {
-                    best = d2;
-                    for (int a = 0; a < 3; ++a) x[a] = 0.5 * (pi[3 * u + a] + pj[3 * v + a] + sh[a]);
-                }
+        int at = 0;
+        for (int u = 0; u < ni; ++u) {
+            const double dd = fabs(pi[3 * u + ax] - plane);
+            if (dd < best) {
+                best = dd;
+                at = u;
             }
+        }
+        y1 = pi[3 * at + t1];
+        y2 = pi[3 * at + t2];
     }
-    if (ni <= kRegPts && nj <= kRegPts)
-        pair_contact(BodyR(pi, P.K + ai, ni), BodyR(pj, P.K + aj, nj), x, h, xi, xj, sh, i, j, rsi,
-                     rsj, P, c, dt, fc);
-    else
-        pair_contact(BodyG{pi, P.K + ai, ni}, BodyG{pj, P.K + aj, nj}, x, h, xi, xj, sh, i, j,
-                     rsi, rsj, P, c, dt, fc);
+    bool conv = false;
+    for (int it = 0; it < c.niter; ++it) {
+        double M = 0.0, gr[3] = {0, 0, 0}, H[6] = {0, 0, 0, 0, 0, 0};
+        for (int u = 0; u < ni; ++u) {
+            const double r[3] = {plane - pi[3 * u + ax], y1 - pi[3 * u + t1], y2 - pi[3 * u + t2]};
+            add_point(Ki[u], r, fast_rcp(dot3(r, r)), M, gr, H);
+        }
+        const double h11 = H[3], h12 = H[4], h22 = H[5];
+        const double det = h11 * h22 - h12 * h12;
+        if (!(fabs(det) > 0.0) || !isfinite(det)) break;
+        const double d1 = -(h22 * gr[1] - h12 * gr[2]) / det;
+        const double d2 = -(-h12 * gr[1] + h11 * gr[2]) / det;
+        y1 += d1;
+        y2 += d2;
+        if (sqrt(d1 * d1 + d2 * d2) < c.ntol) {
+            conv = true;
+            break;
+        }
+    }
+    if (!conv) return clear_record(h);
+    double M = 0.0, gr[3] = {0, 0, 0};
+    for (int u = 0; u < ni; ++u) {
+        const double r[3] = {plane - pi[3 * u + ax], y1 - pi[3 * u + t1], y2 - pi[3 * u + t2]};
+        const double t = Ki[u] / dot3(r, r), s = 2.0 * t / dot3(r, r);
+        M += t;
+        for (int a = 0; a < 3; ++a) gr[a] -= s * r[a];
+    }
+    if (!(sgn * gr[0] > 0.0)) return clear_record(h);
+    const double rel[3] = {plane - xa, y1 - S.pos[3 * i + t1], y2 - S.pos[3 * i + t2]};
+    h[0] = 1.0;
+    h[4 + ax] = rel[0];
+    h[4 + t1] = rel[1];
+    h[4 + t2] = rel[2];
+    const double qR = (1.0 - M) / dot3(gr, gr);
+    const double delta = S.rs[i] - sgn * (qR * gr[0]);
+    if (delta <= 0.0) {
+        h[1] = h[2] = h[3] = 0.0;
+        return;
+    }
+    // back in (x, y, z)
+    double n[3], ra[3];
+    for (int a = 0; a < 3; ++a) {
+        n[a] = a == ax ? sgn : 0.0;
+        ra[a] = (a == ax ? rel[0] : (a == t1 ? rel[1] : rel[2])) - 0.5 * delta * n[a];
+    }
+    double ca[3], vrel[3], Fi[3], tq[3], spring[3] = {h[1], h[2], h[3]};
+    cross3(S.omega + 3 * i, ra, ca);
+    for (int a = 0; a < 3; ++a) vrel[a] = S.vel[3 * i + a] + ca[a];
+    contact_force(c, delta, n, vrel, dt, spring, Fi);
+    cross3(ra, Fi, tq);
+    for (int a = 0; a < 3; ++a) {
+        h[1 + a] = spring[a];
+        atomicAdd(S.fc + 6 * i + a, Fi[a]);
+        atomicAdd(S.fc + 6 * i + 3 + a, tq[a]);
+    }
 }
 
-// Whether pair (i, j) is a candidate of a dem_step call of duration T: the
-// centres are within the reach radii, R_s and a skin that covers the
+// ---------------------------------------------------------------------------
+// Broad phase.  Pair (i, j) is a candidate of a dem_step call of duration T
+// when the centres are within the reach radii, R_s and a skin that covers the
 // relative displacement of the call, (|v_i| + |v_j|) T + 1/2 (velocities
 // change by far less than 1/4 lu per lattice step under the accelerations of
-// a stable run).  A pair outside it cannot come into reach during the call.
-__device__ bool pair_candidate(const PartDev& P, int i, int j, double T, const Geom& g)
+// a stable run), i.e. within bound_i + bound_j with bound = reach + R_s +
+// |v| T + 1/4.  A pair outside it cannot come into reach during the call.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ bool within(const double xi[3], const double* xj, double lim,
+                                       const Geom& g)
 {
     double d2 = 0.0;
     for (int a = 0; a < 3; ++a) {
-        double d = P.pos[3 * j + a] - P.pos[3 * i + a];
+        double d = xj[a] - xi[a];
         if (g.per[a]) {
             const double L = g.n[a];
             if (d > 0.5 * L) d -= L;
@@ -427,80 +593,76 @@ __device__ bool pair_candidate(const PartDev& P, int i, int j, double T, const G
         }
         d2 += d * d;
     }
-    const double* vi = P.vel + 3 * i;
-    const double* vj = P.vel + 3 * j;
-    const double skin = (sqrt(dot3(vi, vi)) + sqrt(dot3(vj, vj))) * T + 0.5;
-    const double thr = reach(P, i) + reach(P, j) + P.rs[i] + P.rs[j] + skin;
-    return sqrt(d2) <= thr;
+    return sqrt(d2) <= lim;
 }
 
-// The history records of pairs that are no longer candidates are released
-// (zeroed, slot freed): one thread per (particle, slot).  A slot's key is
-// the partner's index + 1, 0 when free, so zeroed state is empty.
-__global__ __launch_bounds__(256) void k_pair_release(PartDev P, double* hist, int32_t* key,
-                                                      double T, Geom g, uint32_t* count)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (count && t == 0) *count = 0u;  // the pair list of this call starts empty
-    if (t >= (int64_t)P.n * kPairSlots) return;
-    const int j = key[t] - 1;
-    if (j < 0) return;
-    const int i = (int)(t / kPairSlots);
-    if (pair_candidate(P, i, j, T, g)) return;
-    double* h = hist + t * kHist;
-    for (int k = 0; k < kHist; ++k) h[k] = 0.0;
-    key[t] = 0;
-}
+// The contact records of particle i, one per lane of its wave (lanes below
+// kPairSlots): each holds its partner's index + 1, 0 when free (zeroed state is
+// empty).  Only i's wave touches i's records.
+struct Slots {
+    int32_t key;
+    bool full;  // a candidate found no free record
+};
 
-// Candidate pairs of one dem_step call, one thread per (i, j): a candidate
-// pair i < j finds its history record among particle i's slots, or claims a
-// free one (released records are zero), and is appended as
-// slot << 32 | i << 16 | j, one atomic per wave.  A particle with more
-// candidate partners than slots latches kDeferredSlots (the pair is left
-// out).
-__global__ __launch_bounds__(256) void k_pairs(PartDev P, int32_t* key, double T, Geom g,
-                                               uint64_t* list, uint32_t* count, uint32_t* deferred)
+// The candidates among the wave's 64 partners (lane's partner jj, `take` when
+// it is one) find their record or claim a free one, in ascending lane order.
+__device__ __forceinline__ void claim(Slots& s, bool take, int jj)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int np = P.n;
-    bool take = false;
-    int i = 0, j = 0, slot = -1;
-    if (t < (int64_t)np * np) {
-        i = (int)(t / np);
-        j = (int)(t % np);
-        take = i < j && pair_candidate(P, i, j, T, g);
-    }
-    if (take) {
-        int32_t* ki = key + (int64_t)i * kPairSlots;
-        for (int s = 0; s < kPairSlots && slot < 0; ++s)
-            if (ki[s] == j + 1) slot = s;
-        for (int s = 0; s < kPairSlots && slot < 0; ++s)
-            if (atomicCAS(ki + s, 0, j + 1) == 0) slot = s;
-        if (slot < 0) {
-            atomicOr(deferred, kDeferredSlots);
-            take = false;
-        }
-    }
-    const uint64_t m = __ballot(take);
-    if (m == 0) return;
     const int lane = threadIdx.x & 63;
-    uint32_t base = 0;
-    if (lane == __ffsll((unsigned long long)m) - 1) base = atomicAdd(count, (uint32_t)__popcll(m));
-    base = __shfl(base, __ffsll((unsigned long long)m) - 1, 64);
-    if (take) {
-        const uint32_t below = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-        list[base + below] = ((uint64_t)slot << 32) | ((uint64_t)i << 16) | (uint64_t)j;
+    uint64_t m = __ballot(take);
+    while (m) {
+        const int src = __ffsll((unsigned long long)m) - 1;
+        m &= m - 1;
+        const int32_t k = __builtin_amdgcn_readlane(jj, src) + 1;
+        if (__ballot(s.key == k)) continue;  // has its record
+        const uint64_t free = __ballot(lane < kPairSlots && s.key == 0);
+        if (!free) {
+            s.full = true;
+            continue;
+        }
+        if (lane == __ffsll((unsigned long long)free) - 1) s.key = k;
     }
 }
 
-// ---------------------------------------------------------------------------
-// Broad phase on a cell grid (many particles): every pair that
-// pair_candidate accepts is at most H = 2 max_p (reach_p + R_s,p) + 2 max_p
-// |v_p| T + 1/2 apart, so with cells at least H wide (fewer cells than the
-// arrays hold: wider) its particles lie in the same or adjacent cells.  The
-// same pairs, records and latch as k_pairs; only the list's order differs,
-// and the contact forces are summed by atomics in any order either way.
-// ---------------------------------------------------------------------------
+// Reach, R_s and the candidate bound of every particle; the pair list emptied.
+__global__ __launch_bounds__(64) void k_reach(PartDev P, double T, double* rch, double* bound,
+                                              uint32_t* count)
+{
+    const int p = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (p == 0) *count = 0u;
+    if (p >= P.n) return;
+    const double r = reach(P, p);
+    const double* v = P.vel + 3 * p;
+    rch[p] = r;
+    bound[p] = r + P.rs[p] + sqrt(dot3(v, v)) * T + 0.25;
+}
+
+// The cells around c along an axis of nc: lo, lo + 1, ... (n of them), wrapped
+// on a periodic axis (each once), clipped at walls.
+struct Around {
+    int lo, n, nc;
+    __device__ __forceinline__ int cell(int k) const
+    {
+        const int v = lo + k;
+        return v < 0 ? v + nc : (v >= nc ? v - nc : v);
+    }
+};
+__device__ __forceinline__ Around around(int c, int nc, int per)
+{
+    if (per) return nc >= 3 ? Around{c - 1, 3, nc} : Around{0, nc, nc};
+    const int lo = max(c - 1, 0);
+    return Around{lo, min(c + 1, nc - 1) - lo + 1, nc};
+}
+
+// Candidate pairs of one dem_step call, a wave per particle i: the records of
+// pairs that are candidates no more are released (zeroed, slot freed), the
+// candidates j > i find their record or claim a free one (a particle with more
+// candidate partners than slots latches kDeferredSlots; the pair is left out),
+// and the pairs with a record are appended as slot << 32 | i << 16 | j, one
+// atomic per workgroup of 16 particles (8000 atomics on the one count, one a
+// wave, took 90 us).  With GRID the partners are those of the cells around i's
+// (every accepted pair lies within H, and cells are at least H wide), else all.
+// A wave per particle keeps the walk short and needs no atomic on a record.
 __device__ __forceinline__ int grid_cell(const PartDev& P, int p, const Geom& g,
                                          const int32_t* gdim, const double* gsize, int c3[3])
 {
@@ -513,16 +675,92 @@ __device__ __forceinline__ int grid_cell(const PartDev& P, int p, const Geom& g,
     return c3[0] + gdim[0] * (c3[1] + gdim[1] * c3[2]);
 }
 
+template <bool GRID>
+__global__ __launch_bounds__(1024) void k_pairs(PartDev P, double* hist, int32_t* key,
+                                               const double* bound, Geom g, const int32_t* gdim,
+                                               const double* gsize, const uint32_t* gstart,
+                                               const uint32_t* gitem, uint64_t* list,
+                                               uint32_t* count, uint32_t* deferred)
+{
+    __shared__ uint32_t found[16], base0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int id = (int)(blockIdx.x * 16u) + wave;
+    const bool on = id < P.n;  // uniform over the wave
+    const int i = on ? id : 0;
+    const double xi[3] = {P.pos[3 * i], P.pos[3 * i + 1], P.pos[3 * i + 2]};
+    const double bi = bound[i];
+    Slots s{0, false};
+    if (on && lane < kPairSlots) {
+        s.key = key[(int64_t)i * kPairSlots + lane];
+        if (s.key > 0 && !within(xi, P.pos + 3 * (s.key - 1), bi + bound[s.key - 1], g)) {
+            clear_record(hist + ((int64_t)i * kPairSlots + lane) * kHist);
+            s.key = 0;
+        }
+    }
+    if constexpr (GRID) {
+        // a lane per cell around i's; their particles flattened over the wave
+        int c3[3];
+        grid_cell(P, i, g, gdim, gsize, c3);
+        const Around A0 = around(c3[0], gdim[0], g.per[0]), A1 = around(c3[1], gdim[1], g.per[1]),
+                     A2 = around(c3[2], gdim[2], g.per[2]);
+        uint32_t first = 0, cnt = 0;
+        const int r = lane % 3, t = (lane / 3) % 3, u = lane / 9;
+        if (on && r < A0.n && t < A1.n && u < A2.n) {
+            const int cell = A0.cell(r) + gdim[0] * (A1.cell(t) + gdim[1] * A2.cell(u));
+            first = gstart[cell];
+            cnt = gstart[cell + 1] - first;
+        }
+        uint32_t incl = cnt;
+        for (int o = 1; o < 32; o <<= 1) {
+            const uint32_t t = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += t;
+        }
+        const uint32_t total = __shfl(incl, 26, 64);  // lanes from 27 on add nothing
+        const uint32_t shift = first - (incl - cnt);  // item of flat index k: k + shift
+        for (uint32_t k0 = 0; k0 < total; k0 += 64u) {
+            const uint32_t k = k0 + (uint32_t)lane;
+            int c = 0;  // the cell of flat index k: the number of cells that end at or before it
+            for (int step = 16; step > 0; step >>= 1)
+                if (__shfl(incl, min(c + step, 27) - 1, 64) <= k && c + step <= 26) c += step;
+            const uint32_t sh = __shfl(shift, c, 64);
+            const int j = k < total ? (int)gitem[k + sh] : -1;
+            claim(s, j > i && within(xi, P.pos + 3 * j, bi + bound[j], g), j);
+        }
+    } else {
+        for (int j0 = on ? i + 1 : P.n; j0 < P.n; j0 += 64) {
+            const int j = j0 + lane;
+            claim(s, j < P.n && within(xi, P.pos + 3 * j, bi + bound[j], g), j);
+        }
+    }
+    if (on && lane < kPairSlots) key[(int64_t)i * kPairSlots + lane] = s.key;
+    if (s.full && lane == 0) atomicOr(deferred, kDeferredSlots);
+    const uint64_t m = __ballot(s.key != 0);
+    if (lane == 0) found[wave] = (uint32_t)__popcll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t total = 0;
+        for (int w = 0; w < 16; ++w) total += found[w];
+        base0 = total ? atomicAdd(count, total) : 0u;
+    }
+    __syncthreads();
+    uint32_t base = base0;
+    for (int w = 0; w < wave; ++w) base += found[w];
+    if (s.key != 0)
+        list[base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] =
+            ((uint64_t)lane << 32) | ((uint64_t)i << 16) | (uint64_t)(s.key - 1);
+}
+
 // One workgroup: the cell width from the particles, the grid's shape, and
 // the counts cleared.
-__global__ __launch_bounds__(1024) void k_grid_setup(PartDev P, double T, Geom g, int32_t* gdim,
+__global__ __launch_bounds__(1024) void k_grid_setup(PartDev P, const double* rch, double T,
+                                                     Geom g, int32_t* gdim,
                                                      double* gsize, uint32_t* gcount, int64_t gcap)
 {
     __shared__ double red[2][16];
     __shared__ int ncell;
     double h = 0.0, v = 0.0;
     for (int p = (int)threadIdx.x; p < P.n; p += (int)blockDim.x) {
-        h = fmax(h, reach(P, p) + P.rs[p]);
+        h = fmax(h, rch[p] + P.rs[p]);
         const double* vp = P.vel + 3 * p;
         v = fmax(v, sqrt(dot3(vp, vp)));
     }
@@ -622,213 +860,176 @@ __global__ __launch_bounds__(256) void k_grid_scatter(PartDev P, Geom g, const i
     gitem[slot] = (uint32_t)p;
 }
 
-// The cells around one along an axis: c - 1, c, c + 1, wrapped on a
-// periodic axis, clipped at walls, each once.
-__device__ __forceinline__ int around(int c, int nc, int per, int out[3])
-{
-    int m = 0;
-    for (int d = -1; d <= 1; ++d) {
-        int k = c + d;
-        if (k < 0 || k >= nc) {
-            if (!per) continue;
-            k = (k + nc) % nc;
-        }
-        bool seen = false;
-        for (int t = 0; t < m; ++t) seen = seen || out[t] == k;
-        if (!seen) out[m++] = k;
-    }
-    return m;
-}
+// ---------------------------------------------------------------------------
+// Substeps, many particles
+// ---------------------------------------------------------------------------
 
-// One thread per particle i: the partners j > i in the cells around i's.
-__global__ __launch_bounds__(256) void k_pairs_grid(PartDev P, int32_t* key, double T, Geom g,
-                                                    const int32_t* gdim, const double* gsize,
-                                                    const uint32_t* gstart, const uint32_t* gitem,
-                                                    uint64_t* list, uint32_t* count,
-                                                    uint32_t* deferred)
-{
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i >= P.n) return;
-    int c3[3];
-    grid_cell(P, i, g, gdim, gsize, c3);
-    int ax[3][3], na[3];
-    for (int a = 0; a < 3; ++a) na[a] = around(c3[a], gdim[a], g.per[a], ax[a]);
-    int32_t* ki = key + (int64_t)i * kPairSlots;
-    // every accepted pair lies within H (gsize[3]): a cheaper distance test
-    // first, then pair_candidate's own decision
-    const double hb2 = gsize[3] * gsize[3];
-    for (int u = 0; u < na[2]; ++u)
-        for (int t = 0; t < na[1]; ++t)
-            for (int s = 0; s < na[0]; ++s) {
-                const int cell = ax[0][s] + gdim[0] * (ax[1][t] + gdim[1] * ax[2][u]);
-                for (uint32_t k = gstart[cell]; k < gstart[cell + 1]; ++k) {
-                    const int j = (int)gitem[k];
-                    if (j <= i) continue;
-                    double d2 = 0.0;
-                    for (int a = 0; a < 3; ++a) {
-                        double d = P.pos[3 * j + a] - P.pos[3 * i + a];
-                        if (g.per[a]) {
-                            const double L = g.n[a];
-                            if (d > 0.5 * L) d -= L;
-                            else if (d < -0.5 * L) d += L;
-                        }
-                        d2 += d * d;
-                    }
-                    if (!(d2 <= hb2) || !pair_candidate(P, i, j, T, g)) continue;
-                    int slot = -1;
-                    for (int q = 0; q < kPairSlots && slot < 0; ++q)
-                        if (ki[q] == j + 1) slot = q;
-                    for (int q = 0; q < kPairSlots && slot < 0; ++q)
-                        if (atomicCAS(ki + q, 0, j + 1) == 0) slot = q;
-                    if (slot < 0) {
-                        atomicOr(deferred, kDeferredSlots);
-                        continue;
-                    }
-                    const uint32_t at = atomicAdd(count, 1u);
-                    list[at] = ((uint64_t)slot << 32) | ((uint64_t)i << 16) | (uint64_t)j;
-                }
-            }
-}
-
-// One substep's contacts: the walls of every body (6 n items), then the
-// listed pairs; thread t of nthreads strides over both.
-__device__ void contacts(const PartDev& P, double* hist, double* hist_w, double* fc,
-                         const double* rch, const DemP& c, double dt, const Geom& g,
-                         const uint64_t* list, const uint32_t* count, int64_t t0, int64_t nthreads)
-{
-    const int64_t nw = (int64_t)P.n * 6;
-    const int64_t total = nw + (int64_t)*count;
-    for (int64_t t = t0; t < total; t += nthreads) {
-        if (t < nw) {
-            wall_contact(P, (int)t, hist_w, fc, rch, c, dt, g);
-        } else {
-            const uint64_t e = list[t - nw];
-            pair_item(P, hist, fc, rch, c, dt, g, (int)((e >> 16) & 0xffffu), (int)(e & 0xffffu),
-                      (int)(e >> 32));
-        }
-    }
-}
-
+// One substep's contacts: the first workgroups take the walls of the
+// non-periodic axes (a thread per particle and wall), the others stride over
+// the listed pairs, G lanes each.
+template <int G>
 __global__ __launch_bounds__(256) void k_contacts(PartDev P, double* hist, double* hist_w, double* fc,
                                                   const double* rch, DemP c, double dt, Geom g,
-                                                  const uint64_t* list, const uint32_t* count)
+                                                  const uint64_t* list, const uint32_t* count,
+                                                  uint32_t wall_blocks, int n_axes, int ax0, int ax1,
+                                                  int ax2)
 {
-    contacts(P, hist, hist_w, fc, rch, c, dt, g, list, count,
-             (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
+    const StateG S{P.pos, P.vel, P.omega, P.rs, rch, fc, P.off};
+    if (blockIdx.x < wall_blocks) {
+        const int t = (int)(blockIdx.x * 256u + threadIdx.x);
+        const int per = 2 * n_axes;
+        if (t >= P.n * per) return;
+        const int k = (t % per) >> 1, i = t / per, side = t & 1;
+        const int ax = k == 0 ? ax0 : (k == 1 ? ax1 : ax2);
+        double* h = hist_w + ((int64_t)i * 6 + 2 * ax + side) * kHist;
+        if (near_wall(S, i, ax, side, g))
+            wall_contact(P, S, h, i, ax, side, c, dt, g);
+        else if (h[0] != 0.0)
+            clear_record(h);
+        return;
+    }
+    const uint32_t n = *count;
+    const uint32_t stride = (gridDim.x - wall_blocks) * (256u / G);
+    for (uint32_t t = (blockIdx.x - wall_blocks) * (256u / G) + threadIdx.x / G; t < n; t += stride) {
+        const uint64_t e = list[t];
+        pair_item<G>(P, S, hist, c, dt, g, (int)((e >> 16) & 0xffffu), (int)(e & 0xffffu),
+                     (int)(e >> 32), (int)(threadIdx.x % G));
+    }
 }
 
-// In-plane Newton for the point of the wall plane where M is largest, the
-// contact test and the force of body i on wall (ax, side); A supplies the
-// body's metaball sums.
-template <class BA>
-__device__ __forceinline__ void wall_newton(const BA& A, double x[3], double* h, const double* xi, int i, int ax,
-                            int t1, int t2, double sgn, const PartDev& P, const DemP& c, double dt,
-                            double* fc)
+// SECOND: the second half kick of a substep; FIRST: the first half kick,
+// drift, rotation and world control points of the next, clearing the contact
+// sums.  Both read the contact sum of the substep before.
+template <bool SECOND, bool FIRST>
+__global__ __launch_bounds__(64) void k_advance(PartDev P, const double* FTh, double* fc, DemP c,
+                                                double dt, Geom g)
 {
-    const double z3[3] = {0.0, 0.0, 0.0};
-    double M, gr[3], H[9];
-    bool conv = false;
-    for (int it = 0; it < c.niter; ++it) {
-        A.eval(z3, x, M, gr, H);
-        const double h11 = H[3 * t1 + t1], h12 = H[3 * t1 + t2], h22 = H[3 * t2 + t2];
-        const double det = h11 * h22 - h12 * h12;
-        if (!(fabs(det) > 0.0) || !isfinite(det)) break;
-        const double d1 = -(h22 * gr[t1] - h12 * gr[t2]) / det;
-        const double d2 = -(-h12 * gr[t1] + h11 * gr[t2]) / det;
-        x[t1] += d1;
-        x[t2] += d2;
-        if (sqrt(d1 * d1 + d2 * d2) < c.ntol) {
-            conv = true;
-            break;
+    const int p = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (p >= P.n) return;
+    Body b = load_body(P, p, FTh, c, 0.5 * dt);
+    double f[6];
+    for (int k = 0; k < 6; ++k) f[k] = fc[6 * p + k];
+    if constexpr (SECOND) half_kick(b, f, true);
+    if constexpr (FIRST) {
+        half_kick(b, f, false);
+        drift(P, b, dt, g);
+        for (int k = 0; k < 6; ++k) fc[6 * p + k] = 0.0;
+    }
+    store_body(P, p, b, FIRST);
+}
+
+// ---------------------------------------------------------------------------
+// A whole dem_step call in one workgroup
+// ---------------------------------------------------------------------------
+constexpr int kBlockThreads = 512;
+// Lanes that share a pair: the Newton chain of one lane over the 4 to 12
+// points of two metaballs is what a substep waits for (32-43 us at 1000
+// metaballs, about 16 with four lanes).
+constexpr int kPairLanes = 4;
+
+__global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* hist, double* hist_w,
+                                                             int32_t* key, const double* FTh,
+                                                             double* fc, uint64_t* list, DemP c,
+                                                             int n_sub, double dt, Geom g,
+                                                             uint32_t* deferred)
+{
+    __shared__ double pos[3 * kBlockParticles], vel[3 * kBlockParticles], om[3 * kBlockParticles];
+    __shared__ double sum[6 * kBlockParticles], rs[kBlockParticles], rch[kBlockParticles];
+    __shared__ double bound[kBlockParticles];
+    __shared__ int32_t off[kBlockParticles + 1];
+    __shared__ uint32_t npairs;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, n = P.n;
+    const StateG S{pos, vel, om, rs, rch, sum, off};
+    Body b{};
+    double f[6] = {0, 0, 0, 0, 0, 0};
+    auto publish = [&](bool pose) {
+        for (int a = 0; a < 3; ++a) {
+            if (pose) pos[3 * tid + a] = b.x[a];
+            vel[3 * tid + a] = b.v[a];
+            om[3 * tid + a] = b.w[a];
         }
+    };
+    uint32_t touched = 0;  // this particle's wall records that are not zero
+    if (tid == 0) npairs = 0u;
+    if (tid <= n) off[tid] = P.off[tid];
+    if (tid < n) {
+        for (int k = 0; k < 6; ++k)
+            touched |= hist_w[((int64_t)tid * 6 + k) * kHist] != 0.0 ? 1u << k : 0u;
+        b = load_body(P, tid, FTh, c, 0.5 * dt);
+        for (int k = 0; k < 6; ++k) f[k] = fc[6 * tid + k];
+        rs[tid] = P.rs[tid];
+        rch[tid] = reach(P, tid);
+        bound[tid] = rch[tid] + rs[tid] + sqrt(dot3(b.v, b.v)) * ((double)n_sub * dt) + 0.25;
+        publish(true);
     }
-    if (!conv) {
-        for (int k = 0; k < kHist; ++k) h[k] = 0.0;
-        return;
-    }
-    A.eval(z3, x, M, gr, H);
-    if (!(sgn * gr[ax] > 0.0)) {
-        for (int k = 0; k < kHist; ++k) h[k] = 0.0;
-        return;
-    }
-    h[0] = 1.0;
-    for (int a = 0; a < 3; ++a) h[4 + a] = x[a] - xi[a];
-    const double qR = (1.0 - M) / dot3(gr, gr);
-    const double delta = P.rs[i] - sgn * (qR * gr[ax]);
-    if (delta <= 0.0) {
-        h[1] = h[2] = h[3] = 0.0;
-        return;
-    }
-    double n[3] = {0.0, 0.0, 0.0}, xcp[3], ra[3];
-    n[ax] = sgn;
-    for (int a = 0; a < 3; ++a) {
-        xcp[a] = x[a] - 0.5 * delta * n[a];
-        ra[a] = xcp[a] - xi[a];
-    }
-    double ca[3], vrel[3], Fi[3], tq[3];
-    cross3(P.omega + 3 * i, ra, ca);
-    for (int a = 0; a < 3; ++a) vrel[a] = P.vel[3 * i + a] + ca[a];
-    contact_force(c, delta, n, vrel, dt, h, Fi);
-    cross3(ra, Fi, tq);
-    for (int a = 0; a < 3; ++a) {
-        atomicAdd(fc + 6 * i + a, Fi[a]);
-        atomicAdd(fc + 6 * i + 3 + a, tq[a]);
-    }
-}
-
-__device__ void wall_contact(const PartDev& P, int t, double* hist, double* fc, const double* rch,
-                             const DemP& c, double dt, const Geom& g)
-{
-    const int i = t / 6, ax = (t % 6) / 2, side = t % 2;
-    if (g.per[ax]) return;
-    double* h = hist + (int64_t)t * kHist;
-    const double plane = side ? g.n[ax] - 0.5 : -0.5, sgn = side ? -1.0 : 1.0;
-    const double* xi = P.pos + 3 * i;
-    if (sgn * (xi[ax] - plane) > rch[i] + P.rs[i]) {
-        if (h[0] != 0.0)
-            for (int k = 0; k < kHist; ++k) h[k] = 0.0;
-        return;
-    }
-    const int ai = P.off[i], ni = min(P.off[i + 1] - ai, kMaxPts);
-    const double* pi = P.wpts + 3 * (int64_t)ai;
-    const int t1 = (ax + 1) % 3, t2 = (ax + 2) % 3;
-    double x[3];
-    if (h[0] != 0.0) {
-        for (int a = 0; a < 3; ++a) x[a] = xi[a] + h[4 + a];
-    } else {
-        double best = INFINITY;
-        for (int u = 0; u < ni; ++u) {
-            const double dd = fabs(pi[3 * u + ax] - plane);
-            if (dd < best) {
-                best = dd;
-                for (int a = 0; a < 3; ++a) x[a] = pi[3 * u + a];
+    __syncthreads();
+    // candidate pairs, as k_pairs
+    for (int i = wave; i < n; i += kBlockThreads / 64) {
+        const double xi[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
+        Slots s{0, false};
+        if (lane < kPairSlots) {
+            s.key = key[i * kPairSlots + lane];
+            const int j = s.key - 1;
+            if (s.key > 0 && !within(xi, pos + 3 * j, bound[i] + bound[j], g)) {
+                clear_record(hist + ((int64_t)i * kPairSlots + lane) * kHist);
+                s.key = 0;
             }
         }
+        for (int j0 = i + 1; j0 < n; j0 += 64) {
+            const int j = j0 + lane;
+            claim(s, j < n && within(xi, pos + 3 * min(j, n - 1), bound[i] + bound[min(j, n - 1)], g), j);
+        }
+        if (lane < kPairSlots) key[i * kPairSlots + lane] = s.key;
+        if (s.full && lane == 0) atomicOr(deferred, kDeferredSlots);
+        const uint64_t m = __ballot(s.key != 0);
+        uint32_t base = 0;
+        if (lane == 0 && m) base = atomicAdd(&npairs, (uint32_t)__popcll(m));
+        base = __shfl(base, 0, 64);
+        if (s.key != 0)
+            list[base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] =
+                ((uint64_t)lane << 32) | ((uint64_t)i << 16) | (uint64_t)(s.key - 1);
     }
-    x[ax] = plane;
-    if (ni <= kRegPts)
-        wall_newton(BodyR(pi, P.K + ai, ni), x, h, xi, i, ax, t1, t2, sgn, P, c, dt, fc);
-    else
-        wall_newton(BodyG{pi, P.K + ai, ni}, x, h, xi, i, ax, t1, t2, sgn, P, c, dt, fc);
-}
-
-__global__ void k_second_half(PartDev P, const double* FTh, const double* fc, DemP c, double dt)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P.n) return;
-    half_kick(P, p, FTh, fc, c, 0.5 * dt, true);
-}
-
-// The second half kick of substep s and the first half of substep s + 1 of
-// particle p in one launch: both read the contact sum of substep s, which
-// the first half then clears.
-__global__ void k_between(PartDev P, const double* FTh, double* fc, double* reach_out, DemP c,
-                          double dt, Geom g)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P.n) return;
-    half_kick(P, p, FTh, fc, c, 0.5 * dt, true);
-    first_half(P, p, FTh, fc, reach_out, c, dt, g);
+    __syncthreads();
+    const int group = (kBlockThreads - 1 - tid) / kPairLanes;
+    const uint64_t e0 = group < (int)npairs ? list[group] : 0;
+    for (int sub = 0; sub < n_sub; ++sub) {
+        if (tid < n) {
+            half_kick(b, f, false);
+            drift(P, b, dt, g);
+            publish(true);
+            for (int k = 0; k < 6; ++k) sum[6 * tid + k] = 0.0;
+        }
+        __syncthreads();
+        // walls by the particles' own threads, pairs from the last wave down
+        if (tid < n)
+            for (int ax = 0; ax < 3; ++ax)
+                if (!g.per[ax])
+                    for (int side = 0; side < 2; ++side) {
+                        const uint32_t bit = 1u << (2 * ax + side);
+                        double* h = hist_w + ((int64_t)tid * 6 + 2 * ax + side) * kHist;
+                        if (near_wall(S, tid, ax, side, g)) {
+                            wall_contact(P, S, h, tid, ax, side, c, dt, g);
+                            touched |= bit;
+                        } else if (touched & bit) {
+                            clear_record(h);
+                            touched &= ~bit;
+                        }
+                    }
+        for (int t = group; t < (int)npairs; t += kBlockThreads / kPairLanes) {
+            const uint64_t e = t == group ? e0 : list[t];
+            pair_item<kPairLanes>(P, S, hist, c, dt, g, (int)((e >> 16) & 0xffffu), (int)(e & 0xffffu),
+                                  (int)(e >> 32), tid % kPairLanes);
+        }
+        __syncthreads();
+        if (tid < n) {
+            for (int k = 0; k < 6; ++k) f[k] = sum[6 * tid + k];
+            half_kick(b, f, true);
+        }
+    }
+    if (tid < n) {
+        store_body(P, tid, b, true);
+        for (int k = 0; k < 6; ++k) fc[6 * tid + k] = f[k];
+    }
 }
 
 }  // namespace
@@ -849,46 +1050,56 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
     c.niter = prm.newton_iter;
     for (int a = 0; a < 3; ++a) c.g[a] = prm.gravity[a];
     c.rhof = prm.rho_f;
-    const uint32_t bp = (np + 63) / 64;
-    // candidate pairs for the whole call: histories of pairs that dropped out
-    // are released first, so that their slots can be claimed again
+    uint32_t* deferred = ctx->ctr + kCtrDeferred;
+    const Geom& g = ctx->geom;
+    if (np <= kBlockParticles) {
+        hipLaunchKernelGGL(k_dem_block, dim3(1), dim3(kBlockThreads), 0, ctx->stream, P, ctx->hist_pp,
+                           ctx->hist_pw, ctx->hist_key, ctx->FT, ctx->fc, ws.pairs, c, n_sub, dt, g,
+                           deferred);
+        return hipGetLastError();
+    }
+    const uint32_t bp = (uint32_t)(np + 63) / 64, bw = (uint32_t)(np + 15) / 16;
     const double T = (double)n_sub * dt;
-    const uint32_t br = (uint32_t)(((int64_t)np * kPairSlots + 255) / 256);
-    const uint32_t bq = (uint32_t)(((int64_t)np * np + 255) / 256);
-    hipLaunchKernelGGL(k_pair_release, dim3(br), dim3(256), 0, ctx->stream, P, ctx->hist_pp,
-                       ctx->hist_key, T, ctx->geom, ws.count);
+    hipLaunchKernelGGL(k_reach, dim3(bp), dim3(64), 0, ctx->stream, P, T, ws.reach, ws.bound, ws.count);
     if (ws.gcount && np >= kGridMinParticles) {
         const uint32_t bn = (uint32_t)((np + 255) / 256);
-        hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(1024), 0, ctx->stream, P, T, ctx->geom,
+        hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(1024), 0, ctx->stream, P, ws.reach, T, g,
                            ws.gdim, ws.gsize, ws.gcount, ws.gcap);
-        hipLaunchKernelGGL(k_grid_count, dim3(bn), dim3(256), 0, ctx->stream, P, ctx->geom, ws.gdim,
+        hipLaunchKernelGGL(k_grid_count, dim3(bn), dim3(256), 0, ctx->stream, P, g, ws.gdim,
                            ws.gsize, ws.gcount);
         hipLaunchKernelGGL(k_grid_scan, dim3(1), dim3(1024), 0, ctx->stream, ws.gdim, ws.gcount,
                            ws.gcursor);
-        hipLaunchKernelGGL(k_grid_scatter, dim3(bn), dim3(256), 0, ctx->stream, P, ctx->geom, ws.gdim,
+        hipLaunchKernelGGL(k_grid_scatter, dim3(bn), dim3(256), 0, ctx->stream, P, g, ws.gdim,
                            ws.gsize, ws.gcursor, ws.gitem);
-        hipLaunchKernelGGL(k_pairs_grid, dim3(bn), dim3(256), 0, ctx->stream, P, ctx->hist_key, T,
-                           ctx->geom, ws.gdim, ws.gsize, ws.gcount, ws.gitem, ws.pairs, ws.count,
-                           ctx->ctr + kCtrDeferred);
+        hipLaunchKernelGGL(k_pairs<true>, dim3(bw), dim3(1024), 0, ctx->stream, P, ctx->hist_pp,
+                           ctx->hist_key, ws.bound, g, ws.gdim, ws.gsize, ws.gcount, ws.gitem,
+                           ws.pairs, ws.count, deferred);
     } else {
-        hipLaunchKernelGGL(k_pairs, dim3(bq), dim3(256), 0, ctx->stream, P, ctx->hist_key, T,
-                           ctx->geom, ws.pairs, ws.count, ctx->ctr + kCtrDeferred);
+        hipLaunchKernelGGL(k_pairs<false>, dim3(bw), dim3(1024), 0, ctx->stream, P, ctx->hist_pp,
+                           ctx->hist_key, ws.bound, g, nullptr, nullptr, nullptr, nullptr, ws.pairs,
+                           ws.count, deferred);
     }
-    const int64_t most = 6 * (int64_t)np + (int64_t)np * kPairSlots;
-    const uint32_t bc = (uint32_t)std::min<int64_t>((most + 255) / 256, 1024);
-    // first half, then per substep the contacts and the two half kicks
-    // around the substep boundary in one launch
-    hipLaunchKernelGGL(k_first_half, dim3(bp), dim3(64), 0, ctx->stream, P, ctx->FT, ctx->fc,
-                       ws.reach, c, dt, ctx->geom);
+    int axes[3] = {0, 0, 0}, n_axes = 0;
+    for (int a = 0; a < 3; ++a)
+        if (!g.per[a]) axes[n_axes++] = a;
+    const uint32_t wb = (uint32_t)(((int64_t)np * 2 * n_axes + 255) / 256);
+    // lanes for eight pairs a particle (more stride over the list)
+    // (spheres: two control points a pair)
+    const int lanes = ctx->cfg.n_ctrl > np ? kPairLanes : 2;
+    const uint32_t pb = (uint32_t)std::min<int64_t>(((int64_t)np * 8 * lanes + 255) / 256, 2048);
+    const auto contacts = lanes == 2 ? k_contacts<2> : k_contacts<kPairLanes>;
+    hipLaunchKernelGGL((k_advance<false, true>), dim3(bp), dim3(64), 0, ctx->stream, P, ctx->FT,
+                       ctx->fc, c, dt, g);
     for (int s = 0; s < n_sub; ++s) {
-        hipLaunchKernelGGL(k_contacts, dim3(bc), dim3(256), 0, ctx->stream, P, ctx->hist_pp,
-                           ctx->hist_pw, ctx->fc, ws.reach, c, dt, ctx->geom, ws.pairs, ws.count);
+        hipLaunchKernelGGL(contacts, dim3(wb + pb), dim3(256), 0, ctx->stream, P,
+                           ctx->hist_pp, ctx->hist_pw, ctx->fc, ws.reach, c, dt, g, ws.pairs, ws.count,
+                           wb, n_axes, axes[0], axes[1], axes[2]);
         if (s + 1 < n_sub)
-            hipLaunchKernelGGL(k_between, dim3(bp), dim3(64), 0, ctx->stream, P, ctx->FT, ctx->fc,
-                               ws.reach, c, dt, ctx->geom);
+            hipLaunchKernelGGL((k_advance<true, true>), dim3(bp), dim3(64), 0, ctx->stream, P, ctx->FT,
+                               ctx->fc, c, dt, g);
         else
-            hipLaunchKernelGGL(k_second_half, dim3(bp), dim3(64), 0, ctx->stream, P, ctx->FT,
-                               ctx->fc, c, dt);
+            hipLaunchKernelGGL((k_advance<true, false>), dim3(bp), dim3(64), 0, ctx->stream, P,
+                               ctx->FT, ctx->fc, c, dt, g);
     }
     return hipGetLastError();
 }
@@ -896,15 +1107,15 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
 // ---------------------------------------------------------------------------
 // The allocation-free work space of dem_step_noalloc: one static array per
 // device (module-scope device memory, loaded with the code object), laid out
-// as the pair count (first 512 bytes), the reach of up to kNoAllocParticles
-// particles, then up to kNoAllocParticles * kPairSlots pair entries.  Host
+// as the pair count (first 512 bytes), the reach and the candidate bound of up
+// to kNoAllocParticles particles, then up to kNoAllocParticles * kPairSlots pair entries.  Host
 // code never uses the array's name as an address: the device address is
 // looked up once per device and kept.
 // ---------------------------------------------------------------------------
 namespace {
 constexpr size_t kNoAllocHead = 64;  // 8-byte words before the reach
 constexpr size_t kNoAllocWords =
-    kNoAllocHead + (size_t)kNoAllocParticles + (size_t)kNoAllocParticles * kPairSlots;
+    kNoAllocHead + 2 * (size_t)kNoAllocParticles + (size_t)kNoAllocParticles * kPairSlots;
 __device__ __align__(256) uint64_t scratch[kNoAllocWords];
 
 constexpr int kMaxDevices = 64;
@@ -938,7 +1149,8 @@ bool dem_noalloc_scratch(int dev, DemScratch* out)
     if (!base) return false;
     out->count = reinterpret_cast<uint32_t*>(base);
     out->reach = reinterpret_cast<double*>(base + kNoAllocHead);
-    out->pairs = base + kNoAllocHead + kNoAllocParticles;
+    out->bound = out->reach + kNoAllocParticles;
+    out->pairs = base + kNoAllocHead + 2 * kNoAllocParticles;
     return true;
 }
 

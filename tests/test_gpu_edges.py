@@ -42,3 +42,44 @@ def test_stream_collide_at_wave_and_row_edges(storage, lattice, dims):
             ora.step(NONE)
         assert np.abs(gpu.populations() - ora.f).max() <= BULK_TOL[storage], per
         gpu.close()
+
+
+@pytest.mark.parametrize("points", [1, 3, 9])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 130])
+def test_dem_paths_match_the_oracle(n, points):
+    """dem_step around the particle count where a whole call moves from one
+    workgroup to a launch per phase, with bodies of one control point, of three
+    (both bodies' points in a group's registers) and of nine (not), touching
+    each other, the floor and each other across a periodic face: five calls of
+    ten substeps against the oracle, within 1e-9."""
+    rng = np.random.default_rng(100 * n + points)
+    if points == 1:
+        shape = W.sphere_shape(6.2, 0.2)
+    else:
+        pts = rng.uniform(-0.4, 0.4, (points, 3))
+        shape = W.metaball_shape(pts, rng.uniform(0.7, 1.3, points) * 0.9 / points, 0.2, d_eq=6.4,
+                                 samples_per_unit=2.0)
+    per_row = 6
+    rows = -(-n // per_row)
+    k = np.arange(n)
+    lat = W.LatticeSpec(36, max(6 * rows, 40), 30, (1, 0, 0))
+    pos = np.stack([(k % per_row) * 6.0 + 3.0, (k // per_row) * 6.0 + 2.7, np.full(n, 2.5)], -1)
+    pos += rng.uniform(-0.1, 0.1, (n, 3))
+    quats = np.array([W.random_quaternion(rng) for _ in range(n)])
+    ps = W.make_particles([shape] * n, pos, quats, 1.5, vel=rng.normal(size=(n, 3)) * 0.02,
+                          omega=rng.normal(size=(n, 3)) * 0.004)
+    kw = W.dem_defaults(ps, gravity=(0.0, 0.0, -2e-4))
+    gpu, dem = B.Lattice.for_particles(lat, ps, storage="f32"), O.OracleDEM(ps, lat)
+    parts, P = B.DeviceParticles(ps), ps.copy()
+    zero = np.zeros((n, 3))
+    for _ in range(5):
+        gpu.dem(parts, 10, 0.1, B.DemParams.make(**kw))
+        dem.step(P, zero, zero, O.DemParams(**kw), 10, 0.1)
+    gpu.sync()
+    G = parts.to_host(ps)
+    gpu.close()
+    if n > 1:
+        assert np.abs(P.vel - ps.vel).max() > 1e-3   # contacts acted
+    for key in ("pos", "vel", "omega", "quat", "world_pts"):
+        a, b = getattr(G, key), getattr(P, key)
+        assert np.abs(a - b).max() <= 1e-9 * max(1.0, np.abs(b).max()), key
