@@ -50,8 +50,7 @@ def run_storage(lat, ps, meta, storage, steps, warmup, profile=True, treatments=
     gpu.classify(parts)
 
     def one_step(sync):
-        # the link pass, then the stream-collide pass with the DEM sub-cycle
-        # beside it (lbm_step_dem: the same results as lbm_step, dem_step)
+        # the lattice step and the DEM sub-cycle in one call
         gpu.step_dem(parts, n_sub, 1.0 / n_sub, prm)
         gpu.forces()
         # timed steps classify without the host read-back of list counts
@@ -76,8 +75,8 @@ def run_storage(lat, ps, meta, storage, steps, warmup, profile=True, treatments=
         gpu.profile(False)
     seq = None
     if seq_steps:
-        # after the timed steps: lbm_step, the forces and dem_step one after
-        # the other, so that the stream-collide pass has the chip to itself
+        # after the timed steps: lbm_step, the forces and dem_step as calls of
+        # their own
         gpu.profile(True)
         torch.cuda.synchronize()
         t2 = time.perf_counter()
@@ -524,7 +523,7 @@ def main():
             "tau": lat.tau,
             "treatments": int(meta.get("treatments", 3)),
             "dem_substeps": meta.get("n_sub", 10),
-            "step": "classify + step with the dem sub-cycle beside its stream-collide pass + forces",
+            "step": "classify + step + dem sub-cycle + forces",
         },
         "fluid_mlups": round(nfluid / (main_res["ms_per_step"] * 1e-3) / 1e6, 1),
         "phase_ms_per_launch": phases,

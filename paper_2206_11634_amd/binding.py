@@ -385,8 +385,7 @@ class Lattice:
         dem_step(self.ctx, parts.struct, n_sub, dt, prm)
 
     def step_dem(self, parts: DeviceParticles, n_sub: int, dt: float, prm: DemParams):
-        """lbm_step_dem: the step, with the DEM sub-cycle beside its
-        stream-collide pass."""
+        """lbm_step_dem: the step, then the DEM sub-cycle, in one call."""
         lbm_step_dem(self.ctx, parts.struct, n_sub, dt, prm)
 
     def dem_noalloc(self, parts: DeviceParticles, n_sub: int, dt: float, prm: DemParams):
