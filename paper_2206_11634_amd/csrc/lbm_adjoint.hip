@@ -22,12 +22,12 @@
 //  2. k_adj_links  per link: adjoint of its reconstructed population (Lambda
 //                  of the fluid node that pulled the ghost slot, left in
 //                  lambda(n) at the solid node, plus the objective), transposed
-//                  through VIBB / halfway by forward-mode dual numbers and
-//                  added to lambda(n) at x_f and x_ff with atomics; momentum-
+//                  through VIBB / halfway by a reverse sweep and added to lambda(n) at x_f and x_ff with atomics; momentum-
 //                  exchange and missing-point objective terms; dJ/dv, dJ/dF.
 // Arithmetic is that of the storage (double for FP64, float otherwise);
 // parameter gradients are summed in FP64.
 #include <algorithm>
+#include <type_traits>
 
 #include "lbm_internal.h"
 #include "lbm_stencil.h"
@@ -36,120 +36,81 @@
 namespace mdlbm {
 namespace {
 
-// ---------------------------------------------------------------------------
-// forward-mode dual numbers with N tangents
-// ---------------------------------------------------------------------------
-template <class A, int N>
-struct Dual {
-    A v;
-    A d[N];
-    __device__ Dual() = default;
-    __device__ Dual(A x) : v(x)
-    {
-#pragma unroll
-        for (int k = 0; k < N; ++k) d[k] = A(0);
-    }
-};
-template <class A, int N>
-__device__ __forceinline__ Dual<A, N> var(A v, int k)
-{
-    Dual<A, N> r(v);
-    r.d[k] = A(1);
-    return r;
-}
-template <class A, int N>
-__device__ __forceinline__ Dual<A, N> operator+(const Dual<A, N>& a, const Dual<A, N>& b)
-{
-    Dual<A, N> r;
-    r.v = a.v + b.v;
-#pragma unroll
-    for (int k = 0; k < N; ++k) r.d[k] = a.d[k] + b.d[k];
-    return r;
-}
-template <class A, int N>
-__device__ __forceinline__ Dual<A, N> operator-(const Dual<A, N>& a, const Dual<A, N>& b)
-{
-    Dual<A, N> r;
-    r.v = a.v - b.v;
-#pragma unroll
-    for (int k = 0; k < N; ++k) r.d[k] = a.d[k] - b.d[k];
-    return r;
-}
-template <class A, int N>
-__device__ __forceinline__ Dual<A, N> operator*(const Dual<A, N>& a, const Dual<A, N>& b)
-{
-    Dual<A, N> r;
-    r.v = a.v * b.v;
-#pragma unroll
-    for (int k = 0; k < N; ++k) r.d[k] = a.d[k] * b.v + a.v * b.d[k];
-    return r;
-}
-template <class A, int N>
-__device__ __forceinline__ Dual<A, N> operator/(const Dual<A, N>& a, const Dual<A, N>& b)
-{
-    Dual<A, N> r;
-    const A ib = A(1) / b.v;
-    r.v = a.v * ib;
-#pragma unroll
-    for (int k = 0; k < N; ++k) r.d[k] = (a.d[k] - r.v * b.d[k]) * ib;
-    return r;
-}
-
-// Equilibrium of direction d at (rho, u), in the deviation form (feq - w) when
-// DEV, generic scalar T.
-template <bool DEV, class A, class T>
-__device__ __forceinline__ T eq_t(int d, const int e[3], const T& rho, const T u[3])
-{
-    const T eu = T(A(e[0])) * u[0] + T(A(e[1])) * u[1] + T(A(e[2])) * u[2];
-    const T uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    const T poly = T(A(3)) * eu + T(A(4.5)) * (eu * eu) - T(A(1.5)) * uu;
-    const T w = T(W<A>(d));
-    if constexpr (DEV)
-        return w * ((rho - T(A(1))) + rho * poly);
-    else
-        return w * (rho + rho * poly);
-}
-
-// The reconstructed population of a link from its inputs: the formulas of
-// the forward link kernel (VIBB, Eqs. eqneq, neqd, rhod, u*_d, u**_d, u_d; or
-// halfway bounce-back), written for a generic scalar; q is a scalar of the
-// same kind so that its derivative can be carried too.
+// The reconstructed population of a link and its transposed derivative: the
+// formulas of the forward link kernel (VIBB, Eqs. eqneq, neqd, rhod, u*_d,
+// u**_d, u_d; or halfway bounce-back) followed by one reverse sweep, which
+// costs about as much as the value (13 tangents carried forward took some 1000
+// more instructions a link).
 template <class A>
-__device__ __forceinline__ A val(const A& x)
-{
-    return x;
-}
-template <class A, int N>
-__device__ __forceinline__ A val(const Dual<A, N>& x)
-{
-    return x.v;
-}
+struct LinkIn {
+    A fdf, rf, uf[3];     // x_f: outgoing population, density, velocity
+    A fdff, rff, uff[3];  // x_ff
+    A uw[3], q;
+};
+// d value / d of each input (of the same names).
+template <class A>
+using LinkGrad = LinkIn<A>;
 
-template <bool DEV, class A, class T>
-__device__ T link_value(int kind, int d, const int e[3], const T& q, const T& fdf, const T& rf,
-                        const T* uf, const T& fdff, const T& rff, const T* uff, const T* uw,
-                        bool neq_split)
+template <bool DEV, class A>
+__device__ __forceinline__ A link_value(int kind, A w, const A e[3], const LinkIn<A>& x,
+                                        bool neq_split, LinkGrad<A>& g)
 {
-    const T ebu = T(A(-e[0])) * uw[0] + T(A(-e[1])) * uw[1] + T(A(-e[2])) * uw[2];
-    const T mw = T(A(6) * W<A>(d)) * rf * ebu;
-    if (kind != LBM_LINK_VIBB) return fdf + mw;
-    const A qv = val(q);
-    const T one = T(A(1));
-    const T tq = T(A(2)) * q, oq = one - tq;
-    const bool hold = neq_split && qv > A(0.5);
-    const T fneq = (hold ? one : tq) * (fdf - eq_t<DEV, A>(d, e, rf, uf)) +
-                   (hold ? T(A(0)) : oq) * (fdff - eq_t<DEV, A>(d, e, rff, uff));
-    const T rd = (qv <= A(0.5)) ? tq * rf + oq * rff : rf;
-    const T c1 = (one - q) / q, c2 = (tq - one) / q;
-    const T c3 = (one - q) / (one + q), c4 = tq / (one + q);
-    T ud[3];
+    const A euw = e[0] * x.uw[0] + e[1] * x.uw[1] + e[2] * x.uw[2];
+    const A w6 = A(-6) * w;
+    const A mw = w6 * x.rf * euw;
+    g.fdf = A(1);
+    g.rf = w6 * euw;
+    g.fdff = g.rff = g.q = A(0);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const T us = (qv <= A(0.5)) ? tq * uf[a] + oq * uff[a] : c1 * uf[a] + c2 * uw[a];
-        const T uss = c3 * uff[a] + c4 * uw[a];
-        ud[a] = us / T(A(3)) + T(A(2)) * uss / T(A(3));
+        g.uf[a] = g.uff[a] = A(0);
+        g.uw[a] = w6 * x.rf * e[a];
     }
-    return eq_t<DEV, A>(d, e, rd, ud) + fneq + mw;
+    if (kind != LBM_LINK_VIBB) return x.fdf + mw;
+    // the equilibrium at (r, u) less its weight, 1 + its polynomial, and the
+    // factors of its derivative in u: w r (3 + 9 e.u) e - 3 w r u
+    auto eq = [&](A r, const A u[3], A& p1, A& eu) {
+        eu = e[0] * u[0] + e[1] * u[1] + e[2] * u[2];
+        const A poly = A(3) * eu + A(4.5) * eu * eu -
+                       A(1.5) * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+        p1 = A(1) + poly;
+        return DEV ? w * ((r - A(1)) + r * poly) : w * (r + r * poly);
+    };
+    const A q = x.q;
+    const bool low = q <= A(0.5), hold = neq_split && !low;
+    const A tq = A(2) * q, oq = A(1) - tq;
+    const A n1 = hold ? A(1) : tq, n2 = hold ? A(0) : oq;
+    const A iq = A(1) / q, i1 = A(1) / (A(1) + q);
+    const A c1 = (A(1) - q) * iq, c2 = (tq - A(1)) * iq, c3 = (A(1) - q) * i1, c4 = tq * i1;
+    const A third = A(1.0 / 3.0);
+    A pf, pff, pd, ef, eff, ed, ud[3];
+    const A nf = x.fdf - eq(x.rf, x.uf, pf, ef), nff = x.fdff - eq(x.rff, x.uff, pff, eff);
+    const A rd = low ? tq * x.rf + oq * x.rff : x.rf;
+    const A a1 = low ? tq : c1, a2 = low ? oq : c2;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const A us = a1 * x.uf[a] + a2 * (low ? x.uff[a] : x.uw[a]);
+        ud[a] = (us + A(2) * (c3 * x.uff[a] + c4 * x.uw[a])) * third;
+    }
+    const A value = eq(rd, ud, pd, ed) + n1 * nf + n2 * nff + mw;
+    g.fdf = n1;
+    g.fdff = n2;
+    g.rf += w * (pd * (low ? tq : A(1)) - n1 * pf);
+    g.rff = w * (pd * (low ? oq : A(0)) - n2 * pff);
+    g.q = (hold ? A(0) : A(2) * (nf - nff)) + (low ? A(2) * w * pd * (x.rf - x.rff) : A(0));
+    const A kd = w * rd * (A(3) + A(9) * ed), ld = A(-3) * w * rd;
+    const A kf = n1 * w * x.rf * (A(3) + A(9) * ef), lf = A(-3) * n1 * w * x.rf;
+    const A kff = n2 * w * x.rff * (A(3) + A(9) * eff), lff = A(-3) * n2 * w * x.rff;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const A du = third * (kd * e[a] + ld * ud[a]);  // d value / d (us + 2 uss)
+        g.uf[a] = du * a1 - (kf * e[a] + lf * x.uf[a]);
+        g.uff[a] = du * ((low ? oq : A(0)) + A(2) * c3) - (kff * e[a] + lff * x.uff[a]);
+        g.uw[a] += du * ((low ? A(0) : c2) + A(2) * c4);
+        const A dus = low ? A(2) * (x.uf[a] - x.uff[a]) : (x.uw[a] - x.uf[a]) * iq * iq;
+        g.q += du * (dus + A(4) * (x.uw[a] - x.uff[a]) * i1 * i1);
+    }
+    return value;
 }
 
 // Metaball sum of one particle at X (world coordinates of the image nearest
@@ -201,22 +162,33 @@ struct GeoArgs {
     double* w_refill = nullptr;     // dJ/domega_p seen by the refill (null: not kept)
 };
 
-// Sum n doubles over the block and add them to out[] (one atomic each).
-template <int NV>
-__device__ __forceinline__ void block_add(double (&v)[NV], double* const* out)
+// Sum NV doubles over a block of T threads and add sum k to *out(k) (one
+// atomic each).
+template <int T, int NV, class Out>
+__device__ __forceinline__ void block_add(const double (&v)[NV], Out out)
 {
-    __shared__ double red[4][NV];
+    static_assert(T == 64 || T == 256, "one wave or four");
+    constexpr int NG = (NV + 5) / 6;
+    __shared__ double red[4][6 * NG];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-        const double s = dsum_wave(v[k]);
-        if (lane == 0) red[wv][k] = s;
+    for (int k = 0; k < NG; ++k) {
+        double t[6];
+#pragma unroll
+        for (int m = 0; m < 6; ++m) t[m] = 6 * k + m < NV ? v[6 * k + m < NV ? 6 * k + m : 0] : 0.0;
+        const double s = wave_sum6(t);
+        if constexpr (T == 64) {
+            if (lane < 6 && 6 * k + lane < NV && s != 0.0) atomicAdd(out(6 * k + lane), s);
+        } else {
+            if (lane < 6) red[wv][6 * k + lane] = s;
+        }
     }
+    if constexpr (T == 64) return;
     __syncthreads();
     if (threadIdx.x < NV) {
         const double s = (red[0][threadIdx.x] + red[1][threadIdx.x]) +
                          (red[2][threadIdx.x] + red[3][threadIdx.x]);
-        if (s != 0.0) atomicAdd(out[threadIdx.x], s);
+        if (s != 0.0) atomicAdd(out((int)threadIdx.x), s);
     }
 }
 
@@ -226,15 +198,14 @@ __device__ __forceinline__ void block_add(double (&v)[NV], double* const* out)
 
 // Lambda = (d post / d pre)^T lambda for BGK + Guo at the pre-collision state
 // pre, in closed form: Lambda_j = (1 - omega) lambda_j + omega a
-// + H . (e_j - u) / rho.  Returns the coefficients; adds dJ/dF (3) and dJ/dtau
-// to acc.
+// + H . (e_j - u) / rho, kept as (1 - omega) lambda_j + c + e_j . h.  Returns
+// the coefficients; adds dJ/dF (3) and dJ/dtau to acc.
 template <class A>
 struct AdjCoef {
-    A om, a, H[3], u[3], ir;
+    A om1, c, h[3];  // Lambda_j = om1 lambda_j + c + e_j.h
     __device__ __forceinline__ A operator()(int j, A lam_j) const
     {
-        return (A(1) - om) * lam_j + om * a +
-               (H[0] * (A(cx(j)) - u[0]) + H[1] * (A(cy(j)) - u[1]) + H[2] * (A(cz(j)) - u[2])) * ir;
+        return j == 0 ? om1 * lam_j + c : om1 * lam_j + (c + edot(j, h[0], h[1], h[2]));
     }
 };
 
@@ -251,48 +222,70 @@ __device__ __forceinline__ AdjCoef<A> adj_collide(const A lam[kQ], const A pre[k
         F[0] = ph.F[0], F[1] = ph.F[1], F[2] = ph.F[2];
         om = ph.omega;
     }
-    A drho, rho, u[3];
-    moments<DEV, A>(pre, A(0.5), F, drho, rho, u[0], u[1], u[2]);
+    // sums over the opposite pairs: populations, and the weighted moments of
+    // lambda, m0 = sum w l, m1 = sum w l e, m2 = sum w l e e: the sums over i
+    // of the equilibrium's and the forcing's derivatives are polynomials in u
+    // and F with these coefficients
+    A s = pre[0], jx = A(0), jy = A(0), jz = A(0);
+    A lsum = lam[0], m0 = W<A>(0) * lam[0], m1[3] = {A(0), A(0), A(0)};
+    A mxx = A(0), myy = A(0), mzz = A(0), mxy = A(0), mxz = A(0), myz = A(0);
+#pragma unroll
+    for (int i = 1; i < kQ; i += 2) {
+        s += pre[i] + pre[i + 1];
+        const A m = pre[i] - pre[i + 1];
+        const A lp = lam[i] + lam[i + 1];
+        lsum += lp;
+        const A p = W<A>(i) * lp, d = W<A>(i) * (lam[i] - lam[i + 1]);
+        m0 += p;
+        if (cx(i)) {
+            jx += cx(i) > 0 ? m : -m;
+            m1[0] += cx(i) > 0 ? d : -d;
+            mxx += p;
+        }
+        if (cy(i)) {
+            jy += cy(i) > 0 ? m : -m;
+            m1[1] += cy(i) > 0 ? d : -d;
+            myy += p;
+        }
+        if (cz(i)) {
+            jz += cz(i) > 0 ? m : -m;
+            m1[2] += cz(i) > 0 ? d : -d;
+            mzz += p;
+        }
+        if (cx(i) && cy(i)) mxy += cx(i) * cy(i) > 0 ? p : -p;
+        if (cx(i) && cz(i)) mxz += cx(i) * cz(i) > 0 ? p : -p;
+        if (cy(i) && cz(i)) myz += cy(i) * cz(i) > 0 ? p : -p;
+    }
+    A drho, rho;
+    if constexpr (DEV) {
+        drho = s;
+        rho = A(1) + s;
+    } else {
+        rho = s;
+        drho = s - A(1);
+    }
+    const A ir = A(1) / rho;
+    const A u[3] = {(jx + A(0.5) * F[0]) * ir, (jy + A(0.5) * F[1]) * ir, (jz + A(0.5) * F[2]) * ir};
     const A uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
     const A uF = u[0] * F[0] + u[1] * F[1] + u[2] * F[2];
     const A gf = A(1) - A(0.5) * om;
-    // feq - pre - S/2 sums to zero over i, so its weight in dJ/domega may be
-    // centred on the mean of lambda, which keeps the sum free of the
-    // cancellation of a large common adjoint density
-    A lbar = A(0);
+    // dJ/domega = sum (lambda - mean)(feq - pre - S/2): the second factor sums
+    // to zero over i, so lambda may be centred on its mean, which keeps the
+    // sum free of the cancellation of a large common adjoint density.  feq -
+    // S/2 = w [drho - 3/2 rho u.u + 3/2 u.F + 9/2 (e.u)(e.h) + 3 e.g] with g =
+    // rho u - F/2, h = rho u - F (rho in place of drho for plain populations).
+    const A lbar = lsum * A(1.0 / kQ);
+    const A c = (DEV ? drho : rho) - (A(1.5) * rho * uu - A(1.5) * uF);
+    const A g[3] = {rho * u[0] - A(0.5) * F[0], rho * u[1] - A(0.5) * F[1], rho * u[2] - A(0.5) * F[2]};
+    const A h[3] = {rho * u[0] - F[0], rho * u[1] - F[1], rho * u[2] - F[2]};
+    A dom = (lam[0] - lbar) * (W<A>(0) * c - pre[0]);
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) lbar += lam[i];
-    lbar *= A(1.0 / kQ);
-    // weighted moments of lambda, m0 = sum w l, m1 = sum w l e, m2 = sum w l e e:
-    // the sums over i of the equilibrium's and the forcing's derivatives are
-    // polynomials in u and F with these coefficients
-    A m0 = A(0), m1[3] = {A(0), A(0), A(0)};
-    A mxx = A(0), myy = A(0), mzz = A(0), mxy = A(0), mxz = A(0), myz = A(0);
-    A dom = A(0);
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-        const A wl = W<A>(i) * lam[i];
-        m0 += wl;
-        if (cx(i)) {
-            m1[0] += A(cx(i)) * wl;
-            mxx += wl;
-        }
-        if (cy(i)) {
-            m1[1] += A(cy(i)) * wl;
-            myy += wl;
-        }
-        if (cz(i)) {
-            m1[2] += A(cz(i)) * wl;
-            mzz += wl;
-        }
-        if (cx(i) && cy(i)) mxy += A(cx(i) * cy(i)) * wl;
-        if (cx(i) && cz(i)) mxz += A(cx(i) * cz(i)) * wl;
-        if (cy(i) && cz(i)) myz += A(cy(i) * cz(i)) * wl;
-        const A eu = A(cx(i)) * u[0] + A(cy(i)) * u[1] + A(cz(i)) * u[2];
-        const A eF = A(cx(i)) * F[0] + A(cy(i)) * F[1] + A(cz(i)) * F[2];
-        const A St_i = W<A>(i) * (A(3) * (eF - uF) + A(9) * eu * eF);
-        const A feq = eq_i<DEV, A>(i, drho, rho, u[0], u[1], u[2]);
-        dom += (lam[i] - lbar) * (feq - pre[i] - A(0.5) * St_i);
+    for (int i = 1; i < kQ; i += 2) {
+        const A eu = edot(i, u[0], u[1], u[2]), eg = edot(i, g[0], g[1], g[2]),
+                eh = edot(i, h[0], h[1], h[2]);
+        const A even = (A(4.5) * eu) * eh + c;
+        dom += (lam[i] - lbar) * (W<A>(i) * (A(3) * eg + even) - pre[i]);
+        dom += (lam[i + 1] - lbar) * (W<A>(i) * (A(-3) * eg + even) - pre[i + 1]);
     }
     const A m2u[3] = {mxx * u[0] + mxy * u[1] + mxz * u[2], mxy * u[0] + myy * u[1] + myz * u[2],
                       mxz * u[0] + myz * u[1] + mzz * u[2]};
@@ -302,23 +295,20 @@ __device__ __forceinline__ AdjCoef<A> adj_collide(const A lam[kQ], const A pre[k
     const A um2u = u[0] * m2u[0] + u[1] * m2u[1] + u[2] * m2u[2];
     // a = sum w l P_i with P_i = 1 + 3 e.u + 4.5 (e.u)^2 - 1.5 u.u
     const A a = m0 * (A(1) - A(1.5) * uu) + A(3) * m1u + A(4.5) * um2u;
-    A B[3], G[3], Fd[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        B[k] = rho * (A(3) * m1[k] + A(9) * m2u[k] - A(3) * u[k] * m0);
-        G[k] = A(-3) * F[k] * m0 + A(9) * m2F[k];
-        Fd[k] = A(3) * m1[k] - A(3) * u[k] * m0 + A(9) * m2u[k];
-    }
     AdjCoef<A> co;
-    co.om = om;
-    co.a = a;
-    co.ir = A(1) / rho;
+    co.om1 = A(1) - om;
+    A hu = A(0);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        co.H[k] = om * B[k] + gf * G[k];
-        co.u[k] = u[k];
-        acc[k] += (double)(co.H[k] * A(0.5) * co.ir + gf * Fd[k]);
+        const A B = rho * (A(3) * m1[k] + A(9) * m2u[k] - A(3) * u[k] * m0);
+        const A G = A(-3) * F[k] * m0 + A(9) * m2F[k];
+        const A Fd = A(3) * m1[k] - A(3) * u[k] * m0 + A(9) * m2u[k];
+        const A H = om * B + gf * G;
+        co.h[k] = H * ir;
+        hu += co.h[k] * u[k];
+        acc[k] += (double)(co.h[k] * A(0.5) + gf * Fd);
     }
+    co.c = om * a - hu;
     acc[3] += -(double)om * (double)om * (double)dom;  // dtau = -omega^2 domega
     return co;
 }
@@ -331,9 +321,12 @@ __device__ __forceinline__ AdjCoef<A> adj_collide(const A lam[kQ], const A pre[k
 // at n (for a solid y that is the adjoint of the ghost slot, which the link
 // kernel takes and clears), and zero otherwise; k_adj_refill then rewrites the
 // entries its refilled nodes read.
+//
+// Bound by memory where the lattice exceeds the caches: f and lambda(n + 1)
+// read, lambda(n) written, owners, 3 x 76 + 8 bytes a node in FP32, 97 us at
+// 128^3 (5.1 TB/s; 105 before sums over opposite pairs took the place of 19
+// terms each); a small FP64 box (48 x 40 x 44) takes 12.4 us (14.0 before).
 template <int S>
-// (the moment form of the transposed collision keeps the FP32 kernel at 85
-// registers, five waves per SIMD; a bound of six spills)
 __global__ __launch_bounds__(256) void k_adj_node(const typename St<S>::T* __restrict__ f,
                                                   const uint32_t* __restrict__ own0,
                                                   const uint32_t* __restrict__ own1,
@@ -347,14 +340,27 @@ __global__ __launch_bounds__(256) void k_adj_node(const typename St<S>::T* __res
     double acc[4] = {0.0, 0.0, 0.0, 0.0};  // dJ/dF (3), dJ/dtau
     bool refilled = false;
     if (cell < g.ncell) {
+        const uint32_t o0 = own0[cell], o1 = own1[cell];
+        const bool live = o0 == kFluid && o1 == kFluid;
+        // a node refilled between n and n + 1 leaves the entries it read from
+        // nodes fluid at n to k_adj_refill, so the two kernels write disjoint
+        // entries
+        refilled = o0 != kFluid && o1 == kFluid;
         const uint32_t nx = g.n[0], ny = g.n[1];
-        const uint32_t x = cell % nx, y = (cell / nx) % ny, z = cell / (nx * ny);
+        uint32_t x, y, z;
+        node_xyz(cell, g, x, y, z);
         uint32_t ox[3], oy[3], oz[3];
         bool vx[3], vy[3], vz[3];
         axis3(x, nx, g.per[0], 1u, ox, vx);
         axis3(y, ny, g.per[1], nx, oy, vy);
         axis3(z, g.n[2], g.per[2], nx * ny, oz, vz);
-        const bool live = own0[cell] == kFluid && own1[cell] == kFluid;
+        // the entry that x reads in direction j: (j, x - e_j), or through a
+        // wall its own (opp j)
+        auto entry = [&](int j) -> int64_t {
+            const int sx = 1 - cx(j), sy = 1 - cy(j), sz = 1 - cz(j);
+            return vx[sx] && vy[sy] && vz[sz] ? (int64_t)j * g.stride + (ox[sx] + oy[sy] + oz[sz])
+                                              : (int64_t)opp(j) * g.stride + cell;
+        };
         A lam[kQ] = {};
         AdjCoef<A> co{};
         if (live) {
@@ -362,29 +368,17 @@ __global__ __launch_bounds__(256) void k_adj_node(const typename St<S>::T* __res
 #pragma unroll
             for (int i = 0; i < kQ; ++i) {
                 lam[i] = lam1[(int64_t)i * g.stride + cell];
-                const int sx = 1 - cx(i), sy = 1 - cy(i), sz = 1 - cz(i);
-                const bool ok = vx[sx] && vy[sy] && vz[sz];
-                const uint32_t s = ok ? ox[sx] + oy[sy] + oz[sz] : cell;
-                const int64_t plane = ok ? i : opp(i);
-                pre[i] = St<S>::ld(f + plane * g.stride + s, ph.inv_scale);
+                pre[i] = St<S>::ld(f + entry(i), ph.inv_scale);
             }
             co = adj_collide<DEV, A>(lam, pre, ph, acc);
         }
-        // a node refilled between n and n + 1 leaves the entries it read from
-        // nodes fluid at n to k_adj_refill, so the two kernels write
-        // disjoint entries
-        refilled = own0[cell] != kFluid && own1[cell] == kFluid;
 #pragma unroll
         for (int j = 0; j < kQ; ++j) {
             const A v = live ? co(j, lam[j]) : A(0);
-            const int sx = 1 - cx(j), sy = 1 - cy(j), sz = 1 - cz(j);  // x - e_j
-            if (vx[sx] && vy[sy] && vz[sz]) {
-                const uint32_t y = ox[sx] + oy[sy] + oz[sz];
-                if (!(refilled && j > 0 && own0[y] == kFluid))
-                    lam0[(int64_t)j * g.stride + y] = v;
-            } else {  // x pulled f_j through a wall: its own f_opp(j)
-                lam0[(int64_t)opp(j) * g.stride + cell] = v;
-            }
+            const int sx = 1 - cx(j), sy = 1 - cy(j), sz = 1 - cz(j);
+            if (!(refilled && j > 0 && vx[sx] && vy[sy] && vz[sz] &&
+                  own0[ox[sx] + oy[sy] + oz[sz]] == kFluid))
+                lam0[entry(j)] = v;
         }
     }
     // list the refilled nodes for k_adj_refill (one atomic per wave); the
@@ -398,8 +392,7 @@ __global__ __launch_bounds__(256) void k_adj_node(const typename St<S>::T* __res
         const uint32_t idx = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
         if (refilled && idx < list.cap) list.node[idx] = cell;
     }
-    double* outs[4] = {grad + 0, grad + 1, grad + 2, grad + 3};
-    block_add<4>(acc, outs);
+    block_add<256>(acc, [=](int k) { return grad + k; });
 }
 
 // Nodes refilled between n and n + 1 (solid at n, fluid at n + 1): their
@@ -410,6 +403,11 @@ __global__ __launch_bounds__(256) void k_adj_node(const typename St<S>::T* __res
 // rules.  The entries (j, x - e_j) of lambda(n) at nodes fluid at n get the
 // adjoint of the streamed f_j, plus that of the bounce-back of direction
 // opp(j) unless x + e_j was fluid.
+//
+// Few nodes, so the time is one wave's chain of loads and arithmetic.  Each
+// neighbour and its owner load once, all before the first use (the upstream
+// candidate of i is the downstream one of opp i): 22 -> 10 us at 128^3 FP32
+// with one body, 15 -> 8 us in 48 x 40 x 44 FP64.
 template <int S>
 __global__ __launch_bounds__(256) void k_adj_refill(const typename St<S>::T* __restrict__ f,
                                                     const uint32_t* __restrict__ own0,
@@ -425,72 +423,73 @@ __global__ __launch_bounds__(256) void k_adj_refill(const typename St<S>::T* __r
     const uint32_t cnt = min(*list.count, list.cap);
     for (uint32_t l = blockIdx.x * 256u + threadIdx.x; l < cnt; l += gridDim.x * 256u) {
         const uint32_t cell = list.node[l];
-        const uint32_t o0 = own0[cell];
-        const uint32_t nx = g.n[0], ny = g.n[1];
-        const int c[3] = {(int)(cell % nx), (int)((cell / nx) % ny), (int)(cell / (nx * ny))};
-        const int p = (int)o0;
+        const int p = (int)own0[cell];
+        // neighbours x - e_i with their owners and f_i, each once (x + e_i and
+        // f_opp(i) are those of opp(i)), before any use
+        uint32_t xc[3];
+        node_xyz(cell, g, xc[0], xc[1], xc[2]);
+        uint32_t o[3][3];
+        bool in[3][3];
+        axis3(xc[0], g.n[0], g.per[0], 1u, o[0], in[0]);
+        axis3(xc[1], g.n[1], g.per[1], g.n[0], o[1], in[1]);
+        axis3(xc[2], g.n[2], g.per[2], (uint32_t)g.n[0] * (uint32_t)g.n[1], o[2], in[2]);
+        A lam[kQ], pre[kQ], fa[kQ];
+        uint32_t nu[kQ], ow[kQ];
+        lam[0] = lam1[cell];
+#pragma unroll
+        for (int i = 1; i < kQ; ++i) {
+            lam[i] = lam1[(int64_t)i * g.stride + cell];
+            nu[i] = o[0][1 - cx(i)] + o[1][1 - cy(i)] + o[2][1 - cz(i)];
+            fa[i] = St<S>::ld(f + (int64_t)i * g.stride + nu[i], ph.inv_scale);
+            ow[i] = own0[nu[i]];
+        }
         double rr[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const double xp = pos1[3 * p + a];
-            rr[a] = image_coord(c[a], g.n[a], g.per[a], xp) - xp;
+            rr[a] = image_coord((int)xc[a], g.n[a], g.per[a], xp) - xp;
         }
-        const double* wp = om1 + 3 * p;
+        const double wp[3] = {om1[3 * p], om1[3 * p + 1], om1[3 * p + 2]};
         const A un[3] = {A(vel1[3 * p] + (wp[1] * rr[2] - wp[2] * rr[1])),
                          A(vel1[3 * p + 1] + (wp[2] * rr[0] - wp[0] * rr[2])),
                          A(vel1[3 * p + 2] + (wp[0] * rr[1] - wp[1] * rr[0]))};
         const A r0 = A(ph.rho0), dr0 = A(ph.rho0 - 1.0);
-        A lam[kQ], pre[kQ];
-        uint32_t nu[kQ];
-        uint64_t rule = 0;  // per direction: 0 streamed, 1 bounce-back, 2 equilibrium
+        const A uu = un[0] * un[0] + un[1] * un[1] + un[2] * un[2];
+        uint32_t fl = 0;  // bit i: x - e_i lies in the lattice and was fluid at n
 #pragma unroll
-        for (int i = 0; i < kQ; ++i) {
-            lam[i] = lam1[(int64_t)i * g.stride + cell];
-            int cuu[3] = {c[0] - cx(i), c[1] - cy(i), c[2] - cz(i)};
-            int cdd[3] = {c[0] + cx(i), c[1] + cy(i), c[2] + cz(i)};
-            const bool iu = i > 0 && wrap3(cuu, g);
-            const bool id = i > 0 && wrap3(cdd, g);
-            // both candidate populations load beside the owners (both indices
-            // are nodes of the lattice), the owners then pick
-            const uint32_t su = iu ? node_of(cuu, g) : cell;
-            const uint32_t nd = id ? node_of(cdd, g) : cell;
-            const A a_up = St<S>::ld(f + (int64_t)i * g.stride + su, ph.inv_scale);
-            const A a_dn = St<S>::ld(f + (int64_t)opp(i) * g.stride + nd, ph.inv_scale);
-            const bool up = iu && own0[su] == kFluid;
-            const bool dn = id && own0[nd] == kFluid;
-            nu[i] = up ? su : kFluid;
-            const A eu = A(cx(i)) * un[0] + A(cy(i)) * un[1] + A(cz(i)) * un[2];
-            if (up) {
-                pre[i] = a_up;
-            } else if (dn) {
-                pre[i] = a_dn + A(6) * W<A>(i) * r0 * eu;
-                rule |= 1ull << (2 * i);
-            } else {
-                pre[i] = eq_i<DEV, A>(i, dr0, r0, un[0], un[1], un[2]);
-                rule |= 2ull << (2 * i);
-            }
+        for (int i = 1; i < kQ; ++i)
+            if (in[0][1 - cx(i)] && in[1][1 - cy(i)] && in[2][1 - cz(i)] && ow[i] == kFluid) fl |= 1u << i;
+        // per direction: streamed, bounced back, or the equilibrium
+        pre[0] = eq_moving<DEV, A>(W<A>(0), dr0, r0, A(0), uu);
+#pragma unroll
+        for (int i = 1; i < kQ; ++i) {
+            const A eu = edot(i, un[0], un[1], un[2]);
+            pre[i] = (fl >> i) & 1u        ? fa[i]
+                     : (fl >> opp(i)) & 1u ? fa[opp(i)] + A(6) * W<A>(i) * r0 * eu
+                                           : eq_moving<DEV, A>(W<A>(i), dr0, r0, eu, uu);
         }
         const AdjCoef<A> co = adj_collide<DEV, A>(lam, pre, ph, acc);
         A Lp[kQ];
 #pragma unroll
         for (int j = 0; j < kQ; ++j) Lp[j] = co(j, lam[j]);
         // d pre_j / d u_new: 6 w rho0 e_j for the bounce-back rule, d feq_j(rho0,
-        // u_new)/du for the equilibrium
-        double dv[3] = {0.0, 0.0, 0.0};
+        // u_new)/du = w rho0 ((3 + 9 e.u) e - 3 u) for the equilibrium
+        // (summed in double)
+        double dva[3] = {0.0, 0.0, 0.0}, su = (double)(A(-3) * W<A>(0) * r0 * Lp[0]);
 #pragma unroll
-        for (int j = 0; j < kQ; ++j) {
-            const uint32_t rj = (uint32_t)(rule >> (2 * j)) & 3u;
-            if (rj) {
-                const A ej[3] = {A(cx(j)), A(cy(j)), A(cz(j))};
-                const A eun = ej[0] * un[0] + ej[1] * un[1] + ej[2] * un[2];
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const A cuk = (rj == 1u) ? A(6) * W<A>(j) * r0 * ej[k]
-                                             : W<A>(j) * r0 * (A(3) * ej[k] + A(9) * eun * ej[k] - A(3) * un[k]);
-                    dv[k] += (double)(Lp[j] * cuk);
-                }
-            }
+        for (int j = 1; j < kQ; ++j) {
+            const bool bounced = !((fl >> j) & 1u) && ((fl >> opp(j)) & 1u);
+            const bool equi = !((fl >> j) & 1u) && !bounced;
+            const A t = W<A>(j) * r0 * Lp[j];
+            const double k = (double)(
+                bounced ? A(6) * t : (equi ? t * (A(3) + A(9) * edot(j, un[0], un[1], un[2])) : A(0)));
+            if (cx(j)) dva[0] += cx(j) > 0 ? k : -k;
+            if (cy(j)) dva[1] += cy(j) > 0 ? k : -k;
+            if (cz(j)) dva[2] += cz(j) > 0 ? k : -k;
+            su += equi ? (double)(A(-3) * t) : 0.0;
         }
+        const double dv[3] = {dva[0] + su * (double)un[0], dva[1] + su * (double)un[1],
+                              dva[2] + su * (double)un[2]};
         double* vout = ga.v_refill ? ga.v_refill + (int64_t)ga.vstride * p : grad + 4 + 3 * p;
         for (int k = 0; k < 3; ++k)
             if (dv[k] != 0.0) atomicAdd(vout + k, dv[k]);
@@ -513,31 +512,24 @@ __global__ __launch_bounds__(256) void k_adj_refill(const typename St<S>::T* __r
         // was not fluid
 #pragma unroll
         for (int j = 1; j < kQ; ++j)
-            if (nu[j] != kFluid) {
-                const bool bb = ((rule >> (2 * opp(j))) & 3u) == 1u;
+            if ((fl >> j) & 1u) {
+                const bool bb = !((fl >> opp(j)) & 1u);
                 lam0[(int64_t)j * g.stride + nu[j]] = bb ? Lp[j] + Lp[opp(j)] : Lp[j];
             }
     }
-    double* outs[4] = {grad + 0, grad + 1, grad + 2, grad + 3};
-    block_add<4>(acc, outs);
+    block_add<256>(acc, [=](int k) { return grad + k; });
 }
 
 // ---------------------------------------------------------------------------
 // 2. links: reconstruction, momentum exchange and missing points
 // ---------------------------------------------------------------------------
-template <class A>
-__device__ __forceinline__ void atomic_add_a(A* p, A v)
-{
-    if (v != A(0)) atomicAdd(p, v);
-}
-
 // With GEO, also dJ/dx_p of the pose the links were built from, with the
 // link set held fixed: through q (Eq. appq, or Eq. calq by the implicit
 // function theorem), which moves the VIBB weights and the wall point
 // x_w = x_n + q e, and through the lever arm r = x_w - x_p of the torque
 // weight and of u_w = v + omega x r.
-template <int S, bool GEO>
-__global__ __launch_bounds__(256) void k_adj_links(const typename St<S>::T* __restrict__ f,
+template <int S, bool GEO, int T>
+__global__ __launch_bounds__(T) void k_adj_links(const typename St<S>::T* __restrict__ f,
                                                    const LinkRec* __restrict__ links,
                                                    const uint32_t* __restrict__ cursor,
                                                    const int64_t* __restrict__ loff,
@@ -549,11 +541,11 @@ __global__ __launch_bounds__(256) void k_adj_links(const typename St<S>::T* __re
 {
     using A = typename St<S>::A;
     constexpr bool DEV = St<S>::dev;
-    constexpr int N = GEO ? 14 : 13;  // tangents: 13 link inputs (+ q)
-    using DN = Dual<A, N>;
-    // one workgroup per 256-record chunk of the step's link layout
-    const int p = (int)chunk[blockIdx.x];
-    const int64_t g0 = (int64_t)blockIdx.x * 256;
+    // one or four workgroups per 256-record chunk of the step's link layout (a
+    // chunk's records are all allocated: they load beside the particle's index)
+    const int64_t g0 = (int64_t)blockIdx.x * T;
+    const LinkRec r = links[g0 + threadIdx.x];
+    const int p = (int)chunk[blockIdx.x / (256 / T)];
     const int64_t cnt = min(loff[p + 1] - loff[p], (int64_t)cursor[(int64_t)p * kCursorPad]);
     if (g0 - loff[p] >= cnt) return;  // uniform over the block
     const int64_t l = g0 - loff[p] + threadIdx.x;
@@ -561,51 +553,55 @@ __global__ __launch_bounds__(256) void k_adj_links(const typename St<S>::T* __re
     // dJ/domega_p (3, GEO)
     double acc[15] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     if (l < cnt) {
-        const LinkRec r = links[g0 + threadIdx.x];
-        const int d = r.d, db = opp(d);
+        const int d = r.d, db = opp_moving(d);
         int e[3];
         dir_of(d, e);
-        const uint32_t nx = g.n[0], ny = g.n[1];
-        const int cs[3] = {(int)(r.node % nx), (int)((r.node / nx) % ny), (int)(r.node / (nx * ny))};
-        int cn[3] = {cs[0] - e[0], cs[1] - e[1], cs[2] - e[2]};
+        const double ed[3] = {(double)e[0], (double)e[1], (double)e[2]};
+        uint32_t sx, sy, sz;
+        node_xyz(r.node, g, sx, sy, sz);
+        int cn[3] = {(int)sx - e[0], (int)sy - e[1], (int)sz - e[2]};
         wrap3(cn, g);
         double rr[3], uw[3], Wv[3], Xn[3];
-        const double* xp = pos + 3 * p;
-        const double* wp = om + 3 * p;
+        const double xp[3] = {pos[3 * p], pos[3 * p + 1], pos[3 * p + 2]};
+        const double wp[3] = {om[3 * p], om[3 * p + 1], om[3 * p + 2]};
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             Xn[a] = image_coord(cn[a], g.n[a], g.per[a], xp[a]);
-            rr[a] = Xn[a] + r.q * (double)e[a] - xp[a];
+            rr[a] = Xn[a] + r.q * ed[a] - xp[a];
         }
         uw[0] = vel[3 * p] + (wp[1] * rr[2] - wp[2] * rr[1]);
         uw[1] = vel[3 * p + 1] + (wp[2] * rr[0] - wp[0] * rr[2]);
         uw[2] = vel[3 * p + 2] + (wp[0] * rr[1] - wp[1] * rr[0]);
         // objective weight of this force point: wF + wT x r (J = F.wF + (r x F).wT)
         const double* wF = wts + 6 * p;
-        const double* wT = wts + 6 * p + 3;
+        const double wT[3] = {wts[6 * p + 3], wts[6 * p + 4], wts[6 * p + 5]};
         Wv[0] = wF[0] + (wT[1] * rr[2] - wT[2] * rr[1]);
         Wv[1] = wF[1] + (wT[2] * rr[0] - wT[0] * rr[2]);
         Wv[2] = wF[2] + (wT[0] * rr[1] - wT[1] * rr[0]);
+        // weights of the outgoing and incoming population in J
+        double d_out = 0.0, d_in = 0.0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            d_out += (ed[a] - uw[a]) * Wv[a];
+            d_in += (ed[a] + uw[a]) * Wv[a];
+        }
         // geometry terms: t = the link's momentum-exchange vector, G = dJ/du_w
         // of the link (all paths), dq = dJ/dq through the reconstruction
         double tv[3] = {0, 0, 0}, G[3] = {0, 0, 0}, dq = 0.0;
         if (r.kind == LBM_LINK_MISSING) {
             // J = [(e_d - u_w) feq_d(rho0, u_w) - (e_db - u_w) feq_db(rho0, u_w)] . W
-            using D3 = Dual<double, 3>;
-            D3 u3[3] = {var<double, 3>(uw[0], 0), var<double, 3>(uw[1], 1), var<double, 3>(uw[2], 2)};
-            int eb[3] = {-e[0], -e[1], -e[2]};
-            const D3 r0 = D3(ph.rho0);
-            const D3 fo = eq_t<false, double>(d, e, r0, u3);
-            const D3 fi = eq_t<false, double>(db, eb, r0, u3);
-            D3 J = D3(0.0);
+            const double w = wgt_moving<double>(d), wr = w * ph.rho0;
+            const double eu = ed[0] * uw[0] + ed[1] * uw[1] + ed[2] * uw[2];
+            const double uu = uw[0] * uw[0] + uw[1] * uw[1] + uw[2] * uw[2];
+            const double fo = eq_moving<false, double>(w, 0.0, ph.rho0, eu, uu);
+            const double fi = eq_moving<false, double>(w, 0.0, ph.rho0, -eu, uu);
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                const D3 ta = (D3((double)e[a]) - u3[a]) * fo - (D3((double)eb[a]) - u3[a]) * fi;
-                J = J + D3(Wv[a]) * ta;
-                tv[a] = ta.v;
+                G[a] = -Wv[a] * (fo - fi) + d_out * wr * (ed[a] * (3.0 + 9.0 * eu) - 3.0 * uw[a]) +
+                       d_in * wr * (ed[a] * (9.0 * eu - 3.0) - 3.0 * uw[a]);
+                tv[a] = (ed[a] - uw[a]) * fo + (ed[a] + uw[a]) * fi;
+                acc[3 + a] = G[a];
             }
-            acc[3] = J.d[0], acc[4] = J.d[1], acc[5] = J.d[2];
-            G[0] = J.d[0], G[1] = J.d[1], G[2] = J.d[2];
         } else {
             A F[3];
             if constexpr (DEV) {
@@ -614,95 +610,71 @@ __global__ __launch_bounds__(256) void k_adj_links(const typename St<S>::T* __re
                 F[0] = ph.F[0], F[1] = ph.F[1], F[2] = ph.F[2];
             }
             const uint32_t xf = node_of(cn, g);
-            A v[kQ];
-#pragma unroll
-            for (int i = 0; i < kQ; ++i) v[i] = St<S>::ld(f + (int64_t)i * g.stride + xf, ph.inv_scale);
-            A drf, rf, uf[3];
-            moments<DEV, A>(v, A(-0.5), F, drf, rf, uf[0], uf[1], uf[2]);
-            A fdf = A(0);
-#pragma unroll
-            for (int i = 0; i < kQ; ++i) fdf = (i == d) ? v[i] : fdf;
+            const bool vibb = r.kind == LBM_LINK_VIBB;
             uint32_t xff = xf;
-            A rff = A(1), uff[3] = {A(0), A(0), A(0)}, fdff = A(0), drff = A(0);
-            if (r.kind == LBM_LINK_VIBB) {
+            if (vibb) {
                 int cf[3] = {cn[0] - e[0], cn[1] - e[1], cn[2] - e[2]};
                 wrap3(cf, g);
                 xff = node_of(cf, g);
-#pragma unroll
-                for (int i = 0; i < kQ; ++i) v[i] = St<S>::ld(f + (int64_t)i * g.stride + xff, ph.inv_scale);
-                moments<DEV, A>(v, A(-0.5), F, drff, rff, uff[0], uff[1], uff[2]);
-#pragma unroll
-                for (int i = 0; i < kQ; ++i) fdff = (i == d) ? v[i] : fdff;
             }
-            // value and gradient of the reconstructed population
-            DN x_fdf = var<A, N>(fdf, 0), x_rf = var<A, N>(rf, 1);
-            DN x_uf[3] = {var<A, N>(uf[0], 2), var<A, N>(uf[1], 3), var<A, N>(uf[2], 4)};
-            DN x_fdff = var<A, N>(fdff, 5), x_rff = var<A, N>(rff, 6);
-            DN x_uff[3] = {var<A, N>(uff[0], 7), var<A, N>(uff[1], 8), var<A, N>(uff[2], 9)};
-            DN x_uw[3] = {var<A, N>(A(uw[0]), 10), var<A, N>(A(uw[1]), 11),
-                          var<A, N>(A(uw[2]), 12)};
-            DN x_q;
-            if constexpr (GEO)
-                x_q = var<A, N>(A(r.q), 13);
-            else
-                x_q = DN(A(r.q));
-            const DN unk = link_value<DEV, A>(r.kind, d, e, x_q, x_fdf, x_rf, x_uf, x_fdff,
-                                              x_rff, x_uff, x_uw, ph.neq_split != 0);
-            // momentum exchange of this link: [(e_d - u_w) out - (e_db - u_w) in] . W
-            double out = (double)fdf, in = (double)unk.v;
-            if constexpr (DEV) {
-                out += wgt(d);
-                in += wgt(db);
-            }
-            double d_out = 0.0, d_in = 0.0;
+            // (halfway links load x_f twice: one batch either way)
+            A v[kQ], vv[kQ];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                d_out += ((double)e[a] - uw[a]) * Wv[a];
-                d_in += ((double)e[a] + uw[a]) * Wv[a];
-                acc[3 + a] += -(out - in) * Wv[a];
-                tv[a] = ((double)e[a] - uw[a]) * out + ((double)e[a] + uw[a]) * in;
-                G[a] = -(out - in) * Wv[a];
+            for (int i = 0; i < kQ; ++i) {
+                v[i] = St<S>::ld(f + (int64_t)i * g.stride + xf, ph.inv_scale);
+                vv[i] = St<S>::ld(f + (int64_t)i * g.stride + xff, ph.inv_scale);
             }
-            // adjoint of the reconstructed value: the fluid node that pulled
-            // the ghost slot, plus the objective
+            LinkIn<A> x;
+            LinkGrad<A> gk;
+            A dr;
+            x.fdf = St<S>::ld(f + (int64_t)d * g.stride + xf, ph.inv_scale);
+            x.fdff = St<S>::ld(f + (int64_t)d * g.stride + xff, ph.inv_scale);
             // the node kernel left the adjoint of the ghost slot (x_s, opp d),
             // which x_f pulled, in lambda(n) at x_s; take it and clear it
             A* ghost = lam0 + (int64_t)db * g.stride + r.node;
             const A lu = *ghost + A(d_in);
             *ghost = A(0);
-            A gk[N];
+            moments<DEV, A>(v, A(-0.5), F, dr, x.rf, x.uf[0], x.uf[1], x.uf[2]);
+            moments<DEV, A>(vv, A(-0.5), F, dr, x.rff, x.uff[0], x.uff[1], x.uff[2]);
 #pragma unroll
-            for (int k = 0; k < N; ++k) gk[k] = lu * unk.d[k];
-            atomic_add_a(lam0 + (int64_t)d * g.stride + xf, gk[0] + A(d_out));
-            const A irf = A(1) / rf;
-#pragma unroll
-            for (int j = 0; j < kQ; ++j) {
-                const A t = gk[1] + (gk[2] * (A(cx(j)) - uf[0]) + gk[3] * (A(cy(j)) - uf[1]) +
-                                     gk[4] * (A(cz(j)) - uf[2])) * irf;
-                atomic_add_a(lam0 + (int64_t)j * g.stride + xf, t);
+            for (int a = 0; a < 3; ++a) x.uw[a] = A(uw[a]);
+            x.q = A(r.q);
+            const A ea[3] = {A(e[0]), A(e[1]), A(e[2])};
+            const A unk = link_value<DEV, A>(r.kind, wgt_moving<A>(d), ea, x, ph.neq_split != 0, gk);
+            // momentum exchange of this link: [(e_d - u_w) out - (e_db - u_w) in] . W
+            double out = (double)x.fdf, inn = (double)unk;
+            if constexpr (DEV) {
+                out += wgt_moving<double>(d);
+                inn += wgt_moving<double>(d);
             }
+            // adjoint of the reconstructed value (lu): the fluid node that
+            // pulled the ghost slot, plus the objective; pushed to the
+            // populations of x_f and x_ff through f_d and the moments
+            auto push = [&](uint32_t node, A gf, A gr, const A gu[3], const A u[3], A rho) {
+                const A ir = A(1) / rho;
+                const A hx = gu[0] * ir, hy = gu[1] * ir, hz = gu[2] * ir;
+                const A c = gr - (hx * u[0] + hy * u[1] + hz * u[2]);
+                atomicAdd(lam0 + (int64_t)d * g.stride + node, gf);
 #pragma unroll
-            for (int a = 0; a < 3; ++a) acc[a] += -(double)(gk[2 + a] * A(0.5) * irf);
-            if (r.kind == LBM_LINK_VIBB) {
-                atomic_add_a(lam0 + (int64_t)d * g.stride + xff, gk[5]);
-                const A irff = A(1) / rff;
-#pragma unroll
-                for (int j = 0; j < kQ; ++j) {
-                    const A t = gk[6] + (gk[7] * (A(cx(j)) - uff[0]) + gk[8] * (A(cy(j)) - uff[1]) +
-                                         gk[9] * (A(cz(j)) - uff[2])) * irff;
-                    atomic_add_a(lam0 + (int64_t)j * g.stride + xff, t);
-                }
-#pragma unroll
-                for (int a = 0; a < 3; ++a) acc[a] += -(double)(gk[7 + a] * A(0.5) * irff);
+                for (int j = 0; j < kQ; ++j)
+                    atomicAdd(lam0 + (int64_t)j * g.stride + node, j ? c + edot(j, hx, hy, hz) : c);
+                acc[0] -= (double)(hx * A(0.5));
+                acc[1] -= (double)(hy * A(0.5));
+                acc[2] -= (double)(hz * A(0.5));
+            };
+            const A gf3[3] = {lu * gk.uf[0], lu * gk.uf[1], lu * gk.uf[2]};
+            push(xf, lu * gk.fdf + A(d_out), lu * gk.rf, gf3, x.uf, x.rf);
+            if (vibb) {
+                const A gff3[3] = {lu * gk.uff[0], lu * gk.uff[1], lu * gk.uff[2]};
+                push(xff, lu * gk.fdff, lu * gk.rff, gff3, x.uff, x.rff);
             }
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                acc[3 + a] += (double)gk[10 + a];
-                G[a] += (double)gk[10 + a];
+                tv[a] = (ed[a] - uw[a]) * out + (ed[a] + uw[a]) * inn;
+                G[a] = -(out - inn) * Wv[a] + (double)(lu * gk.uw[a]);
+                acc[3 + a] = G[a];
             }
-            if constexpr (GEO) dq = (double)gk[13];
-            (void)drf;
-            (void)drff;
+            if constexpr (GEO) dq = (double)(lu * gk.q);
         }
         if constexpr (GEO) {
             // dJ/dr: torque weight (wT x r).t and u_w = v + omega x r
@@ -737,6 +709,7 @@ __global__ __launch_bounds__(256) void k_adj_links(const typename St<S>::T* __re
                     qt[a] = an * rn[a] + as * rs[a];
                 }
             }
+#pragma unroll
             for (int a = 0; a < 3; ++a) {
                 acc[6 + a] = dq * qx[a] - Jr[a];
                 acc[9 + a] = dq * qt[a];
@@ -750,27 +723,36 @@ __global__ __launch_bounds__(256) void k_adj_links(const typename St<S>::T* __re
     if constexpr (GEO) {
         double* gl = ga.g_links + (int64_t)ga.gstride * p;
         double* vl = ga.v_links ? ga.v_links + (int64_t)ga.vstride * p : grad + 4 + 3 * p;
+        double* wl = ga.w_links + (int64_t)ga.vstride * p;
+        auto out = [=](int k) {
+            double* o = k < 3 ? grad + k : vl + (k - 3);
+            o = k < 6 ? o : gl + (k - 6);
+            return k < 12 ? o : wl + (k - 12);
+        };
         if (ga.w_links) {
-            double* wl = ga.w_links + (int64_t)ga.vstride * p;
-            double* outs[15] = {grad + 0, grad + 1, grad + 2, vl, vl + 1, vl + 2, gl, gl + 1, gl + 2,
-                                gl + 3, gl + 4, gl + 5, wl, wl + 1, wl + 2};
-            block_add<15>(acc, outs);
+            block_add<T>(acc, out);
         } else {
             double a12[12];
+#pragma unroll
             for (int k = 0; k < 12; ++k) a12[k] = acc[k];
-            double* outs[12] = {grad + 0, grad + 1, grad + 2, vl, vl + 1, vl + 2, gl, gl + 1, gl + 2,
-                                gl + 3, gl + 4, gl + 5};
-            block_add<12>(a12, outs);
+            block_add<T>(a12, out);
         }
     } else {
         double a6[6] = {acc[0], acc[1], acc[2], acc[3], acc[4], acc[5]};
-        double* outs[6] = {grad + 0, grad + 1, grad + 2, grad + 4 + 3 * p, grad + 5 + 3 * p,
-                           grad + 6 + 3 * p};
-        block_add<6>(a6, outs);
+        block_add<T>(a6, [=](int k) { return k < 3 ? grad + k : grad + 4 + 3 * p + (k - 3); });
     }
 }
 
 inline uint32_t blocks_for(int64_t n) { return (uint32_t)((n + 255) / 256); }
+
+// Up to one chunk per CU the link adjoint runs a wave per workgroup: its
+// gathers and its scattered atomics go lane by lane through a CU's address
+// unit, and one chunk's four waves then use four of them (one body in 128^3
+// FP32: 30.7 -> 18.8 us; two in 48 x 40 x 44 FP64 with the poses: 23.7 -> 13.2).
+// With 500 chunks and more the four-wave workgroup, with a quarter of the
+// per-body sums, is as fast or faster (500: 96 us against 101; 20000: 3.12 ms
+// against 3.28).
+constexpr uint32_t kWaveChunks = 256;
 
 template <int S>
 struct RunAdj {
@@ -795,17 +777,21 @@ struct RunAdj {
         if ((parts & kAdjLinks) && c->cfg.n_particles > 0 && ts.link_max > 0 && ts.lay &&
             ts.lay->chunks() > 0) {
             const int np = c->cfg.n_particles;
-            const dim3 grid((uint32_t)ts.lay->chunks());
+            const uint32_t nch = (uint32_t)ts.lay->chunks();
+            auto go = [&](auto geo, auto threads) {
+                constexpr int T_ = decltype(threads)::value;
+                hipLaunchKernelGGL((k_adj_links<S, decltype(geo)::value, T_>), dim3(nch * (256 / T_)),
+                                   dim3(T_), 0, c->stream, (const T*)ts.f, ts.links_use, ts.cursor,
+                                   ts.lay->off_dev, ts.lay->chunk_dev, ts.part, ts.part + 3 * np,
+                                   ts.part + 6 * np, (A*)lam0, wts, c->geom, c->phys, grad, ga);
+            };
+            using One = std::integral_constant<int, 64>;
+            using Four = std::integral_constant<int, 256>;
+            const bool waves = nch <= kWaveChunks;
             if (ga.g_links)
-                hipLaunchKernelGGL((k_adj_links<S, true>), grid, dim3(256), 0, c->stream,
-                                   (const T*)ts.f, ts.links_use, ts.cursor, ts.lay->off_dev,
-                                   ts.lay->chunk_dev, ts.part, ts.part + 3 * np,
-                                   ts.part + 6 * np, (A*)lam0, wts, c->geom, c->phys, grad, ga);
+                waves ? go(std::true_type{}, One{}) : go(std::true_type{}, Four{});
             else
-                hipLaunchKernelGGL((k_adj_links<S, false>), grid, dim3(256), 0, c->stream,
-                                   (const T*)ts.f, ts.links_use, ts.cursor, ts.lay->off_dev,
-                                   ts.lay->chunk_dev, ts.part, ts.part + 3 * np,
-                                   ts.part + 6 * np, (A*)lam0, wts, c->geom, c->phys, grad, ga);
+                waves ? go(std::false_type{}, One{}) : go(std::false_type{}, Four{});
         }
         return hipGetLastError();
     }

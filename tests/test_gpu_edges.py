@@ -83,3 +83,35 @@ def test_dem_paths_match_the_oracle(n, points):
     for key in ("pos", "vel", "omega", "quat", "world_pts"):
         a, b = getattr(G, key), getattr(P, key)
         assert np.abs(a - b).max() <= 1e-9 * max(1.0, np.abs(b).max()), key
+
+
+def test_link_adjoint_on_both_sides_of_the_wave_split():
+    """The adjoint of the links of 40 spheres (a wave per 64 records) and of 530
+    (a workgroup per 256-record chunk): the dot products of the larger set, and
+    the derivatives of the 40 spheres, which the other 490, more than two nodes
+    away, do not change beyond the order of the sums."""
+    from test_gpu_adjoint_dot import _Replay, _near_equilibrium, _replay_case
+    rng = np.random.default_rng(8)
+    m, n = 40, 530
+    k = np.arange(n)
+    lat = W.LatticeSpec(60, 60, 40, (1, 1, 0), tau=0.62, body_force=(1e-5, 0.0, 2e-5))
+    pos = np.stack([(k % 10) * 6.0 + 3.0, (k // 10 % 10) * 6.0 + 3.0, (k // 100) * 6.0 + 4.0], -1)
+    pos += rng.uniform(-0.4, 0.4, (n, 3))
+
+    def spheres(count):
+        rng = np.random.default_rng(9)
+        v, om = rng.normal(size=(n, 3)) * 0.02, rng.normal(size=(n, 3)) * 0.01
+        return W.make_particles([W.sphere_shape(3.3, 0.2)] * count, pos[:count],
+                                np.tile([1.0, 0, 0, 0], (count, 1)), 1.5, vel=v[:count],
+                                omega=om[:count])
+    f0 = _near_equilibrium(lat, rng)
+    few, many = _Replay(lat, spheres(m), 3), _Replay(lat, spheres(n), 3)
+    _replay_case(many, f0, 31, 1e-7)
+    lam1 = rng.normal(size=f0.shape) * (many.owners(f0)[1] == 0)[None, :]
+    w = rng.normal(size=(n, 6))
+    lam_a, g_a, x_a = few.run(f0, lam1=lam1, w=w[:m], adjoint=True)
+    lam_b, g_b, x_b = many.run(f0, lam1=lam1, w=w, adjoint=True)
+    inner = lambda a: a.reshape(-1, 40, 60, 60)[:, :6, 5:20]   # nodes of the 40 spheres alone
+    for a, b in ((inner(lam_a), inner(lam_b)), (g_a[4:], g_b[4:4 + 3 * m]), (x_a, x_b[:, :m])):
+        assert np.abs(a).max() > 0.1
+        assert np.abs(a - b).max() <= 1e-12 * np.abs(a).max()
