@@ -11,8 +11,7 @@
 // Work is organised per particle: a particle's nodes lie in a ball of radius
 // R <= h - 1 about x_p (a rigorous bound from the metaball weights), inside the
 // box of (2h+1)^3 nodes around floor(x_p).  One workgroup takes one z plane
-// of the box and walks the rows of the ball in it, a wave per row and a lane
-// per node.  Coordinates are unwrapped, so on a periodic axis they are exactly
+// of the box.  Coordinates are unwrapped, so on a periodic axis they are exactly
 // the node's image nearest x_p (the box is narrower than half the period).
 #pragma clang fp contract(off)
 
@@ -20,6 +19,7 @@
 
 #include "lbm_internal.h"
 #include "lbm_stencil.h"
+#include "lbm_kernels.h"
 
 namespace mdlbm {
 namespace {
@@ -40,15 +40,38 @@ __device__ __forceinline__ int stage_ctrl(const PartDev& P, int p, double* sp)
     return n;
 }
 
+// (four quotients in flight; the sum takes them in order)
 __device__ __forceinline__ double metaball(const double* sp, int n, double X, double Y, double Z)
 {
-    double M = 0.0;
-    for (int i = 0; i < n; ++i) {
+    auto term = [&](int i) {
         const double dx = X - sp[4 * i + 0];
         const double dy = Y - sp[4 * i + 1];
         const double dz = Z - sp[4 * i + 2];
         const double r2 = (dx * dx + dy * dy) + dz * dz;
-        M = M + sp[4 * i + 3] / r2;
+        return sp[4 * i + 3] / r2;
+    };
+    double M = 0.0;
+    int i = 0;
+    for (; i + 4 <= n; i += 4) {
+        const double a = term(i), b = term(i + 1), c = term(i + 2), d = term(i + 3);
+        M = (((M + a) + b) + c) + d;
+    }
+    for (; i < n; ++i) M = M + term(i);
+    return M;
+}
+
+// The same, point by point from global memory, where it is rarely needed.
+__device__ __forceinline__ double metaball_rare(const double* w, const double* K, int n, double X,
+                                                double Y, double Z)
+{
+    double M = 0.0;
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) {
+        const double dx = X - w[3 * i + 0];
+        const double dy = Y - w[3 * i + 1];
+        const double dz = Z - w[3 * i + 2];
+        const double r2 = (dx * dx + dy * dy) + dz * dz;
+        M = M + K[i] / r2;
     }
     return M;
 }
@@ -56,6 +79,13 @@ __device__ __forceinline__ double metaball(const double* sp, int n, double X, do
 __device__ __forceinline__ uint32_t node_idx(const int c[3], const Geom& g)
 {
     return (uint32_t)c[0] + (uint32_t)g.n[0] * ((uint32_t)c[1] + (uint32_t)g.n[1] * (uint32_t)c[2]);
+}
+
+// An unwrapped coordinate beyond the lattice, wrapped onto a periodic axis.
+__device__ __forceinline__ int wrap_axis(int v, int n)
+{
+    v += v < 0 ? n : -n;
+    return v >= 0 && v < n ? v : ((v % n) + n) % n;
 }
 
 // Wrap unwrapped coordinates onto the lattice; false beyond a wall.
@@ -67,7 +97,7 @@ __device__ __forceinline__ bool wrap_cell(const int ii[3], const Geom& g, int c[
         int v = ii[a];
         if (v < 0 || v >= g.n[a]) {
             if (g.per[a])
-                v = ((v % g.n[a]) + g.n[a]) % g.n[a];
+                v = wrap_axis(v, g.n[a]);
             else
                 ok = false;
         }
@@ -76,32 +106,13 @@ __device__ __forceinline__ bool wrap_cell(const int ii[3], const Geom& g, int c[
     return ok;
 }
 
-// Neighbour c - e (wrapped); false when it lies beyond a wall.
-__device__ __forceinline__ bool neighbour(const int c[3], int ex, int ey, int ez, const Geom& g,
-                                          int out[3])
-{
-    const int e[3] = {ex, ey, ez};
-    bool ok = true;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        int v = c[a] - e[a];
-        if (v < 0 || v >= g.n[a]) {
-            if (g.per[a])
-                v = v < 0 ? v + g.n[a] : v - g.n[a];
-            else
-                ok = false;
-        }
-        out[a] = v;
-    }
-    return ok;
-}
-
-// Visit the nodes of one z plane (blockIdx.x of the box) inside the ball
-// (x_p, R): the block's waves take rows y in turn and the lanes of a wave the
-// consecutive x of a row.  fn(ii, active) is called by every lane of a wave
-// together, so it may use wave-wide operations.
+// Visit the nodes of one z plane of the box (blockIdx.x) in the square around
+// the ball (x_p, R)'s circle there, 32 x 8 nodes a workgroup and two such tiles
+// at once: fn(node, on) for each tile, called by every lane of a wave together
+// (on: the node exists and lies in the ball).  A wave per row with the row's
+// FP64 ends first, one row after the other, was a longer chain.
 template <class Fn>
-__device__ __forceinline__ void walk_ball_plane(const double* ball, int h, Fn&& fn)
+__device__ __forceinline__ void walk_ball_plane(const double* ball, int h, const Geom& g, Fn&& fn)
 {
     const double bx = ball[0], by = ball[1], bz = ball[2], R = ball[3];
     const int zi = (int)floor(bz) - h + (int)blockIdx.x;
@@ -110,18 +121,21 @@ __device__ __forceinline__ void walk_ball_plane(const double* ball, int h, Fn&& 
     if (r2z < 0.0) return;  // uniform over the block
     const double ry = sqrt(r2z);
     const int ylo = (int)ceil(by - ry), yhi = (int)floor(by + ry);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-    for (int yi = ylo + wave; yi <= yhi; yi += nw) {
-        const double dy = (double)yi - by;
-        const double r2x = r2z - dy * dy;
-        if (r2x < 0.0) continue;  // uniform over the wave
-        const double rx = sqrt(r2x);
-        const int xlo = (int)ceil(bx - rx), xhi = (int)floor(bx + rx);
-        for (int x0 = xlo; x0 <= xhi; x0 += 64) {
-            const int ii[3] = {x0 + lane, yi, zi};
-            fn(ii, x0 + lane <= xhi);
+    const int xlo = (int)ceil(bx - ry), xhi = (int)floor(bx + ry);
+    for (int y0 = ylo + (int)(threadIdx.x >> 5); y0 - (int)(threadIdx.x >> 5) <= yhi; y0 += 16)
+        for (int x = xlo + (int)(threadIdx.x & 31); x - (int)(threadIdx.x & 31) <= xhi; x += 32) {
+            uint32_t node[2];
+            bool on[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int ii[3] = {x, y0 + 8 * k, zi};
+                const double dx = (double)ii[0] - bx, dy = (double)ii[1] - by;
+                int c[3];
+                on[k] = dx * dx + dy * dy <= r2z && wrap_cell(ii, g, c);
+                node[k] = on[k] ? node_idx(c, g) : 0u;
+            }
+            fn(node, on);
         }
-    }
 }
 
 // Wave-wide exclusive offset of `count` within a reservation of `total`
@@ -140,23 +154,6 @@ __device__ __forceinline__ uint32_t wave_reserve(uint32_t count, uint32_t* curso
     if (lane == 63 && total != 0) base = atomicAdd(cursor, total);
     base = __shfl(base, 63, 64);
     return base + incl - count;
-}
-
-// First slot of a block of sum(count) slots taken from *cursor with one
-// atomic per wave (the same value on every lane).  Every lane must call it.
-__device__ __forceinline__ uint32_t wave_base(uint32_t count, uint32_t* cursor)
-{
-    const int lane = threadIdx.x & 63;
-    uint32_t incl = count;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-    }
-    const uint32_t total = __shfl(incl, 63, 64);
-    uint32_t base = 0;
-    if (lane == 63 && total != 0) base = atomicAdd(cursor, total);
-    return __shfl(base, 63, 64);
 }
 
 // Block (bx, by) of a gx x gy work grid launched as a 1D grid of a multiple of
@@ -186,6 +183,12 @@ __device__ __forceinline__ double wave_sum_d(double v)
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
+}
+
+// v of lane j (the same j on every lane).
+__device__ __forceinline__ float lane_of(float v, int j)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j));
 }
 
 // One wave per particle, a lane per control point (n <= 64).
@@ -229,30 +232,32 @@ __global__ __launch_bounds__(64) void k_boxes(PartDev P, int h, double* ball, ui
     if (!(lim > rmax) || !(bound(lim) < c0)) {
         bad |= 4u;
     } else {
-        // B decreases beyond rmax.  A 64-way search keeps B(hi) < c0, so hi
-        // bounds the body at every round: the lanes test 64 points of
-        // (lo, hi], each summing B over the control points itself, and the
-        // first that passes becomes hi; six rounds shrink an interval below
-        // 2 h under 1e-9
+        // B decreases beyond rmax.  A 64-way search in FP32 closes in on its
+        // root: the lanes test 64 points of (lo, hi], each summing B over the
+        // control points itself, and the first below c0 becomes hi; five
+        // rounds reach FP32's spacing.  The FP64 sum then has to pass at the
+        // radius found, widened past the FP32 sum's error; else the box's own
+        // bound, tested above, stands.
         const int nn = min(n, kMaxCtrl);
-        double lo = rmax, hi = lim;
-        for (int round = 0; round < 6; ++round) {
-            const double step = (hi - lo) * (1.0 / 64.0);
-            const double d = lane == 63 ? hi : lo + step * (double)(lane + 1);
-            double B = 0.0;
+        const float rf = (float)ri, Kf = (float)Ki, cf = (float)c0 * 0.9999f;
+        float lo = (float)rmax, hi = (float)lim;
+        for (int round = 0; round < 5; ++round) {
+            const float step = (hi - lo) * (1.0f / 64.0f);
+            const float d = lane == 63 ? hi : lo + step * (float)(lane + 1);
+            float B = 0.0f;
             for (int j = 0; j < nn; ++j) {
-                const double t = d - __shfl(ri, j, 64);
-                B += __shfl(Ki, j, 64) / (t * t);
+                const float t = d - lane_of(rf, j);
+                B += lane_of(Kf, j) * __builtin_amdgcn_rcpf(t * t);
             }
-            const uint64_t pass = __ballot(B < c0);
+            const uint64_t pass = __ballot(B < cf);
             if (!pass) break;  // uniform; hi keeps its bound
             const int first = __ffsll((unsigned long long)pass) - 1;
-            const double nh = __shfl(d, first, 64);
-            const double nl = __shfl(d, first > 0 ? first - 1 : 0, 64);
+            const float nh = lane_of(d, first), nl = lane_of(d, first > 0 ? first - 1 : 0);
             hi = nh;
             if (first > 0) lo = nl;
         }
-        R = hi;
+        const double near = (double)hi * (1.0 + 1e-5) + 1e-5;
+        if (near > rmax && near < lim && bound(near) < c0) R = near;
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) bad |= __shfl_xor(bad, o, 64);
@@ -294,9 +299,10 @@ __global__ __launch_bounds__(256) void k_clear(const uint32_t* __restrict__ err,
 {
     if (*err) return;  // the boxes failed their check: leave every plane as it is
     const int p = blockIdx.y;
-    walk_ball_plane(ball + 4 * p, h, [&](const int* ii, bool act) {
-        int c[3];
-        if (act && wrap_cell(ii, g, c)) own[node_idx(c, g)] = kFluid;
+    walk_ball_plane(ball + 4 * p, h, g, [&](const uint32_t* node, const bool* on) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (on[k]) own[node[k]] = kFluid;
     });
 }
 
@@ -305,10 +311,15 @@ __global__ __launch_bounds__(256) void k_clear(const uint32_t* __restrict__ err,
 // Which nodes are visited.  If every control point lies farther than
 // rho = sqrt(sum_i K_i / c0) from a node, M_p < c0 there, so p's body lies
 // in the union of the balls (x_i, rho); it also lies in the ball (x_p, R) of
-// k_boxes.  One workgroup takes one z plane of p's box: it tabulates, for
-// every row y of the plane, the x range of the union's hull on that row
-// intersected with the centre ball, prefix-sums the row lengths in LDS and
-// hands the flattened nodes to its lanes, so no lane idles at row ends.
+// k_boxes.  One workgroup takes one z plane of p's box: for every row y of the
+// plane it takes the x range of the union's hull on that row intersected with
+// the centre ball, cuts it into segments of 8 nodes, lists them in LDS (a
+// prefix sum over the rows places them) and hands them to its lanes, so a lane
+// finds its node by one LDS read and few lanes idle at row ends.  The ranges
+// are FP32 and widened by more than their error: with coordinates relative to
+// o off by at most (3h + 1) 2^-24, squares and their sums are off by less than
+// (2h + 4)^2 2^-21 and ends by less than (2h + 4) 2^-21; a node visited in vain
+// is decided as not solid.
 //
 // How a node is decided.  The FP64 sum alone decides, bit for bit; an FP32
 // estimate settles the nodes far from the decision.  The estimate works in
@@ -327,78 +338,89 @@ __global__ __launch_bounds__(256) void k_clear(const uint32_t* __restrict__ err,
 // node where the FP32 value of this bound (E rounded up) clears c0 by the
 // same margin (its relative error stays below 3.5e-5 for h <= 127: the
 // r_i + E terms are never small) has M_p >= c0 at every neighbour, hence no
-// link of any kind, and is left off p's candidate list.  Every other solid
-// node of p goes on the list.
-constexpr int kRows = 2 * kMaxBoxHalf + 1;
-constexpr uint32_t kCandBuf = 2048;
-
-__global__ __launch_bounds__(256, 8) void k_mark(const uint32_t* __restrict__ err, uint32_t* own, const double* ball, int h, PartDev P,
+// link of any kind, and is left off p's candidate list; and it is solid, so
+// this bound comes first and the interior of a body needs no other.  Every
+// other solid node of p goes on the list.
+//
+// Bound by the arithmetic of the visited nodes and of each plane's preparation
+// where bodies are many (1000 in 512^3: 317 us; 425 with FP64 row ends, a
+// binary search for each node's row and the bound of the interior after the
+// estimate), by the chain of one plane's steps where they are few (one body:
+// 6.4 us, before 7.1).
+template <int T>
+__global__ __launch_bounds__(T, 8) void k_mark(const uint32_t* __restrict__ err, uint32_t* own, const double* ball, int h, PartDev P,
                                               Geom g, uint8_t* flag, int store_flag, uint32_t* cand,
                                               int64_t cap, uint32_t* cursors)
 {
     if (*err) return;  // the boxes failed their check: leave every plane as it is
-    __shared__ double sp[4 * kMaxCtrl];
+    constexpr int kSegs = 8 * T;           // segments of 8 nodes listed at a time
+    constexpr uint32_t kCandBuf = 8 * T;
     __shared__ float4 sf[kMaxCtrl];
-    __shared__ int rlo[kRows];
-    __shared__ int rstart[kRows + 1];
+    __shared__ uint32_t seg[kSegs];  // row, first x (both from the box's corner)
     __shared__ int wsum[4];
     __shared__ uint32_t cbuf[kCandBuf];  // this plane's candidates, in walk order
-    __shared__ uint32_t ccount;
+    __shared__ uint32_t ccount, gbase;
     const int p = blockIdx.y;
-    const int n = stage_ctrl(P, p, sp);
-    const double c0 = P.c0[p];
     const double bx = ball[4 * p + 0], by = ball[4 * p + 1], bz = ball[4 * p + 2];
     const double R = ball[4 * p + 3];
     const int ox = (int)floor(bx), oy = (int)floor(by), oz = (int)floor(bz);
     const int zi = oz - h + (int)blockIdx.x;
-    const int S = 2 * h + 1;
-    double ksum = 0.0;
-    for (int i = 0; i < n; ++i) ksum += sp[4 * i + 3];
-    const double rho2 = ksum / c0 * (1.0 + 1e-6);
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const double dz = (double)zi - sp[4 * i + 2];
-        sf[i] = make_float4((float)(sp[4 * i + 0] - (double)ox), (float)(sp[4 * i + 1] - (double)oy),
-                            (float)(dz * dz), (float)sp[4 * i + 3]);
-    }
-    // row table: thread t takes rows rpt t .. rpt t + rpt - 1, rpt = 1 for
-    // S <= 256 (so every wave shares the FP64 row bounds), up to 4
-    const int rpt = (S + 255) >> 8;
     const double dzc = (double)zi - bz;
     const double r2z = R * R - dzc * dzc;
-    int len[4];
+    if (r2z < 0.0) return;  // uniform over the block
+    const int S = 2 * h + 1;
+    const int a0 = P.off[p], n = min(P.off[p + 1] - a0, kMaxCtrl);
+    const double c0 = P.c0[p];
+    const double* wp = P.wpts + 3 * (int64_t)a0;
+    const double* Kp = P.K + a0;
+    for (int i = threadIdx.x; i < n; i += T) {
+        const double dz = (double)zi - wp[3 * i + 2];
+        sf[i] = make_float4((float)(wp[3 * i] - (double)ox), (float)(wp[3 * i + 1] - (double)oy),
+                            (float)(dz * dz), (float)Kp[i]);
+    }
+    if (threadIdx.x == 0) ccount = 0;
+    __syncthreads();
+    const float c0f = (float)c0;
+    float ksum = 0.0f;
+    for (int i = 0; i < n; ++i) ksum += sf[i].w;
+    const float span = (float)(2 * h + 4), slack = span * 0x1p-21f, slack2 = span * span * 0x1p-20f;
+    const float rho2 = ksum / c0f * 1.00002f + slack2;
+    // rows: thread t takes rows rpt t .. rpt t + rpt - 1, rpt up to 4
+    const int rpt = (S + T - 1) / T;
+    const float bxf = (float)(bx - (double)ox), byf = (float)(by - (double)oy);
+    const float r2zf = (float)r2z * 1.000001f + slack2;
+    uint32_t span8[4];  // first x from the box's corner << 16 | segments
     int tsum = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int r = rpt * (int)threadIdx.x + k;
-        len[k] = 0;
-        if (k < rpt && r < S && r2z >= 0.0) {
-            const int yi = oy - h + r;
-            const double dyc = (double)yi - by;
-            const double r2x = r2z - dyc * dyc;
-            if (r2x >= 0.0) {
-                const double rx = sqrt(r2x);
-                double lo = 1e300, hi = -1e300;
+        span8[k] = 0;
+        if (k < rpt && r < S) {
+            const float Y = (float)(r - h), dyc = Y - byf;
+            const float r2x = r2zf - dyc * dyc;
+            if (r2x >= 0.0f) {
+                const float rx = __builtin_amdgcn_sqrtf(r2x) * 1.000001f + slack;
+                float lo = 3e38f, hi = -3e38f;
                 for (int i = 0; i < n; ++i) {
-                    const double dy = (double)yi - sp[4 * i + 1];
-                    const double dz = (double)zi - sp[4 * i + 2];
-                    const double rem = rho2 - (dy * dy + dz * dz);
-                    if (rem >= 0.0) {
-                        const double w = sqrt(rem) + 1e-6;
-                        lo = fmin(lo, sp[4 * i + 0] - w);
-                        hi = fmax(hi, sp[4 * i + 0] + w);
+                    const float4 q = sf[i];
+                    const float dy = Y - q.y;
+                    const float rem = rho2 - (dy * dy + q.z);
+                    if (rem >= 0.0f) {
+                        const float w = __builtin_amdgcn_sqrtf(rem) * 1.000001f + slack;
+                        lo = fminf(lo, q.x - w);
+                        hi = fmaxf(hi, q.x + w);
                     }
                 }
+                lo = ceilf(fmaxf(lo - slack, bxf - rx));
+                hi = floorf(fminf(hi + slack, bxf + rx));
                 if (hi >= lo) {  // some control-point ball meets the row
-                    const int xlo = max((int)ceil(bx - rx), (int)ceil(lo));
-                    const int xhi = min((int)floor(bx + rx), (int)floor(hi));
-                    if (xhi >= xlo) {
-                        rlo[r] = xlo;
-                        len[k] = xhi - xlo + 1;
-                    }
+                    const int x = max((int)lo, -h);
+                    const int c = (min((int)hi, h) - x + 8) >> 3;
+                    span8[k] = (uint32_t)(x + h) << 16 | (uint32_t)c;
+                    tsum += c;
                 }
             }
         }
-        tsum += len[k];
     }
     // block-wide exclusive scan of the per-thread sums
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -408,65 +430,49 @@ __global__ __launch_bounds__(256, 8) void k_mark(const uint32_t* __restrict__ er
         const int t = __shfl_up(incl, o, 64);
         if (lane >= o) incl += t;
     }
-    if (lane == 63) wsum[wv] = incl;
-    __syncthreads();
-    int off = incl - tsum;
-    for (int w = 0; w < wv; ++w) off += wsum[w];
-    const int total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int r = rpt * (int)threadIdx.x + k;
-        if (k < rpt && r < S) rstart[r] = off;
-        off += len[k];
+    int off = incl - tsum, total;
+    if constexpr (T == 64) {
+        total = __shfl(incl, 63, 64);
+    } else {
+        if (lane == 63) wsum[wv] = incl;
+        __syncthreads();
+        for (int w = 0; w < wv; ++w) off += wsum[w];
+        total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
     }
-    if (threadIdx.x == 0) {
-        rstart[S] = total;
-        ccount = 0;
-    }
-    __syncthreads();
     if (total == 0) return;  // uniform over the block
 
     uint32_t* list = cand + (int64_t)p * cap;
     uint32_t* cursor = cursors + (int64_t)p * kCursorPad;
-    const float c0f = (float)c0;
     const float c0hi = c0f * 1.0001f, c0lo = c0f * 0.9999f;
     const float gr = fmaxf(0.5f, 0.0085f * (float)(2 * h + 4));
     const float guard2 = h <= 127 ? gr * gr : 3.0e38f;
-    int top = 1;
-    while (top <= S) top <<= 1;
-    for (int j0 = 0; j0 < total; j0 += 256) {
-        const int j = j0 + (int)threadIdx.x;
-        bool keep = false;
-        uint32_t node = 0;
-        if (j < total) {
-            // row of flattened node j: the last r with rstart[r] <= j
-            int r = 0;
-            for (int step = top >> 1; step > 0; step >>= 1)
-                if (r + step <= S && rstart[r + step] <= j) r += step;
-            const int ii[3] = {rlo[r] + (j - rstart[r]), oy - h + r, zi};
-            int c[3];
-            if (wrap_cell(ii, g, c)) {
-                node = node_idx(c, g);
-                const float X = (float)(ii[0] - ox), Y = (float)(ii[1] - oy);
-                float Mf = 0.0f, m2 = 3.0e38f;
-                for (int i = 0; i < n; ++i) {
-                    const float4 q = sf[i];
-                    const float dx = X - q.x, dy = Y - q.y;
-                    const float r2 = fmaf(dx, dx, fmaf(dy, dy, q.z));
-                    Mf = fmaf(q.w, __builtin_amdgcn_rcpf(r2), Mf);
-                    m2 = fminf(m2, r2);
-                }
-                const bool settled = Mf >= c0hi || Mf <= c0lo;  // false for NaN
-                const bool solid =
-                    (m2 < guard2 || !settled)
-                        ? metaball(sp, n, (double)ii[0], (double)ii[1], (double)ii[2]) >= c0
-                        : Mf >= c0hi;
-                if (solid) {
-                    atomicMin(own + node, (uint32_t)p);
-                    if (store_flag) flag[node] = 1;
-                    bool interior = false;
-                    if (h <= 127) {
-                        float lb = 0.0f;
+    for (int s0 = 0; s0 < total; s0 += kSegs) {
+        int at = off - s0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (k < rpt) {
+                const uint32_t row = (uint32_t)(rpt * (int)threadIdx.x + k) << 16;
+                const uint32_t x = span8[k] >> 16;
+                for (uint32_t i = 0; i < (span8[k] & 0xFFFFu); ++i, ++at)
+                    if (at >= 0 && at < kSegs) seg[at] = row | (x + 8u * i);
+            }
+        }
+        __syncthreads();
+        const int nodes = 8 * min(total - s0, kSegs);
+        for (int j0 = 0; j0 < nodes; j0 += T) {
+            const int j = j0 + (int)threadIdx.x;
+            bool keep = false;
+            uint32_t node = 0;
+            if (j < nodes) {
+                const uint32_t sg = seg[j >> 3];
+                const int xr = (int)(sg & 0xFFFFu) - h + (j & 7), yr = (int)(sg >> 16) - h;
+                const int ii[3] = {ox + xr, oy + yr, zi};
+                int c[3];
+                if (wrap_cell(ii, g, c)) {
+                    node = node_idx(c, g);
+                    const float X = (float)xr, Y = (float)yr;
+                    float lb = 0.0f;
+                    if (h <= 127)
                         for (int i = 0; i < n; ++i) {
                             const float4 q = sf[i];
                             const float dx = X - q.x, dy = Y - q.y;
@@ -474,35 +480,55 @@ __global__ __launch_bounds__(256, 8) void k_mark(const uint32_t* __restrict__ er
                             const float t = __builtin_amdgcn_sqrtf(r2) + kMaxSpeedUp;
                             lb = fmaf(q.w, __builtin_amdgcn_rcpf(t * t), lb);
                         }
-                        interior = lb >= c0hi;
+                    const bool interior = lb >= c0hi;
+                    bool solid = interior;
+                    if (!interior) {
+                        float Mf = 0.0f, m2 = 3.0e38f;
+                        for (int i = 0; i < n; ++i) {
+                            const float4 q = sf[i];
+                            const float dx = X - q.x, dy = Y - q.y;
+                            const float r2 = fmaf(dx, dx, fmaf(dy, dy, q.z));
+                            Mf = fmaf(q.w, __builtin_amdgcn_rcpf(r2), Mf);
+                            m2 = fminf(m2, r2);
+                        }
+                        const bool settled = Mf >= c0hi || Mf <= c0lo;  // false for NaN
+                        solid = Mf >= c0hi;
+                        if (m2 < guard2 || !settled)
+                            solid = metaball_rare(wp, Kp, n, (double)ii[0], (double)ii[1],
+                                                  (double)ii[2]) >= c0;
                     }
-                    keep = !interior;
+                    if (solid) {
+                        atomicMin(own + node, (uint32_t)p);
+                        if (store_flag) flag[node] = 1;
+                        keep = !interior;
+                    }
+                }
+            }
+            // candidates gather in LDS so that the plane's list stays contiguous
+            // and in row order (neighbouring candidates then share owner rows in
+            // k_links); a full buffer spills lanes straight to the list
+            const uint64_t m = __ballot(keep);
+            if (m) {  // uniform over the wave
+                uint32_t wbase = 0;
+                if (lane == 0) wbase = atomicAdd(&ccount, (uint32_t)__popcll(m));
+                wbase = __shfl(wbase, 0, 64);
+                if (keep) {
+                    const uint32_t idx = wbase + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                    if (idx < kCandBuf) {
+                        cbuf[idx] = node;
+                    } else {
+                        const uint32_t slot = atomicAdd(cursor, 1u);
+                        if (slot < cap) list[slot] = node;
+                    }
                 }
             }
         }
-        // candidates gather in LDS so that the plane's list stays contiguous
-        // and in row order (neighbouring candidates then share owner rows in
-        // k_links); a full buffer spills lanes straight to the list
-        const uint64_t m = __ballot(keep);
-        uint32_t wbase = 0;
-        if (lane == 0 && m) wbase = atomicAdd(&ccount, (uint32_t)__popcll(m));
-        wbase = __shfl(wbase, 0, 64);
-        if (keep) {
-            const uint32_t idx = wbase + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-            if (idx < kCandBuf) {
-                cbuf[idx] = node;
-            } else {
-                const uint32_t slot = atomicAdd(cursor, 1u);
-                if (slot < cap) list[slot] = node;
-            }
-        }
+        __syncthreads();
     }
-    __syncthreads();
-    __shared__ uint32_t gbase;
     const uint32_t nb = min(ccount, (uint32_t)kCandBuf);
     if (threadIdx.x == 0) gbase = nb ? atomicAdd(cursor, nb) : 0u;
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < nb; i += blockDim.x)
+    for (uint32_t i = threadIdx.x; i < nb; i += T)
         if (gbase + i < cap) list[gbase + i] = cbuf[i];
 }
 
@@ -514,20 +540,28 @@ __global__ __launch_bounds__(256) void k_finish(const uint32_t* __restrict__ err
 {
     if (*err) return;  // the boxes failed their check: leave every plane as it is
     const int p = blockIdx.y;
-    walk_ball_plane(ball + 4 * p, h, [&](const int* ii, bool act) {
-        int c[3];
-        bool refill = false;
-        uint32_t node = 0;
-        if (act && wrap_cell(ii, g, c)) {
-            node = node_idx(c, g);
-            const uint32_t on = own_new[node];
-            flag[node] = on != kFluid;
-            refill = own_prev[node] == (uint32_t)p && on == kFluid;
+    const int lane = threadIdx.x & 63;
+    walk_ball_plane(ball + 4 * p, h, g, [&](const uint32_t* node, const bool* on) {
+        uint32_t now[2], was[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            now[k] = on[k] ? own_new[node[k]] : 0u;
+            was[k] = on[k] ? own_prev[node[k]] : kFluid;
         }
-        const uint32_t slot = wave_reserve(refill ? 1u : 0u, cursor);
-        if (refill && slot < cap) {
-            rec[slot].node = node;
-            rec[slot].part = (uint32_t)p;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (on[k]) flag[node[k]] = now[k] != kFluid;
+            const bool refill = now[k] == kFluid && was[k] == (uint32_t)p;
+            const uint64_t m = __ballot(refill);
+            if (!m) continue;  // uniform over the wave
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(cursor, (uint32_t)__popcll(m));
+            base = __shfl(base, 0, 64);
+            const uint32_t slot = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+            if (refill && slot < cap) {
+                rec[slot].node = node[k];
+                rec[slot].part = (uint32_t)p;
+            }
         }
     });
 }
@@ -573,33 +607,23 @@ __device__ double exact_q(const double* sp, int n, const double Xn[3], const int
     return q;
 }
 
-// Position of the k-th (from 0) set bit of m; m has more than k set bits.
-__device__ __forceinline__ int select_bit(uint64_t m, uint32_t k)
-{
-    int pos = 0;
-#pragma unroll
-    for (int w = 32; w >= 1; w >>= 1) {
-        const uint64_t low = m & ((1ull << w) - 1ull);
-        const uint32_t c = (uint32_t)__popcll(low);
-        if (k >= c) {
-            k -= c;
-            m >>= w;
-            pos += w;
-        }
-    }
-    return pos;
-}
-
 // Link records of the candidate nodes of p (those p owns), written
 // direction-major within each wave: the links of one direction over a run of
 // neighbouring candidates are contiguous, so the link kernel's gathers
 // coalesce.  Each lane first finds the link directions of its candidate; the
-// wave then enumerates its links in that order and gives one link to each
-// lane (candidate data by lane shuffles), so the FP64 work of q runs on full
-// waves.  A grid of a few workgroups per particle strides over the list.
-// With few particles a wave takes cpw = 16 candidates instead of 64: about
-// one link per lane then, and four times the waves, so the serial
-// enumeration is short where the list is too small to fill the chip.
+// wave then lists its (direction, candidate) pairs in LDS in that order and
+// gives one to each lane (candidate data by lane shuffles), so the FP64 work of
+// q runs on full waves.  A grid of a few workgroups per particle strides over
+// the list.
+// With few particles a wave takes cpw = 12 candidates instead of 64: at about
+// five links each one round of the lanes then, and more waves where the list is
+// too small to fill the chip.
+//
+// One body is bound by the chain of loads, quotients and the cursor's atomic
+// (8.6 us; 14.4 with directions compared at run time, the list's k-th link
+// searched by each lane, the quotients of M one after the other and 16
+// candidates a wave), many by issue and gathers (1000 in 512^3: 444 us, before
+// 575; 60 with exact fractions 38 us, before 48).
 __global__ __launch_bounds__(256, 6) void k_links(const uint32_t* __restrict__ err, const uint32_t* own, const double* ball, PartDev P,
                                                Geom g, const uint32_t* cand, int64_t cand_cap,
                                                const uint32_t* cand_cursors, LinkRec* links,
@@ -609,116 +633,125 @@ __global__ __launch_bounds__(256, 6) void k_links(const uint32_t* __restrict__ e
 {
     if (*err) return;  // the boxes failed their check: leave every plane as it is
     __shared__ double sp[4 * kMaxCtrl];
+    __shared__ uint16_t pairs[4][64 * (kQ - 1)];  // per wave: direction << 6 | lane
     uint32_t bx, by;
     if (!xcd_tile(gx, (uint32_t)P.n, bx, by)) return;  // uniform over the block
     const int p = (int)by;
+    const uint32_t count = min((uint32_t)cand_cap, cand_cursors[(int64_t)p * kCursorPad]);
+    const uint32_t chunk = 4u * cpw;  // candidates of one workgroup per round
+    if (bx * chunk >= count) return;  // uniform over the block
     const int n = stage_ctrl(P, p, sp);
     const double c0 = P.c0[p];
     const double B[3] = {ball[4 * p], ball[4 * p + 1], ball[4 * p + 2]};  // loaded once
     const uint32_t* list = cand + (int64_t)p * cand_cap;
-    const uint32_t count = min((uint32_t)cand_cap, cand_cursors[(int64_t)p * kCursorPad]);
     LinkRec* out = links + loff[p];
     const int64_t cap = loff[p + 1] - loff[p];  // p's segment
     uint32_t* cursor = cursors + (int64_t)p * kCursorPad;
     const int lane = threadIdx.x & 63;
-    const uint32_t chunk = 4u * cpw;  // candidates of one workgroup per round
+    uint16_t* pl = pairs[threadIdx.x >> 6];
     for (uint32_t base0 = bx * chunk; base0 < count; base0 += gx * chunk) {
         const uint32_t k = base0 + (threadIdx.x >> 6) * cpw + (uint32_t)lane;
         uint32_t node = 0, mask = 0, fmask = 0;  // link directions; those with x_f fluid
-        int c[3] = {0, 0, 0};
-        double X = 0.0, Y = 0.0, Z = 0.0;
+        int u[3] = {0, 0, 0};  // unwrapped: the image nearest the particle centre
         if ((uint32_t)lane < cpw && k < count) {
             node = list[k];
-            c[0] = (int)(node % (uint32_t)g.n[0]);
-            c[1] = (int)((node / (uint32_t)g.n[0]) % (uint32_t)g.n[1]);
-            c[2] = (int)(node / ((uint32_t)g.n[0] * (uint32_t)g.n[1]));
-            // unwrapped coordinates: the image nearest the particle centre
-            double Xc[3];
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                double v = (double)c[a];
-                if (g.per[a]) {
-                    const double d = v - B[a];
-                    if (d > 0.5 * g.n[a]) v -= g.n[a];
-                    else if (d < -0.5 * g.n[a]) v += g.n[a];
-                }
-                Xc[a] = v;
-            }
-            X = Xc[0], Y = Xc[1], Z = Xc[2];
+            uint32_t c[3], o[3][3];
+            bool in[3][3];
+            node_xyz(node, g, c[0], c[1], c[2]);
+            axis3(c[0], g.n[0], g.per[0], 1u, o[0], in[0]);
+            axis3(c[1], g.n[1], g.per[1], g.n[0], o[1], in[1]);
+            axis3(c[2], g.n[2], g.per[2], (uint32_t)g.n[0] * (uint32_t)g.n[1], o[2], in[2]);
             // the node's owner and its neighbours' in one batch of loads
             // (each from a valid address), before any branch on them
             const uint32_t self = own[node];
             uint32_t onv[kQ];
-            uint32_t okm = 0;
 #pragma unroll
-            for (int d = 1; d < kQ; ++d) {
-                int cn[3];
-                const bool ok = neighbour(c, cx(d), cy(d), cz(d), g, cn);
-                const uint32_t v = own[ok ? node_idx(cn, g) : node];
-                okm |= ok ? 1u << d : 0u;
-                onv[d] = ok ? v : kFluid;
-            }
-            if (self == (uint32_t)p) {
+            for (int d = 1; d < kQ; ++d)
+                onv[d] = own[o[0][1 - cx(d)] + o[1][1 - cy(d)] + o[2][1 - cz(d)]];
 #pragma unroll
-                for (int d = 1; d < kQ; ++d) {
-                    const bool ok = (okm >> d) & 1u;
-                    const uint32_t on = onv[d];
-                    if (ok && on == (uint32_t)p) continue;
-                    if (ok && on == kFluid) {
-                        mask |= 1u << d;
-                        fmask |= 1u << d;
-                    } else if (treat & LBM_TREAT_MISSING) {
-                        const double Mn = metaball(sp, n, X - cx(d), Y - cy(d), Z - cz(d));
-                        if (Mn < c0) mask |= 1u << d;
-                    }
+            for (int a = 0; a < 3; ++a) {
+                u[a] = (int)c[a];
+                if (g.per[a]) {
+                    const double d = (double)u[a] - B[a];
+                    if (d > 0.5 * g.n[a]) u[a] -= g.n[a];
+                    else if (d < -0.5 * g.n[a]) u[a] += g.n[a];
                 }
             }
+            if (self == (uint32_t)p) {
+                uint32_t rest = 0;  // neither p's nor fluid: of another body or beyond a wall
+#pragma unroll
+                for (int d = 1; d < kQ; ++d) {
+                    const bool ok = in[0][1 - cx(d)] && in[1][1 - cy(d)] && in[2][1 - cz(d)];
+                    if (ok && onv[d] == kFluid) fmask |= 1u << d;
+                    if (!ok || (onv[d] != kFluid && onv[d] != (uint32_t)p)) rest |= 1u << d;
+                }
+                mask = fmask;
+                if (treat & LBM_TREAT_MISSING)
+                    while (rest) {
+                        const int d = __ffs(rest) - 1;
+                        rest &= rest - 1u;
+                        int e[3];
+                        dir_of(d, e);
+                        if (metaball(sp, n, (double)(u[0] - e[0]), (double)(u[1] - e[1]),
+                                     (double)(u[2] - e[2])) < c0)
+                            mask |= 1u << d;
+                    }
+            }
         }
-        double Ms = 0.0;
-        if (mask) Ms = metaball(sp, n, X, Y, Z);
-        // direction-major enumeration of the wave's links
-        uint64_t bal[kQ];
-        uint32_t cum[kQ + 1];
-        cum[0] = cum[1] = 0;
-        bal[0] = 0;
+        // direction-major list of the wave's links
+        uint32_t total = 0;
 #pragma unroll
         for (int d = 1; d < kQ; ++d) {
-            bal[d] = __ballot((mask >> d) & 1u);
-            cum[d + 1] = cum[d] + (uint32_t)__popcll(bal[d]);
+            const bool on = (mask >> d) & 1u;
+            const uint64_t m = __ballot(on);
+            if (on)
+                pl[total + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+                    (uint16_t)(d << 6 | lane);
+            total += (uint32_t)__popcll(m);
         }
-        const uint32_t total = cum[kQ];
         if (total == 0) continue;  // uniform over the wave
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         uint32_t wbase = 0;
         if (lane == 0) wbase = atomicAdd(cursor, total);
+        double Ms = 0.0;
+        if (mask) Ms = metaball(sp, n, (double)u[0], (double)u[1], (double)u[2]);
         wbase = __shfl(wbase, 0, 64);
         for (uint32_t j0 = 0; j0 < total; j0 += 64) {
             const uint32_t j = j0 + (uint32_t)lane;
-            int d = 1;
-            uint64_t m = bal[1];
-#pragma unroll
-            for (int dd = 2; dd < kQ; ++dd)
-                if (cum[dd] <= j) {
-                    d = dd;
-                    m = bal[dd];
-                }
-            const int src = j < total ? select_bit(m, j - cum[d]) : lane;
+            const uint32_t e16 = j < total ? pl[j] : 64u;
+            const int src = (int)(e16 & 63u), d = (int)(e16 >> 6);
             const uint32_t snode = __shfl(node, src, 64);
-            const int sc[3] = {__shfl(c[0], src, 64), __shfl(c[1], src, 64), __shfl(c[2], src, 64)};
-            const double sX = __shfl(X, src, 64), sY = __shfl(Y, src, 64), sZ = __shfl(Z, src, 64);
+            const int su[3] = {__shfl(u[0], src, 64), __shfl(u[1], src, 64), __shfl(u[2], src, 64)};
             const double sMs = __shfl(Ms, src, 64);
             const uint32_t sfmask = __shfl(fmask, src, 64);
             if (j < total) {
-                const int ex = cx(d), ey = cy(d), ez = cz(d);
-                const double Mn = metaball(sp, n, sX - ex, sY - ey, sZ - ez);
+                int e[3];
+                dir_of(d, e);
                 int kind = LBM_LINK_MISSING;
                 if ((sfmask >> d) & 1u) {  // x_f exists and is fluid
-                    int cn[3];
-                    neighbour(sc, ex, ey, ez, g, cn);
+                    // x_ff = x_s - 2 e (u lies within half a period of the
+                    // lattice: one wrap)
                     int cff[3];
-                    const bool okf = neighbour(cn, ex, ey, ez, g, cff);
+                    bool okf = true;
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        int v = su[a] - 2 * e[a];
+                        if (v < 0 || v >= g.n[a]) {
+                            if (g.per[a])
+                                v = wrap_axis(v, g.n[a]);
+                            else
+                                okf = false;
+                        }
+                        cff[a] = v;
+                    }
                     const bool ff = okf && own[node_idx(cff, g)] == kFluid;
                     kind = ((treat & LBM_TREAT_VIBB) && ff) ? LBM_LINK_VIBB : LBM_LINK_HALFWAY;
                 }
+                const double Xn[3] = {(double)(su[0] - e[0]), (double)(su[1] - e[1]),
+                                      (double)(su[2] - e[2])};
+                const double Mn = metaball(sp, n, Xn[0], Xn[1], Xn[2]);
                 const uint32_t slot = wbase + j;
                 if (slot < cap) {
                     LinkRec r;
@@ -726,17 +759,14 @@ __global__ __launch_bounds__(256, 6) void k_links(const uint32_t* __restrict__ e
                     r.part = (uint16_t)p;
                     r.d = (uint8_t)d;
                     r.kind = (uint8_t)kind;
-                    if (treat & LBM_TREAT_EXACT_Q) {
-                        const double Xn[3] = {sX - ex, sY - ey, sZ - ez};
-                        const int e[3] = {ex, ey, ez};
-                        r.q = exact_q(sp, n, Xn, e, c0, Mn, sMs);
-                    } else {
-                        r.q = (c0 - Mn) / (sMs - Mn);
-                    }
+                    r.q = (treat & LBM_TREAT_EXACT_Q) ? exact_q(sp, n, Xn, e, c0, Mn, sMs)
+                                                      : (c0 - Mn) / (sMs - Mn);
                     out[slot] = r;
                 }
             }
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -913,6 +943,13 @@ hipError_t launch_clear_boxes(lbm_ctx* c, uint32_t* own, int slot, int np)
     return hipGetLastError();
 }
 
+// From 4096 planes a wave per plane fills the chip, and the preparation of a
+// plane is done by one wave, not four (200 bodies in 256^3: 12.4 us against 15.2,
+// 1000 in 512^3 with both kernels' other changes 317 against 354); below, four
+// waves share a plane's nodes (60 bodies: 8.9 us against 11.0, two 8.1 against
+// 11.6).  Boxes beyond 256 rows take four waves (a lane keeps four rows).
+constexpr int64_t kWavePlanes = 4096;
+
 hipError_t launch_mark(lbm_ctx* c, uint32_t* own, const PartDev& P, int slot, bool inc)
 {
     const int np = c->cfg.n_particles;
@@ -920,9 +957,11 @@ hipError_t launch_mark(lbm_ctx* c, uint32_t* own, const PartDev& P, int slot, bo
     // in dense mode the lattice sweep of k_finish_all writes every flag,
     // unless the candidate pass runs (then the solid nodes' flags come from
     // here)
-    hipLaunchKernelGGL(k_mark, dim3(c->box.S, np), dim3(256), 0, c->stream, c->err, own,
-                       c->ball_hist + (int64_t)slot * 4 * np, c->box.h, P, c->geom, c->flag,
-                       (c->dense && !inc) ? 0 : 1, c->cand, c->cand_cap, c->cand_cursor);
+    const bool waves = (int64_t)c->box.S * np >= kWavePlanes && c->box.S <= 256;
+    hipLaunchKernelGGL(waves ? k_mark<64> : k_mark<256>, dim3(c->box.S, np), dim3(waves ? 64 : 256), 0,
+                       c->stream, c->err, own, c->ball_hist + (int64_t)slot * 4 * np, c->box.h, P,
+                       c->geom, c->flag, (c->dense && !inc) ? 0 : 1, c->cand, c->cand_cap,
+                       c->cand_cursor);
     return hipGetLastError();
 }
 
@@ -959,11 +998,12 @@ hipError_t launch_links(lbm_ctx* c, const uint32_t* own, const PartDev& P, int s
 {
     const int np = c->cfg.n_particles;
     if (np == 0) return hipSuccess;
-    // few particles: 16 candidates per wave and up to 64 workgroups each
-    const uint32_t cpw = np <= 64 ? 16u : 64u;
+    // few particles: 12 candidates per wave and up to 96 workgroups each (60
+    // bodies with exact fractions: 38 us; 42 with 16, 44 with 24)
+    const uint32_t cpw = np <= 64 ? 12u : 64u;
     const int64_t chunk = 4 * (int64_t)cpw;
     const uint32_t per =
-        (uint32_t)std::min<int64_t>(np <= 64 ? 64 : 16, (c->cand_cap + chunk - 1) / chunk);
+        (uint32_t)std::min<int64_t>(np <= 64 ? 96 : 16, (c->cand_cap + chunk - 1) / chunk);
     const uint32_t nb = (per * (uint32_t)np + 7u) & ~7u;
     hipLaunchKernelGGL(k_links, dim3(nb), dim3(256), 0, c->stream, c->err, own,
                        c->ball_hist + (int64_t)slot * 4 * np, P, c->geom, c->cand, c->cand_cap,

@@ -115,3 +115,35 @@ def test_link_adjoint_on_both_sides_of_the_wave_split():
     for a, b in ((inner(lam_a), inner(lam_b)), (g_a[4:], g_b[4:4 + 3 * m]), (x_a, x_b[:, :m])):
         assert np.abs(a).max() > 0.1
         assert np.abs(a - b).max() <= 1e-12 * np.abs(a).max()
+
+
+# bodies, diameter, box, periodic axes: boxes below and above a wave of rows
+# with few planes (a workgroup each) and with many (a wave each), planes of more
+# segments and more candidates than are listed at a time, squares around the
+# ball of 1, 2 and 3 tiles
+@pytest.mark.parametrize("n,d,dims,per,lattice",
+                         [(1, 6.0, (33, 40, 35), (1, 1, 1), 15), (2, 29.0, (70, 64, 66), (0, 0, 0), 19),
+                          (1, 31.6, (130, 64, 66), (1, 0, 0), 19), (1, 150.0, (160, 158, 156), (0, 0, 0), 19),
+                          (230, 7.0, (47, 60, 50), (1, 1, 0), 19), (60, 72.0, (84, 90, 88), (0, 0, 0), 15),
+                          (60, 28.0, (131, 60, 62), (1, 0, 0), 19)])
+def test_classification_at_plane_and_tile_edges(n, d, dims, per, lattice):
+    """Owners, links with q and refills of overlapping spheres, moved once,
+    against the oracle bit for bit."""
+    from test_gpu_parity import _compare_geometry
+    rng = np.random.default_rng(3 * n + lattice)
+    lat = W.LatticeSpec(*dims, per)
+    pos = np.array(dims) * 0.5 + (rng.uniform(-0.5, 0.5, (n, 3)) * (np.array(dims) - d * 0.9) if n > 1
+                                  else rng.uniform(-1, 1, (n, 3)))
+    pos = np.where(np.array(per, bool), np.mod(pos, dims), pos)
+    ps = W.make_particles([W.sphere_shape(d, 0.2)] * n, pos, np.tile([1.0, 0, 0, 0], (n, 1)), 1.5)
+    gpu, ora = (B.Lattice.for_particles(lat, ps, storage="f32", lattice=lattice, classify="balls"),
+                O.Oracle(lat, Q=lattice))
+    for _ in range(2):
+        gpu.classify(B.DeviceParticles(ps))
+        ora.classify(ps)
+        _compare_geometry(gpu, ora, f"{n} of {d}")
+        ps = ps.copy()
+        ps.pos += rng.uniform(-0.4, 0.4, (n, 3))
+        ps.pos = np.where(np.array(per, bool), np.mod(ps.pos, dims), ps.pos)
+        ps.refresh_world()
+    gpu.close()
