@@ -8,17 +8,24 @@
 //
 // The work is latency-bound (chains of FP64 operations on a few thousand
 // particles at most), not HBM-bound.  Up to kBlockParticles particles one
-// workgroup runs the whole call: the broad phase and every substep, a thread
-// per particle and kPairLanes lanes per candidate pair, with barriers where
-// more particles take a launch.  Beyond, a substep is two launches: the
-// contacts (2 or kPairLanes lanes per candidate pair, a thread per
-// particle-wall pair, FP64 atomics into the sums), then the second half kick,
-// and the first half of the next substep (a thread per particle).
-// Measured, microseconds a call of ten substeps (before: a thread per pair,
-// per pair test and per particle's cells, 23 launches whatever the count):
-//   1 sphere 32 (83), 2 flat metaballs 60 (153), 64 packed spheres 98 (173),
-//   1000 metaballs of the 512^3 run 275 (535), packed spheres 1000: 145 (226),
-//   2548: 164 (420), 8000: 186 (462), 27 000: 328 (745).
+// workgroup runs the whole call: the broad phase and every substep, with
+// barriers where more particles take a launch; the first wave moves the
+// particles (a lane each) and takes their wall contacts, the other waves take
+// the candidate pairs (kPairLanes lanes each), and what a substep hands over
+// lies in LDS.  Beyond, a substep is two launches: the contacts (2 or kPairLanes
+// lanes per candidate pair, a thread per particle-wall pair, FP64 atomics into
+// the sums), then the second half kick, and the first half of the next substep
+// (a thread per particle).  Both half kicks around a substep's start act in the
+// body frame, with one rotation matrix a pose and Euler's terms as products of
+// two components; half angles come from their series.
+// Measured, microseconds a call of ten substeps (in parentheses a thread per
+// pair, per pair test and per particle's cells, 23 launches whatever the count):
+//   1 sphere 17 (83), 2 flat metaballs 35 (153), 64 packed spheres 72 (173),
+//   1000 metaballs of the 512^3 run 238 (535), packed spheres 1000: 134 (226),
+//   2548: 144 (420), 8000: 167 (462), 27 000: 316 (745).
+// In one workgroup with the points and records in global memory, a matrix a
+// half kick and the library's division, square root and sincos the first three
+// took 32, 60 and 98.
 #include <algorithm>
 #include <mutex>
 
@@ -85,14 +92,19 @@ __device__ __forceinline__ double gsum(double v)
     return v;
 }
 
-// 1/x for a Newton iteration: the hardware's estimate and two Newton steps
-// (an ulp or so; the iteration corrects itself, and the sums that the contact
-// force is built from divide).
+// 1/x and 1/sqrt(x): the hardware's estimate and two Newton steps (an ulp or
+// so; a third of the instructions of a division).  Not a number at 0.
 __device__ __forceinline__ double fast_rcp(double x)
 {
     double y = __builtin_amdgcn_rcp(x);
     y = fma(fma(-x, y, 1.0), y, y);
     return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ double fast_rsqrt(double x)
+{
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(fma(-x * y, y, 1.0), 0.5 * y, y);
+    return fma(fma(-x * y, y, 1.0), 0.5 * y, y);
 }
 
 // Terms of one control point at distance r: its share of M, grad M (negated:
@@ -154,12 +166,12 @@ __device__ __forceinline__ void contact_force(const DemP& c, double delta, const
     const double xin = dot3(xi, n);
     for (int a = 0; a < 3; ++a) xi[a] = xi[a] - xin * n[a] + vt[a] * dt;
     for (int a = 0; a < 3; ++a) Ft[a] = -c.kt * xi[a] - c.etat * vt[a];
-    const double ftn = sqrt(dot3(Ft, Ft));
-    if (ftn > c.mu * Fn && ftn > 0.0) {
-        const double s = c.mu * Fn / ftn;
+    const double ft2 = dot3(Ft, Ft), lim = c.mu * Fn;
+    if (ft2 > lim * lim && ft2 > 0.0) {
+        const double s = lim * fast_rsqrt(ft2), ik = 1.0 / c.kt;
         for (int a = 0; a < 3; ++a) {
             Ft[a] *= s;
-            xi[a] = -(Ft[a] + c.etat * vt[a]) / c.kt;
+            xi[a] = -(Ft[a] + c.etat * vt[a]) * ik;
         }
     }
     for (int a = 0; a < 3; ++a) Fi[a] = Fn * n[a] + Ft[a];
@@ -168,10 +180,21 @@ __device__ __forceinline__ void contact_force(const DemP& c, double delta, const
 // A particle's state and constants in registers.
 struct Body {
     double x[3], q[4], v[3], w[3];  // centre, orientation, velocity, angular velocity
+    double R[9], wb[3];             // rotation of q, angular velocity in the body frame
     double F[3], T[3];              // F^h + relative gravity, T^h
-    double hm, I[3], hI[3];         // half step over the mass and the moments
+    double hm, hI[3], kI[3];        // half step over the mass and the moments; of Euler's terms
     int c0, c1;                     // control points
 };
+
+__device__ __forceinline__ void to_body(Body& b)
+{
+    for (int i = 0; i < 3; ++i) b.wb[i] = b.R[i] * b.w[0] + b.R[3 + i] * b.w[1] + b.R[6 + i] * b.w[2];
+}
+__device__ __forceinline__ void to_world(Body& b)
+{
+    for (int i = 0; i < 3; ++i)
+        b.w[i] = b.R[3 * i] * b.wb[0] + b.R[3 * i + 1] * b.wb[1] + b.R[3 * i + 2] * b.wb[2];
+}
 
 __device__ __forceinline__ Body load_body(const PartDev& P, int p, const double* FTh, const DemP& c,
                                           double h)
@@ -182,49 +205,64 @@ __device__ __forceinline__ Body load_body(const PartDev& P, int p, const double*
     b.hm = h / m;
     b.c0 = P.off[p];
     b.c1 = P.off[p + 1];
+    double I[3];
     for (int a = 0; a < 3; ++a) {
         b.x[a] = P.pos[3 * p + a];
         b.v[a] = P.vel[3 * p + a];
         b.w[a] = P.omega[3 * p + a];
-        b.I[a] = P.inertia[3 * p + a];
-        b.hI[a] = h / b.I[a];
+        I[a] = P.inertia[3 * p + a];
+        b.hI[a] = h / I[a];
         b.F[a] = FTh[6 * p + a] + mrel * c.g[a];
         b.T[a] = FTh[6 * p + 3 + a];
     }
+    // (w x I w)_0 = (I_2 - I_1) w_1 w_2, and so on
+    for (int a = 0; a < 3; ++a) b.kI[a] = b.hI[a] * (I[(a + 2) % 3] - I[(a + 1) % 3]);
     for (int a = 0; a < 4; ++a) b.q[a] = P.quat[4 * p + a];
+    rotmat(b.q, b.R);
+    to_body(b);
     return b;
 }
 
-// Half a kick under F, T and the contact sum fc; the rotational part by one
-// explicit or four fixed-point sweeps of Euler's equations.
-__device__ __forceinline__ void half_kick(Body& b, const double fc[6], bool implicit)
+// What half a kick under F, T and the contact sum fc adds to v and, without
+// Euler's terms, to the angular velocity in the body frame.
+struct Kick {
+    double v[3], w[3];
+};
+
+__device__ __forceinline__ Kick kick_of(const Body& b, const double fc[6])
 {
+    Kick k;
     double T[3];
     for (int a = 0; a < 3; ++a) {
-        b.v[a] += b.hm * (b.F[a] + fc[a]);
+        k.v[a] = b.hm * (b.F[a] + fc[a]);
         T[a] = b.T[a] + fc[3 + a];
     }
-    double R[9];
-    rotmat(b.q, R);
-    double w0[3], Tb[3], wb[3];
-    for (int i = 0; i < 3; ++i) {
-        w0[i] = R[i] * b.w[0] + R[3 + i] * b.w[1] + R[6 + i] * b.w[2];
-        Tb[i] = R[i] * T[0] + R[3 + i] * T[1] + R[6 + i] * T[2];
-        wb[i] = w0[i];
-    }
-    const int iters = implicit ? 4 : 1;
-    for (int it = 0; it < iters; ++it) {
-        const double Iw[3] = {b.I[0] * wb[0], b.I[1] * wb[1], b.I[2] * wb[2]};
-        double cc[3];
-        cross3(wb, Iw, cc);
-        for (int a = 0; a < 3; ++a) wb[a] = w0[a] + b.hI[a] * (Tb[a] - cc[a]);
-    }
-    for (int i = 0; i < 3; ++i)
-        b.w[i] = R[3 * i] * wb[0] + R[3 * i + 1] * wb[1] + R[3 * i + 2] * wb[2];
+    for (int a = 0; a < 3; ++a)
+        k.w[a] = b.hI[a] * (b.R[a] * T[0] + b.R[3 + a] * T[1] + b.R[6 + a] * T[2]);
+    return k;
 }
 
-// Drift and rotation over dt, and the world control points of the new pose.
-__device__ __forceinline__ void drift(const PartDev& P, Body& b, double dt, const Geom& g)
+// Half a kick; the rotational part by one explicit or four fixed-point sweeps
+// of Euler's equations.
+template <bool IMPLICIT>
+__device__ __forceinline__ void half_kick(Body& b, const Kick& k)
+{
+    double w0[3];
+    for (int a = 0; a < 3; ++a) {
+        b.v[a] += k.v[a];
+        w0[a] = b.wb[a] + k.w[a];
+    }
+#pragma unroll
+    for (int it = 0; it < (IMPLICIT ? 4 : 1); ++it) {
+        const double p0 = b.wb[1] * b.wb[2], p1 = b.wb[2] * b.wb[0], p2 = b.wb[0] * b.wb[1];
+        b.wb[0] = w0[0] - b.kI[0] * p0;
+        b.wb[1] = w0[1] - b.kI[1] * p1;
+        b.wb[2] = w0[2] - b.kI[2] * p2;
+    }
+}
+
+// Drift and rotation over dt (w and wb both hold the angular velocity).
+__device__ __forceinline__ void drift(Body& b, double dt, const Geom& g)
 {
     for (int a = 0; a < 3; ++a) {
         double x = b.x[a] + dt * b.v[a];
@@ -234,10 +272,19 @@ __device__ __forceinline__ void drift(const PartDev& P, Body& b, double dt, cons
         }
         b.x[a] = x;
     }
-    const double wn = sqrt(dot3(b.w, b.w));
-    double dq[4], sn;
-    sincos(0.5 * wn * dt, &sn, &dq[0]);
-    const double s = wn > 0.0 ? sn / wn : 0.0;
+    // cos(t) and sin(t) / |w| of half the angle t = |w| dt / 2: below 1/8 by
+    // their series in t^2 (truncated under 1e-19 of the value)
+    const double z = (0.25 * dt * dt) * dot3(b.w, b.w);
+    double dq[4], s;
+    if (z < 0x1p-6) {
+        dq[0] = 1.0 + z * (-1.0 / 2 + z * (1.0 / 24 + z * (-1.0 / 720 + z * (1.0 / 40320 - z * (1.0 / 3628800)))));
+        s = (0.5 * dt) * (1.0 + z * (-1.0 / 6 + z * (1.0 / 120 + z * (-1.0 / 5040 + z * (1.0 / 362880 - z * (1.0 / 39916800))))));
+    } else {
+        const double wn = sqrt(dot3(b.w, b.w));
+        double sn;
+        sincos(0.5 * wn * dt, &sn, &dq[0]);
+        s = sn / wn;
+    }
     for (int a = 0; a < 3; ++a) dq[1 + a] = s * b.w[a];
     const double* q = b.q;
     double qn[4];
@@ -245,16 +292,30 @@ __device__ __forceinline__ void drift(const PartDev& P, Body& b, double dt, cons
     qn[1] = dq[0] * q[1] + dq[1] * q[0] + dq[2] * q[3] - dq[3] * q[2];
     qn[2] = dq[0] * q[2] - dq[1] * q[3] + dq[2] * q[0] + dq[3] * q[1];
     qn[3] = dq[0] * q[3] + dq[1] * q[2] - dq[2] * q[1] + dq[3] * q[0];
-    const double nrm = sqrt(qn[0] * qn[0] + qn[1] * qn[1] + qn[2] * qn[2] + qn[3] * qn[3]);
-    const double in = 1.0 / nrm;
+    const double in = fast_rsqrt(qn[0] * qn[0] + qn[1] * qn[1] + qn[2] * qn[2] + qn[3] * qn[3]);
     for (int a = 0; a < 4; ++a) b.q[a] = qn[a] * in;
-    double R[9];
-    rotmat(b.q, R);
-    for (int i = b.c0; i < b.c1; ++i) {
-        const double* bp = P.body_pts + 3 * (int64_t)i;
-        for (int a = 0; a < 3; ++a)
-            P.wpts[3 * (int64_t)i + a] =
-                b.x[a] + (R[3 * a] * bp[0] + R[3 * a + 1] * bp[1] + R[3 * a + 2] * bp[2]);
+    rotmat(b.q, b.R);
+    to_body(b);
+}
+
+// The world control points of the pose, from and to arrays indexed alike; N
+// points' loads go before the first store, which could alias them (from global
+// memory N = 4: a call's substep of 200 metaballs 4.5 us, point by point 5.7).
+template <int N>
+__device__ __forceinline__ void place_points(const Body& b, int i0, int i1, const double* body,
+                                             double* world)
+{
+    for (int i = i0; i < i1; i += N) {
+        double r[N][3];
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            for (int a = 0; a < 3; ++a) r[k][a] = body[3 * (int64_t)min(i + k, i1 - 1) + a];
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            if (i + k < i1)
+                for (int a = 0; a < 3; ++a)
+                    world[3 * (int64_t)(i + k) + a] =
+                        b.x[a] + (b.R[3 * a] * r[k][0] + b.R[3 * a + 1] * r[k][1] + b.R[3 * a + 2] * r[k][2]);
     }
 }
 
@@ -275,6 +336,7 @@ struct StateG {
     const double *pos, *vel, *omega, *rs, *reach;
     double* fc;
     const int32_t* off;
+    const double *wpts, *K;
 };
 
 __device__ __forceinline__ void clear_record(double* h)
@@ -288,11 +350,9 @@ __device__ __forceinline__ void clear_record(double* h)
 // share a pair: each sums every G-th control point of the two bodies (kept in
 // registers up to 4 a lane), and all follow the same branches on the same bits.
 template <int G>
-__device__ __forceinline__ void pair_item(const PartDev& P, const StateG& S, double* hist,
-                                          const DemP& c, double dt, const Geom& g, int i, int j,
-                                          int slot, int l)
+__device__ __forceinline__ void pair_item(const StateG& S, double* h, const DemP& c, double dt,
+                                          const Geom& g, int i, int j, int l)
 {
-    double* h = hist + ((int64_t)i * kPairSlots + slot) * kHist;
     double xi[3], xj[3], sh[3], dv[3];
     for (int a = 0; a < 3; ++a) {
         xi[a] = S.pos[3 * i + a];
@@ -308,7 +368,8 @@ __device__ __forceinline__ void pair_item(const PartDev& P, const StateG& S, dou
     }
     const double rsi = S.rs[i], rsj = S.rs[j];
     const double active = h[0];
-    if (sqrt(dot3(dv, dv)) > S.reach[i] + S.reach[j] + rsi + rsj) {
+    const double far = S.reach[i] + S.reach[j] + rsi + rsj;
+    if (dot3(dv, dv) > far * far) {
         // out of reach: forget the pair's contact (read one double instead of
         // writing eight when the record is zero already)
         if (active != 0.0 && l == 0) clear_record(h);
@@ -316,10 +377,10 @@ __device__ __forceinline__ void pair_item(const PartDev& P, const StateG& S, dou
     }
     const int ai = S.off[i], ni = min(S.off[i + 1] - ai, kMaxPts);
     const int aj = S.off[j], nj = min(S.off[j + 1] - aj, kMaxPts);
-    const double* pi = P.wpts + 3 * (int64_t)ai;
-    const double* pj = P.wpts + 3 * (int64_t)aj;
-    const double* Ki = P.K + ai;
-    const double* Kj = P.K + aj;
+    const double* pi = S.wpts + 3 * (int64_t)ai;
+    const double* pj = S.wpts + 3 * (int64_t)aj;
+    const double* Ki = S.K + ai;
+    const double* Kj = S.K + aj;
     const int nt = ni + nj;
     // point u of the pair: body i's, then body j's at their image nearest i
     auto point = [&](int u, double r[3], double& K) {
@@ -395,7 +456,7 @@ __device__ __forceinline__ void pair_item(const PartDev& P, const StateG& S, dou
         }
         if (!solve3(H, gg, dx)) break;
         for (int a = 0; a < 3; ++a) x[a] += dx[a];
-        if (sqrt(dot3(dx, dx)) < c.ntol) {
+        if (dot3(dx, dx) < c.ntol * c.ntol) {
             conv = true;
             break;
         }
@@ -410,7 +471,7 @@ __device__ __forceinline__ void pair_item(const PartDev& P, const StateG& S, dou
         double r[3], K;
         point(u, r, K);
         for (int a = 0; a < 3; ++a) r[a] = x[a] - r[a];
-        const double t = K / dot3(r, r), s = 2.0 * t / dot3(r, r);
+        const double i2 = fast_rcp(dot3(r, r)), t = K * i2, s = 2.0 * t * i2;
         if (u < ni) {
             MA += t;
             for (int a = 0; a < 3; ++a) gA[a] -= s * r[a];
@@ -436,16 +497,17 @@ __device__ __forceinline__ void pair_item(const PartDev& P, const StateG& S, dou
     // overlaps beyond 2 (R_si + R_sj) are stationary points inside a body,
     // where the projection of Eq. k0 does not hold, and are not contacts
     if (!(MA > c.ctol && MB > c.ctol)) return clear_record(h);
-    const double qA = (1.0 - MA) / dot3(gA, gA), qB = (1.0 - MB) / dot3(gB, gB);
+    const double qA = (1.0 - MA) * fast_rcp(dot3(gA, gA)), qB = (1.0 - MB) * fast_rcp(dot3(gB, gB));
     double xa[3], dd[3], n[3];
     for (int a = 0; a < 3; ++a) {
         xa[a] = x[a] + qA * gA[a];
         dd[a] = xa[a] - (x[a] + qB * gB[a]);
         n[a] = gA[a] - gB[a];
     }
-    const double un = sqrt(dot3(n, n));
-    if (!(un > 0.0)) return clear_record(h);
-    for (int a = 0; a < 3; ++a) n[a] = n[a] / un;
+    const double n2 = dot3(n, n);
+    if (!(n2 > 0.0)) return clear_record(h);
+    const double un = fast_rsqrt(n2);
+    for (int a = 0; a < 3; ++a) n[a] = n[a] * un;
     const double delta = rsi + rsj - dot3(dd, n);
     if (!(delta <= 2.0 * (rsi + rsj))) return clear_record(h);
     h[0] = 1.0;
@@ -486,16 +548,15 @@ __device__ __forceinline__ bool near_wall(const StateG& S, int i, int ax, int si
 // Contact of particle i with wall (ax, side) near it, record h: in-plane Newton
 // for the point of the wall plane where M is largest, the contact test and the
 // force.
-__device__ __forceinline__ void wall_contact(const PartDev& P, const StateG& S, double* h, int i,
-                                             int ax, int side, const DemP& c, double dt,
-                                             const Geom& g)
+__device__ __forceinline__ void wall_contact(const StateG& S, double* h, int i, int ax, int side,
+                                             const DemP& c, double dt, const Geom& g)
 {
     const double plane = side ? g.n[ax] - 0.5 : -0.5, sgn = side ? -1.0 : 1.0;
     const double xa = S.pos[3 * i + ax];
     const double active = h[0];
     const int ai = S.off[i], ni = min(S.off[i + 1] - ai, kMaxPts);
-    const double* pi = P.wpts + 3 * (int64_t)ai;
-    const double* Ki = P.K + ai;
+    const double* pi = S.wpts + 3 * (int64_t)ai;
+    const double* Ki = S.K + ai;
     const int t1 = (ax + 1) % 3, t2 = (ax + 2) % 3;
     // coordinates along (ax, t1, t2)
     double y1, y2;
@@ -525,11 +586,12 @@ __device__ __forceinline__ void wall_contact(const PartDev& P, const StateG& S, 
         const double h11 = H[3], h12 = H[4], h22 = H[5];
         const double det = h11 * h22 - h12 * h12;
         if (!(fabs(det) > 0.0) || !isfinite(det)) break;
-        const double d1 = -(h22 * gr[1] - h12 * gr[2]) / det;
-        const double d2 = -(-h12 * gr[1] + h11 * gr[2]) / det;
+        const double s = -fast_rcp(det);
+        const double d1 = s * (h22 * gr[1] - h12 * gr[2]);
+        const double d2 = s * (h11 * gr[2] - h12 * gr[1]);
         y1 += d1;
         y2 += d2;
-        if (sqrt(d1 * d1 + d2 * d2) < c.ntol) {
+        if (d1 * d1 + d2 * d2 < c.ntol * c.ntol) {
             conv = true;
             break;
         }
@@ -538,7 +600,7 @@ __device__ __forceinline__ void wall_contact(const PartDev& P, const StateG& S, 
     double M = 0.0, gr[3] = {0, 0, 0};
     for (int u = 0; u < ni; ++u) {
         const double r[3] = {plane - pi[3 * u + ax], y1 - pi[3 * u + t1], y2 - pi[3 * u + t2]};
-        const double t = Ki[u] / dot3(r, r), s = 2.0 * t / dot3(r, r);
+        const double i2 = fast_rcp(dot3(r, r)), t = Ki[u] * i2, s = 2.0 * t * i2;
         M += t;
         for (int a = 0; a < 3; ++a) gr[a] -= s * r[a];
     }
@@ -548,7 +610,7 @@ __device__ __forceinline__ void wall_contact(const PartDev& P, const StateG& S, 
     h[4 + ax] = rel[0];
     h[4 + t1] = rel[1];
     h[4 + t2] = rel[2];
-    const double qR = (1.0 - M) / dot3(gr, gr);
+    const double qR = (1.0 - M) * fast_rcp(dot3(gr, gr));
     const double delta = S.rs[i] - sgn * (qR * gr[0]);
     if (delta <= 0.0) {
         h[1] = h[2] = h[3] = 0.0;
@@ -874,7 +936,7 @@ __global__ __launch_bounds__(256) void k_contacts(PartDev P, double* hist, doubl
                                                   uint32_t wall_blocks, int n_axes, int ax0, int ax1,
                                                   int ax2)
 {
-    const StateG S{P.pos, P.vel, P.omega, P.rs, rch, fc, P.off};
+    const StateG S{P.pos, P.vel, P.omega, P.rs, rch, fc, P.off, P.wpts, P.K};
     if (blockIdx.x < wall_blocks) {
         const int t = (int)(blockIdx.x * 256u + threadIdx.x);
         const int per = 2 * n_axes;
@@ -883,7 +945,7 @@ __global__ __launch_bounds__(256) void k_contacts(PartDev P, double* hist, doubl
         const int ax = k == 0 ? ax0 : (k == 1 ? ax1 : ax2);
         double* h = hist_w + ((int64_t)i * 6 + 2 * ax + side) * kHist;
         if (near_wall(S, i, ax, side, g))
-            wall_contact(P, S, h, i, ax, side, c, dt, g);
+            wall_contact(S, h, i, ax, side, c, dt, g);
         else if (h[0] != 0.0)
             clear_record(h);
         return;
@@ -892,8 +954,9 @@ __global__ __launch_bounds__(256) void k_contacts(PartDev P, double* hist, doubl
     const uint32_t stride = (gridDim.x - wall_blocks) * (256u / G);
     for (uint32_t t = (blockIdx.x - wall_blocks) * (256u / G) + threadIdx.x / G; t < n; t += stride) {
         const uint64_t e = list[t];
-        pair_item<G>(P, S, hist, c, dt, g, (int)((e >> 16) & 0xffffu), (int)(e & 0xffffu),
-                     (int)(e >> 32), (int)(threadIdx.x % G));
+        const int i = (int)((e >> 16) & 0xffffu);
+        pair_item<G>(S, hist + ((int64_t)i * kPairSlots + (int)(e >> 32)) * kHist, c, dt, g, i,
+                     (int)(e & 0xffffu), (int)(threadIdx.x % G));
     }
 }
 
@@ -909,11 +972,14 @@ __global__ __launch_bounds__(64) void k_advance(PartDev P, const double* FTh, do
     Body b = load_body(P, p, FTh, c, 0.5 * dt);
     double f[6];
     for (int k = 0; k < 6; ++k) f[k] = fc[6 * p + k];
-    if constexpr (SECOND) half_kick(b, f, true);
+    const Kick k = kick_of(b, f);
+    if constexpr (SECOND) half_kick<true>(b, k);
+    if constexpr (FIRST) half_kick<false>(b, k);
+    to_world(b);
     if constexpr (FIRST) {
-        half_kick(b, f, false);
-        drift(P, b, dt, g);
-        for (int k = 0; k < 6; ++k) fc[6 * p + k] = 0.0;
+        drift(b, dt, g);
+        place_points<4>(b, b.c0, b.c1, P.body_pts, P.wpts);
+        for (int a = 0; a < 6; ++a) fc[6 * p + a] = 0.0;
     }
     store_body(P, p, b, FIRST);
 }
@@ -922,10 +988,16 @@ __global__ __launch_bounds__(64) void k_advance(PartDev P, const double* FTh, do
 // A whole dem_step call in one workgroup
 // ---------------------------------------------------------------------------
 constexpr int kBlockThreads = 512;
+// Most control points of such a call (they and the records fill the 64 KB of
+// LDS a workgroup may declare; bodies with more take the launches).
+constexpr int kBlockPoints = 384;
 // Lanes that share a pair: the Newton chain of one lane over the 4 to 12
 // points of two metaballs is what a substep waits for (32-43 us at 1000
 // metaballs, about 16 with four lanes).
 constexpr int kPairLanes = 4;
+
+// Groups of pair lanes: every wave but the first.
+constexpr int kPairGroups = (kBlockThreads - 64) / kPairLanes;
 
 __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* hist, double* hist_w,
                                                              int32_t* key, const double* FTh,
@@ -936,31 +1008,30 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
     __shared__ double pos[3 * kBlockParticles], vel[3 * kBlockParticles], om[3 * kBlockParticles];
     __shared__ double sum[6 * kBlockParticles], rs[kBlockParticles], rch[kBlockParticles];
     __shared__ double bound[kBlockParticles];
+    __shared__ double body[3 * kBlockPoints], world[3 * kBlockPoints], K[kBlockPoints];
+    __shared__ double wall[6 * kBlockParticles * kHist];  // the particles' wall records
+    __shared__ double rec[kPairGroups * kHist];           // the groups' first pairs' records
     __shared__ int32_t off[kBlockParticles + 1];
     __shared__ uint32_t npairs;
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, n = P.n;
-    const StateG S{pos, vel, om, rs, rch, sum, off};
-    Body b{};
-    double f[6] = {0, 0, 0, 0, 0, 0};
-    auto publish = [&](bool pose) {
-        for (int a = 0; a < 3; ++a) {
-            if (pose) pos[3 * tid + a] = b.x[a];
-            vel[3 * tid + a] = b.v[a];
-            om[3 * tid + a] = b.w[a];
-        }
-    };
-    uint32_t touched = 0;  // this particle's wall records that are not zero
+    const int tid = (int)threadIdx.x, lane = tid & 63, n = P.n;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const StateG S{pos, vel, om, rs, rch, sum, off, world, K};
+    const int p0 = P.off[0], np = min(P.off[n] - p0, kBlockPoints);
     if (tid == 0) npairs = 0u;
-    if (tid <= n) off[tid] = P.off[tid];
+    if (tid <= n) off[tid] = min(P.off[tid] - p0, kBlockPoints);
+    for (int i = tid; i < np; i += kBlockThreads) K[i] = P.K[p0 + i];
+    for (int i = tid; i < 3 * np; i += kBlockThreads) body[i] = P.body_pts[3 * (int64_t)p0 + i];
+    for (int i = tid; i < 6 * n * kHist; i += kBlockThreads) wall[i] = hist_w[i];
     if (tid < n) {
-        for (int k = 0; k < 6; ++k)
-            touched |= hist_w[((int64_t)tid * 6 + k) * kHist] != 0.0 ? 1u << k : 0u;
-        b = load_body(P, tid, FTh, c, 0.5 * dt);
-        for (int k = 0; k < 6; ++k) f[k] = fc[6 * tid + k];
+        double v2 = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            pos[3 * tid + a] = P.pos[3 * tid + a];
+            const double v = P.vel[3 * tid + a];
+            v2 += v * v;
+        }
         rs[tid] = P.rs[tid];
         rch[tid] = reach(P, tid);
-        bound[tid] = rch[tid] + rs[tid] + sqrt(dot3(b.v, b.v)) * ((double)n_sub * dt) + 0.25;
-        publish(true);
+        bound[tid] = rch[tid] + rs[tid] + sqrt(v2) * ((double)n_sub * dt) + 0.25;
     }
     __syncthreads();
     // candidate pairs, as k_pairs
@@ -990,46 +1061,81 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
                 ((uint64_t)lane << 32) | ((uint64_t)i << 16) | (uint64_t)(s.key - 1);
     }
     __syncthreads();
-    const int group = (kBlockThreads - 1 - tid) / kPairLanes;
-    const uint64_t e0 = group < (int)npairs ? list[group] : 0;
-    for (int sub = 0; sub < n_sub; ++sub) {
-        if (tid < n) {
-            half_kick(b, f, false);
-            drift(P, b, dt, g);
-            publish(true);
-            for (int k = 0; k < 6; ++k) sum[6 * tid + k] = 0.0;
+    // the first wave moves the particles and takes their wall contacts, the
+    // others take the pairs (the same barriers on both sides: two a substep)
+    if (wave == 0) {
+        const bool on = tid < n;
+        Body b{};
+        double f[6] = {0, 0, 0, 0, 0, 0};
+        if (on) {
+            b = load_body(P, tid, FTh, c, 0.5 * dt);
+            for (int k = 0; k < 6; ++k) f[k] = fc[6 * tid + k];
+            half_kick<false>(b, kick_of(b, f));
         }
-        __syncthreads();
-        // walls by the particles' own threads, pairs from the last wave down
-        if (tid < n)
-            for (int ax = 0; ax < 3; ++ax)
-                if (!g.per[ax])
-                    for (int side = 0; side < 2; ++side) {
-                        const uint32_t bit = 1u << (2 * ax + side);
-                        double* h = hist_w + ((int64_t)tid * 6 + 2 * ax + side) * kHist;
-                        if (near_wall(S, tid, ax, side, g)) {
-                            wall_contact(P, S, h, tid, ax, side, c, dt, g);
-                            touched |= bit;
-                        } else if (touched & bit) {
-                            clear_record(h);
-                            touched &= ~bit;
+        for (int sub = 0; sub < n_sub; ++sub) {
+            if (on) {
+                to_world(b);
+                drift(b, dt, g);
+                place_points<1>(b, off[tid], off[tid + 1], body, world);
+                for (int a = 0; a < 3; ++a) {
+                    pos[3 * tid + a] = b.x[a];
+                    vel[3 * tid + a] = b.v[a];
+                    om[3 * tid + a] = b.w[a];
+                }
+                for (int k = 0; k < 6; ++k) sum[6 * tid + k] = 0.0;
+            }
+            __syncthreads();
+            if (on)
+                for (int ax = 0; ax < 3; ++ax)
+                    if (!g.per[ax])
+                        for (int side = 0; side < 2; ++side) {
+                            double* h = wall + (6 * tid + 2 * ax + side) * kHist;
+                            if (near_wall(S, tid, ax, side, g))
+                                wall_contact(S, h, tid, ax, side, c, dt, g);
+                            else if (h[0] != 0.0)
+                                clear_record(h);
                         }
-                    }
-        for (int t = group; t < (int)npairs; t += kBlockThreads / kPairLanes) {
-            const uint64_t e = t == group ? e0 : list[t];
-            pair_item<kPairLanes>(P, S, hist, c, dt, g, (int)((e >> 16) & 0xffffu), (int)(e & 0xffffu),
-                                  (int)(e >> 32), tid % kPairLanes);
+            __syncthreads();
+            if (on) {
+                for (int k = 0; k < 6; ++k) f[k] = sum[6 * tid + k];
+                const Kick k = kick_of(b, f);
+                half_kick<true>(b, k);
+                if (sub + 1 < n_sub) half_kick<false>(b, k);
+            }
         }
-        __syncthreads();
-        if (tid < n) {
-            for (int k = 0; k < 6; ++k) f[k] = sum[6 * tid + k];
-            half_kick(b, f, true);
+        if (on) {
+            to_world(b);
+            store_body(P, tid, b, true);
+            for (int k = 0; k < 6; ++k) fc[6 * tid + k] = f[k];
         }
+    } else {
+        const int group = kPairGroups - 1 - (tid - 64) / kPairLanes, l = tid % kPairLanes;
+        const int total = (int)npairs;
+        const bool mine = group < total;
+        const uint64_t e0 = mine ? list[group] : 0;
+        const int i0 = (int)((e0 >> 16) & 0xffffu), j0 = (int)(e0 & 0xffffu);
+        double* h0 = rec + group * kHist;
+        double* g0 = hist + ((int64_t)i0 * kPairSlots + (int)(e0 >> 32)) * kHist;
+        if (mine)
+            for (int k = l; k < kHist; k += kPairLanes) h0[k] = g0[k];
+        for (int sub = 0; sub < n_sub; ++sub) {
+            __syncthreads();
+            if (mine) pair_item<kPairLanes>(S, h0, c, dt, g, i0, j0, l);
+            for (int t = group + kPairGroups; t < total; t += kPairGroups) {
+                const uint64_t e = list[t];
+                const int i = (int)((e >> 16) & 0xffffu);
+                pair_item<kPairLanes>(S, hist + ((int64_t)i * kPairSlots + (int)(e >> 32)) * kHist, c,
+                                      dt, g, i, (int)(e & 0xffffu), l);
+            }
+            __syncthreads();
+        }
+        if (mine)
+            for (int k = l; k < kHist; k += kPairLanes) g0[k] = h0[k];
     }
-    if (tid < n) {
-        store_body(P, tid, b, true);
-        for (int k = 0; k < 6; ++k) fc[6 * tid + k] = f[k];
-    }
+    __syncthreads();
+    if (n_sub > 0)
+        for (int i = tid; i < 3 * np; i += kBlockThreads) P.wpts[3 * (int64_t)p0 + i] = world[i];
+    for (int i = tid; i < 6 * n * kHist; i += kBlockThreads) hist_w[i] = wall[i];
 }
 
 }  // namespace
@@ -1052,7 +1158,7 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
     c.rhof = prm.rho_f;
     uint32_t* deferred = ctx->ctr + kCtrDeferred;
     const Geom& g = ctx->geom;
-    if (np <= kBlockParticles) {
+    if (np <= kBlockParticles && ctx->cfg.n_ctrl <= kBlockPoints) {
         hipLaunchKernelGGL(k_dem_block, dim3(1), dim3(kBlockThreads), 0, ctx->stream, P, ctx->hist_pp,
                            ctx->hist_pw, ctx->hist_key, ctx->FT, ctx->fc, ws.pairs, c, n_sub, dt, g,
                            deferred);

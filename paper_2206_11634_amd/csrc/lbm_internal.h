@@ -313,10 +313,10 @@ struct DemScratch {
     double* gsize = nullptr;      // cell widths, then H (the largest accepted distance)
     int64_t gcap = 0;             // cells the arrays hold
 };
-// Most particles whose whole dem_step call runs in one workgroup: a barrier
-// costs less than a launch while one compute unit keeps up with the contacts
-// (64 packed spheres 98 against 120 us a call of ten substeps, 100 spheres 140
-// against 123).
+// Most particles whose whole dem_step call runs in one workgroup: a lane of
+// its first wave each, and a barrier costs less than a launch (a call of ten
+// substeps, launches in parentheses: 1 sphere 17 us (61), 2 flat metaballs 35
+// (86), 64 packed spheres 72 (114)).
 constexpr int kBlockParticles = 64;
 // Particle counts from which dem_step uses the cell grid.
 constexpr int kGridMinParticles = 2048;

@@ -44,12 +44,13 @@ def test_stream_collide_at_wave_and_row_edges(storage, lattice, dims):
         gpu.close()
 
 
-@pytest.mark.parametrize("points", [1, 3, 9])
+@pytest.mark.parametrize("points", [1, 3, 6, 9])
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 130])
 def test_dem_paths_match_the_oracle(n, points):
     """dem_step around the particle count where a whole call moves from one
     workgroup to a launch per phase, with bodies of one control point, of three
-    (both bodies' points in a group's registers) and of nine (not), touching
+    (both bodies' points in a group's registers), of six (64 bodies fill the
+    workgroup's points) and of nine (neither), touching
     each other, the floor and each other across a periodic face: five calls of
     ten substeps against the oracle, within 1e-9."""
     rng = np.random.default_rng(100 * n + points)
