@@ -806,7 +806,8 @@ __global__ void k_tape_small(uint32_t* __restrict__ tcur, const uint32_t* __rest
                              double* __restrict__ part, const double* __restrict__ pos,
                              const double* __restrict__ vel, const double* __restrict__ om,
                              const double* __restrict__ wpts, const double* __restrict__ quat,
-                             const double* __restrict__ FT, int np, int nctrl,
+                             const double* __restrict__ sums,
+                             const unsigned long long* __restrict__ fx, int np, int nctrl,
                              double* __restrict__ dem, int32_t* __restrict__ dem_key,
                              const double* __restrict__ hpp, const double* __restrict__ hpw,
                              const double* __restrict__ fc, const int32_t* __restrict__ hkey)
@@ -821,7 +822,7 @@ __global__ void k_tape_small(uint32_t* __restrict__ tcur, const uint32_t* __rest
     if (i < 3 * nctrl) part[9 * np + i] = wpts[i];
     double* tq = part + 9 * np + 3 * nctrl;
     if (quat && i < 4 * np) tq[i] = quat[i];
-    if (i < 6 * np) tq[4 * np + i] = FT[i];
+    if (i < 6 * np) tq[4 * np + i] = force_sum(sums, fx, i);
     const int npp = np * kPairSlots;
     if (i < 8 * npp) dem[i] = hpp[i];
     if (i < 48 * np) dem[8 * npp + i] = hpw[i];
@@ -841,7 +842,7 @@ hipError_t launch_tape_small(lbm_ctx* c, TapeStep& t, const lbm_particles* P)
                                          3 * (int64_t)nctrl});
     hipLaunchKernelGGL(k_tape_small, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, c->stream,
                        t.cursor, c->link_cursor, t.part, P->pos, P->vel, P->omega, P->world_pts,
-                       P->quat, c->FT, np, nctrl, t.dem, t.dem_key, c->hist_pp, c->hist_pw, c->fc,
+                       P->quat, c->sums, c->FX, np, nctrl, t.dem, t.dem_key, c->hist_pp, c->hist_pw, c->fc,
                        c->hist_key);
     return hipGetLastError();
 }

@@ -463,8 +463,9 @@ int lbm_init(const lbm_config* cfg, const lbm_buffers* bufs, lbm_ctx** out)
     const size_t np1 = (size_t)std::max(np, 1);
     if (e == hipSuccess) e = alloc(&c->ctr, (size_t)kStageHead + 2 * (size_t)kCursorPad * np1);
     if (e == hipSuccess) {
-        c->refill_cursor = c->ctr + kCtrRefill;
-        c->err = c->ctr + kCtrErr;
+        c->refill_cursor = c->ctr + kCtrSet[0] + kSetRefill;
+        c->err = c->ctr + kCtrSet[0] + kSetErr;
+        c->inc = c->ctr + kCtrSet[0] + kSetIncremental;
         c->numeric = c->ctr + kCtrNumeric;
         c->link_cursor = c->ctr + kStageHead;
         c->cand_cursor = c->ctr + kStageHead + (size_t)kCursorPad * np1;
@@ -487,8 +488,12 @@ int lbm_init(const lbm_config* cfg, const lbm_buffers* bufs, lbm_ctx** out)
     if (e == hipSuccess && np) e = alloc(&c->links, (size_t)c->lay->total);
     if (e == hipSuccess) e = alloc(&c->refill, (size_t)c->refill_cap);
     if (e == hipSuccess) e = alloc(&c->FT, (size_t)6 * std::max(np, 1));
-    if (e == hipSuccess && np && cfg->force_sum == LBM_FORCE_SUM_EXACT)
+    if (e == hipSuccess) e = alloc(&c->sums, (size_t)6 * std::max(np, 1));
+    if (e == hipSuccess && np && cfg->force_sum == LBM_FORCE_SUM_EXACT) {
         e = alloc(&c->FX, (size_t)12 * np);
+        if (e == hipSuccess)
+            e = hipMemsetAsync(c->FX, 0, sizeof(unsigned long long) * 12 * np, c->stream);
+    }
     if (e == hipSuccess) e = alloc(&c->fc, (size_t)6 * std::max(np, 1));
     if (e == hipSuccess) e = alloc(&c->reach, (size_t)2 * std::max(np, 1));
     if (e == hipSuccess)
@@ -519,6 +524,7 @@ int lbm_init(const lbm_config* cfg, const lbm_buffers* bufs, lbm_ctx** out)
     if (e == hipSuccess) e = hipMemsetAsync(c->own[1], 0xFF, sz.owner_bytes, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->flag, 0, sz.flag_bytes, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->FT, 0, sizeof(double) * 6 * std::max(np, 1), c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(c->sums, 0, sizeof(double) * 6 * std::max(np, 1), c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->fc, 0, sizeof(double) * 6 * std::max(np, 1), c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
@@ -541,6 +547,7 @@ int lbm_destroy(lbm_ctx* c)
     (void)hipFree(c->refill);
     (void)hipFree(c->ctr);
     (void)hipFree(c->FT);
+    (void)hipFree(c->sums);
     (void)hipFree(c->FX);
     (void)hipFree(c->cand_prev);
     (void)hipFree(c->cand_prev_count);
@@ -605,9 +612,10 @@ ClassifyPlan classify_plan(const lbm_ctx* c)
     return cp;
 }
 
-// Enqueue a classification: counters reset, boxes, owners, flags, candidates,
-// links, then the refill, which reads its list's length on the device.
-int classify_enqueue(lbm_ctx* c, const PartDev& Pd, const ClassifyPlan& cp)
+// Enqueue a classification: counters reset, boxes and the old balls cleared,
+// owners, flags, candidates, links, then the refill, which reads its list's
+// length on the device and reports or latches the counters.
+int classify_enqueue(lbm_ctx* c, const PartDev& Pd, const ClassifyPlan& cp, Report report)
 {
     const int np = c->cfg.n_particles;
     if (c->dense && c->cand_prev) {
@@ -625,26 +633,26 @@ int classify_enqueue(lbm_ctx* c, const PartDev& Pd, const ClassifyPlan& cp)
         std::swap(c->cand, c->cand_prev);
         std::swap(c->cand_cap, c->cand_prev_cap);
     }
-    HIPCHK(c, LQ(c, launch_reset_counters)(c));
-    // the boxes' check is read back with the list counts; the kernels that
-    // write the owner planes, flags and lists do nothing when it failed, so
-    // the context keeps its current geometry
-    HIPCHK(c, LQ(c, launch_boxes)(c, Pd, cp.slot, cp.slot_prev, cp.inc || (c->dense && np > 0)));
     {
         PhaseTimer tm(c, LBM_PHASE_CLASSIFY);
-        if (cp.k >= 2) HIPCHK(c, LQ(c, launch_clear_boxes)(c, cp.own_new, cp.slot_prev2, np));
+        // the boxes' check is read back with the list counts; the kernels that
+        // write the owner planes in use, flags and lists do nothing when it
+        // failed, so the context keeps its current geometry
+        HIPCHK(c, LQ(c, launch_begin)(c, Pd, cp.slot, cp.slot_prev, cp.inc || (c->dense && np > 0),
+                                      cp.k >= 2 ? cp.own_new : nullptr, cp.slot_prev2));
         HIPCHK(c, LQ(c, launch_mark)(c, cp.own_new, Pd, cp.slot, cp.inc));
         // the lattice sweep also runs on a first classification (own_prev
         // is all fluid then): in dense mode it writes every flag
-        if (cp.k >= 1 || c->dense)
-            HIPCHK(c, LQ(c, launch_finish)(c, cp.own_prev, cp.own_new, cp.slot_prev, np, cp.inc));
-        HIPCHK(c, LQ(c, launch_links)(c, cp.own_new, Pd, cp.slot));
+        HIPCHK(c, LQ(c, launch_finish_links)(c, cp.own_prev, cp.own_new, Pd, cp.slot, cp.slot_prev,
+                                             cp.inc, cp.k >= 1 || c->dense, true));
     }
     if (cp.k >= 1) {
         // should the list overflow, lbm_classify_nodes runs it again over
         // the grown list
         PhaseTimer tm(c, LBM_PHASE_REFILL);
-        HIPCHK(c, LQ(c, launch_refill)(c, cp.refill_src, c->f[c->cur], cp.own_prev, Pd));
+        HIPCHK(c, LQ(c, launch_refill)(c, cp.refill_src, c->f[c->cur], cp.own_prev, Pd, report));
+    } else if (report == Report::latch) {
+        HIPCHK(c, LQ(c, launch_latch_deferred)(c));
     }
     return LBM_OK;
 }
@@ -715,21 +723,23 @@ int lbm_classify_nodes(lbm_ctx* c, const lbm_particles* P, lbm_counts* out)
     const size_t cur_bytes = sizeof(uint32_t) * kCursorPad * std::max(np, 1);
 
     if (np > 0) {
-        rc = classify_enqueue(c, Pd, cp);
+        rc = classify_enqueue(c, Pd, cp, Report::host);
         if (rc) return rc;
         uint32_t* link_counts = c->host_stage + kStageHead;
         uint32_t* cand_counts = c->host_stage + kStageHead + (size_t)kCursorPad * np;
         for (int attempt = 0;; ++attempt) {
-            // one copy of the whole counter block
-            HIPCHK(c, hipMemcpyAsync(c->host_stage, c->ctr,
-                                     sizeof(uint32_t) * kStageHead + 2 * cur_bytes,
-                                     hipMemcpyDeviceToHost, c->stream));
+            // one copy of the whole counter block, where the refill's launch
+            // did not send it (5 us less for a small run)
+            if (attempt > 0 || k < 1)
+                HIPCHK(c, hipMemcpyAsync(c->host_stage, c->ctr,
+                                         sizeof(uint32_t) * kStageHead + 2 * cur_bytes,
+                                         hipMemcpyDeviceToHost, c->stream));
             HIPCHK(c, hipStreamSynchronize(c->stream));
             rc = deferred_status(c, "lbm_classify_nodes");
             if (rc) return rc;
-            if (c->host_stage[kCtrErr])
-                return fail(c, LBM_EINVAL,
-                            "lbm_classify_nodes: " + err_text(c->host_stage[kCtrErr]));
+            const uint32_t* set = c->host_stage + kCtrSet[c->ctr_set];
+            if (set[kSetErr])
+                return fail(c, LBM_EINVAL, "lbm_classify_nodes: " + err_text(set[kSetErr]));
             int64_t lmax = 0, ltot = 0, cmax = 0, ctot = 0;
             for (int p = 0; p < np; ++p) {
                 const int64_t v = link_counts[(size_t)p * kCursorPad];
@@ -738,7 +748,7 @@ int lbm_classify_nodes(lbm_ctx* c, const lbm_particles* P, lbm_counts* out)
                 cmax = std::max<int64_t>(cmax, cand_counts[(size_t)p * kCursorPad]);
                 ctot += cand_counts[(size_t)p * kCursorPad];
             }
-            const int64_t nref = c->host_stage[kCtrRefill];
+            const int64_t nref = set[kSetRefill];
             const bool grow_cand = cmax > c->cand_cap;
             // a segment outgrown, or the first counts: every segment sized
             // from its own particle's count (and never below what it was,
@@ -784,7 +794,8 @@ int lbm_classify_nodes(lbm_ctx* c, const lbm_particles* P, lbm_counts* out)
             }
             if (grow_cand || grow_links) {
                 HIPCHK(c, hipMemsetAsync(c->link_cursor, 0, cur_bytes, c->stream));
-                HIPCHK(c, LQ(c, launch_links)(c, cp.own_new, Pd, cp.slot));
+                HIPCHK(c, LQ(c, launch_finish_links)(c, cp.own_prev, cp.own_new, Pd, cp.slot,
+                                                     cp.slot_prev, cp.inc, false, true));
             }
             if (grow_refill) {
                 HIPCHK(c, hipFree(c->refill));
@@ -794,10 +805,11 @@ int lbm_classify_nodes(lbm_ctx* c, const lbm_particles* P, lbm_counts* out)
                     return fail(c, LBM_ENOMEM, "refill list allocation failed");
                 HIPCHK(c, hipMemsetAsync(c->refill_cursor, 0, sizeof(uint32_t), c->stream));
                 if (k >= 1) {
-                    HIPCHK(c, LQ(c, launch_finish)(c, cp.own_prev, cp.own_new, cp.slot_prev, np,
-                                                   cp.inc));
+                    HIPCHK(c, LQ(c, launch_finish_links)(c, cp.own_prev, cp.own_new, Pd, cp.slot,
+                                                         cp.slot_prev, cp.inc, true, false));
                     PhaseTimer tm(c, LBM_PHASE_REFILL);
-                    HIPCHK(c, LQ(c, launch_refill)(c, cp.refill_src, c->f[c->cur], cp.own_prev, Pd));
+                    HIPCHK(c, LQ(c, launch_refill)(c, cp.refill_src, c->f[c->cur], cp.own_prev, Pd,
+                                                   Report::none));
                 }
             }
         }
@@ -822,9 +834,8 @@ int lbm_classify_nodes_async(lbm_ctx* c, const lbm_particles* P)
     if (rc) return rc;
     const ClassifyPlan cp = classify_plan(c);
     if (c->cfg.n_particles > 0) {
-        rc = classify_enqueue(c, to_dev(P), cp);
+        rc = classify_enqueue(c, to_dev(P), cp, Report::latch);
         if (rc) return rc;
-        HIPCHK(c, LQ(c, launch_latch_deferred)(c));
         c->link_max = c->lay->max_seg;  // lbm_step covers every segment whole
         c->deferred = true;
     } else {
@@ -856,12 +867,16 @@ int lbm_step(lbm_ctx* c, const lbm_particles* P)
                                                  : (src == c->fu[0] ? c->fu[1] : c->fu[0]);
     {
         PhaseTimer tm(c, LBM_PHASE_BOUNDARY);
-        HIPCHK(c, LQ(c, launch_zero_f64)(c, c->FT, 6 * (int64_t)np));
         if (np > 0 && c->n_classify > 0) HIPCHK(c, LQ(c, launch_boundary)(c, src, to_dev(P)));
     }
     if (taped) {
         int rc2 = record_tape_step(c, P);
-        if (rc2) return rc2;
+        if (rc2) {
+            // no bulk pass will take the sums: the next step starts from zero
+            (void)hipMemsetAsync(c->sums, 0, sizeof(double) * 6 * np, c->stream);
+            if (c->FX) (void)hipMemsetAsync(c->FX, 0, sizeof(unsigned long long) * 12 * np, c->stream);
+            return rc2;
+        }
     }
     {
         PhaseTimer tm(c, LBM_PHASE_BULK);
@@ -1220,7 +1235,8 @@ int lbm_geometry_load(lbm_ctx* c, const void* src_dev, uint64_t tag, const lbm_p
     if (np > 0) {
         if (cp.k >= 1) {
             PhaseTimer tm(c, LBM_PHASE_REFILL);
-            HIPCHK(c, LQ(c, launch_refill)(c, cp.refill_src, c->f[c->cur], cp.own_prev, to_dev(P)));
+            HIPCHK(c, LQ(c, launch_refill)(c, cp.refill_src, c->f[c->cur], cp.own_prev, to_dev(P),
+                                           Report::none));
         }
         c->link_max = c->lay->max_seg;  // lbm_step covers every segment whole
     } else {

@@ -106,16 +106,17 @@ __device__ __forceinline__ bool wrap_cell(const int ii[3], const Geom& g, int c[
     return ok;
 }
 
-// Visit the nodes of one z plane of the box (blockIdx.x) in the square around
+// Visit the nodes of z plane `plane` of the box in the square around
 // the ball (x_p, R)'s circle there, 32 x 8 nodes a workgroup and two such tiles
 // at once: fn(node, on) for each tile, called by every lane of a wave together
 // (on: the node exists and lies in the ball).  A wave per row with the row's
 // FP64 ends first, one row after the other, was a longer chain.
 template <class Fn>
-__device__ __forceinline__ void walk_ball_plane(const double* ball, int h, const Geom& g, Fn&& fn)
+__device__ __forceinline__ void walk_ball_plane(const double* ball, int h, int plane, const Geom& g,
+                                                Fn&& fn)
 {
     const double bx = ball[0], by = ball[1], bz = ball[2], R = ball[3];
-    const int zi = (int)floor(bz) - h + (int)blockIdx.x;
+    const int zi = (int)floor(bz) - h + plane;
     const double dz = (double)zi - bz;
     const double r2z = R * R - dz * dz;
     if (r2z < 0.0) return;  // uniform over the block
@@ -156,14 +157,15 @@ __device__ __forceinline__ uint32_t wave_reserve(uint32_t count, uint32_t* curso
     return base + incl - count;
 }
 
-// Block (bx, by) of a gx x gy work grid launched as a 1D grid of a multiple of
-// 8 workgroups.  The hardware hands workgroup b to XCD b % 8; mapping XCD k to
+// Block (bx, by) of a gx x gy work grid launched as the first `blocks`, a
+// multiple of 8, workgroups of a 1D grid.  The hardware hands workgroup b to XCD b % 8; mapping XCD k to
 // the k-th eighth of the work keeps all blocks of a particle (by) on one XCD,
 // so the owner rows its candidates share are fetched into one L2.  False for
 // the padding workgroups.
-__device__ __forceinline__ bool xcd_tile(uint32_t gx, uint32_t gy, uint32_t& bx, uint32_t& by)
+__device__ __forceinline__ bool xcd_tile(uint32_t blocks, uint32_t gx, uint32_t gy, uint32_t& bx,
+                                         uint32_t& by)
 {
-    const uint32_t per = gridDim.x >> 3;
+    const uint32_t per = blocks >> 3;
     const uint32_t logical = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
     if (logical >= gx * gy) return false;
     bx = logical % gx;
@@ -191,12 +193,11 @@ __device__ __forceinline__ float lane_of(float v, int j)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j));
 }
 
-// One wave per particle, a lane per control point (n <= 64).
-__global__ __launch_bounds__(64) void k_boxes(PartDev P, int h, double* ball, uint32_t* err, Geom g,
-                                             const double* ball_prev, double* quat_prev,
-                                             uint32_t* inc_bad)
+// Box and radius of particle p by one wave, a lane per control point (n <= 64).
+__device__ __forceinline__ void box_of(const PartDev& P, int p, int h, double* ball, uint32_t* err,
+                                       const Geom& g, const double* ball_prev, double* quat_prev,
+                                       uint32_t* inc_bad)
 {
-    const int p = blockIdx.x;
     const int lane = threadIdx.x;
     uint32_t bad = 0;
     double xp[3];
@@ -294,16 +295,38 @@ __global__ __launch_bounds__(64) void k_boxes(PartDev P, int h, double* ball, ui
     }
 }
 
-__global__ __launch_bounds__(256) void k_clear(const uint32_t* __restrict__ err, uint32_t* own,
-                                               const double* ball, int h, Geom g)
+// The first kernel of a classification, a column of workgroups per particle:
+// the first of a column resets the particle's counters (the candidate counts of
+// the previous classification are kept for its lists) and finds its box, the
+// others, given a plane to clear, clear a z plane of its ball of two
+// classifications ago (also where the check of the boxes fails: that plane is
+// not in use, and the next attempt clears it again).  One launch for the chain
+// of three that a small run waited 12 us for.
+__global__ __launch_bounds__(256) void k_begin(PartDev P, int h, double* ball, uint32_t* err, Geom g,
+                                               const double* ball_prev, double* quat_prev,
+                                               uint32_t* inc_bad,
+                                               uint32_t* link_cursor, uint32_t* cand_cursor,
+                                               uint32_t* cand_prev_count, uint32_t* own,
+                                               const double* ball_clear)
 {
-    if (*err) return;  // the boxes failed their check: leave every plane as it is
     const int p = blockIdx.y;
-    walk_ball_plane(ball + 4 * p, h, g, [&](const uint32_t* node, const bool* on) {
+    if (blockIdx.x > 0) {
+        walk_ball_plane(ball_clear + 4 * p, h, (int)blockIdx.x - 1, g,
+                        [&](const uint32_t* node, const bool* on) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
-            if (on[k]) own[node[k]] = kFluid;
-    });
+                            for (int k = 0; k < 2; ++k)
+                                if (on[k]) own[node[k]] = kFluid;
+                        });
+        return;
+    }
+    if (threadIdx.x >= 64) return;
+    if (threadIdx.x == 0) {
+        const int64_t at = (int64_t)p * kCursorPad;
+        if (cand_prev_count) cand_prev_count[p] = cand_cursor[at];
+        cand_cursor[at] = 0;
+        link_cursor[at] = 0;
+    }
+    box_of(P, p, h, ball, err, g, ball_prev, quat_prev, inc_bad);
 }
 
 // Node owners: the lowest particle index with M_p >= c0_p.
@@ -350,8 +373,9 @@ __global__ __launch_bounds__(256) void k_clear(const uint32_t* __restrict__ err,
 template <int T>
 __global__ __launch_bounds__(T, 8) void k_mark(const uint32_t* __restrict__ err, uint32_t* own, const double* ball, int h, PartDev P,
                                               Geom g, uint8_t* flag, int store_flag, uint32_t* cand,
-                                              int64_t cap, uint32_t* cursors)
+                                              int64_t cap, uint32_t* cursors, uint32_t* other_set)
 {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kSetWords) other_set[threadIdx.x] = 0u;
     if (*err) return;  // the boxes failed their check: leave every plane as it is
     constexpr int kSegs = 8 * T;           // segments of 8 nodes listed at a time
     constexpr uint32_t kCandBuf = 8 * T;
@@ -534,33 +558,39 @@ __global__ __launch_bounds__(T, 8) void k_mark(const uint32_t* __restrict__ err,
 
 // Over the previous balls: flags of the new classification and the nodes that
 // particle p covered before and that are fluid now.
-__global__ __launch_bounds__(256) void k_finish(const uint32_t* __restrict__ err, const uint32_t* own_prev, const uint32_t* own_new,
-                                                const double* ball, int h, Geom g, uint8_t* flag,
-                                                RefillRec* rec, int64_t cap, uint32_t* cursor)
+struct Finish {
+    const uint32_t* own_prev;
+    const double* ball;  // the previous classification's
+    uint8_t* flag;
+    RefillRec* rec;
+    int64_t cap;
+    uint32_t* cursor;
+};
+
+__device__ __forceinline__ void finish_plane(const Finish& F, const uint32_t* own_new, int p, int h,
+                                             int plane, const Geom& g)
 {
-    if (*err) return;  // the boxes failed their check: leave every plane as it is
-    const int p = blockIdx.y;
     const int lane = threadIdx.x & 63;
-    walk_ball_plane(ball + 4 * p, h, g, [&](const uint32_t* node, const bool* on) {
+    walk_ball_plane(F.ball + 4 * p, h, plane, g, [&](const uint32_t* node, const bool* on) {
         uint32_t now[2], was[2];
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             now[k] = on[k] ? own_new[node[k]] : 0u;
-            was[k] = on[k] ? own_prev[node[k]] : kFluid;
+            was[k] = on[k] ? F.own_prev[node[k]] : kFluid;
         }
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            if (on[k]) flag[node[k]] = now[k] != kFluid;
+            if (on[k]) F.flag[node[k]] = now[k] != kFluid;
             const bool refill = now[k] == kFluid && was[k] == (uint32_t)p;
             const uint64_t m = __ballot(refill);
             if (!m) continue;  // uniform over the wave
             uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(cursor, (uint32_t)__popcll(m));
+            if (lane == 0) base = atomicAdd(F.cursor, (uint32_t)__popcll(m));
             base = __shfl(base, 0, 64);
             const uint32_t slot = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-            if (refill && slot < cap) {
-                rec[slot].node = node[k];
-                rec[slot].part = (uint32_t)p;
+            if (refill && slot < F.cap) {
+                F.rec[slot].node = node[k];
+                F.rec[slot].part = (uint32_t)p;
             }
         }
     });
@@ -624,18 +654,27 @@ __device__ double exact_q(const double* sp, int n, const double Xn[3], const int
 // searched by each lane, the quotients of M one after the other and 16
 // candidates a wave), many by issue and gathers (1000 in 512^3: 444 us, before
 // 575; 60 with exact fractions 38 us, before 48).
-__global__ __launch_bounds__(256, 6) void k_links(const uint32_t* __restrict__ err, const uint32_t* own, const double* ball, PartDev P,
+// FINISH: workgroups after the links' take the planes of finish_plane, which
+// need nothing of the links (200 bodies 28.5 us together; apart 27.4 and 9.5).
+template <bool FINISH>
+__global__ __launch_bounds__(256, FINISH ? 5 : 6) void k_links(const uint32_t* __restrict__ err, const uint32_t* own, const double* ball, PartDev P,
                                                Geom g, const uint32_t* cand, int64_t cand_cap,
                                                const uint32_t* cand_cursors, LinkRec* links,
                                                const int64_t* __restrict__ loff,
                                                uint32_t* cursors, int treat, uint32_t gx,
-                                               uint32_t cpw)
+                                               uint32_t cpw, uint32_t link_blocks, Finish F, int h)
 {
     if (*err) return;  // the boxes failed their check: leave every plane as it is
     __shared__ double sp[4 * kMaxCtrl];
     __shared__ uint16_t pairs[4][64 * (kQ - 1)];  // per wave: direction << 6 | lane
+    if constexpr (FINISH)
+        if (blockIdx.x >= link_blocks) {  // uniform over the block
+            const uint32_t b = blockIdx.x - link_blocks, S = 2u * (uint32_t)h + 1u;
+            finish_plane(F, own, (int)(b / S), h, (int)(b % S), g);
+            return;
+        }
     uint32_t bx, by;
-    if (!xcd_tile(gx, (uint32_t)P.n, bx, by)) return;  // uniform over the block
+    if (!xcd_tile(link_blocks, gx, (uint32_t)P.n, bx, by)) return;  // uniform over the block
     const int p = (int)by;
     const uint32_t count = min((uint32_t)cand_cap, cand_cursors[(int64_t)p * kCursorPad]);
     const uint32_t chunk = 4u * cpw;  // candidates of one workgroup per round
@@ -852,41 +891,8 @@ __global__ __launch_bounds__(256) void k_finish_cand(const uint32_t* __restrict_
     }
 }
 
-// Zero the counters a classification fills: the refill count, the box check
-// and the first word of every link and candidate cursor line (the
-// non-finite force flag is left for the classification to report).
-__global__ void k_reset_counters(uint32_t* ctr, int np, uint32_t* cand_prev_count)
-{
-    const int i = (int)(blockIdx.x * 256u + threadIdx.x);
-    // the candidate counts of the previous classification, kept for its lists
-    if (cand_prev_count && i >= np && i < 2 * np)
-        cand_prev_count[i - np] = ctr[kStageHead + (int64_t)i * kCursorPad];
-    if (i == 0) {
-        ctr[kCtrRefill] = 0;
-        ctr[kCtrErr] = 0;
-        ctr[kCtrIncremental] = 0;
-    }
-    if (i < 2 * np) ctr[kStageHead + (int64_t)i * kCursorPad] = 0;
-}
-
-// After an asynchronous classification: latch its box check and any list
-// overflow (a count above its capacity) into the deferred word, which no
-// classification clears.
-__global__ void k_latch_deferred(uint32_t* ctr, int np, int np1, const int64_t* loff,
-                                 uint32_t cand_cap, uint32_t refill_cap)
-{
-    uint32_t bad = 0;
-    for (int p = (int)threadIdx.x; p < np; p += (int)blockDim.x) {
-        const uint32_t nl = ctr[kStageHead + (int64_t)p * kCursorPad];
-        const uint32_t nc = ctr[kStageHead + (int64_t)(np1 + p) * kCursorPad];
-        if ((int64_t)nl > loff[p + 1] - loff[p] || nc > cand_cap) bad = kDeferredOverflow;
-    }
-    if (threadIdx.x == 0) {
-        if (ctr[kCtrRefill] > refill_cap) bad |= kDeferredOverflow;
-        bad |= ctr[kCtrErr] & 0xFFu;
-    }
-    if (bad) atomicOr(ctr + kCtrDeferred, bad);
-}
+// A first classification has no refill whose launch could report.
+__global__ __launch_bounds__(256) void k_latch_deferred(CounterReport r) { report_counters(r); }
 
 __global__ void k_owner_export(const uint32_t* own, int32_t* out, uint32_t ncell)
 {
@@ -922,24 +928,26 @@ inline uint32_t blocks_for(int64_t n) { return (uint32_t)((n + 255) / 256); }
 
 namespace MDLBM_QNS {
 
-hipError_t launch_boxes(lbm_ctx* c, const PartDev& P, int slot, int slot_prev, bool inc)
+hipError_t launch_begin(lbm_ctx* c, const PartDev& P, int slot, int slot_prev, bool inc,
+                        uint32_t* own, int slot_clear)
 {
     const int np = c->cfg.n_particles;
     if (np == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_boxes, dim3(np), dim3(64), 0, c->stream, P, c->box.h,
-                       c->ball_hist + (int64_t)slot * 4 * np, c->err, c->geom,
+    c->ctr_set ^= 1;
+    uint32_t* set = c->ctr + kCtrSet[c->ctr_set];
+    c->refill_cursor = set + kSetRefill;
+    c->err = set + kSetErr;
+    c->inc = set + kSetIncremental;
+    if (own && c->dense) {
+        const hipError_t e = hipMemsetAsync(own, 0xFF, sizeof(uint32_t) * (size_t)c->geom.ncell, c->stream);
+        if (e != hipSuccess) return e;
+        own = nullptr;
+    }
+    hipLaunchKernelGGL(k_begin, dim3(own ? 1 + c->box.S : 1, np), dim3(own ? 256 : 64), 0, c->stream, P,
+                       c->box.h, c->ball_hist + (int64_t)slot * 4 * np, c->err, c->geom,
                        c->ball_hist + (int64_t)slot_prev * 4 * np, c->quat_prev,
-                       inc ? c->ctr + kCtrIncremental : nullptr);
-    return hipGetLastError();
-}
-
-// One workgroup per (z plane of the box, particle).
-hipError_t launch_clear_boxes(lbm_ctx* c, uint32_t* own, int slot, int np)
-{
-    if (np == 0) return hipSuccess;
-    if (c->dense) return hipMemsetAsync(own, 0xFF, sizeof(uint32_t) * (size_t)c->geom.ncell, c->stream);
-    hipLaunchKernelGGL(k_clear, dim3(c->box.S, np), dim3(256), 0, c->stream, c->err, own,
-                       c->ball_hist + (int64_t)slot * 4 * np, c->box.h, c->geom);
+                       inc ? c->inc : nullptr, c->link_cursor, c->cand_cursor, c->cand_prev_count,
+                       own, c->ball_hist + (int64_t)slot_clear * 4 * np);
     return hipGetLastError();
 }
 
@@ -961,71 +969,64 @@ hipError_t launch_mark(lbm_ctx* c, uint32_t* own, const PartDev& P, int slot, bo
     hipLaunchKernelGGL(waves ? k_mark<64> : k_mark<256>, dim3(c->box.S, np), dim3(waves ? 64 : 256), 0,
                        c->stream, c->err, own, c->ball_hist + (int64_t)slot * 4 * np, c->box.h, P,
                        c->geom, c->flag, (c->dense && !inc) ? 0 : 1, c->cand, c->cand_cap,
-                       c->cand_cursor);
+                       c->cand_cursor, c->ctr + kCtrSet[c->ctr_set ^ 1]);
     return hipGetLastError();
 }
 
-hipError_t launch_finish(lbm_ctx* c, const uint32_t* own_prev, const uint32_t* own_new, int slot,
-                         int np_prev, bool inc)
+// The flags and refills of dense mode.
+static hipError_t launch_finish_dense(lbm_ctx* c, const uint32_t* own_prev, const uint32_t* own_new,
+                                      int np_prev, bool inc)
 {
-    if (np_prev == 0) return hipSuccess;
-    if (c->dense) {
-        if (inc) {
-            // the candidate pass, or, should k_boxes have found a body that
-            // moved too far, the lattice sweep (each kernel checks the word)
-            const uint32_t nb = (uint32_t)std::min<int64_t>(
-                std::max<int64_t>(1, (c->cand_prev_cap + 255) / 256), 64);
-            hipLaunchKernelGGL(k_finish_cand, dim3(nb, np_prev), dim3(256), 0, c->stream, c->err,
-                               c->ctr + kCtrIncremental, own_prev, own_new, c->cand_prev,
-                               c->cand_prev_cap, c->cand_prev_count, c->flag, c->refill,
-                               c->refill_cap, c->refill_cursor);
-        }
-        // 2048 workgroups (eight per compute unit) stride over the lattice
-        const uint32_t nb = (uint32_t)std::min<int64_t>(((int64_t)c->geom.ncell + 1023) / 1024, 2048);
-        hipLaunchKernelGGL(k_finish_all, dim3(nb), dim3(256), 0,
-                           c->stream, c->err, own_prev, own_new, c->geom, c->flag, c->refill,
-                           c->refill_cap, c->refill_cursor,
-                           inc ? c->ctr + kCtrIncremental : nullptr);
-        return hipGetLastError();
+    if (inc) {
+        // the candidate pass, or, should k_begin have found a body that moved
+        // too far, the lattice sweep (each kernel checks the word)
+        const uint32_t nb =
+            (uint32_t)std::min<int64_t>(std::max<int64_t>(1, (c->cand_prev_cap + 255) / 256), 64);
+        hipLaunchKernelGGL(k_finish_cand, dim3(nb, np_prev), dim3(256), 0, c->stream, c->err, c->inc,
+                           own_prev, own_new, c->cand_prev, c->cand_prev_cap, c->cand_prev_count,
+                           c->flag, c->refill, c->refill_cap, c->refill_cursor);
     }
-    hipLaunchKernelGGL(k_finish, dim3(c->box.S, np_prev), dim3(256), 0, c->stream, c->err, own_prev,
-                       own_new, c->ball_hist + (int64_t)slot * 4 * np_prev, c->box.h, c->geom,
-                       c->flag, c->refill, c->refill_cap, c->refill_cursor);
+    // 2048 workgroups (eight per compute unit) stride over the lattice
+    const uint32_t nb = (uint32_t)std::min<int64_t>(((int64_t)c->geom.ncell + 1023) / 1024, 2048);
+    hipLaunchKernelGGL(k_finish_all, dim3(nb), dim3(256), 0, c->stream, c->err, own_prev, own_new,
+                       c->geom, c->flag, c->refill, c->refill_cap, c->refill_cursor,
+                       inc ? c->inc : nullptr);
     return hipGetLastError();
 }
 
-hipError_t launch_links(lbm_ctx* c, const uint32_t* own, const PartDev& P, int slot)
+hipError_t launch_finish_links(lbm_ctx* c, const uint32_t* own_prev, const uint32_t* own_new,
+                               const PartDev& P, int slot, int slot_prev, bool inc, bool finish,
+                               bool links)
 {
     const int np = c->cfg.n_particles;
     if (np == 0) return hipSuccess;
+    if (finish && c->dense) {
+        const hipError_t e = launch_finish_dense(c, own_prev, own_new, np, inc);
+        if (e != hipSuccess) return e;
+        finish = false;
+    }
+    if (!finish && !links) return hipSuccess;
     // few particles: 12 candidates per wave and up to 96 workgroups each (60
     // bodies with exact fractions: 38 us; 42 with 16, 44 with 24)
     const uint32_t cpw = np <= 64 ? 12u : 64u;
     const int64_t chunk = 4 * (int64_t)cpw;
     const uint32_t per =
         (uint32_t)std::min<int64_t>(np <= 64 ? 96 : 16, (c->cand_cap + chunk - 1) / chunk);
-    const uint32_t nb = (per * (uint32_t)np + 7u) & ~7u;
-    hipLaunchKernelGGL(k_links, dim3(nb), dim3(256), 0, c->stream, c->err, own,
+    const uint32_t nb = links ? (per * (uint32_t)np + 7u) & ~7u : 0u;
+    const uint32_t nf = finish ? (uint32_t)c->box.S * (uint32_t)np : 0u;
+    const Finish F{own_prev, c->ball_hist + (int64_t)slot_prev * 4 * np, c->flag, c->refill,
+                   c->refill_cap, c->refill_cursor};
+    hipLaunchKernelGGL(finish ? k_links<true> : k_links<false>, dim3(nb + nf), dim3(256), 0,
+                       c->stream, c->err, own_new,
                        c->ball_hist + (int64_t)slot * 4 * np, P, c->geom, c->cand, c->cand_cap,
                        c->cand_cursor, c->links, c->lay->off_dev, c->link_cursor,
-                       c->cfg.treatments, per, cpw);
-    return hipGetLastError();
-}
-
-hipError_t launch_reset_counters(lbm_ctx* c)
-{
-    const int np = c->cfg.n_particles;
-    hipLaunchKernelGGL(k_reset_counters, dim3(blocks_for(2 * (int64_t)std::max(np, 1))), dim3(256), 0,
-                       c->stream, c->ctr, np, c->cand_prev_count);
+                       c->cfg.treatments, per, cpw, nb, F, c->box.h);
     return hipGetLastError();
 }
 
 hipError_t launch_latch_deferred(lbm_ctx* c)
 {
-    const int np = c->cfg.n_particles;
-    hipLaunchKernelGGL(k_latch_deferred, dim3(1), dim3(256), 0, c->stream, c->ctr, np,
-                       std::max(np, 1), c->lay->off_dev, (uint32_t)c->cand_cap,
-                       (uint32_t)c->refill_cap);
+    hipLaunchKernelGGL(k_latch_deferred, dim3(1), dim3(256), 0, c->stream, counter_report(c, false));
     return hipGetLastError();
 }
 

@@ -23,8 +23,6 @@ constexpr uint32_t kFluid = 0xFFFFFFFFu;
 // host block so that a single copy reads them all: the refill count, the box
 // check, the non-finite force flag (one 128-byte line), then one line per
 // particle for its link count and one per particle for its candidate count.
-constexpr int kCtrRefill = 0;
-constexpr int kCtrErr = 1;
 constexpr int kCtrNumeric = 2;
 // Latched by asynchronous classifications: the box check's bits (low byte)
 // and kDeferredOverflow when a list outgrew its capacity.
@@ -34,11 +32,18 @@ constexpr uint32_t kDeferredOverflow = 0x100u;
 // linked to it through broad-phase candidate pairs of one dem_step call)
 // has more than kAdjCluster members.
 constexpr int kCtrAdjCluster = 4;
-// Set by the boxes' kernel when a particle moved too far since the previous
-// classification for the candidate-list flag and refill pass (every node
-// that leaves a body was on its previous candidate list); the lattice sweep
-// then writes flags and refills instead.
-constexpr int kCtrIncremental = 5;
+// Two sets of the words that a classification counts in, used in turn: each
+// classification's owner kernel clears the other set, so that its first kernel
+// finds its own set clear (a launch of its own for that took 5 us).  The refill
+// count; the box check; and, set by the boxes' kernel when a particle moved too
+// far since the previous classification for the candidate-list flag and refill
+// pass (every node that leaves a body was on its previous candidate list): the
+// lattice sweep then writes flags and refills instead.
+constexpr int kCtrSet[2] = {8, 16};
+constexpr int kSetRefill = 0;
+constexpr int kSetErr = 1;
+constexpr int kSetIncremental = 2;
+constexpr int kSetWords = 3;
 // Latched by dem_step when a particle had more candidate contact partners
 // than its history slots (reported like the asynchronous classifications).
 constexpr uint32_t kDeferredSlots = 0x200u;
@@ -215,10 +220,15 @@ struct lbm_ctx {
     uint32_t* refill_cursor = nullptr;
     int64_t refill_total = 0;
     uint32_t* err = nullptr;      // error bits written by kernels
-    uint32_t* ctr = nullptr;      // the counter block: refill_cursor, err, numeric,
+    uint32_t* inc = nullptr;      // kSetIncremental of the current set
+    int ctr_set = 0;              // the set of the last classification
+    uint32_t* ctr = nullptr;      // the counter block: refill_cursor, err, inc, numeric,
                                   // link_cursor and cand_cursor point into it
     double* FT = nullptr;         // [np][6] force, torque of the last step
-    unsigned long long* FX = nullptr;  // [np][6][lo, hi]: exact sums (LBM_FORCE_SUM_EXACT)
+    // the sums of the step under way, zero between steps: [np][6] doubles, or
+    // [np][6][lo, hi] exact (LBM_FORCE_SUM_EXACT); the bulk pass moves them to FT
+    double* sums = nullptr;
+    unsigned long long* FX = nullptr;
     uint32_t* host_stage = nullptr; // pinned staging for counters
     // DEM
     double* hist_pp = nullptr;    // [np][kPairSlots][8] pair histories
@@ -285,6 +295,9 @@ struct AdjList {
     uint32_t* count = nullptr;
     uint32_t cap = 0;
 };
+
+// What a classification's last kernel does with its counters.
+enum class Report { none, host, latch };
 
 // Launchers of the lattice kernels, one set per lattice (D3Q19, D3Q15).
 namespace q19 {

@@ -414,41 +414,109 @@ __device__ __forceinline__ A eq_moving(A w, A drho, A rho, A eu, A uu)
 // Sums of six values over a wave: lane k (k < 6) gets the sum of v[k] over all
 // lanes (lanes 6 and 7 zero).  Each of the first three exchanges halves the number
 // of values a lane carries, so ten exchanges do what 36 would value by value.
-__device__ __forceinline__ double wave_sum6(const double v[6])
+__device__ __forceinline__ double shfl_xor(double v, int m) { return __shfl_xor(v, m, 64); }
+
+template <class V>
+__device__ __forceinline__ V wave_sum6(const V v[6])
 {
     const int lane = threadIdx.x & 63;
-    double a[4];
+    V a[4];
     {
         // lanes with bit 2 set keep values 4-7
         const bool up = lane & 4;
-        const double w[8] = {v[0], v[1], v[2], v[3], v[4], v[5], 0.0, 0.0};
+        const V w[8] = {v[0], v[1], v[2], v[3], v[4], v[5], V{}, V{}};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const double give = up ? w[k] : w[k + 4], keep = up ? w[k + 4] : w[k];
-            a[k] = keep + __shfl_xor(give, 4, 64);
+            const V give = up ? w[k] : w[k + 4], keep = up ? w[k + 4] : w[k];
+            a[k] = keep + shfl_xor(give, 4);
         }
     }
-    double b[2];
+    V b[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const bool up = lane & 2;
-        const double give = up ? a[k] : a[k + 2], keep = up ? a[k + 2] : a[k];
-        b[k] = keep + __shfl_xor(give, 2, 64);
+        const V give = up ? a[k] : a[k + 2], keep = up ? a[k + 2] : a[k];
+        b[k] = keep + shfl_xor(give, 2);
     }
     const bool up = lane & 1;
-    double s = (up ? b[1] : b[0]) + __shfl_xor(up ? b[0] : b[1], 1, 64);
-    s += __shfl_xor(s, 8, 64);
-    s += __shfl_xor(s, 16, 64);
-    s += __shfl_xor(s, 32, 64);
+    V s = (up ? b[1] : b[0]) + shfl_xor(up ? b[0] : b[1], 1);
+    s = s + shfl_xor(s, 8);
+    s = s + shfl_xor(s, 16);
+    s = s + shfl_xor(s, 32);
     return s;
 }
 
-__device__ __forceinline__ double dsum_wave(double v)
+// The force and torque sums of the step under way, which k_boundary adds to,
+// and where they go: n = 6 np numbers, doubles or exact 128-bit integers.
+struct ForceSums {
+    double* sums;
+    unsigned long long* fx;
+    double* FT;
+    uint32_t n;
+};
+
+__device__ __forceinline__ double force_sum(const double* sums, const unsigned long long* fx, int64_t i)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-    return v;
+    return fx ? (double)(int64_t)fx[2 * i + 1] * 0x1p-16 + (double)fx[2 * i] * 0x1p-80 : sums[i];
 }
 
+// Finished sums to FT, by the whole grid of a one-dimensional kernel; they are
+// left zero for the next step (a launch of its own to clear them took 1-3 us a
+// step, with the exact sums three took 10).
+__device__ __forceinline__ void settle_sums(const ForceSums& s)
+{
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < s.n; i += gridDim.x * blockDim.x) {
+        s.FT[i] = force_sum(s.sums, s.fx, i);
+        if (s.fx)
+            s.fx[2 * (int64_t)i] = s.fx[2 * (int64_t)i + 1] = 0ull;
+        else
+            s.sums[i] = 0.0;
+    }
+}
+
+// The counters of a classification whose lists are complete, for one workgroup.
+struct CounterReport {
+    uint32_t* ctr;
+    const uint32_t* set;  // this classification's words
+    uint32_t* host;       // the pinned block, or null: latch instead
+    const int64_t* loff;
+    int np;
+    uint32_t cand_cap, refill_cap;
+};
+
+// To the host block: the head line and the first word of every cursor line.
+// Or, after an asynchronous classification: its box check and any list overflow
+// (a count above its capacity) into the deferred word, which no classification
+// clears.
+__device__ __forceinline__ void report_counters(const CounterReport& r)
+{
+    if (r.host) {
+        for (int i = (int)threadIdx.x; i < kStageHead; i += (int)blockDim.x) r.host[i] = r.ctr[i];
+        for (int i = (int)threadIdx.x; i < 2 * r.np; i += (int)blockDim.x) {
+            const int64_t at = kStageHead + (int64_t)i * kCursorPad;
+            r.host[at] = r.ctr[at];
+        }
+        __threadfence_system();
+        return;
+    }
+    uint32_t bad = 0;
+    for (int p = (int)threadIdx.x; p < r.np; p += (int)blockDim.x) {
+        const uint32_t nl = r.ctr[kStageHead + (int64_t)p * kCursorPad];
+        const uint32_t nc = r.ctr[kStageHead + (int64_t)(r.np + p) * kCursorPad];
+        if ((int64_t)nl > r.loff[p + 1] - r.loff[p] || nc > r.cand_cap) bad = kDeferredOverflow;
+    }
+    if (threadIdx.x == 0) {
+        if (r.set[kSetRefill] > r.refill_cap) bad |= kDeferredOverflow;
+        bad |= r.set[kSetErr] & 0xFFu;
+    }
+    if (bad) atomicOr(r.ctr + kCtrDeferred, bad);
+}
+
+inline CounterReport counter_report(const lbm_ctx* c, bool host)
+{
+    return CounterReport{c->ctr, c->ctr + kCtrSet[c->ctr_set], host ? c->host_stage : nullptr,
+                         c->lay->off_dev, c->cfg.n_particles, (uint32_t)c->cand_cap,
+                         (uint32_t)c->refill_cap};
+}
 
 }  // namespace mdlbm

@@ -55,10 +55,11 @@ __global__ __launch_bounds__(256) void k_stream_collide(const typename St<S>::T*
                                                         typename St<S>::T* __restrict__ dst,
                                                         typename St<S>::M* __restrict__ mom,
                                                         const uint8_t* __restrict__ flag, Geom g,
-                                                        Phys ph)
+                                                        Phys ph, ForceSums sums)
 {
     using A = typename St<S>::A;
     constexpr bool DEV = St<S>::dev;
+    settle_sums(sums);
     const uint32_t first = xcd_block() * 256u;
     const uint32_t cell = first + threadIdx.x;
     if (cell >= g.ncell) return;
@@ -165,8 +166,9 @@ __global__ __launch_bounds__(256, 6) void k_stream_collide_x2(const __half* __re
                                                            __half* __restrict__ dst,
                                                            Mom16* __restrict__ mom,
                                                            const uint8_t* __restrict__ flag,
-                                                           Geom g, Phys ph)
+                                                           Geom g, Phys ph, ForceSums sums)
 {
+    settle_sums(sums);
     const uint32_t first = xcd_block() * 512u;
     const uint32_t cell = first + 2u * threadIdx.x;
     if (cell >= g.ncell) return;
@@ -241,11 +243,19 @@ __device__ __forceinline__ bool to_fixed(double v, uint64_t& lo, int64_t& hi)
     }
     return bad;
 }
-__device__ __forceinline__ void add128(uint64_t& lo, int64_t& hi, uint64_t blo, int64_t bhi)
+struct Fixed {
+    uint64_t lo;
+    int64_t hi;
+};
+__device__ __forceinline__ Fixed operator+(const Fixed& a, const Fixed& b)
 {
-    const uint64_t s = lo + blo;
-    hi = (int64_t)((uint64_t)hi + (uint64_t)bhi + (s < lo ? 1u : 0u));
-    lo = s;
+    const uint64_t s = a.lo + b.lo;
+    return Fixed{s, (int64_t)((uint64_t)a.hi + (uint64_t)b.hi + (s < a.lo ? 1u : 0u))};
+}
+__device__ __forceinline__ Fixed shfl_xor(const Fixed& v, int m)
+{
+    return Fixed{(uint64_t)__shfl_xor((unsigned long long)v.lo, m, 64),
+                 (int64_t)__shfl_xor((long long)v.hi, m, 64)};
 }
 
 template <int S, bool EXACT>
@@ -255,14 +265,14 @@ __global__ __launch_bounds__(256) void k_boundary(typename St<S>::T* __restrict_
                                                   const uint32_t* __restrict__ cursor,
                                                   const int64_t* __restrict__ loff,
                                                   const uint32_t* __restrict__ chunk,
-                                                  PartDev P, double* __restrict__ FT,
+                                                  PartDev P, double* __restrict__ sums,
                                                   unsigned long long* __restrict__ FX, Geom g,
                                                   Phys ph, uint32_t* __restrict__ numeric)
 {
     using A = typename St<S>::A;
     constexpr bool DEV = St<S>::dev;
     // one workgroup per 256-record chunk of the link layout (chunks do not
-    // straddle particles)
+    // straddle particles; a wave per 64 records gained nothing at any size)
     const int64_t g0 = (int64_t)blockIdx.x * 256;
     // (every record of a chunk is allocated: it loads beside the particle's
     // index, and counts only if it lies below the particle's link count)
@@ -382,34 +392,22 @@ __global__ __launch_bounds__(256) void k_boundary(typename St<S>::T* __restrict_
         // per link in 128-bit integers, then wave, workgroup and the
         // particle's accumulator (the carry of the low word's atomic goes
         // into the high word's)
-        __shared__ uint64_t rlo[4][6];
-        __shared__ int64_t rhi[4][6];
+        Fixed v[6];
         bool bad = false;
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            uint64_t lo;
-            int64_t hi;
-            bad = to_fixed(acc[k], lo, hi) || bad;
-            for (int m = 32; m >= 1; m >>= 1) {
-                const uint64_t blo = __shfl_xor((unsigned long long)lo, m, 64);
-                const int64_t bhi = __shfl_xor((long long)hi, m, 64);
-                add128(lo, hi, blo, bhi);
-            }
-            if (lane == 0) {
-                rlo[wv][k] = lo;
-                rhi[wv][k] = hi;
-            }
-        }
+        for (int k = 0; k < 6; ++k) bad = to_fixed(acc[k], v[k].lo, v[k].hi) || bad;
         if (__ballot(bad) && lane == 0) atomicOr(numeric, 1u);  // reported by the next classification
+        __shared__ Fixed red[4][6];
+        const Fixed sum = wave_sum6(v);
+        if (lane < 6) red[wv][lane] = sum;
         __syncthreads();
         if (threadIdx.x < 6) {
-            uint64_t lo = rlo[0][threadIdx.x];
-            int64_t hi = rhi[0][threadIdx.x];
-            for (int w = 1; w < 4; ++w) add128(lo, hi, rlo[w][threadIdx.x], rhi[w][threadIdx.x]);
+            Fixed s = red[0][threadIdx.x];
+            for (int w = 1; w < 4; ++w) s = s + red[w][threadIdx.x];
             unsigned long long* a = FX + 2 * (6 * (int64_t)p + threadIdx.x);
-            const unsigned long long old = atomicAdd(a, (unsigned long long)lo);
-            const unsigned long long carry = old + lo < old ? 1ull : 0ull;
-            atomicAdd(a + 1, (unsigned long long)hi + carry);
+            const unsigned long long old = atomicAdd(a, (unsigned long long)s.lo);
+            const unsigned long long carry = old + s.lo < old ? 1ull : 0ull;
+            atomicAdd(a + 1, (unsigned long long)s.hi + carry);
         }
     } else {
         __shared__ double red[4][6];
@@ -419,26 +417,19 @@ __global__ __launch_bounds__(256) void k_boundary(typename St<S>::T* __restrict_
         if (threadIdx.x < 6) {
             const double s = (red[0][threadIdx.x] + red[1][threadIdx.x]) +
                              (red[2][threadIdx.x] + red[3][threadIdx.x]);
-            atomicAdd(FT + 6 * p + threadIdx.x, s);
+            atomicAdd(sums + 6 * p + threadIdx.x, s);
             if (!isfinite(s)) atomicOr(numeric, 1u);  // reported by the next classification
         }
     }
 }
 
-// The exact sums as doubles (rounded once each word).
-__global__ __launch_bounds__(256) void k_fixed_to_f64(const unsigned long long* __restrict__ FX,
-                                                      double* __restrict__ FT, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    FT[i] = (double)(int64_t)FX[2 * i + 1] * 0x1p-16 + (double)FX[2 * i] * 0x1p-80;
-}
-
 // ---------------------------------------------------------------------------
 // Refill: one thread per node uncovered since the previous classification.
 // The count is read on the device (the list's cursor, at most cap), so the
-// launch needs no read-back; a grid of at most a few thousand workgroups
-// strides over the list.  Each node reads only the previous populations and
+// launch needs no read-back; a grid of at most a few thousand waves strides over
+// the list (64 nodes a workgroup spread its gathers over more compute units than
+// 256: 200 bodies 20 -> 11 us, 1000 in 512^3 42 -> 23), and the last workgroup
+// reports the classification's counters.  Each node reads only the previous populations and
 // owners and writes only its own populations and moments, so running the
 // kernel again over a longer list (after the list has grown) gives the same
 // values at the nodes of the first run.  Bound by the latency of one node's
@@ -517,18 +508,19 @@ __device__ __forceinline__ void refill_node(const typename St<S>::T* __restrict_
 }
 
 template <int S>
-__global__ __launch_bounds__(256) void k_refill(const typename St<S>::T* __restrict__ prev,
+__global__ __launch_bounds__(64) void k_refill(const typename St<S>::T* __restrict__ prev,
                                                 typename St<S>::T* __restrict__ cur,
                                                 typename St<S>::M* __restrict__ mom,
                                                 const RefillRec* __restrict__ rec,
                                                 const uint32_t* __restrict__ cursor, uint32_t cap,
                                                 const uint32_t* __restrict__ err,
                                                 const uint32_t* __restrict__ own_prev, PartDev P,
-                                                Geom g, Phys ph)
+                                                Geom g, Phys ph, CounterReport report)
 {
+    if (report.ctr && blockIdx.x == gridDim.x - 1u) report_counters(report);
     if (*err) return;  // the classification's box check failed: nothing was listed
     const uint32_t cnt = min(*cursor, cap);
-    for (uint32_t l = blockIdx.x * 256u + threadIdx.x; l < cnt; l += gridDim.x * 256u)
+    for (uint32_t l = blockIdx.x * 64u + threadIdx.x; l < cnt; l += gridDim.x * 64u)
         refill_node<S>(prev, cur, mom, rec[l], own_prev, P, g, ph);
 }
 
@@ -590,12 +582,6 @@ __global__ void k_set(typename St<S>::T* f, typename St<S>::M* mom, const double
                   A((jy - 0.5 * ph.F[1]) / rho), A((jz - 0.5 * ph.F[2]) / rho), ph.scale);
 }
 
-__global__ void k_zero(double* p, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0.0;
-}
-
 __global__ void k_split(const double* FT, double* F, double* T, int n)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
@@ -634,6 +620,7 @@ template <int S>
 struct RunSC {
     static hipError_t run(lbm_ctx* c, const void* src, void* dst)
     {
+        const ForceSums sums{c->sums, c->FX, c->FT, 6u * (uint32_t)c->cfg.n_particles};
         // FP16 only: for FP32 the pair kernel was measured slower (4.8 against
         // 4.4 ms on 512^3), the single-node pass already runs at copy speed
         if constexpr (S == LBM_STORE_F16) {
@@ -642,7 +629,7 @@ struct RunSC {
                 nb = (nb + 7u) & ~7u;
                 hipLaunchKernelGGL(k_stream_collide_x2, dim3(nb), dim3(256), 0, c->stream,
                                    (const typename St<S>::T*)src, (typename St<S>::T*)dst,
-                                   (typename St<S>::M*)c->mom, c->flag, c->geom, c->phys);
+                                   (typename St<S>::M*)c->mom, c->flag, c->geom, c->phys, sums);
                 return hipGetLastError();
             }
         }
@@ -650,7 +637,7 @@ struct RunSC {
         nb = (nb + 7u) & ~7u;  // whole rounds over the 8 XCDs
         hipLaunchKernelGGL(k_stream_collide<S>, dim3(nb), dim3(256), 0, c->stream,
                            (const typename St<S>::T*)src, (typename St<S>::T*)dst,
-                           (typename St<S>::M*)c->mom, c->flag, c->geom, c->phys);
+                           (typename St<S>::M*)c->mom, c->flag, c->geom, c->phys, sums);
         return hipGetLastError();
     }
 };
@@ -661,23 +648,11 @@ struct RunBC {
     {
         if (c->cfg.n_particles == 0 || c->link_max == 0 || c->lay->chunks() == 0)
             return hipSuccess;
-        const dim3 grid((uint32_t)c->lay->chunks());
-        if (c->FX) {
-            const int64_t n6 = 6 * (int64_t)c->cfg.n_particles;
-            hipLaunchKernelGGL(k_zero, dim3(blocks_for(2 * n6)), dim3(256), 0, c->stream,
-                               reinterpret_cast<double*>(c->FX), 2 * n6);
-            hipLaunchKernelGGL((k_boundary<S, true>), grid, dim3(256), 0, c->stream,
-                               (typename St<S>::T*)f, (const typename St<S>::M*)c->mom, c->links,
-                               c->link_cursor, c->lay->off_dev, c->lay->chunk_dev, P, c->FT, c->FX,
-                               c->geom, c->phys, c->numeric);
-            hipLaunchKernelGGL(k_fixed_to_f64, dim3(blocks_for(n6)), dim3(256), 0, c->stream, c->FX,
-                               c->FT, n6);
-        } else {
-            hipLaunchKernelGGL((k_boundary<S, false>), grid, dim3(256), 0, c->stream,
-                               (typename St<S>::T*)f, (const typename St<S>::M*)c->mom, c->links,
-                               c->link_cursor, c->lay->off_dev, c->lay->chunk_dev, P, c->FT,
-                               nullptr, c->geom, c->phys, c->numeric);
-        }
+        hipLaunchKernelGGL((c->FX ? k_boundary<S, true> : k_boundary<S, false>),
+                           dim3((uint32_t)c->lay->chunks()), dim3(256), 0, c->stream,
+                           (typename St<S>::T*)f, (const typename St<S>::M*)c->mom, c->links,
+                           c->link_cursor, c->lay->off_dev, c->lay->chunk_dev, P, c->sums, c->FX,
+                           c->geom, c->phys, c->numeric);
         return hipGetLastError();
     }
 };
@@ -685,13 +660,14 @@ struct RunBC {
 template <int S>
 struct RunRefill {
     static hipError_t run(lbm_ctx* c, const void* fprev, void* fcur, const uint32_t* own_prev,
-                          const PartDev& P)
+                          const PartDev& P, Report report)
     {
-        const uint32_t nb = std::min<uint32_t>(blocks_for(c->refill_cap), 2048u);
-        hipLaunchKernelGGL(k_refill<S>, dim3(nb), dim3(256), 0, c->stream,
+        const uint32_t nb = std::min<uint32_t>((uint32_t)((c->refill_cap + 63) / 64), 4096u);
+        const CounterReport r = report == Report::none ? CounterReport{} : counter_report(c, report == Report::host);
+        hipLaunchKernelGGL(k_refill<S>, dim3(nb), dim3(64), 0, c->stream,
                            (const typename St<S>::T*)fprev, (typename St<S>::T*)fcur,
                            (typename St<S>::M*)c->mom, c->refill, c->refill_cursor,
-                           (uint32_t)c->refill_cap, c->err, own_prev, P, c->geom, c->phys);
+                           (uint32_t)c->refill_cap, c->err, own_prev, P, c->geom, c->phys, r);
         return hipGetLastError();
     }
 };
@@ -760,9 +736,9 @@ hipError_t launch_boundary(lbm_ctx* c, void* f, const PartDev& P)
     return dispatch<RunBC>(c->cfg.storage, c, f, P);
 }
 hipError_t launch_refill(lbm_ctx* c, const void* fprev, void* fcur, const uint32_t* own_prev,
-                         const PartDev& P)
+                         const PartDev& P, Report report)
 {
-    return dispatch<RunRefill>(c->cfg.storage, c, fprev, fcur, own_prev, P);
+    return dispatch<RunRefill>(c->cfg.storage, c, fprev, fcur, own_prev, P, report);
 }
 hipError_t launch_get_populations(lbm_ctx* c, const void* f, double* out)
 {
@@ -775,12 +751,6 @@ hipError_t launch_set_populations(lbm_ctx* c, void* f, const double* in)
 hipError_t launch_get_moments(lbm_ctx* c, double* rho, double* u)
 {
     return dispatch<RunMoments>(c->cfg.storage, c, rho, u);
-}
-hipError_t launch_zero_f64(lbm_ctx* c, double* p, int64_t n)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero, dim3(blocks_for(n)), dim3(256), 0, c->stream, p, n);
-    return hipGetLastError();
 }
 hipError_t launch_split_forces(const lbm_ctx* c, double* F, double* T)
 {

@@ -148,3 +148,55 @@ def test_classification_at_plane_and_tile_edges(n, d, dims, per, lattice):
         ps.pos = np.where(np.array(per, bool), np.mod(ps.pos, dims), ps.pos)
         ps.refresh_world()
     gpu.close()
+
+
+@pytest.mark.parametrize("exact", [False, True])
+def test_force_sums_and_counters_between_steps(exact):
+    """Forces of steps with and without a classification before them, after a
+    classification that failed, and of replayed captured steps with eager work
+    between the replays: the sums start from zero each time, and the counters of
+    one classification do not reach the next."""
+    lat, ps = W.tiny_case(21, dims=(34, 30, 32), periodic=(1, 0, 1), n_particles=3,
+                          diameter_range=(5.0, 8.0), speed=0.05, spin=0.004, u0=(0.02, 0.0, 0.01))
+    import torch
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        gpu, ora = (B.Lattice.for_particles(lat, ps, storage="f64", exact_forces=exact),
+                    O.Oracle(lat, Q=19))
+        parts, bad = B.DeviceParticles(ps), B.DeviceParticles(ps)
+        bad.t["pos"][1, 0] = float("nan")
+
+        def same(what):
+            Fo, To = ora.step(P)
+            F, T = (t.cpu().numpy()[:ps.n] for t in gpu.forces())
+            assert np.abs(F - Fo).max() <= 1e-10 * np.abs(Fo).max(), what
+            assert np.abs(T - To).max() <= 1e-10 * np.abs(To).max(), what
+
+        for n in range(4):
+            P = W.prescribed_state(ps, lat, float(n))
+            parts.set_state(P)
+            if n == 2:
+                with pytest.raises(B.LbmError):
+                    gpu.classify(bad)
+            c = gpu.classify(parts)
+            ora.classify(P)
+            assert c.n_links == len(ora.links) and (n == 0 or c.n_refill == len(ora.refill_nodes))
+            for k in range(2):
+                gpu.step(parts)
+                same((n, k))
+        gpu.sync()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            gpu.step(parts)
+            gpu.step(parts)
+        for n in range(3):
+            graph.replay()
+            ora.step(P)
+            same(("replay", n))
+            gpu.step(parts)      # eager steps between the replays
+            same(("eager", n, 0))
+            gpu.step(parts)
+            same(("eager", n, 1))
+        gpu.sync()
+        gpu.close()
