@@ -6,6 +6,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "lbm_internal.h"
@@ -85,6 +86,8 @@ hipError_t alloc(T** p, size_t count)
     return hipMalloc((void**)p, count * sizeof(T));
 }
 
+size_t align256(size_t n) { return (n + 255) / 256 * 256; }
+
 hipEvent_t take_event(lbm_ctx* c)
 {
     if (!c->event_pool.empty()) {
@@ -154,15 +157,14 @@ std::shared_ptr<const LinkLayout> make_layout(const std::vector<int64_t>& seg)
             h *= 1099511628211ull;
         }
     L->tag = h;
-    if (hipMalloc((void**)&L->off_dev, sizeof(int64_t) * (np + 1)) != hipSuccess) return nullptr;
-    if (hipMalloc((void**)&L->chunk_dev, sizeof(uint32_t) * std::max<size_t>(chunk.size(), 1)) !=
+    // both tables in one allocation and one copy
+    std::vector<int64_t> both(np + 1 + (chunk.size() + 1) / 2);
+    std::copy(L->off.begin(), L->off.end(), both.begin());
+    std::memcpy(both.data() + np + 1, chunk.data(), sizeof(uint32_t) * chunk.size());
+    if (hipMalloc((void**)&L->off_dev, sizeof(int64_t) * both.size()) != hipSuccess) return nullptr;
+    L->chunk_dev = reinterpret_cast<uint32_t*>(L->off_dev + np + 1);
+    if (hipMemcpy(L->off_dev, both.data(), sizeof(int64_t) * both.size(), hipMemcpyHostToDevice) !=
         hipSuccess)
-        return nullptr;
-    if (hipMemcpy(L->off_dev, L->off.data(), sizeof(int64_t) * (np + 1), hipMemcpyHostToDevice) !=
-        hipSuccess)
-        return nullptr;
-    if (!chunk.empty() && hipMemcpy(L->chunk_dev, chunk.data(), sizeof(uint32_t) * chunk.size(),
-                                    hipMemcpyHostToDevice) != hipSuccess)
         return nullptr;
     return L;
 }
@@ -272,29 +274,52 @@ size_t dem_tape_doubles(int np)
     return n * kPairSlots * 8 + n * 48 + n * 6;
 }
 
-// Contact histories (kPairSlots keyed records per particle for its pairs,
-// six per particle for the walls) and the pair list of a dem_step call;
-// allocated by lbm_init, so that dem_step never allocates.
-int dem_alloc(lbm_ctx* c)
+// Everything of a context that keeps its size: counters, force sums, the
+// particles' histories and, for the DEM, the contact histories (kPairSlots keyed
+// records per particle for its pairs, six per particle for the walls), the pair
+// list and the broad phase's grid, so that dem_step never allocates.  One
+// zeroed allocation, as each hipMalloc and hipFree costs some 10 us: a gradient
+// that makes and closes two contexts waited 0.5 ms for them.
+hipError_t carve_fixed(lbm_ctx* c)
 {
-    const size_t np = (size_t)c->cfg.n_particles;
-    if (c->hist_pp || np == 0) return LBM_OK;
+    const size_t np = (size_t)c->cfg.n_particles, np1 = std::max<size_t>(np, 1);
     const size_t slots = np * kPairSlots;
-    if (alloc(&c->hist_pp, slots * 8) != hipSuccess || alloc(&c->hist_key, slots) != hipSuccess ||
-        alloc(&c->hist_pw, np * 6 * 8) != hipSuccess || alloc(&c->pairs, slots) != hipSuccess ||
-        alloc(&c->pair_count, 1) != hipSuccess)
-        return fail(c, LBM_ENOMEM, "contact history allocation failed");
-    HIPCHK(c, hipMemsetAsync(c->hist_pp, 0, sizeof(double) * slots * 8, c->stream));
-    HIPCHK(c, hipMemsetAsync(c->hist_key, 0, sizeof(int32_t) * slots, c->stream));
-    HIPCHK(c, hipMemsetAsync(c->hist_pw, 0, sizeof(double) * np * 6 * 8, c->stream));
-    if (np >= (size_t)kGridMinParticles) {
+    const bool exact = np && c->cfg.force_sum == LBM_FORCE_SUM_EXACT;
+    const bool sweep = np && c->dense, grid = np >= (size_t)kGridMinParticles;
+    if (grid) c->grid_cap = (int64_t)std::max<size_t>(4096, 4 * np);
+    uint8_t* base = nullptr;
+    size_t at = 0;
+    auto put = [&](auto*& p, size_t count) {
+        if (base && count) p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(base + at);
+        at += align256(count * sizeof(*p));
+    };
+    auto carve = [&] {
+        at = 0;
+        put(c->ctr, (size_t)kStageHead + 2 * (size_t)kCursorPad * np1);
+        put(c->ball_hist, 3 * 4 * np1);
+        put(c->FT, 6 * np1);
+        put(c->sums, 6 * np1);
+        put(c->FX, exact ? 12 * np : 0);
+        put(c->fc, 6 * np1);
+        put(c->reach, 2 * np1);
+        put(c->cand_prev_count, sweep ? np : 0);
+        put(c->quat_prev, sweep ? 4 * np : 0);
+        put(c->adj_wts, 6 * np1);
+        put(c->hist_pp, slots * 8);
+        put(c->hist_key, slots);
+        put(c->hist_pw, np * 6 * 8);
+        put(c->pairs, slots);
+        put(c->pair_count, np ? 1 : 0);
         // counts and starts, cursors, the binned particles, the grid's shape
-        c->grid_cap = (int64_t)std::max<size_t>(4096, 4 * np);
-        const size_t words = 2 * (size_t)c->grid_cap + 1 + np + 4;
-        if (alloc(&c->grid, words) != hipSuccess || alloc(&c->grid_size, 4) != hipSuccess)
-            return fail(c, LBM_ENOMEM, "broad-phase grid allocation failed");
-    }
-    return LBM_OK;
+        put(c->grid, grid ? 2 * (size_t)c->grid_cap + 1 + np + 4 : 0);
+        put(c->grid_size, grid ? 4 : 0);
+    };
+    carve();
+    hipError_t e = hipMalloc(&c->slab, at);
+    if (e != hipSuccess) return e;
+    base = static_cast<uint8_t*>(c->slab);
+    carve();
+    return hipMemsetAsync(c->slab, 0, at, c->stream);
 }
 
 // The work space of a dem_step call on the context.
@@ -458,10 +483,8 @@ int lbm_init(const lbm_config* cfg, const lbm_buffers* bufs, lbm_ctx** out)
     const int64_t seg0 = std::max<int64_t>(256, (32 * S2 + 255) / 256 * 256);
     c->cand_cap = std::max<int64_t>(256, (8 * S2 + 255) / 256 * 256);
     c->refill_cap = std::max<int64_t>(1 << 16, (int64_t)np * S2);
-    hipError_t e = hipSuccess;
-    if (e == hipSuccess) e = alloc(&c->ball_hist, (size_t)3 * 4 * std::max(np, 1));
+    hipError_t e = carve_fixed(c);
     const size_t np1 = (size_t)std::max(np, 1);
-    if (e == hipSuccess) e = alloc(&c->ctr, (size_t)kStageHead + 2 * (size_t)kCursorPad * np1);
     if (e == hipSuccess) {
         c->refill_cursor = c->ctr + kCtrSet[0] + kSetRefill;
         c->err = c->ctr + kCtrSet[0] + kSetErr;
@@ -469,16 +492,11 @@ int lbm_init(const lbm_config* cfg, const lbm_buffers* bufs, lbm_ctx** out)
         c->numeric = c->ctr + kCtrNumeric;
         c->link_cursor = c->ctr + kStageHead;
         c->cand_cursor = c->ctr + kStageHead + (size_t)kCursorPad * np1;
-        e = hipMemsetAsync(c->ctr, 0, sizeof(uint32_t) * (kStageHead + 2 * kCursorPad * np1),
-                           c->stream);
     }
     if (e == hipSuccess && np) e = alloc(&c->cand, (size_t)np * c->cand_cap);
     if (e == hipSuccess && np && c->dense) {
         c->cand_prev_cap = c->cand_cap;
         e = alloc(&c->cand_prev, (size_t)np * c->cand_prev_cap);
-        if (e == hipSuccess) e = alloc(&c->cand_prev_count, (size_t)np);
-        if (e == hipSuccess) e = alloc(&c->quat_prev, (size_t)4 * np);
-        if (e == hipSuccess) e = hipMemsetAsync(c->cand_prev_count, 0, sizeof(uint32_t) * np, c->stream);
     }
     if (e == hipSuccess) {
         c->lay = make_layout(std::vector<int64_t>((size_t)np, seg0));
@@ -487,26 +505,12 @@ int lbm_init(const lbm_config* cfg, const lbm_buffers* bufs, lbm_ctx** out)
     }
     if (e == hipSuccess && np) e = alloc(&c->links, (size_t)c->lay->total);
     if (e == hipSuccess) e = alloc(&c->refill, (size_t)c->refill_cap);
-    if (e == hipSuccess) e = alloc(&c->FT, (size_t)6 * std::max(np, 1));
-    if (e == hipSuccess) e = alloc(&c->sums, (size_t)6 * std::max(np, 1));
-    if (e == hipSuccess && np && cfg->force_sum == LBM_FORCE_SUM_EXACT) {
-        e = alloc(&c->FX, (size_t)12 * np);
-        if (e == hipSuccess)
-            e = hipMemsetAsync(c->FX, 0, sizeof(unsigned long long) * 12 * np, c->stream);
-    }
-    if (e == hipSuccess) e = alloc(&c->fc, (size_t)6 * std::max(np, 1));
-    if (e == hipSuccess) e = alloc(&c->reach, (size_t)2 * std::max(np, 1));
     if (e == hipSuccess)
         e = hipHostMalloc((void**)&c->host_stage,
                           sizeof(uint32_t) * (kStageHead + 2 * (size_t)kCursorPad * np1),
                           hipHostMallocDefault);
     if (e != hipSuccess) {
         std::string msg = std::string("scratch allocation failed: ") + hipGetErrorString(e);
-        lbm_destroy(c);
-        return fail(nullptr, LBM_ENOMEM, msg);
-    }
-    if (dem_alloc(c) != LBM_OK) {
-        std::string msg = c->last_error;
         lbm_destroy(c);
         return fail(nullptr, LBM_ENOMEM, msg);
     }
@@ -523,9 +527,6 @@ int lbm_init(const lbm_config* cfg, const lbm_buffers* bufs, lbm_ctx** out)
     if (e == hipSuccess) e = hipMemsetAsync(c->own[0], 0xFF, sz.owner_bytes, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->own[1], 0xFF, sz.owner_bytes, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->flag, 0, sz.flag_bytes, c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(c->FT, 0, sizeof(double) * 6 * std::max(np, 1), c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(c->sums, 0, sizeof(double) * 6 * std::max(np, 1), c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(c->fc, 0, sizeof(double) * 6 * std::max(np, 1), c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         std::string msg = std::string("initialisation failed: ") + hipGetErrorString(e);
@@ -541,32 +542,16 @@ int lbm_destroy(lbm_ctx* c)
 {
     if (!c) return LBM_OK;
     if (c->stream) (void)hipStreamSynchronize(c->stream);
-    (void)hipFree(c->ball_hist);
+    (void)hipFree(c->slab);
     (void)hipFree(c->links);
     (void)hipFree(c->cand);
     (void)hipFree(c->refill);
-    (void)hipFree(c->ctr);
-    (void)hipFree(c->FT);
-    (void)hipFree(c->sums);
-    (void)hipFree(c->FX);
     (void)hipFree(c->cand_prev);
-    (void)hipFree(c->cand_prev_count);
-    (void)hipFree(c->quat_prev);
-    (void)hipFree(c->fc);
-    (void)hipFree(c->reach);
     free_tape(c);
     (void)hipFree(c->adj_scratch);
-    (void)hipFree(c->adj_wts);
     (void)hipFree(c->adj_sig);
     (void)hipFree(c->adj_list);
     (void)hipFree(c->adj_count);
-    (void)hipFree(c->hist_pp);
-    (void)hipFree(c->hist_key);
-    (void)hipFree(c->pairs);
-    (void)hipFree(c->pair_count);
-    (void)hipFree(c->grid);
-    (void)hipFree(c->grid_size);
-    (void)hipFree(c->hist_pw);
     if (c->host_stage) (void)hipHostFree(c->host_stage);
     for (auto& t : c->timed) {
         (void)hipEventDestroy(t.start);
@@ -1148,8 +1133,6 @@ struct GeometryLayout {
     size_t own, flag, links, cursors, refill_ctr, refill, ball, total;
 };
 
-static size_t align256(size_t n) { return (n + 255) / 256 * 256; }
-
 static GeometryLayout geometry_layout(const lbm_ctx* c)
 {
     const size_t np = (size_t)std::max(c->cfg.n_particles, 1);
@@ -1367,8 +1350,6 @@ int lbm_adjoint(lbm_ctx* c, const lbm_particles* P, const double* weights, void*
     if (np > 0 && !weights) return fail(c, LBM_EINVAL, "null objective weights");
     if (!c->adj_scratch && hipMalloc(&c->adj_scratch, c->sizes.adjoint_bytes) != hipSuccess)
         return fail(c, LBM_ENOMEM, "adjoint scratch allocation failed");
-    if (!c->adj_wts && alloc(&c->adj_wts, (size_t)6 * std::max(np, 1)) != hipSuccess)
-        return fail(c, LBM_ENOMEM, "adjoint weight allocation failed");
     if (np > 0)
         HIPCHK(c, hipMemcpyAsync(c->adj_wts, weights, sizeof(double) * 6 * np,
                                  hipMemcpyHostToDevice, c->stream));
@@ -1422,8 +1403,6 @@ int lbm_adjoint_coupled(lbm_ctx* c, const lbm_particles* P, const double* weight
     if (!c->adj_scratch && hipMalloc(&c->adj_scratch, c->sizes.adjoint_bytes) != hipSuccess)
         return fail(c, LBM_ENOMEM, "adjoint scratch allocation failed");
     const size_t nps = (size_t)std::max(np, 1);
-    if (!c->adj_wts && alloc(&c->adj_wts, 6 * nps) != hipSuccess)
-        return fail(c, LBM_ENOMEM, "adjoint weight allocation failed");
     // state adjoints [2][np][12], objective weights [np][6], contact-state
     // adjoints [2][np][kAdjContact]
     if (!c->adj_sig && alloc(&c->adj_sig, 2 * 12 * nps + 6 * nps + 2 * kAdjContact * nps) != hipSuccess)

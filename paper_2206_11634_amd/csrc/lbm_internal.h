@@ -86,14 +86,10 @@ struct LinkLayout {
     int64_t total = 0;               // records: off[np]
     int64_t max_seg = 0;             // the largest segment
     int64_t* off_dev = nullptr;      // [np + 1]
-    uint32_t* chunk_dev = nullptr;   // [total / 256]
+    uint32_t* chunk_dev = nullptr;   // [total / 256], in off_dev's allocation
     uint64_t tag = 0;                // hash of off
     int64_t chunks() const { return total / 256; }
-    ~LinkLayout()
-    {
-        (void)hipFree(off_dev);
-        (void)hipFree(chunk_dev);
-    }
+    ~LinkLayout() { (void)hipFree(off_dev); }
 };
 
 // One recorded lattice step for the adjoint: populations after the link
@@ -195,7 +191,9 @@ struct lbm_ctx {
     bool dense = false;     // particle balls cover most of the lattice: sweep it whole
     bool failed = false;
 
-    // library scratch
+    // library scratch; what keeps its size for the context's life is carved from
+    // one allocation
+    void* slab = nullptr;
     double* ball_hist = nullptr;  // [3][np][4] centre and bounding radius of each particle
                                   // at the last three classifications
     uint32_t* cand = nullptr;     // per particle: nodes that may carry links
