@@ -29,6 +29,7 @@
 #include <algorithm>
 #include <mutex>
 
+#include "lbm_fp64.h"
 #include "lbm_internal.h"
 
 namespace mdlbm {
@@ -92,21 +93,6 @@ __device__ __forceinline__ double gsum(double v)
     return v;
 }
 
-// 1/x and 1/sqrt(x): the hardware's estimate and two Newton steps (an ulp or
-// so; a third of the instructions of a division).  Not a number at 0.
-__device__ __forceinline__ double fast_rcp(double x)
-{
-    double y = __builtin_amdgcn_rcp(x);
-    y = fma(fma(-x, y, 1.0), y, y);
-    return fma(fma(-x, y, 1.0), y, y);
-}
-__device__ __forceinline__ double fast_rsqrt(double x)
-{
-    double y = __builtin_amdgcn_rsq(x);
-    y = fma(fma(-x * y, y, 1.0), 0.5 * y, y);
-    return fma(fma(-x * y, y, 1.0), 0.5 * y, y);
-}
-
 // Terms of one control point at distance r: its share of M, grad M (negated:
 // s r with s = 2 K / r^4) and the upper triangle of the Hessian.
 __device__ __forceinline__ void add_point(double K, const double r[3], double i2, double& M,
@@ -143,13 +129,7 @@ __device__ __forceinline__ bool solve3(const double H[6], const double g[3], dou
 
 __device__ __forceinline__ double reach(const PartDev& P, int p)
 {
-    double sk = 0.0, r = 0.0;
-    for (int i = P.off[p]; i < P.off[p + 1]; ++i) {
-        const double* b = P.body_pts + 3 * (int64_t)i;
-        r = fmax(r, sqrt(b[0] * b[0] + b[1] * b[1] + b[2] * b[2]));
-        sk += P.K[i];
-    }
-    return r + sqrt(sk);
+    return reach_of(P.body_pts, P.K, P.off[p], P.off[p + 1]);
 }
 
 // Normal spring-dashpot (clamped at zero) and tangential spring with Coulomb
@@ -272,13 +252,12 @@ __device__ __forceinline__ void drift(Body& b, double dt, const Geom& g)
         }
         b.x[a] = x;
     }
-    // cos(t) and sin(t) / |w| of half the angle t = |w| dt / 2: below 1/8 by
-    // their series in t^2 (truncated under 1e-19 of the value)
+    // cos(t) and sin(t) / |w| of half the angle t = |w| dt / 2
     const double z = (0.25 * dt * dt) * dot3(b.w, b.w);
     double dq[4], s;
-    if (z < 0x1p-6) {
-        dq[0] = 1.0 + z * (-1.0 / 2 + z * (1.0 / 24 + z * (-1.0 / 720 + z * (1.0 / 40320 - z * (1.0 / 3628800)))));
-        s = (0.5 * dt) * (1.0 + z * (-1.0 / 6 + z * (1.0 / 120 + z * (-1.0 / 5040 + z * (1.0 / 362880 - z * (1.0 / 39916800))))));
+    if (z < kSmallAngle2) {
+        dq[0] = cos_series(z);
+        s = (0.5 * dt) * sinc_series(z);
     } else {
         const double wn = sqrt(dot3(b.w, b.w));
         double sn;

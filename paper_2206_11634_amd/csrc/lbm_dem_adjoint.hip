@@ -32,8 +32,15 @@
 // the in-plane point of a wall contact likewise.  Branches (contact on or
 // off, the clamp of the normal force, the Coulomb limit) follow the values,
 // as in dem_step.
+//
+// Bound by one thread's chain of FP64 operations over the substeps.  A particle
+// on its own (the common cluster) runs in registers, both half kicks around a
+// substep's start in the body frame as in dem_step: 27 us a call of ten substeps
+// for two bodies apart, where members indexed in scratch memory, with the
+// library's divisions, roots and sine, took 76.
 #include <cmath>
 
+#include "lbm_fp64.h"
 #include "lbm_internal.h"
 
 namespace mdlbm {
@@ -43,7 +50,6 @@ constexpr int kHist = 8;   // active, xi[3], warm start[3], pad
 constexpr int NPIN = 24;   // particle inputs: x 0-2, theta 3-5, v 6-8, omega 9-11, F 12-14,
                            // T 15-17, carried contact force 18-20 and torque 21-23
 constexpr int NSEED = NPIN + 3 * kPairSlots + 3 * 6;
-constexpr int kMaxPairs = kAdjCluster * (kAdjCluster - 1) / 2;
 
 struct D {
     double v, d;
@@ -62,13 +68,13 @@ __device__ __forceinline__ D operator*(const D& a, const D& b)
 __device__ __forceinline__ D operator*(double s, const D& b) { return D(s * b.v, s * b.d); }
 __device__ __forceinline__ D operator/(const D& a, const D& b)
 {
-    const double ib = 1.0 / b.v, r = a.v * ib;
+    const double ib = fast_rcp(b.v), r = a.v * ib;
     return D(r, (a.d - r * b.d) * ib);
 }
 __device__ __forceinline__ D dsqrt(const D& a)
 {
-    const double r = sqrt(a.v);
-    return D(r, r > 0.0 ? 0.5 * a.d / r : 0.0);
+    const double y = a.v > 0.0 ? fast_rsqrt(a.v) : 0.0;
+    return D(a.v * y, 0.5 * a.d * y);
 }
 // f(a) with f(a.v) = fv and f'(a.v) = fp
 __device__ __forceinline__ D chain(const D& a, double fv, double fp) { return D(fv, fp * a.d); }
@@ -107,29 +113,6 @@ __device__ __forceinline__ void rot(const D q[4], D R[9])
     R[8] = one - 2.0 * (x * x + y * y);
 }
 
-// Half kick of the rotation: body-frame Euler equations with `iters`
-// fixed-point sweeps, as in the forward integrator.
-__device__ void spin_kick(const D q[4], D w[3], const D T[3], const double I[3], double h, int iters)
-{
-    D R[9];
-    rot(q, R);
-    D w0[3], Tb[3], wb[3];
-    for (int i = 0; i < 3; ++i) {
-        w0[i] = R[i] * w[0] + R[3 + i] * w[1] + R[6 + i] * w[2];
-        Tb[i] = R[i] * T[0] + R[3 + i] * T[1] + R[6 + i] * T[2];
-        wb[i] = w0[i];
-    }
-    for (int it = 0; it < iters; ++it) {
-        const D Iw[3] = {I[0] * wb[0], I[1] * wb[1], I[2] * wb[2]};
-        D cc[3];
-        cross3(wb, Iw, cc);
-        D nw[3];
-        for (int a = 0; a < 3; ++a) nw[a] = w0[a] + (h / I[a]) * (Tb[a] - cc[a]);
-        for (int a = 0; a < 3; ++a) wb[a] = nw[a];
-    }
-    for (int i = 0; i < 3; ++i) w[i] = R[3 * i] * wb[0] + R[3 * i + 1] * wb[1] + R[3 * i + 2] * wb[2];
-}
-
 // What the kernel reads of the particles: shapes and rigid-body constants.
 struct Shapes {
     const int32_t* off;
@@ -161,15 +144,9 @@ struct Consts {
     double rhof;
 };
 
-__device__ double body_reach(const Shapes& S, int p)
+__device__ __forceinline__ double body_reach(const Shapes& S, int p)
 {
-    double sk = 0.0, r = 0.0;
-    for (int i = S.off[p]; i < S.off[p + 1]; ++i) {
-        const double* b = S.body_pts + 3 * (int64_t)i;
-        r = fmax(r, sqrt(b[0] * b[0] + b[1] * b[1] + b[2] * b[2]));
-        sk += S.K[i];
-    }
-    return r + sqrt(sk);
+    return reach_of(S.body_pts, S.K, S.off[p], S.off[p + 1]);
 }
 
 // The broad-phase test of dem_step for pair (i, j) at the start of the call.
@@ -197,14 +174,15 @@ __device__ bool candidate(const Shapes& S, const DemTape& s, int i, int j, doubl
 struct Body {
     int gi;               // global index
     int a0, n;            // control points
-    D x[3], q[4], v[3], w[3], F[3], T[3], fc[6];
-    D R[9];
-    double m, mrel, I[3], rs, reach;
+    D x[3], q[4], v[3], w[3], F[3], T[3], fc[6];  // F with the relative gravity
+    D R[9], wb[3];    // rotation of q, angular velocity in the body frame
+    D kv[3], kw[3];   // what half a kick adds to v and, without Euler's terms, to wb
+    double hm, hI[3], kI[3], rs, reach;  // half step over the mass and the moments; Euler's terms
 };
 
 // M, grad M and the Hessian of body b (world points x + R b_i, shifted by
 // sh) at X, in dual numbers.
-__device__ void mb_d2(const Shapes& S, const Body& b, const double sh[3], const D X[3], D& M,
+__device__ __forceinline__ void mb_d2(const Shapes& S, const Body& b, const double sh[3], const D X[3], D& M,
                       D g[3], D H[9])
 {
     M = D(0.0);
@@ -231,7 +209,7 @@ __device__ void mb_d2(const Shapes& S, const Body& b, const double sh[3], const 
 }
 
 // The same on values only (the Newton iterations).
-__device__ void mb_d2v(const Shapes& S, const Body& b, const double sh[3], const double X[3],
+__device__ __forceinline__ void mb_d2v(const Shapes& S, const Body& b, const double sh[3], const double X[3],
                        double& M, double g[3], double H[9])
 {
     M = 0.0;
@@ -247,7 +225,7 @@ __device__ void mb_d2v(const Shapes& S, const Body& b, const double sh[3], const
             r[a] = X[a] - (wp + sh[a]);
         }
         const double r2 = (r[0] * r[0] + r[1] * r[1]) + r[2] * r[2];
-        const double i2 = 1.0 / r2, i4 = i2 * i2, i6 = i4 * i2;
+        const double i2 = fast_rcp(r2), i4 = i2 * i2, i6 = i4 * i2;
         M += K * i2;
         for (int a = 0; a < 3; ++a) {
             g[a] += -2.0 * K * r[a] * i4;
@@ -258,7 +236,7 @@ __device__ void mb_d2v(const Shapes& S, const Body& b, const double sh[3], const
 }
 
 // World control point u of body b (values).
-__device__ void world_pt(const Shapes& S, const Body& b, int u, double out[3])
+__device__ __forceinline__ void world_pt(const Shapes& S, const Body& b, int u, double out[3])
 {
     const double* bp = S.body_pts + 3 * (int64_t)(b.a0 + u);
     for (int a = 0; a < 3; ++a)
@@ -266,7 +244,7 @@ __device__ void world_pt(const Shapes& S, const Body& b, int u, double out[3])
 }
 
 template <class T>
-__device__ bool solve3(const T H[9], const T g[3], T dx[3])
+__device__ __forceinline__ bool solve3(const T H[9], const T g[3], T dx[3])
 {
     T c[9];
     c[0] = H[4] * H[8] - H[5] * H[7];
@@ -302,7 +280,7 @@ struct Rec {
 
 // Spring-dashpot normal force (clamped at zero) and the tangential spring
 // with the Coulomb limit, as dem_step evaluates them; updates the spring.
-__device__ void contact_force(const Consts& c, const D& delta, const D n[3], const D vrel[3],
+__device__ __forceinline__ void contact_force(const Consts& c, const D& delta, const D n[3], const D vrel[3],
                               double dt, Rec& h, D Fi[3])
 {
     const D vn = dot3(vrel, n);
@@ -327,17 +305,46 @@ __device__ void contact_force(const Consts& c, const D& delta, const D n[3], con
     }
 }
 
-__device__ void half_kick(Body& b, const Consts& c, double h, bool implicit)
+// As in the forward integrator: the kick of the contact sum at the pose, half a
+// kick (the rotational part by one explicit or four fixed-point sweeps in the
+// body frame), and the angular velocity between the frames.
+__device__ __forceinline__ void set_kick(Body& b)
 {
     D T[3];
     for (int a = 0; a < 3; ++a) {
-        b.v[a] = b.v[a] + (h / b.m) * (b.F[a] + D(b.mrel * c.g[a]) + b.fc[a]);
+        b.kv[a] = b.hm * (b.F[a] + b.fc[a]);
         T[a] = b.T[a] + b.fc[3 + a];
     }
-    spin_kick(b.q, b.w, T, b.I, h, implicit ? 4 : 1);
+    for (int a = 0; a < 3; ++a)
+        b.kw[a] = b.hI[a] * (b.R[a] * T[0] + b.R[3 + a] * T[1] + b.R[6 + a] * T[2]);
+}
+template <bool IMPLICIT>
+__device__ __forceinline__ void half_kick(Body& b)
+{
+    D w0[3];
+    for (int a = 0; a < 3; ++a) {
+        b.v[a] = b.v[a] + b.kv[a];
+        w0[a] = b.wb[a] + b.kw[a];
+    }
+#pragma unroll
+    for (int it = 0; it < (IMPLICIT ? 4 : 1); ++it) {
+        const D p0 = b.wb[1] * b.wb[2], p1 = b.wb[2] * b.wb[0], p2 = b.wb[0] * b.wb[1];
+        b.wb[0] = w0[0] - b.kI[0] * p0;
+        b.wb[1] = w0[1] - b.kI[1] * p1;
+        b.wb[2] = w0[2] - b.kI[2] * p2;
+    }
+}
+__device__ __forceinline__ void to_body(Body& b)
+{
+    for (int i = 0; i < 3; ++i) b.wb[i] = b.R[i] * b.w[0] + b.R[3 + i] * b.w[1] + b.R[6 + i] * b.w[2];
+}
+__device__ __forceinline__ void to_world(Body& b)
+{
+    for (int i = 0; i < 3; ++i)
+        b.w[i] = b.R[3 * i] * b.wb[0] + b.R[3 * i + 1] * b.wb[1] + b.R[3 * i + 2] * b.wb[2];
 }
 
-__device__ void drift_rotate(Body& b, double dt, const Geom& g)
+__device__ __forceinline__ void drift_rotate(Body& b, double dt, const Geom& g)
 {
     for (int a = 0; a < 3; ++a) {
         D x = b.x[a] + dt * b.v[a];
@@ -347,15 +354,15 @@ __device__ void drift_rotate(Body& b, double dt, const Geom& g)
         }
         b.x[a] = x;
     }
-    // dq = (cos(|w| dt / 2), sin(|w| dt / 2) w / |w|), smooth through w = 0
-    const D ww = b.w[0] * b.w[0] + b.w[1] * b.w[1] + b.w[2] * b.w[2];
+    // dq = (cos t, sin t w / |w|), t = |w| dt / 2
+    const D z = (0.25 * dt * dt) * dot3(b.w, b.w);
     D cs, sn;
-    if (sqrt(ww.v) * dt < 1e-4) {
-        const D z = (0.25 * dt * dt) * ww;
-        cs = D(1.0) - 0.5 * z + (1.0 / 24.0) * (z * z);
-        sn = (0.5 * dt) * (D(1.0) - (1.0 / 6.0) * z);
+    if (z.v < kSmallAngle2) {
+        const double S = sinc_series(z.v);
+        cs = chain(z, cos_series(z.v), -0.5 * S);
+        sn = (0.5 * dt) * chain(z, S, sinc_slope(z.v));
     } else {
-        const D wn = dsqrt(ww);
+        const D wn = dsqrt(dot3(b.w, b.w));
         const double ang = 0.5 * wn.v * dt;
         cs = chain(wn, cos(ang), -0.5 * dt * sin(ang));
         const D sa = chain(wn, sin(ang), 0.5 * dt * cos(ang));
@@ -364,20 +371,26 @@ __device__ void drift_rotate(Body& b, double dt, const Geom& g)
     const D dq[4] = {cs, sn * b.w[0], sn * b.w[1], sn * b.w[2]};
     D qn[4];
     qmul(dq, b.q, qn);
-    const D nrm = dsqrt(qn[0] * qn[0] + qn[1] * qn[1] + qn[2] * qn[2] + qn[3] * qn[3]);
-    for (int a = 0; a < 4; ++a) b.q[a] = qn[a] / nrm;
+    const D q2 = qn[0] * qn[0] + qn[1] * qn[1] + qn[2] * qn[2] + qn[3] * qn[3];
+    const double y = fast_rsqrt(q2.v);
+    const D in(y, -0.5 * y * y * y * q2.d);
+    for (int a = 0; a < 4; ++a) b.q[a] = qn[a] * in;
     rot(b.q, b.R);
+    to_body(b);
 }
 
-// Metaball-wall contact of body b with wall (ax, side), as dem_step.
-__device__ void wall_item(const Shapes& S, Body& b, int ax, int side, Rec& h, const Consts& c,
-                          double dt, const Geom& g)
+// Whether body b can touch wall (ax, side), as dem_step.
+__device__ __forceinline__ bool near_wall(const Body& b, int ax, int side, const Geom& g)
 {
     const double plane = side ? g.n[ax] - 0.5 : -0.5, sgn = side ? -1.0 : 1.0;
-    if (sgn * (b.x[ax].v - plane) > b.reach + b.rs) {
-        h.clear();
-        return;
-    }
+    return !(sgn * (b.x[ax].v - plane) > b.reach + b.rs);
+}
+
+// Metaball-wall contact of body b with wall (ax, side) near it, as dem_step.
+__device__ __forceinline__ void wall_item(const Shapes& S, Body& b, int ax, int side, Rec& h,
+                                          const Consts& c, double dt, const Geom& g)
+{
+    const double plane = side ? g.n[ax] - 0.5 : -0.5, sgn = side ? -1.0 : 1.0;
     const int t1 = (ax + 1) % 3, t2 = (ax + 2) % 3;
     const double z3[3] = {0.0, 0.0, 0.0};
     double x[3];
@@ -407,7 +420,7 @@ __device__ void wall_item(const Shapes& S, Body& b, int ax, int side, Rec& h, co
         const double d2 = -(-h12 * gr[t1] + h11 * gr[t2]) / det;
         x[t1] += d1;
         x[t2] += d2;
-        if (sqrt(d1 * d1 + d2 * d2) < c.ntol) {
+        if (d1 * d1 + d2 * d2 < c.ntol * c.ntol) {
             conv = true;
             break;
         }
@@ -504,7 +517,7 @@ __device__ void pair_item(const Shapes& S, Body& A, Body& B, Rec& h, const Const
         for (int a = 0; a < 9; ++a) H[a] = HA[a] + HB[a];
         if (!solve3(H, gg, dx)) break;
         for (int a = 0; a < 3; ++a) x[a] += dx[a];
-        if (sqrt(dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2]) < c.ntol) {
+        if (dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2] < c.ntol * c.ntol) {
             conv = true;
             break;
         }
@@ -583,6 +596,188 @@ __device__ int find_slot(const int32_t* key, int i, int j)
     return -1;
 }
 
+// A call of one thread's input.
+struct Call {
+    const DemTape& st;
+    const int32_t* key_next;
+    const Consts& c;
+    const Geom& g;
+    int n_sub;
+    double dt;
+    const double *sig1, *sc1;
+    int p, seed, pslot, pwall, pa;  // the input
+};
+
+// The input's column of the Jacobian, times the adjoint of the state after the
+// call, for a cluster of up to N particles.  A particle on its own (N = 1) stays
+// in registers; larger clusters index their members at run time and so lie in
+// scratch memory.
+template <int N>
+__device__ __forceinline__ double column(const Shapes& S, const Call& call, const int (&mem)[kAdjCluster],
+                                         int nm)
+{
+    const DemTape& st = call.st;
+    const int32_t* key_next = call.key_next;
+    const Consts& c = call.c;
+    const Geom& g = call.g;
+    const int n_sub = call.n_sub;
+    const double dt = call.dt, Tcall = (double)n_sub * dt;
+    const double *sig1 = call.sig1, *sc1 = call.sc1;
+    const int p = call.p, seed = call.seed, pslot = call.pslot, pwall = call.pwall, pa = call.pa;
+    if constexpr (N == 1) nm = 1;
+    Body B[N];
+    for (int m = 0; m < nm; ++m) {
+        Body& b = B[m];
+        const int gi = mem[m];
+        const bool me = gi == p;
+        b.gi = gi;
+        b.a0 = S.off[gi];
+        b.n = S.off[gi + 1] - b.a0;
+        const double m_ = S.mass[gi], mrel = m_ - c.rhof * S.volume[gi], hdt = 0.5 * dt;
+        const double I[3] = {S.inertia[3 * gi], S.inertia[3 * gi + 1], S.inertia[3 * gi + 2]};
+        b.hm = hdt / m_;
+        for (int a = 0; a < 3; ++a) b.hI[a] = hdt / I[a];
+        for (int a = 0; a < 3; ++a) b.kI[a] = b.hI[a] * (I[(a + 2) % 3] - I[(a + 1) % 3]);
+        b.rs = S.rs[gi];
+        b.reach = body_reach(S, gi);
+        for (int a = 0; a < 3; ++a) {
+            b.x[a] = var(st.pos[3 * gi + a], me && seed == a);
+            b.v[a] = var(st.vel[3 * gi + a], me && seed == 6 + a);
+            b.w[a] = var(st.om[3 * gi + a], me && seed == 9 + a);
+            b.F[a] = var(st.FT[6 * gi + a] + mrel * c.g[a], me && seed == 12 + a);
+            b.T[a] = var(st.FT[6 * gi + 3 + a], me && seed == 15 + a);
+        }
+        for (int k = 0; k < 6; ++k) b.fc[k] = var(st.fc[6 * gi + k], me && seed == 18 + k);
+        // q(theta) = exp(theta / 2) q: dq/dtheta_a = (0, e_a)/2 (x) q
+        const double* qq = st.quat + 4 * gi;
+        for (int k = 0; k < 4; ++k) b.q[k] = D(qq[k]);
+        if (me && seed >= 3 && seed < 6) {
+            const int a = seed - 3;
+            double u[4] = {0.0, 0.0, 0.0, 0.0};
+            u[1 + a] = 1.0;
+            const double r[4] = {u[0] * qq[0] - u[1] * qq[1] - u[2] * qq[2] - u[3] * qq[3],
+                                 u[0] * qq[1] + u[1] * qq[0] + u[2] * qq[3] - u[3] * qq[2],
+                                 u[0] * qq[2] - u[1] * qq[3] + u[2] * qq[0] + u[3] * qq[1],
+                                 u[0] * qq[3] + u[1] * qq[2] - u[2] * qq[1] + u[3] * qq[0]};
+            for (int k = 0; k < 4; ++k) b.q[k].d = 0.5 * r[k];
+        }
+        rot(b.q, b.R);
+        to_body(b);
+        set_kick(b);
+    }
+    // contact records: the candidate pairs of the cluster (as the call keeps
+    // or claims them) and the walls of every member
+    constexpr int kPairs = N > 1 ? N * (N - 1) / 2 : 1;
+    int pi_[kPairs], pj_[kPairs];
+    Rec pr[kPairs];
+    int npair = 0;
+    if constexpr (N > 1) {
+        for (int u = 0; u < nm; ++u)
+            for (int w = u + 1; w < nm; ++w) {
+                const int gi = mem[u], gj = mem[w];
+                if (!candidate(S, st, gi, gj, Tcall, g)) continue;
+                Rec& h = pr[npair];
+                h.clear();
+                const int s = find_slot(st.key, gi, gj);
+                if (s >= 0) {
+                    const double* src = st.hist + ((int64_t)gi * kPairSlots + s) * kHist;
+                    h.active = src[0];
+                    for (int a = 0; a < 3; ++a) {
+                        h.xi[a] = var(src[1 + a], gi == p && s == pslot && a == pa);
+                        h.warm[a] = src[4 + a];
+                    }
+                }
+                pi_[npair] = u;
+                pj_[npair] = w;
+                ++npair;
+            }
+    }
+    // the wall records: of a particle on its own in LDS, where they take no
+    // registers (they are used near a wall only)
+    Rec own[N > 1 ? N : 1][6];
+    __shared__ Rec shared[N > 1 ? 1 : 6][64];
+    auto wr = [&](int m, int k) -> Rec& {
+        if constexpr (N == 1)
+            return shared[k][threadIdx.x];
+        else
+            return own[m][k];
+    };
+    for (int m = 0; m < nm; ++m)
+        for (int k = 0; k < 6; ++k) {
+            Rec& h = wr(m, k);
+            const double* src = st.hist_w + ((int64_t)mem[m] * 6 + k) * kHist;
+            h.active = src[0];
+            for (int a = 0; a < 3; ++a) {
+                h.xi[a] = var(src[1 + a], mem[m] == p && k == pwall && a == pa);
+                h.warm[a] = src[4 + a];
+            }
+        }
+    uint64_t live = ~0ull;  // records that may not be clear
+
+    // the call's substeps
+    for (int s = 0; s < n_sub; ++s) {
+        for (int m = 0; m < nm; ++m) {
+            half_kick<false>(B[m]);
+            to_world(B[m]);
+            for (int k = 0; k < 6; ++k) B[m].fc[k] = D(0.0);
+            drift_rotate(B[m], dt, g);
+        }
+        for (int m = 0; m < nm; ++m)
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                if (g.per[ax]) continue;
+                // one copy of the code for both sides
+#pragma unroll 1
+                for (int side = 0; side < 2; ++side) {
+                    const uint64_t bit = 1ull << (6 * m + 2 * ax + side);
+                    if (near_wall(B[m], ax, side, g)) {
+                        wall_item(S, B[m], ax, side, wr(m, 2 * ax + side), c, dt, g);
+                        live |= bit;
+                    } else if (live & bit) {
+                        wr(m, 2 * ax + side).clear();
+                        live &= ~bit;
+                    }
+                }
+            }
+        if constexpr (N > 1)
+            for (int k = 0; k < npair; ++k) pair_item(S, B[pi_[k]], B[pj_[k]], pr[k], c, dt, g);
+        for (int m = 0; m < nm; ++m) {
+            set_kick(B[m]);
+            half_kick<true>(B[m]);
+        }
+    }
+    for (int m = 0; m < nm; ++m) to_world(B[m]);
+
+    // this input's column of the Jacobian times the adjoint of the output
+    double acc = 0.0;
+    for (int m = 0; m < nm; ++m) {
+        const Body& b = B[m];
+        const double* s1 = sig1 + 12 * (int64_t)b.gi;
+        for (int a = 0; a < 3; ++a)
+            acc += b.x[a].d * s1[a] + b.v[a].d * s1[6 + a] + b.w[a].d * s1[9 + a];
+        {
+            // rotation tangent 2 vec(dq (x) conj(q))
+            const double dw = b.q[0].d, dx = b.q[1].d, dy = b.q[2].d, dz = b.q[3].d;
+            const double cw = b.q[0].v, cx_ = -b.q[1].v, cy_ = -b.q[2].v, cz_ = -b.q[3].v;
+            acc += 2.0 * (dw * cx_ + dx * cw + dy * cz_ - dz * cy_) * s1[3];
+            acc += 2.0 * (dw * cy_ - dx * cz_ + dy * cw + dz * cx_) * s1[4];
+            acc += 2.0 * (dw * cz_ + dx * cy_ - dy * cx_ + dz * cw) * s1[5];
+        }
+        const double* c1 = sc1 + (int64_t)kAdjContact * b.gi;
+        for (int k = 0; k < 6; ++k) acc += b.fc[k].d * c1[k];
+        for (int k = 0; k < 6; ++k)
+            for (int a = 0; a < 3; ++a) acc += wr(m, k).xi[a].d * c1[6 + 3 * kPairSlots + 3 * k + a];
+    }
+    for (int k = 0; k < npair; ++k) {
+        const int gi = mem[pi_[k]], gj = mem[pj_[k]];
+        const int s = find_slot(key_next, gi, gj);
+        if (s < 0) continue;
+        const double* c1 = sc1 + (int64_t)kAdjContact * gi + 6 + 3 * s;
+        for (int a = 0; a < 3; ++a) acc += pr[k].xi[a].d * c1[a];
+    }
+    return acc;
+}
+
 // One thread per (particle p, input).  sig: [np][12] state adjoints (x,
 // theta, v, omega); sc: [np][kAdjContact] contact-state adjoints (carried
 // force and torque, then the springs of the kPairSlots pair records and of
@@ -636,122 +831,8 @@ __global__ __launch_bounds__(64) void k_dem_adjoint(int np, Shapes S, DemTape st
             mem[b - 1] = tmp;
         }
 
-    Body B[kAdjCluster];
-    for (int m = 0; m < nm; ++m) {
-        Body& b = B[m];
-        const int gi = mem[m];
-        const bool me = gi == p;
-        b.gi = gi;
-        b.a0 = S.off[gi];
-        b.n = S.off[gi + 1] - b.a0;
-        b.m = S.mass[gi];
-        b.mrel = b.m - c.rhof * S.volume[gi];
-        for (int a = 0; a < 3; ++a) b.I[a] = S.inertia[3 * gi + a];
-        b.rs = S.rs[gi];
-        b.reach = body_reach(S, gi);
-        for (int a = 0; a < 3; ++a) {
-            b.x[a] = var(st.pos[3 * gi + a], me && seed == a);
-            b.v[a] = var(st.vel[3 * gi + a], me && seed == 6 + a);
-            b.w[a] = var(st.om[3 * gi + a], me && seed == 9 + a);
-            b.F[a] = var(st.FT[6 * gi + a], me && seed == 12 + a);
-            b.T[a] = var(st.FT[6 * gi + 3 + a], me && seed == 15 + a);
-        }
-        for (int k = 0; k < 6; ++k) b.fc[k] = var(st.fc[6 * gi + k], me && seed == 18 + k);
-        // q(theta) = exp(theta / 2) q: dq/dtheta_a = (0, e_a)/2 (x) q
-        const double* qq = st.quat + 4 * gi;
-        for (int k = 0; k < 4; ++k) b.q[k] = D(qq[k]);
-        if (me && seed >= 3 && seed < 6) {
-            const int a = seed - 3;
-            double u[4] = {0.0, 0.0, 0.0, 0.0};
-            u[1 + a] = 1.0;
-            const double r[4] = {u[0] * qq[0] - u[1] * qq[1] - u[2] * qq[2] - u[3] * qq[3],
-                                 u[0] * qq[1] + u[1] * qq[0] + u[2] * qq[3] - u[3] * qq[2],
-                                 u[0] * qq[2] - u[1] * qq[3] + u[2] * qq[0] + u[3] * qq[1],
-                                 u[0] * qq[3] + u[1] * qq[2] - u[2] * qq[1] + u[3] * qq[0]};
-            for (int k = 0; k < 4; ++k) b.q[k].d = 0.5 * r[k];
-        }
-        rot(b.q, B[m].R);
-    }
-    // contact records: the candidate pairs of the cluster (as the call keeps
-    // or claims them) and the walls of every member
-    int pi_[kMaxPairs], pj_[kMaxPairs];
-    Rec pr[kMaxPairs];
-    int npair = 0;
-    for (int u = 0; u < nm; ++u)
-        for (int w = u + 1; w < nm; ++w) {
-            const int gi = mem[u], gj = mem[w];
-            if (!candidate(S, st, gi, gj, Tcall, g)) continue;
-            Rec& h = pr[npair];
-            h.clear();
-            const int s = find_slot(st.key, gi, gj);
-            if (s >= 0) {
-                const double* src = st.hist + ((int64_t)gi * kPairSlots + s) * kHist;
-                h.active = src[0];
-                for (int a = 0; a < 3; ++a) {
-                    h.xi[a] = var(src[1 + a], gi == p && s == pslot && a == pa);
-                    h.warm[a] = src[4 + a];
-                }
-            }
-            pi_[npair] = u;
-            pj_[npair] = w;
-            ++npair;
-        }
-    Rec wr[kAdjCluster][6];
-    for (int m = 0; m < nm; ++m)
-        for (int k = 0; k < 6; ++k) {
-            Rec& h = wr[m][k];
-            const double* src = st.hist_w + ((int64_t)mem[m] * 6 + k) * kHist;
-            h.active = src[0];
-            for (int a = 0; a < 3; ++a) {
-                h.xi[a] = var(src[1 + a], mem[m] == p && k == pwall && a == pa);
-                h.warm[a] = src[4 + a];
-            }
-        }
-
-    // the call's substeps
-    for (int s = 0; s < n_sub; ++s) {
-        for (int m = 0; m < nm; ++m) {
-            half_kick(B[m], c, 0.5 * dt, false);
-            for (int k = 0; k < 6; ++k) B[m].fc[k] = D(0.0);
-            drift_rotate(B[m], dt, g);
-        }
-        for (int m = 0; m < nm; ++m)
-            for (int ax = 0; ax < 3; ++ax) {
-                if (g.per[ax]) continue;
-                for (int side = 0; side < 2; ++side)
-                    wall_item(S, B[m], ax, side, wr[m][2 * ax + side], c, dt, g);
-            }
-        for (int k = 0; k < npair; ++k) pair_item(S, B[pi_[k]], B[pj_[k]], pr[k], c, dt, g);
-        for (int m = 0; m < nm; ++m) half_kick(B[m], c, 0.5 * dt, true);
-    }
-
-    // this input's column of the Jacobian times the adjoint of the output
-    double acc = 0.0;
-    for (int m = 0; m < nm; ++m) {
-        const Body& b = B[m];
-        const double* s1 = sig1 + 12 * (int64_t)b.gi;
-        for (int a = 0; a < 3; ++a)
-            acc += b.x[a].d * s1[a] + b.v[a].d * s1[6 + a] + b.w[a].d * s1[9 + a];
-        {
-            // rotation tangent 2 vec(dq (x) conj(q))
-            const double dw = b.q[0].d, dx = b.q[1].d, dy = b.q[2].d, dz = b.q[3].d;
-            const double cw = b.q[0].v, cx_ = -b.q[1].v, cy_ = -b.q[2].v, cz_ = -b.q[3].v;
-            acc += 2.0 * (dw * cx_ + dx * cw + dy * cz_ - dz * cy_) * s1[3];
-            acc += 2.0 * (dw * cy_ - dx * cz_ + dy * cw + dz * cx_) * s1[4];
-            acc += 2.0 * (dw * cz_ + dx * cy_ - dy * cx_ + dz * cw) * s1[5];
-        }
-        const double* c1 = sc1 + (int64_t)kAdjContact * b.gi;
-        for (int k = 0; k < 6; ++k) acc += b.fc[k].d * c1[k];
-        for (int k = 0; k < 6; ++k)
-            for (int a = 0; a < 3; ++a) acc += wr[m][k].xi[a].d * c1[6 + 3 * kPairSlots + 3 * k + a];
-    }
-    for (int k = 0; k < npair; ++k) {
-        const int gi = mem[pi_[k]], gj = mem[pj_[k]];
-        const int s = find_slot(key_next, gi, gj);
-        if (s < 0) continue;
-        const double* c1 = sc1 + (int64_t)kAdjContact * gi + 6 + 3 * s;
-        for (int a = 0; a < 3; ++a) acc += pr[k].xi[a].d * c1[a];
-    }
+    const Call call{st, key_next, c, g, n_sub, dt, sig1, sc1, p, seed, pslot, pwall, pa};
+    const double acc = nm == 1 ? column<1>(S, call, mem, nm) : column<kAdjCluster>(S, call, mem, nm);
     if (seed < 12)
         sig0[12 * (int64_t)p + seed] = acc;
     else if (seed < 18)

@@ -1,0 +1,64 @@
+// FP64 device arithmetic shared by the DEM kernels and their adjoint.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace mdlbm {
+
+// 1/x and 1/sqrt(x): the hardware's estimate and two Newton steps (an ulp or
+// so; a third of the instructions of a division).  Not a number at 0.
+__device__ __forceinline__ double fast_rcp(double x)
+{
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ double fast_rsqrt(double x)
+{
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(fma(-x * y, y, 1.0), 0.5 * y, y);
+    return fma(fma(-x * y, y, 1.0), 0.5 * y, y);
+}
+
+// cos t, sin t / t and the derivative of the latter by z = t^2, from their
+// series, for z < 2^-6 (truncated under 1e-19).  The derivative of cos t by z
+// is -(sin t / t) / 2.
+constexpr double kSmallAngle2 = 0x1p-6;
+__device__ __forceinline__ double cos_series(double z)
+{
+    return 1.0 + z * (-1.0 / 2 + z * (1.0 / 24 + z * (-1.0 / 720 + z * (1.0 / 40320 - z * (1.0 / 3628800)))));
+}
+__device__ __forceinline__ double sinc_series(double z)
+{
+    return 1.0 + z * (-1.0 / 6 + z * (1.0 / 120 + z * (-1.0 / 5040 + z * (1.0 / 362880 - z * (1.0 / 39916800)))));
+}
+__device__ __forceinline__ double sinc_slope(double z)
+{
+    return -1.0 / 6 + z * (2.0 / 120 + z * (-3.0 / 5040 + z * (4.0 / 362880 - z * (5.0 / 39916800))));
+}
+
+// How far the body with control points i0 .. i1 - 1 may reach from its centre:
+// the largest distance of a point plus sqrt(sum K).  Four points' loads at once.
+__device__ __forceinline__ double reach_of(const double* __restrict__ body, const double* __restrict__ K,
+                                           int i0, int i1)
+{
+    double sk = 0.0, r2 = 0.0;
+    for (int i = i0; i < i1; i += 4) {
+        double b[4][3], k[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t at = i + j < i1 ? i + j : i1 - 1;
+            for (int a = 0; a < 3; ++a) b[j][a] = body[3 * at + a];
+            k[j] = K[at];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (i + j < i1) {
+                r2 = fmax(r2, b[j][0] * b[j][0] + b[j][1] * b[j][1] + b[j][2] * b[j][2]);
+                sk += k[j];
+            }
+    }
+    return sqrt(r2) + sqrt(sk);
+}
+
+}  // namespace mdlbm
