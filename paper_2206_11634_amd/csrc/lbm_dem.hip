@@ -21,8 +21,8 @@
 // Measured, microseconds a call of ten substeps (in parentheses a thread per
 // pair, per pair test and per particle's cells, 23 launches whatever the count):
 //   1 sphere 17 (83), 2 flat metaballs 35 (153), 64 packed spheres 72 (173),
-//   1000 metaballs of the 512^3 run 238 (535), packed spheres 1000: 134 (226),
-//   2548: 144 (420), 8000: 167 (462), 27 000: 316 (745).
+//   1000 metaballs of the 512^3 run 234 (535), packed spheres 1000: 130 (226),
+//   2548: 136 (420), 8000: 156 (462), 27 000: 302 (745).
 // In one workgroup with the points and records in global memory, a matrix a
 // half kick and the library's division, square root and sincos the first three
 // took 32, 60 and 98.
@@ -328,9 +328,11 @@ __device__ __forceinline__ void clear_record(double* h)
 // of control points, the contact test and the force.  The G lanes of a group
 // share a pair: each sums every G-th control point of the two bodies (kept in
 // registers up to 4 a lane), and all follow the same branches on the same bits.
-template <int G>
+// A contact's force on i and the torques of it about i and, the other way, j go
+// to emit(F, ti, tj) on the group's first lane.
+template <int G, class Emit>
 __device__ __forceinline__ void pair_item(const StateG& S, double* h, const DemP& c, double dt,
-                                          const Geom& g, int i, int j, int l)
+                                          const Geom& g, int i, int j, int l, Emit&& emit)
 {
     double xi[3], xj[3], sh[3], dv[3];
     for (int a = 0; a < 3; ++a) {
@@ -501,20 +503,15 @@ __device__ __forceinline__ void pair_item(const StateG& S, double* h, const DemP
         ra[a] = xcp[a] - xi[a];
         rb[a] = xcp[a] - (xj[a] + sh[a]);
     }
-    double ca[3], cb[3], vrel[3], Fi[3], tq[3], spring[3] = {h[1], h[2], h[3]};
+    double ca[3], cb[3], vrel[3], Fi[3], ti[3], tj[3], spring[3] = {h[1], h[2], h[3]};
     cross3(S.omega + 3 * i, ra, ca);
     cross3(S.omega + 3 * j, rb, cb);
     for (int a = 0; a < 3; ++a) vrel[a] = (S.vel[3 * i + a] + ca[a]) - (S.vel[3 * j + a] + cb[a]);
     contact_force(c, delta, n, vrel, dt, spring, Fi);
-    for (int a = 0; a < 3; ++a) {
-        h[1 + a] = spring[a];
-        atomicAdd(S.fc + 6 * i + a, Fi[a]);
-        atomicAdd(S.fc + 6 * j + a, -Fi[a]);
-    }
-    cross3(ra, Fi, tq);
-    for (int a = 0; a < 3; ++a) atomicAdd(S.fc + 6 * i + 3 + a, tq[a]);
-    cross3(rb, Fi, tq);
-    for (int a = 0; a < 3; ++a) atomicAdd(S.fc + 6 * j + 3 + a, -tq[a]);
+    for (int a = 0; a < 3; ++a) h[1 + a] = spring[a];
+    cross3(ra, Fi, ti);
+    cross3(rb, Fi, tj);
+    emit(Fi, ti, tj);
 }
 
 // Whether particle i can touch wall (ax, side).
@@ -704,13 +701,14 @@ __device__ __forceinline__ Around around(int c, int nc, int per)
 // wave, took 90 us).  With GRID the partners are those of the cells around i's
 // (every accepted pair lies within H, and cells are at least H wide), else all.
 // A wave per particle keeps the walk short and needs no atomic on a record.
-__device__ __forceinline__ int grid_cell(const PartDev& P, int p, const Geom& g,
-                                         const int32_t* gdim, const double* gsize, int c3[3])
+__device__ __forceinline__ int grid_cell(const double pos[3], const Geom& g, const int32_t* gdim,
+                                         const double* gsize, int c3[3])
 {
     for (int a = 0; a < 3; ++a) {
-        double x = P.pos[3 * p + a];
-        if (g.per[a]) x -= (double)g.n[a] * floor(x / (double)g.n[a]);  // into [0, n]
-        int k = (int)floor(x / gsize[a]);
+        double x = pos[a];
+        if (g.per[a] && !(x >= 0.0 && x <= (double)g.n[a]))
+            x -= (double)g.n[a] * floor(x / (double)g.n[a]);  // into [0, n]
+        const int k = (int)floor(x * gsize[a]);
         c3[a] = min(max(k, 0), gdim[a] - 1);
     }
     return c3[0] + gdim[0] * (c3[1] + gdim[1] * c3[2]);
@@ -741,7 +739,7 @@ __global__ __launch_bounds__(1024) void k_pairs(PartDev P, double* hist, int32_t
     if constexpr (GRID) {
         // a lane per cell around i's; their particles flattened over the wave
         int c3[3];
-        grid_cell(P, i, g, gdim, gsize, c3);
+        grid_cell(xi, g, gdim, gsize, c3);
         const Around A0 = around(c3[0], gdim[0], g.per[0]), A1 = around(c3[1], gdim[1], g.per[1]),
                      A2 = around(c3[2], gdim[2], g.per[2]);
         uint32_t first = 0, cnt = 0;
@@ -791,19 +789,29 @@ __global__ __launch_bounds__(1024) void k_pairs(PartDev P, double* hist, int32_t
             ((uint64_t)lane << 32) | ((uint64_t)i << 16) | (uint64_t)(s.key - 1);
 }
 
-// One workgroup: the cell width from the particles, the grid's shape, and
-// the counts cleared.
-__global__ __launch_bounds__(1024) void k_grid_setup(PartDev P, const double* rch, double T,
-                                                     Geom g, int32_t* gdim,
-                                                     double* gsize, uint32_t* gcount, int64_t gcap)
+// The cell width and the grid's shape from the particles, by one workgroup of
+// 1024; the number of cells on every thread.
+__device__ __forceinline__ int grid_shape(const PartDev& P, const double* rch, double T, const Geom& g,
+                                          int32_t* gdim, double* gsize, int64_t gcap)
 {
     __shared__ double red[2][16];
     __shared__ int ncell;
     double h = 0.0, v = 0.0;
-    for (int p = (int)threadIdx.x; p < P.n; p += (int)blockDim.x) {
-        h = fmax(h, rch[p] + P.rs[p]);
-        const double* vp = P.vel + 3 * p;
-        v = fmax(v, sqrt(dot3(vp, vp)));
+    // (four particles' loads at once; the last particle again beyond the end)
+    for (int p0 = (int)threadIdx.x; p0 < P.n; p0 += 4 * (int)blockDim.x) {
+        double r[4], s[4], vp[4][3];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int p = min(p0 + k * (int)blockDim.x, P.n - 1);
+            r[k] = rch[p];
+            s[k] = P.rs[p];
+            for (int a = 0; a < 3; ++a) vp[k][a] = P.vel[3 * p + a];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            h = fmax(h, r[k] + s[k]);
+            v = fmax(v, dot3(vp[k], vp[k]));
+        }
     }
     for (int m = 32; m >= 1; m >>= 1) {
         h = fmax(h, __shfl_xor(h, m, 64));
@@ -822,7 +830,7 @@ __global__ __launch_bounds__(1024) void k_grid_setup(PartDev P, const double* rc
             vm = fmax(vm, red[1][w]);
         }
         // the largest accepted distance, with a margin for rounding
-        double H = (2.0 * hm + 2.0 * vm * T + 0.5) * (1.0 + 1e-9) + 1e-9;
+        double H = (2.0 * hm + 2.0 * sqrt(vm) * T + 0.5) * (1.0 + 1e-9) + 1e-9;
         int nc[3];
         int64_t total = 1;
         for (int it = 0; it < 64; ++it) {
@@ -836,13 +844,86 @@ __global__ __launch_bounds__(1024) void k_grid_setup(PartDev P, const double* rc
         }
         for (int a = 0; a < 3; ++a) {
             gdim[a] = nc[a];
-            gsize[a] = (double)g.n[a] / (double)nc[a];
+            gsize[a] = (double)nc[a] / (double)g.n[a];
         }
         gsize[3] = H;
         gdim[3] = (int32_t)total;
         ncell = (int)total;
     }
     __syncthreads();
+    return ncell;
+}
+
+// The whole grid by one workgroup, up to kGridBlock particles: shape, counts and
+// starts in LDS, and the particles by cell (15 us at 8000; a launch each for
+// the shape, the counts, the starts and the scatter, as beyond, 21 and three
+// gaps).
+constexpr int kGridBlock = 16384, kGridBlockCells = 8192;
+
+__global__ __launch_bounds__(1024) void k_grid_block(PartDev P, const double* rch, double T, Geom g,
+                                                     int32_t* gdim, double* gsize, uint32_t* gstart,
+                                                     uint32_t* gitem, int64_t gcap)
+{
+    constexpr int kEach = kGridBlock / 1024, kCells = kGridBlockCells / 1024;
+    __shared__ uint32_t count[kGridBlockCells];
+    __shared__ uint32_t wsum[16];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
+#pragma unroll
+    for (int k = 0; k < kCells; ++k) count[tid + 1024 * k] = 0u;
+    const int C = grid_shape(P, rch, T, g, gdim, gsize, min(gcap, (int64_t)kGridBlockCells));
+    int cell[kEach];
+    uint32_t rank[kEach];
+    const int32_t nc[3] = {gdim[0], gdim[1], gdim[2]};
+    const double per_node[3] = {gsize[0], gsize[1], gsize[2]};
+#pragma unroll
+    for (int k0 = 0; k0 < kEach; k0 += 4) {
+        if (1024 * k0 >= P.n) continue;  // uniform
+        double x[4][3];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            for (int a = 0; a < 3; ++a) x[k][a] = P.pos[3 * min(tid + 1024 * (k0 + k), P.n - 1) + a];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            int c3[3];
+            cell[k0 + k] = grid_cell(x[k], g, nc, per_node, c3);
+            if (tid + 1024 * (k0 + k) < P.n) rank[k0 + k] = atomicAdd(count + cell[k0 + k], 1u);
+        }
+    }
+    __syncthreads();
+    // exclusive starts: each thread's kCells cells, then the wave and the block
+    uint32_t own[kCells], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kCells; ++k) {
+        own[k] = sum;
+        sum += count[kCells * tid + k];
+    }
+    uint32_t incl = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
+    }
+    if (lane == 63) wsum[wv] = incl;
+    __syncthreads();
+    uint32_t before = incl - sum;
+    for (int w = 0; w < wv; ++w) before += wsum[w];
+#pragma unroll
+    for (int k = 0; k < kCells; ++k) count[kCells * tid + k] = before + own[k];
+    __syncthreads();
+    for (int i = tid; i < C; i += 1024) gstart[i] = count[i];
+    if (tid == 0) gstart[C] = (uint32_t)P.n;
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+        const int p = tid + 1024 * k;
+        if (p < P.n) gitem[count[cell[k]] + rank[k]] = (uint32_t)p;
+    }
+}
+
+// One workgroup: the grid's shape, and the counts cleared.
+__global__ __launch_bounds__(1024) void k_grid_setup(PartDev P, const double* rch, double T,
+                                                     Geom g, int32_t* gdim,
+                                                     double* gsize, uint32_t* gcount, int64_t gcap)
+{
+    const int ncell = grid_shape(P, rch, T, g, gdim, gsize, gcap);
     for (int i = (int)threadIdx.x; i <= ncell; i += (int)blockDim.x) gcount[i] = 0u;
 }
 
@@ -852,7 +933,7 @@ __global__ __launch_bounds__(256) void k_grid_count(PartDev P, Geom g, const int
     const int p = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (p >= P.n) return;
     int c3[3];
-    atomicAdd(gcount + grid_cell(P, p, g, gdim, gsize, c3), 1u);
+    atomicAdd(gcount + grid_cell(P.pos + 3 * p, g, gdim, gsize, c3), 1u);
 }
 
 // One workgroup: exclusive starts of the cells in place (gcount[C] = n),
@@ -897,7 +978,7 @@ __global__ __launch_bounds__(256) void k_grid_scatter(PartDev P, Geom g, const i
     const int p = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (p >= P.n) return;
     int c3[3];
-    const uint32_t slot = atomicAdd(gcursor + grid_cell(P, p, g, gdim, gsize, c3), 1u);
+    const uint32_t slot = atomicAdd(gcursor + grid_cell(P.pos + 3 * p, g, gdim, gsize, c3), 1u);
     gitem[slot] = (uint32_t)p;
 }
 
@@ -929,13 +1010,56 @@ __global__ __launch_bounds__(256) void k_contacts(PartDev P, double* hist, doubl
             clear_record(h);
         return;
     }
+    // the wave's contacts, gathered so that consecutive lanes add the twelve
+    // numbers of one: the sums of a particle lie in one line, and six lanes'
+    // additions to it are one request (a lane that adds its own contact's
+    // numbers one after the other makes twelve: 8000 packed spheres 15.2 us a
+    // substep, 8.0 of them without any addition)
+    constexpr int kPairs = 64 / G;
+    __shared__ double add[4][12 * kPairs];
+    __shared__ int who[4][2 * kPairs];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double* wa = add[wave];
+    int* ww = who[wave];
     const uint32_t n = *count;
     const uint32_t stride = (gridDim.x - wall_blocks) * (256u / G);
-    for (uint32_t t = (blockIdx.x - wall_blocks) * (256u / G) + threadIdx.x / G; t < n; t += stride) {
-        const uint64_t e = list[t];
-        const int i = (int)((e >> 16) & 0xffffu);
-        pair_item<G>(S, hist + ((int64_t)i * kPairSlots + (int)(e >> 32)) * kHist, c, dt, g, i,
-                     (int)(e & 0xffffu), (int)(threadIdx.x % G));
+    for (uint32_t t0 = (blockIdx.x - wall_blocks) * (256u / G) + (uint32_t)(wave * kPairs); t0 < n;
+         t0 += stride) {  // uniform over the wave
+        const uint32_t t = t0 + (uint32_t)(lane / G);
+        int i = 0, j = 0;
+        double v[12];
+        bool on = false;
+        if (t < n) {
+            const uint64_t e = list[t];
+            i = (int)((e >> 16) & 0xffffu), j = (int)(e & 0xffffu);
+            pair_item<G>(S, hist + ((int64_t)i * kPairSlots + (int)(e >> 32)) * kHist, c, dt, g, i, j,
+                         lane % G, [&](const double F[3], const double ti[3], const double tj[3]) {
+                             on = true;
+                             for (int a = 0; a < 3; ++a) {
+                                 v[a] = F[a];
+                                 v[3 + a] = ti[a];
+                                 v[6 + a] = -F[a];
+                                 v[9 + a] = -tj[a];
+                             }
+                         });
+        }
+        const uint64_t m = __ballot(on);
+        if (!m) continue;
+        if (on) {
+            const int r = __popcll(m & ((1ull << lane) - 1ull));
+            for (int k = 0; k < 12; ++k) wa[12 * r + k] = v[k];
+            ww[2 * r] = i;
+            ww[2 * r + 1] = j;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int total = 12 * __popcll(m);
+        for (int u = lane; u < total; u += 64) {
+            const int q = u / 6;
+            atomicAdd(fc + 6 * (int64_t)ww[q] + (u - 6 * q), wa[u]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -1089,6 +1213,16 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
         }
     } else {
         const int group = kPairGroups - 1 - (tid - 64) / kPairLanes, l = tid % kPairLanes;
+        auto adder = [&](int i, int j) {
+            return [&, i, j](const double F[3], const double ti[3], const double tj[3]) {
+                for (int a = 0; a < 3; ++a) {
+                    atomicAdd(sum + 6 * i + a, F[a]);
+                    atomicAdd(sum + 6 * j + a, -F[a]);
+                    atomicAdd(sum + 6 * i + 3 + a, ti[a]);
+                    atomicAdd(sum + 6 * j + 3 + a, -tj[a]);
+                }
+            };
+        };
         const int total = (int)npairs;
         const bool mine = group < total;
         const uint64_t e0 = mine ? list[group] : 0;
@@ -1099,12 +1233,12 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
             for (int k = l; k < kHist; k += kPairLanes) h0[k] = g0[k];
         for (int sub = 0; sub < n_sub; ++sub) {
             __syncthreads();
-            if (mine) pair_item<kPairLanes>(S, h0, c, dt, g, i0, j0, l);
+            if (mine) pair_item<kPairLanes>(S, h0, c, dt, g, i0, j0, l, adder(i0, j0));
             for (int t = group + kPairGroups; t < total; t += kPairGroups) {
                 const uint64_t e = list[t];
-                const int i = (int)((e >> 16) & 0xffffu);
+                const int i = (int)((e >> 16) & 0xffffu), j = (int)(e & 0xffffu);
                 pair_item<kPairLanes>(S, hist + ((int64_t)i * kPairSlots + (int)(e >> 32)) * kHist, c,
-                                      dt, g, i, (int)(e & 0xffffu), l);
+                                      dt, g, i, j, l, adder(i, j));
             }
             __syncthreads();
         }
@@ -1147,15 +1281,20 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
     const double T = (double)n_sub * dt;
     hipLaunchKernelGGL(k_reach, dim3(bp), dim3(64), 0, ctx->stream, P, T, ws.reach, ws.bound, ws.count);
     if (ws.gcount && np >= kGridMinParticles) {
-        const uint32_t bn = (uint32_t)((np + 255) / 256);
-        hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(1024), 0, ctx->stream, P, ws.reach, T, g,
-                           ws.gdim, ws.gsize, ws.gcount, ws.gcap);
-        hipLaunchKernelGGL(k_grid_count, dim3(bn), dim3(256), 0, ctx->stream, P, g, ws.gdim,
-                           ws.gsize, ws.gcount);
-        hipLaunchKernelGGL(k_grid_scan, dim3(1), dim3(1024), 0, ctx->stream, ws.gdim, ws.gcount,
-                           ws.gcursor);
-        hipLaunchKernelGGL(k_grid_scatter, dim3(bn), dim3(256), 0, ctx->stream, P, g, ws.gdim,
-                           ws.gsize, ws.gcursor, ws.gitem);
+        if (np <= kGridBlock) {
+            hipLaunchKernelGGL(k_grid_block, dim3(1), dim3(1024), 0, ctx->stream, P, ws.reach, T, g,
+                               ws.gdim, ws.gsize, ws.gcount, ws.gitem, ws.gcap);
+        } else {
+            const uint32_t bn = (uint32_t)((np + 255) / 256);
+            hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(1024), 0, ctx->stream, P, ws.reach, T, g,
+                               ws.gdim, ws.gsize, ws.gcount, ws.gcap);
+            hipLaunchKernelGGL(k_grid_count, dim3(bn), dim3(256), 0, ctx->stream, P, g, ws.gdim,
+                               ws.gsize, ws.gcount);
+            hipLaunchKernelGGL(k_grid_scan, dim3(1), dim3(1024), 0, ctx->stream, ws.gdim, ws.gcount,
+                               ws.gcursor);
+            hipLaunchKernelGGL(k_grid_scatter, dim3(bn), dim3(256), 0, ctx->stream, P, g, ws.gdim,
+                               ws.gsize, ws.gcursor, ws.gitem);
+        }
         hipLaunchKernelGGL(k_pairs<true>, dim3(bw), dim3(1024), 0, ctx->stream, P, ctx->hist_pp,
                            ctx->hist_key, ws.bound, g, ws.gdim, ws.gsize, ws.gcount, ws.gitem,
                            ws.pairs, ws.count, deferred);

@@ -86,6 +86,38 @@ def test_dem_paths_match_the_oracle(n, points):
         assert np.abs(a - b).max() <= 1e-9 * max(1.0, np.abs(b).max()), key
 
 
+@pytest.mark.parametrize("n,spacing", [(2048, 3.0), (2050, 13.0), (16384, 3.0), (16385, 3.0)])
+def test_dem_cell_grids_match_the_oracle(n, spacing):
+    """dem_step on the cell grid where its making moves from one workgroup to a
+    launch per phase, and on a sparse box with more room than cells: spheres
+    next to each other in couples, on walls and across a periodic face, one call
+    of two substeps against the oracle, within 1e-9."""
+    rng = np.random.default_rng(n)
+    m = int(np.ceil((n / 2) ** (1 / 3)))
+    k = np.arange(n) // 2
+    pitch = np.array([2 * spacing, spacing, spacing])
+    pos = np.stack([k % m, k // m % m, k // (m * m)], -1) * pitch
+    pos[:, 0] += np.where(np.arange(n) % 2, 2.9, 0.0)
+    pos += 0.9 + rng.uniform(0, 0.2, (n, 3))
+    dims = [int(np.ceil(2 * spacing * m)), int(np.ceil(spacing * m)), int(np.ceil(spacing * m)) + 2]
+    lat = W.LatticeSpec(*dims, (1, 0, 0))
+    ps = W.make_particles([W.sphere_shape(3.0, 0.2)] * n, pos, np.tile([1.0, 0, 0, 0], (n, 1)), 1.5,
+                          vel=rng.normal(size=(n, 3)) * 0.02, omega=rng.normal(size=(n, 3)) * 0.004)
+    kw = W.dem_defaults(ps, gravity=(0.0, 0.0, -2e-4))
+    gpu, dem = B.Lattice.for_particles(lat, ps, storage="f16"), O.OracleDEM(ps, lat)
+    parts, P = B.DeviceParticles(ps), ps.copy()
+    gpu.dem(parts, 2, 0.25, B.DemParams.make(**kw))
+    zero = np.zeros((n, 3))
+    dem.step(P, zero, zero, O.DemParams(**kw), 2, 0.25)
+    gpu.sync()
+    G = parts.to_host(ps)
+    gpu.close()
+    assert np.count_nonzero(np.abs(P.vel - ps.vel).max(1) > 1e-4) > n // 4   # contacts acted
+    for key in ("pos", "vel", "omega"):
+        a, b = getattr(G, key), getattr(P, key)
+        assert np.abs(a - b).max() <= 1e-9 * max(1.0, np.abs(b).max()), key
+
+
 def test_link_adjoint_on_both_sides_of_the_wave_split():
     """The adjoint of the links of 40 spheres (a wave per 64 records) and of 530
     (a workgroup per 256-record chunk): the dot products of the larger set, and
