@@ -797,22 +797,25 @@ struct RunAdj {
     }
 };
 
-// The small arrays of one taped step in one launch: the first word of every
-// link cursor line, the particle state (position, velocity, angular
-// velocity, world control points, quaternion, F^h and T^h of the step), and
-// the DEM state the next dem_step starts from (pair records, wall records,
-// carried contact sums; the pair records' keys).
-__global__ void k_tape_small(uint32_t* __restrict__ tcur, const uint32_t* __restrict__ cur,
-                             double* __restrict__ part, const double* __restrict__ pos,
-                             const double* __restrict__ vel, const double* __restrict__ om,
-                             const double* __restrict__ wpts, const double* __restrict__ quat,
-                             const double* __restrict__ sums,
-                             const unsigned long long* __restrict__ fx, int np, int nctrl,
-                             double* __restrict__ dem, int32_t* __restrict__ dem_key,
-                             const double* __restrict__ hpp, const double* __restrict__ hpw,
-                             const double* __restrict__ fc, const int32_t* __restrict__ hkey)
+// One taped step in one launch: the owner plane and the links; and by the first
+// threads the small arrays: the first word of every link cursor line, the
+// particle state (position, velocity, angular velocity, world control points,
+// quaternion, F^h and T^h of the step), and the DEM state the next dem_step
+// starts from (pair records, wall records, carried contact sums; the pair
+// records' keys).
+__global__ __launch_bounds__(256) void k_tape(CopySeg own, CopySeg links, uint32_t* __restrict__ tcur, const uint32_t* __restrict__ cur,
+                       double* __restrict__ part, const double* __restrict__ pos,
+                       const double* __restrict__ vel, const double* __restrict__ om,
+                       const double* __restrict__ wpts, const double* __restrict__ quat,
+                       const double* __restrict__ sums,
+                       const unsigned long long* __restrict__ fx, int np, int nctrl,
+                       double* __restrict__ dem, int32_t* __restrict__ dem_key,
+                       const double* __restrict__ hpp, const double* __restrict__ hpw,
+                       const double* __restrict__ fc, const int32_t* __restrict__ hkey)
 {
     const int i = (int)(blockIdx.x * 256u + threadIdx.x);
+    copy_segment(own, (uint64_t)i, (uint64_t)gridDim.x * 256u);
+    copy_segment(links, (uint64_t)i, (uint64_t)gridDim.x * 256u);
     if (i < np) tcur[(int64_t)i * kCursorPad] = cur[(int64_t)i * kCursorPad];
     if (i < 3 * np) {
         part[i] = pos[i];
@@ -834,16 +837,21 @@ __global__ void k_tape_small(uint32_t* __restrict__ tcur, const uint32_t* __rest
 
 namespace MDLBM_QNS {
 
-hipError_t launch_tape_small(lbm_ctx* c, TapeStep& t, const lbm_particles* P)
+hipError_t launch_tape(lbm_ctx* c, TapeStep& t, const lbm_particles* P, const CopySeg& own,
+                       const CopySeg& links)
 {
     const int np = c->cfg.n_particles, nctrl = c->cfg.n_ctrl;
-    if (np == 0) return hipSuccess;
-    const int64_t n = std::max<int64_t>({8 * (int64_t)np * kPairSlots, 48 * (int64_t)np,
-                                         3 * (int64_t)nctrl});
-    hipLaunchKernelGGL(k_tape_small, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, c->stream,
-                       t.cursor, c->link_cursor, t.part, P->pos, P->vel, P->omega, P->world_pts,
-                       P->quat, c->sums, c->FX, np, nctrl, t.dem, t.dem_key, c->hist_pp, c->hist_pw, c->fc,
-                       c->hist_key);
+    // a thread per number of the small arrays, and as many as copy the large
+    // ones well
+    const uint64_t n = np ? std::max<uint64_t>({8 * (uint64_t)np * kPairSlots, 48 * (uint64_t)np,
+                                                3 * (uint64_t)nctrl})
+                          : 1;
+    const uint64_t most = std::min<uint64_t>(std::max(own.bytes, links.bytes) / 16, 2048 * 256);
+    hipLaunchKernelGGL(k_tape, dim3((uint32_t)((std::max(n, most) + 255) / 256)), dim3(256), 0,
+                       c->stream, own, links, t.cursor, c->link_cursor, t.part, P ? P->pos : nullptr,
+                       P ? P->vel : nullptr, P ? P->omega : nullptr, P ? P->world_pts : nullptr,
+                       P ? P->quat : nullptr, c->sums, c->FX, np, np ? nctrl : 0, t.dem, t.dem_key,
+                       c->hist_pp, c->hist_pw, c->fc, c->hist_key);
     return hipGetLastError();
 }
 

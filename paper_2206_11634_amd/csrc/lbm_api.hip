@@ -235,12 +235,11 @@ int record_tape_step(lbm_ctx* c, const lbm_particles* P)
         t.links_use = c->geo_links;
         t.lay = c->lay;
         t.link_max = c->link_max;
-        if (np > 0) HIPCHK(c, LQ(c, launch_tape_small)(c, t, P));
+        if (np > 0) HIPCHK(c, LQ(c, launch_tape)(c, t, P, CopySeg{}, CopySeg{}));
         c->tape_len += 1;
         return LBM_OK;
     }
-    HIPCHK(c, hipMemcpyAsync(t.own, c->own[c->own_cur], c->sizes.owner_bytes,
-                             hipMemcpyDeviceToDevice, c->stream));
+    CopySeg own{(const uint8_t*)c->own[c->own_cur], (uint8_t*)t.own, c->sizes.owner_bytes, 0}, links{};
     t.own_use = t.own;
     t.links_use = t.links;
     if (np > 0) {
@@ -256,12 +255,12 @@ int record_tape_step(lbm_ctx* c, const lbm_particles* P)
         t.lay = c->lay;
         t.link_max = c->link_max;
         if (c->link_max > 0 && c->lay->total > 0)
-            HIPCHK(c, hipMemcpyAsync(t.links, c->links, sizeof(LinkRec) * (size_t)c->lay->total,
-                                     hipMemcpyDeviceToDevice, c->stream));
-        // cursors, particle state and the DEM state the next dem_step starts
-        // from (for the coupled adjoint), in one launch
-        HIPCHK(c, LQ(c, launch_tape_small)(c, t, P));
+            links = CopySeg{(const uint8_t*)c->links, (uint8_t*)t.links,
+                            sizeof(LinkRec) * (uint64_t)c->lay->total, 0};
     }
+    // with them, in one launch: cursors, particle state and the DEM state the
+    // next dem_step starts from (for the coupled adjoint)
+    HIPCHK(c, LQ(c, launch_tape)(c, t, P, own, links));
     c->tape_len += 1;
     return LBM_OK;
 }
@@ -337,6 +336,27 @@ DemScratch dem_scratch(lbm_ctx* c)
     return ws;
 }
 
+// Up to eight device-to-device copies or fills in one launch.
+struct CopyList {
+    CopySeg s[8];
+    int n;
+};
+
+__global__ __launch_bounds__(256) void k_copy_segments(CopyList L)
+{
+    for (int k = 0; k < L.n; ++k)
+        copy_segment(L.s[k], (uint64_t)blockIdx.x * 256u + threadIdx.x, (uint64_t)gridDim.x * 256u);
+}
+
+hipError_t copy_segments(lbm_ctx* c, const CopyList& L)
+{
+    uint64_t most = 0;
+    for (int k = 0; k < L.n; ++k) most = std::max<uint64_t>(most, L.s[k].bytes);
+    const uint32_t nb = (uint32_t)std::min<uint64_t>(2048, std::max<uint64_t>(1, (most / 16 + 255) / 256));
+    hipLaunchKernelGGL(k_copy_segments, dim3(nb), dim3(256), 0, c->stream, L);
+    return hipGetLastError();
+}
+
 // Bytes of the DEM state saved by lbm_dem_checkpoint_save, in its order: the
 // pair histories, their partner keys, the wall histories, the contact sums.
 struct DemStateBytes {
@@ -346,6 +366,23 @@ DemStateBytes dem_state_bytes(size_t np)
 {
     return {sizeof(double) * np * kPairSlots * 8, sizeof(int32_t) * np * kPairSlots,
             sizeof(double) * np * 6 * 8, sizeof(double) * np * 6};
+}
+
+// The copies of the DEM state to (save) or from its checkpoint.
+CopyList dem_state_copies(lbm_ctx* c, uint8_t* at, bool save)
+{
+    const DemStateBytes b = dem_state_bytes((size_t)c->cfg.n_particles);
+    CopyList L{};
+    auto seg = [&](void* mine, size_t bytes) {
+        uint8_t* m = static_cast<uint8_t*>(mine);
+        L.s[L.n++] = save ? CopySeg{m, at, bytes, 0} : CopySeg{at, m, bytes, 0};
+        at += bytes;
+    };
+    seg(c->hist_pp, b.pp);
+    seg(c->hist_key, b.key);
+    seg(c->hist_pw, b.pw);
+    seg(c->fc, b.fc);
+    return L;
 }
 
 // Number of lattice velocities of the configured lattice (0 selects D3Q19).
@@ -1043,9 +1080,11 @@ int lbm_checkpoint_load(lbm_ctx* c, const void* src_dev)
                              hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->mom, (const char*)src_dev + c->sizes.population_bytes,
                              c->sizes.moment_bytes, hipMemcpyDeviceToDevice, c->stream));
-    HIPCHK(c, hipMemsetAsync(c->own[0], 0xFF, c->sizes.owner_bytes, c->stream));
-    HIPCHK(c, hipMemsetAsync(c->own[1], 0xFF, c->sizes.owner_bytes, c->stream));
-    HIPCHK(c, hipMemsetAsync(c->flag, 0, c->sizes.flag_bytes, c->stream));
+    CopyList cl{};
+    for (int i = 0; i < 2; ++i)
+        cl.s[cl.n++] = CopySeg{nullptr, (uint8_t*)c->own[i], c->sizes.owner_bytes, 0xFFFFFFFFu};
+    cl.s[cl.n++] = CopySeg{nullptr, c->flag, c->sizes.flag_bytes, 0};
+    HIPCHK(c, copy_segments(c, cl));
     c->n_classify = 0;
     c->own_cur = 0;
     c->stepped_since_classify = false;
@@ -1062,14 +1101,7 @@ int lbm_dem_checkpoint_save(const lbm_ctx* cc, void* dst_dev)
     if (!c || !dst_dev) return fail(c, LBM_EINVAL, "null argument");
     const size_t np = (size_t)c->cfg.n_particles;
     if (np == 0) return LBM_OK;
-    char* d = (char*)dst_dev;
-    const DemStateBytes b = dem_state_bytes(np);
-    HIPCHK(c, hipMemcpyAsync(d, c->hist_pp, b.pp, hipMemcpyDeviceToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(d + b.pp, c->hist_key, b.key, hipMemcpyDeviceToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(d + b.pp + b.key, c->hist_pw, b.pw, hipMemcpyDeviceToDevice,
-                             c->stream));
-    HIPCHK(c, hipMemcpyAsync(d + b.pp + b.key + b.pw, c->fc, b.fc, hipMemcpyDeviceToDevice,
-                             c->stream));
+    HIPCHK(c, copy_segments(c, dem_state_copies(c, (uint8_t*)dst_dev, true)));
     return LBM_OK;
 }
 
@@ -1079,51 +1111,8 @@ int lbm_dem_checkpoint_load(lbm_ctx* c, const void* src_dev)
     if (c->failed) return fail(c, LBM_ESTATE, "context failed earlier: " + c->last_error);
     const size_t np = (size_t)c->cfg.n_particles;
     if (np == 0) return LBM_OK;
-    const char* d = (const char*)src_dev;
-    const DemStateBytes b = dem_state_bytes(np);
-    HIPCHK(c, hipMemcpyAsync(c->hist_pp, d, b.pp, hipMemcpyDeviceToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->hist_key, d + b.pp, b.key, hipMemcpyDeviceToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->hist_pw, d + b.pp + b.key, b.pw, hipMemcpyDeviceToDevice,
-                             c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->fc, d + b.pp + b.key + b.pw, b.fc, hipMemcpyDeviceToDevice,
-                             c->stream));
+    HIPCHK(c, copy_segments(c, dem_state_copies(c, (uint8_t*)const_cast<void*>(src_dev), false)));
     return LBM_OK;
-}
-
-// Up to eight device-to-device copies (a null source: zeros) in one launch.
-struct CopySeg {
-    const uint8_t* src;
-    uint8_t* dst;
-    uint64_t bytes;
-};
-struct CopyList {
-    CopySeg s[8];
-    int n;
-};
-
-__global__ __launch_bounds__(256) void k_copy_segments(CopyList L)
-{
-    const uint64_t t = (uint64_t)blockIdx.x * 256u + threadIdx.x;
-    const uint64_t stride = (uint64_t)gridDim.x * 256u;
-    for (int k = 0; k < L.n; ++k) {
-        const CopySeg g = L.s[k];
-        const bool v16 = ((reinterpret_cast<uintptr_t>(g.src) | reinterpret_cast<uintptr_t>(g.dst)) &
-                          15u) == 0;
-        const uint64_t n16 = v16 ? g.bytes / 16 : 0;
-        for (uint64_t i = t; i < n16; i += stride)
-            reinterpret_cast<uint4*>(g.dst)[i] =
-                g.src ? reinterpret_cast<const uint4*>(g.src)[i] : make_uint4(0, 0, 0, 0);
-        for (uint64_t i = n16 * 16 + t; i < g.bytes; i += stride) g.dst[i] = g.src ? g.src[i] : 0;
-    }
-}
-
-static hipError_t copy_segments(lbm_ctx* c, const CopyList& L)
-{
-    uint64_t most = 0;
-    for (int k = 0; k < L.n; ++k) most = std::max<uint64_t>(most, L.s[k].bytes);
-    const uint32_t nb = (uint32_t)std::min<uint64_t>(2048, std::max<uint64_t>(1, (most / 16 + 255) / 256));
-    hipLaunchKernelGGL(k_copy_segments, dim3(nb), dim3(256), 0, c->stream, L);
-    return hipGetLastError();
 }
 
 // Layout of a geometry snapshot: owner plane, flags, link records, link
@@ -1171,7 +1160,7 @@ int lbm_geometry_save(lbm_ctx* c, void* dst_dev)
     uint8_t* d = (uint8_t*)dst_dev;
     CopyList cl{};
     auto seg = [&](const void* src, size_t off, size_t bytes) {
-        cl.s[cl.n++] = CopySeg{(const uint8_t*)src, d + off, bytes};
+        cl.s[cl.n++] = CopySeg{(const uint8_t*)src, d + off, bytes, 0};
     };
     seg(c->own[c->own_cur], L.own, c->sizes.owner_bytes);
     seg(c->flag, L.flag, c->sizes.flag_bytes);
@@ -1202,7 +1191,7 @@ int lbm_geometry_load(lbm_ctx* c, const void* src_dev, uint64_t tag, const lbm_p
     const ClassifyPlan cp = classify_plan(c);
     CopyList cl{};
     auto seg = [&](void* dst, size_t off, size_t bytes) {
-        cl.s[cl.n++] = CopySeg{d + off, (uint8_t*)dst, bytes};
+        cl.s[cl.n++] = CopySeg{d + off, (uint8_t*)dst, bytes, 0};
     };
     seg(cp.own_new, L.own, c->sizes.owner_bytes);
     seg(c->flag, L.flag, c->sizes.flag_bytes);
@@ -1212,7 +1201,7 @@ int lbm_geometry_load(lbm_ctx* c, const void* src_dev, uint64_t tag, const lbm_p
         seg(c->refill_cursor, L.refill_ctr, sizeof(uint32_t));
         seg(c->refill, L.refill, sizeof(RefillRec) * c->refill_cap);
         seg(c->ball_hist + (int64_t)cp.slot * 4 * np, L.ball, sizeof(double) * 4 * np);
-        cl.s[cl.n++] = CopySeg{nullptr, (uint8_t*)c->err, sizeof(uint32_t)};  // a valid geometry
+        cl.s[cl.n++] = CopySeg{nullptr, (uint8_t*)c->err, sizeof(uint32_t), 0};  // a valid geometry
     }
     HIPCHK(c, copy_segments(c, cl));
     if (np > 0) {

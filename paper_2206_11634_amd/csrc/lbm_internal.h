@@ -155,6 +155,26 @@ struct PartDev {
     double* wpts;
 };
 
+// A device-to-device copy, or (a null source) a fill with a 32-bit word, as part
+// of a larger launch: thread t of `threads`.
+struct CopySeg {
+    const uint8_t* src;
+    uint8_t* dst;
+    uint64_t bytes;
+    uint32_t word;
+};
+__device__ __forceinline__ void copy_segment(const CopySeg& g, uint64_t t, uint64_t threads)
+{
+    const bool v16 =
+        ((reinterpret_cast<uintptr_t>(g.src) | reinterpret_cast<uintptr_t>(g.dst)) & 15u) == 0;
+    const uint64_t n16 = v16 ? g.bytes / 16 : 0;
+    for (uint64_t i = t; i < n16; i += threads)
+        reinterpret_cast<uint4*>(g.dst)[i] = g.src ? reinterpret_cast<const uint4*>(g.src)[i]
+                                                   : make_uint4(g.word, g.word, g.word, g.word);
+    for (uint64_t i = n16 * 16 + t; i < g.bytes; i += threads)
+        g.dst[i] = g.src ? g.src[i] : (uint8_t)(g.word >> (8 * (i & 3)));
+}
+
 // Per-particle node box: origin (unwrapped) and edge S = 2h + 1.
 struct BoxSpec {
     int h, S, vol, tiles;  // tiles of 256 box cells
