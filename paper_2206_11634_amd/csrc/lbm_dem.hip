@@ -20,8 +20,8 @@
 // two components; half angles come from their series.
 // Measured, microseconds a call of ten substeps (in parentheses a thread per
 // pair, per pair test and per particle's cells, 23 launches whatever the count):
-//   1 sphere 17 (83), 2 flat metaballs 35 (153), 64 packed spheres 72 (173),
-//   1000 metaballs of the 512^3 run 234 (535), packed spheres 1000: 130 (226),
+//   1 sphere 13 (83), 2 flat metaballs 35 (153), 64 packed spheres 67 (173),
+//   1000 metaballs of the 512^3 run 235 (535), packed spheres 1000: 130 (226),
 //   2548: 136 (420), 8000: 156 (462), 27 000: 302 (745).
 // In one workgroup with the points and records in global memory, a matrix a
 // half kick and the library's division, square root and sincos the first three
@@ -1165,15 +1165,21 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
     }
     __syncthreads();
     // the first wave moves the particles and takes their wall contacts, the
-    // others take the pairs (the same barriers on both sides: two a substep)
+    // others take the pairs (the same barriers on both sides: two a substep,
+    // none if there are no pairs)
+    const bool pairs = __builtin_amdgcn_readfirstlane((int)npairs) > 0;
     if (wave == 0) {
         const bool on = tid < n;
+        uint32_t live = 0;  // wall records that are not zero
+        double lim = 0.0;   // how near a wall must be to be touched
         Body b{};
         double f[6] = {0, 0, 0, 0, 0, 0};
         if (on) {
             b = load_body(P, tid, FTh, c, 0.5 * dt);
             for (int k = 0; k < 6; ++k) f[k] = fc[6 * tid + k];
             half_kick<false>(b, kick_of(b, f));
+            for (int k = 0; k < 6; ++k) live |= wall[(6 * tid + k) * kHist] != 0.0 ? 1u << k : 0u;
+            lim = rch[tid] + rs[tid];
         }
         for (int sub = 0; sub < n_sub; ++sub) {
             if (on) {
@@ -1187,18 +1193,27 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
                 }
                 for (int k = 0; k < 6; ++k) sum[6 * tid + k] = 0.0;
             }
-            __syncthreads();
-            if (on)
+            if (pairs) __syncthreads();
+            if (on) {
+                uint32_t near = 0;  // as near_wall
                 for (int ax = 0; ax < 3; ++ax)
-                    if (!g.per[ax])
-                        for (int side = 0; side < 2; ++side) {
-                            double* h = wall + (6 * tid + 2 * ax + side) * kHist;
-                            if (near_wall(S, tid, ax, side, g))
-                                wall_contact(S, h, tid, ax, side, c, dt, g);
-                            else if (h[0] != 0.0)
-                                clear_record(h);
-                        }
-            __syncthreads();
+                    if (!g.per[ax]) {
+                        if (!(b.x[ax] + 0.5 > lim)) near |= 1u << (2 * ax);
+                        if (!((double)g.n[ax] - 0.5 - b.x[ax] > lim)) near |= 2u << (2 * ax);
+                    }
+                for (uint32_t m = near | live; m; m &= m - 1u) {
+                    const int k = __ffs(m) - 1;
+                    double* h = wall + (6 * tid + k) * kHist;
+                    if ((near >> k) & 1u) {
+                        wall_contact(S, h, tid, k >> 1, k & 1, c, dt, g);
+                        live |= 1u << k;
+                    } else {
+                        clear_record(h);
+                        live &= ~(1u << k);
+                    }
+                }
+            }
+            if (pairs) __syncthreads();
             if (on) {
                 for (int k = 0; k < 6; ++k) f[k] = sum[6 * tid + k];
                 const Kick k = kick_of(b, f);
@@ -1211,7 +1226,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
             store_body(P, tid, b, true);
             for (int k = 0; k < 6; ++k) fc[6 * tid + k] = f[k];
         }
-    } else {
+    } else if (pairs) {
         const int group = kPairGroups - 1 - (tid - 64) / kPairLanes, l = tid % kPairLanes;
         auto adder = [&](int i, int j) {
             return [&, i, j](const double F[3], const double ti[3], const double tj[3]) {
