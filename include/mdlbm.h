@@ -305,7 +305,7 @@ int lbm_step_dem(lbm_ctx* ctx, lbm_particles* P, int n_sub, double dt, const dem
  * with the call's work space (candidate pairs, their count, the bodies'
  * reach) in a static device array instead of the context's, looked up once
  * per device by lbm_init.  The array holds at most 1024 particles (about
- * 270 KB per device, held until the process ends); EINVAL for a context with
+ * 870 KB per device, held until the process ends); EINVAL for a context with
  * more.  Every call on one device shares that array and leaves its contents
  * there: calls that overlap on one device (on different streams or
  * contexts) race and must not be issued.  Calls no hipMalloc, hipFree or

@@ -309,6 +309,7 @@ hipError_t carve_fixed(lbm_ctx* c)
         put(c->hist_pw, np * 6 * 8);
         put(c->pairs, slots);
         put(c->pair_count, np ? 1 : 0);
+        put(c->dem_state, np * kDemStateDoubles);
         // counts and starts, cursors, the binned particles, the grid's shape
         put(c->grid, grid ? 2 * (size_t)c->grid_cap + 1 + np + 4 : 0);
         put(c->grid_size, grid ? 4 : 0);
@@ -324,7 +325,8 @@ hipError_t carve_fixed(lbm_ctx* c)
 // The work space of a dem_step call on the context.
 DemScratch dem_scratch(lbm_ctx* c)
 {
-    DemScratch ws{c->pairs, c->pair_count, c->reach, c->reach + std::max(c->cfg.n_particles, 1)};
+    DemScratch ws{c->pairs, c->pair_count, c->reach, c->reach + std::max(c->cfg.n_particles, 1),
+                  c->dem_state};
     if (c->grid) {
         ws.gcount = c->grid;
         ws.gcursor = c->grid + c->grid_cap + 1;

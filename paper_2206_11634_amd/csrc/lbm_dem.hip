@@ -222,16 +222,17 @@ __device__ __forceinline__ Kick kick_of(const Body& b, const double fc[6])
     return k;
 }
 
-// Half a kick; the rotational part by one explicit or four fixed-point sweeps
-// of Euler's equations.
+// Half a kick: of the velocity, and of the rotation by one explicit or four
+// fixed-point sweeps of Euler's equations.
+__device__ __forceinline__ void kick_v(Body& b, const Kick& k)
+{
+    for (int a = 0; a < 3; ++a) b.v[a] += k.v[a];
+}
 template <bool IMPLICIT>
-__device__ __forceinline__ void half_kick(Body& b, const Kick& k)
+__device__ __forceinline__ void kick_w(Body& b, const Kick& k)
 {
     double w0[3];
-    for (int a = 0; a < 3; ++a) {
-        b.v[a] += k.v[a];
-        w0[a] = b.wb[a] + k.w[a];
-    }
+    for (int a = 0; a < 3; ++a) w0[a] = b.wb[a] + k.w[a];
 #pragma unroll
     for (int it = 0; it < (IMPLICIT ? 4 : 1); ++it) {
         const double p0 = b.wb[1] * b.wb[2], p1 = b.wb[2] * b.wb[0], p2 = b.wb[0] * b.wb[1];
@@ -241,8 +242,8 @@ __device__ __forceinline__ void half_kick(Body& b, const Kick& k)
     }
 }
 
-// Drift and rotation over dt (w and wb both hold the angular velocity).
-__device__ __forceinline__ void drift(Body& b, double dt, const Geom& g)
+// The centre's drift over dt.
+__device__ __forceinline__ void move(Body& b, double dt, const Geom& g)
 {
     for (int a = 0; a < 3; ++a) {
         double x = b.x[a] + dt * b.v[a];
@@ -252,6 +253,11 @@ __device__ __forceinline__ void drift(Body& b, double dt, const Geom& g)
         }
         b.x[a] = x;
     }
+}
+
+// The rotation over dt (w and wb both hold the angular velocity).
+__device__ __forceinline__ void rotate(Body& b, double dt)
+{
     // cos(t) and sin(t) / |w| of half the angle t = |w| dt / 2
     const double z = (0.25 * dt * dt) * dot3(b.w, b.w);
     double dq[4], s;
@@ -309,13 +315,11 @@ __device__ __forceinline__ void store_body(const PartDev& P, int p, const Body& 
         for (int a = 0; a < 4; ++a) P.quat[4 * p + a] = b.q[a];
 }
 
-// What a contact reads of a particle at the current substep, wherever it is
-// kept: the caller's arrays and the library's reach, or a workgroup's copies.
-struct StateG {
-    const double *pos, *vel, *omega, *rs, *reach;
-    double* fc;
-    const int32_t* off;
-    const double *wpts, *K;
+// What a contact reads of a particle at the current substep.
+struct Kin {
+    double x[3], v[3], w[3], rs, reach;
+    const double* K;  // its control points' weights
+    int n;            // their number
 };
 
 __device__ __forceinline__ void clear_record(double* h)
@@ -323,21 +327,13 @@ __device__ __forceinline__ void clear_record(double* h)
     for (int k = 0; k < kHist; ++k) h[k] = 0.0;
 }
 
-// Contact of pair (i < j), record h of particle i: test on the reach radii,
-// Newton on grad(M_i + M_j) = 0 from the recorded point or the closest pair
-// of control points, the contact test and the force.  The G lanes of a group
-// share a pair: each sums every G-th control point of the two bodies (kept in
-// registers up to 4 a lane), and all follow the same branches on the same bits.
-// A contact's force on i and the torques of it about i and, the other way, j go
-// to emit(F, ti, tj) on the group's first lane.
-template <int G, class Emit>
-__device__ __forceinline__ void pair_item(const StateG& S, double* h, const DemP& c, double dt,
-                                          const Geom& g, int i, int j, int l, Emit&& emit)
+// Whether a pair is within reach; sh takes the second centre to its image
+// nearest the first.
+__device__ __forceinline__ bool near_pair(const double xi[3], const double xj[3], double far,
+                                          const Geom& g, double sh[3])
 {
-    double xi[3], xj[3], sh[3], dv[3];
+    double dv[3];
     for (int a = 0; a < 3; ++a) {
-        xi[a] = S.pos[3 * i + a];
-        xj[a] = S.pos[3 * j + a];
         const double d = xj[a] - xi[a];
         sh[a] = 0.0;
         if (g.per[a]) {
@@ -347,39 +343,32 @@ __device__ __forceinline__ void pair_item(const StateG& S, double* h, const DemP
         }
         dv[a] = d + sh[a];
     }
-    const double rsi = S.rs[i], rsj = S.rs[j];
+    return !(dot3(dv, dv) > far * far);
+}
+
+// Contact of pair (A, B) within reach, A the lower index, record h of A:
+// Newton on grad(M_A + M_B) = 0 from the recorded point or the closest pair
+// of control points (point(u, r, K): world coordinates and weight of point u of
+// the pair, A's, then B's at their image nearest A), the contact test and the
+// force.  The G lanes of a group share a pair: each sums every G-th control
+// point of the two bodies (kept in registers up to 4 a lane), and all follow the
+// same branches on the same bits.  A contact's force on A and the torques of it
+// about A and, the other way, B go to emit(F, tA, tB) on the group's first lane.
+template <int G, class Point, class Emit>
+__device__ __forceinline__ void pair_item(const Kin& A, const Kin& B, const double sh[3], Point&& point,
+                                          double* h, const DemP& c, double dt, int l, Emit&& emit)
+{
+    const double *xi = A.x, *xj = B.x;
+    const double rsi = A.rs, rsj = B.rs;
     const double active = h[0];
-    const double far = S.reach[i] + S.reach[j] + rsi + rsj;
-    if (dot3(dv, dv) > far * far) {
-        // out of reach: forget the pair's contact (read one double instead of
-        // writing eight when the record is zero already)
-        if (active != 0.0 && l == 0) clear_record(h);
-        return;
-    }
-    const int ai = S.off[i], ni = min(S.off[i + 1] - ai, kMaxPts);
-    const int aj = S.off[j], nj = min(S.off[j + 1] - aj, kMaxPts);
-    const double* pi = S.wpts + 3 * (int64_t)ai;
-    const double* pj = S.wpts + 3 * (int64_t)aj;
-    const double* Ki = S.K + ai;
-    const double* Kj = S.K + aj;
-    const int nt = ni + nj;
-    // point u of the pair: body i's, then body j's at their image nearest i
-    auto point = [&](int u, double r[3], double& K) {
-        const bool second = u >= ni;
-        const double* q = second ? pj + 3 * (u - ni) : pi + 3 * u;
-        for (int a = 0; a < 3; ++a) r[a] = q[a] + (second ? sh[a] : 0.0);
-        K = second ? Kj[u - ni] : Ki[u];
-    };
-    constexpr int R = 4;
+    const int ni = A.n, nj = B.n, nt = ni + nj;
+    constexpr int R = G == 2 ? 1 : 4;  // two lanes: two spheres
     double pr[R][3], kr[R];
     const bool regs = nt <= G * R;
     if (regs) {
+        // (the last point again beyond the end: no branch between the loads)
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-            const int u = l + G * k;
-            pr[k][0] = pr[k][1] = pr[k][2] = kr[k] = 0.0;
-            if (u < nt) point(u, pr[k], kr[k]);
-        }
+        for (int k = 0; k < R; ++k) point(min(l + G * k, nt - 1), pr[k], kr[k]);
     }
     double x[3];
     if (active != 0.0) {
@@ -388,12 +377,10 @@ __device__ __forceinline__ void pair_item(const StateG& S, double* h, const DemP
         double best = INFINITY;
         int at = 0x7fffffff;
         for (int t = l; t < ni * nj; t += G) {
-            const int u = t / nj, v = t % nj;
-            double d2 = 0.0;
-            for (int a = 0; a < 3; ++a) {
-                const double dd = pi[3 * u + a] - (pj[3 * v + a] + sh[a]);
-                d2 += dd * dd;
-            }
+            double p[3], q[3], K, d2 = 0.0;
+            point(t / nj, p, K);
+            point(ni + t % nj, q, K);
+            for (int a = 0; a < 3; ++a) d2 += (p[a] - q[a]) * (p[a] - q[a]);
             if (d2 < best) {
                 best = d2;
                 at = t;
@@ -410,8 +397,10 @@ __device__ __forceinline__ void pair_item(const StateG& S, double* h, const DemP
             }
         }
         if (at == 0x7fffffff) at = 0;
-        const int u = at / nj, v = at % nj;
-        for (int a = 0; a < 3; ++a) x[a] = 0.5 * (pi[3 * u + a] + pj[3 * v + a] + sh[a]);
+        double p[3], q[3], K;
+        point(at / nj, p, K);
+        point(ni + at % nj, q, K);
+        for (int a = 0; a < 3; ++a) x[a] = 0.5 * (p[a] + q[a]);
     }
     bool conv = false;
     for (int it = 0; it < c.niter; ++it) {
@@ -448,10 +437,8 @@ __device__ __forceinline__ void pair_item(const StateG& S, double* h, const DemP
     }
     // M and grad M of each body at the stationary point
     double MA = 0.0, MB = 0.0, gA[3] = {0, 0, 0}, gB[3] = {0, 0, 0};
-    for (int u = l; u < nt; u += G) {
-        double r[3], K;
-        point(u, r, K);
-        for (int a = 0; a < 3; ++a) r[a] = x[a] - r[a];
+    auto field = [&](int u, double K, const double p[3]) __attribute__((always_inline)) {
+        const double r[3] = {x[0] - p[0], x[1] - p[1], x[2] - p[2]};
         const double i2 = fast_rcp(dot3(r, r)), t = K * i2, s = 2.0 * t * i2;
         if (u < ni) {
             MA += t;
@@ -459,6 +446,17 @@ __device__ __forceinline__ void pair_item(const StateG& S, double* h, const DemP
         } else {
             MB += t;
             for (int a = 0; a < 3; ++a) gB[a] -= s * r[a];
+        }
+    };
+    if (regs) {
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+            if (l + G * k < nt) field(l + G * k, kr[k], pr[k]);
+    } else {
+        for (int u = l; u < nt; u += G) {
+            double p[3], K;
+            point(u, p, K);
+            field(u, K, p);
         }
     }
     if constexpr (G > 1) {
@@ -504,9 +502,9 @@ __device__ __forceinline__ void pair_item(const StateG& S, double* h, const DemP
         rb[a] = xcp[a] - (xj[a] + sh[a]);
     }
     double ca[3], cb[3], vrel[3], Fi[3], ti[3], tj[3], spring[3] = {h[1], h[2], h[3]};
-    cross3(S.omega + 3 * i, ra, ca);
-    cross3(S.omega + 3 * j, rb, cb);
-    for (int a = 0; a < 3; ++a) vrel[a] = (S.vel[3 * i + a] + ca[a]) - (S.vel[3 * j + a] + cb[a]);
+    cross3(A.w, ra, ca);
+    cross3(B.w, rb, cb);
+    for (int a = 0; a < 3; ++a) vrel[a] = (A.v[a] + ca[a]) - (B.v[a] + cb[a]);
     contact_force(c, delta, n, vrel, dt, spring, Fi);
     for (int a = 0; a < 3; ++a) h[1 + a] = spring[a];
     cross3(ra, Fi, ti);
@@ -514,51 +512,84 @@ __device__ __forceinline__ void pair_item(const StateG& S, double* h, const DemP
     emit(Fi, ti, tj);
 }
 
-// Whether particle i can touch wall (ax, side).
-__device__ __forceinline__ bool near_wall(const StateG& S, int i, int ax, int side, const Geom& g)
+// Component a of v (a known at run time).
+__device__ __forceinline__ double component(const double v[3], int a)
 {
-    const double plane = side ? g.n[ax] - 0.5 : -0.5, sgn = side ? -1.0 : 1.0;
-    return !(sgn * (S.pos[3 * i + ax] - plane) > S.reach[i] + S.rs[i]);
+    return a == 0 ? v[0] : (a == 1 ? v[1] : v[2]);
 }
 
-// Contact of particle i with wall (ax, side) near it, record h: in-plane Newton
+// Whether a particle whose centre lies at xa along axis ax can touch that
+// axis's wall on a side.
+__device__ __forceinline__ bool near_wall(double xa, double lim, int ax, int side, const Geom& g)
+{
+    return !((side ? (double)g.n[ax] - 0.5 - xa : xa + 0.5) > lim);
+}
+
+// Contact of particle A with wall (ax, side) near it, record h: in-plane Newton
 // for the point of the wall plane where M is largest, the contact test and the
-// force.
-__device__ __forceinline__ void wall_contact(const StateG& S, double* h, int i, int ax, int side,
-                                             const DemP& c, double dt, const Geom& g)
+// force; the force and its torque go to emit(F, t).
+template <int R, class PA, class Emit>
+__device__ __forceinline__ void wall_contact(const Kin& A, PA&& pa, double* h, int ax, int side,
+                                             const DemP& c, double dt, const Geom& g, Emit&& emit)
 {
     const double plane = side ? g.n[ax] - 0.5 : -0.5, sgn = side ? -1.0 : 1.0;
-    const double xa = S.pos[3 * i + ax];
-    const double active = h[0];
-    const int ai = S.off[i], ni = min(S.off[i + 1] - ai, kMaxPts);
-    const double* pi = S.wpts + 3 * (int64_t)ai;
-    const double* Ki = S.K + ai;
     const int t1 = (ax + 1) % 3, t2 = (ax + 2) % 3;
-    // coordinates along (ax, t1, t2)
-    double y1, y2;
-    if (active != 0.0) {
-        y1 = S.pos[3 * i + t1] + h[4 + t1];
-        y2 = S.pos[3 * i + t2] + h[4 + t2];
-    } else {
-        double best = INFINITY;
-        int at = 0;
-        for (int u = 0; u < ni; ++u) {
-            const double dd = fabs(pi[3 * u + ax] - plane);
-            if (dd < best) {
-                best = dd;
-                at = u;
+    const double xa = component(A.x, ax), x1 = component(A.x, t1), x2 = component(A.x, t2);
+    const double active = h[0];
+    const int ni = A.n;
+    // the points along (ax, t1, t2), up to R in registers: a loop that reads them
+    // from memory again waits for each (1000 metaballs, some near a wall: 36 us a
+    // substep, 17 from registers); from LDS (R = 0) the loop is as good
+    double pr[R ? R : 1][3], kr[R ? R : 1];
+    const bool regs = R && ni <= R && ni > 0;
+    auto load = [&](int u, double r[3], double& K) __attribute__((always_inline)) {
+        double p[3];
+        pa(u, p);
+        r[0] = component(p, ax), r[1] = component(p, t1), r[2] = component(p, t2);
+        K = A.K[u];
+    };
+    if (regs) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) load(min(k, ni - 1), pr[k], kr[k]);
+    }
+    auto each = [&](auto&& fn) __attribute__((always_inline)) {
+        if (regs) {
+#pragma unroll
+            for (int k = 0; k < R; ++k)
+                if (k < ni) fn(pr[k], kr[k]);
+        } else {
+            for (int u = 0; u < ni; ++u) {
+                double p[3], K;
+                load(u, p, K);
+                fn(p, K);
             }
         }
-        y1 = pi[3 * at + t1];
-        y2 = pi[3 * at + t2];
+    };
+    double y1, y2;
+    if (active != 0.0) {
+        y1 = x1 + h[4 + t1];
+        y2 = x2 + h[4 + t2];
+    } else {
+        double best = INFINITY;
+        y1 = y2 = 0.0;
+        bool first = true;
+        each([&](const double p[3], double) __attribute__((always_inline)) {
+            const double dd = fabs(p[0] - plane);
+            if (dd < best || first) {
+                best = dd;
+                y1 = p[1];
+                y2 = p[2];
+            }
+            first = false;
+        });
     }
     bool conv = false;
     for (int it = 0; it < c.niter; ++it) {
         double M = 0.0, gr[3] = {0, 0, 0}, H[6] = {0, 0, 0, 0, 0, 0};
-        for (int u = 0; u < ni; ++u) {
-            const double r[3] = {plane - pi[3 * u + ax], y1 - pi[3 * u + t1], y2 - pi[3 * u + t2]};
-            add_point(Ki[u], r, fast_rcp(dot3(r, r)), M, gr, H);
-        }
+        each([&](const double p[3], double K) __attribute__((always_inline)) {
+            const double r[3] = {plane - p[0], y1 - p[1], y2 - p[2]};
+            add_point(K, r, fast_rcp(dot3(r, r)), M, gr, H);
+        });
         const double h11 = H[3], h12 = H[4], h22 = H[5];
         const double det = h11 * h22 - h12 * h12;
         if (!(fabs(det) > 0.0) || !isfinite(det)) break;
@@ -574,20 +605,20 @@ __device__ __forceinline__ void wall_contact(const StateG& S, double* h, int i, 
     }
     if (!conv) return clear_record(h);
     double M = 0.0, gr[3] = {0, 0, 0};
-    for (int u = 0; u < ni; ++u) {
-        const double r[3] = {plane - pi[3 * u + ax], y1 - pi[3 * u + t1], y2 - pi[3 * u + t2]};
-        const double i2 = fast_rcp(dot3(r, r)), t = Ki[u] * i2, s = 2.0 * t * i2;
+    each([&](const double p[3], double K) __attribute__((always_inline)) {
+        const double r[3] = {plane - p[0], y1 - p[1], y2 - p[2]};
+        const double i2 = fast_rcp(dot3(r, r)), t = K * i2, s = 2.0 * t * i2;
         M += t;
         for (int a = 0; a < 3; ++a) gr[a] -= s * r[a];
-    }
+    });
     if (!(sgn * gr[0] > 0.0)) return clear_record(h);
-    const double rel[3] = {plane - xa, y1 - S.pos[3 * i + t1], y2 - S.pos[3 * i + t2]};
+    const double rel[3] = {plane - xa, y1 - x1, y2 - x2};
     h[0] = 1.0;
     h[4 + ax] = rel[0];
     h[4 + t1] = rel[1];
     h[4 + t2] = rel[2];
     const double qR = (1.0 - M) * fast_rcp(dot3(gr, gr));
-    const double delta = S.rs[i] - sgn * (qR * gr[0]);
+    const double delta = A.rs - sgn * (qR * gr[0]);
     if (delta <= 0.0) {
         h[1] = h[2] = h[3] = 0.0;
         return;
@@ -599,15 +630,12 @@ __device__ __forceinline__ void wall_contact(const StateG& S, double* h, int i, 
         ra[a] = (a == ax ? rel[0] : (a == t1 ? rel[1] : rel[2])) - 0.5 * delta * n[a];
     }
     double ca[3], vrel[3], Fi[3], tq[3], spring[3] = {h[1], h[2], h[3]};
-    cross3(S.omega + 3 * i, ra, ca);
-    for (int a = 0; a < 3; ++a) vrel[a] = S.vel[3 * i + a] + ca[a];
+    cross3(A.w, ra, ca);
+    for (int a = 0; a < 3; ++a) vrel[a] = A.v[a] + ca[a];
     contact_force(c, delta, n, vrel, dt, spring, Fi);
     cross3(ra, Fi, tq);
-    for (int a = 0; a < 3; ++a) {
-        h[1 + a] = spring[a];
-        atomicAdd(S.fc + 6 * i + a, Fi[a]);
-        atomicAdd(S.fc + 6 * i + 3 + a, tq[a]);
-    }
+    for (int a = 0; a < 3; ++a) h[1 + a] = spring[a];
+    emit(Fi, tq);
 }
 
 // ---------------------------------------------------------------------------
@@ -662,17 +690,91 @@ __device__ __forceinline__ void claim(Slots& s, bool take, int jj)
     }
 }
 
-// Reach, R_s and the candidate bound of every particle; the pair list emptied.
-__global__ __launch_bounds__(64) void k_reach(PartDev P, double T, double* rch, double* bound,
-                                              uint32_t* count)
+// What a call of many particles keeps of each between its launches, one or two
+// lines a particle: its constants (half step over the mass and the moments,
+// Euler's terms, F^h + relative gravity, T^h, R_s, reach, points), its state at
+// two substeps in turn (x, v, q, angular velocity in the body frame), and the
+// contact sums of three.
+constexpr int kCon = 16, kState = 16, kSums = 8;
+struct Ws {
+    double* con;
+    double* st[2];
+    double* sum[3];
+    int last;  // the last control point
+};
+inline Ws ws_of(double* at, int n, int n_ctrl)
+{
+    Ws w;
+    w.last = n_ctrl - 1;
+    w.con = at;
+    w.st[0] = at + (int64_t)kCon * n;
+    w.st[1] = w.st[0] + (int64_t)kState * n;
+    for (int k = 0; k < 3; ++k) w.sum[k] = w.st[1] + (int64_t)kState * n + (int64_t)kSums * n * k;
+    return w;
+}
+static_assert(kDemStateDoubles == kCon + 2 * kState + 3 * kSums, "work space of a particle");
+
+__device__ __forceinline__ void save_state(double* st, const Body& b)
+{
+    for (int a = 0; a < 3; ++a) {
+        st[a] = b.x[a];
+        st[3 + a] = b.v[a];
+        st[10 + a] = b.wb[a];
+    }
+    for (int a = 0; a < 4; ++a) st[6 + a] = b.q[a];
+}
+// The body without its rotation matrix, and its contact view.
+__device__ __forceinline__ Body load_state(const double* con, const double* st)
+{
+    Body b;
+    b.hm = con[0];
+    for (int a = 0; a < 3; ++a) {
+        b.F[a] = con[1 + a];
+        b.T[a] = con[4 + a];
+        b.hI[a] = con[7 + a];
+        b.kI[a] = con[10 + a];
+        b.x[a] = st[a];
+        b.v[a] = st[3 + a];
+        b.wb[a] = st[10 + a];
+    }
+    for (int a = 0; a < 4; ++a) b.q[a] = st[6 + a];
+    const int2 pts = *reinterpret_cast<const int2*>(con + 15);
+    b.c0 = pts.x;
+    b.c1 = pts.y;
+    return b;
+}
+
+// Every particle's reach, candidate bound, constants, state and carried contact
+// sum; the pair list emptied.
+__global__ __launch_bounds__(64) void k_open(PartDev P, const double* FTh, const double* fc, DemP c,
+                                             double dt, double T, double* rch, double* bound, Ws w,
+                                             uint32_t* count)
 {
     const int p = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (p == 0) *count = 0u;
     if (p >= P.n) return;
-    const double r = reach(P, p);
-    const double* v = P.vel + 3 * p;
+    const Body b = load_body(P, p, FTh, c, 0.5 * dt);
+    double f[6];
+    for (int k = 0; k < 6; ++k) f[k] = fc[6 * p + k];
+    const double rs = P.rs[p], r = reach(P, p);
     rch[p] = r;
-    bound[p] = r + P.rs[p] + sqrt(dot3(v, v)) * T + 0.25;
+    bound[p] = r + rs + sqrt(dot3(b.v, b.v)) * T + 0.25;
+    double* con = w.con + (int64_t)kCon * p;
+    con[0] = b.hm;
+    for (int a = 0; a < 3; ++a) {
+        con[1 + a] = b.F[a];
+        con[4 + a] = b.T[a];
+        con[7 + a] = b.hI[a];
+        con[10 + a] = b.kI[a];
+    }
+    con[13] = rs;
+    con[14] = r;
+    *reinterpret_cast<int2*>(con + 15) = make_int2(b.c0, b.c1);
+    save_state(w.st[1] + (int64_t)kState * p, b);
+    for (int k = 0; k < 6; ++k) {
+        w.sum[2][(int64_t)kSums * p + k] = f[k];
+        w.sum[0][(int64_t)kSums * p + k] = 0.0;
+    }
 }
 
 // The cells around c along an axis of nc: lo, lo + 1, ... (n of them), wrapped
@@ -986,44 +1088,118 @@ __global__ __launch_bounds__(256) void k_grid_scatter(PartDev P, Geom g, const i
 // Substeps, many particles
 // ---------------------------------------------------------------------------
 
-// One substep's contacts: the first workgroups take the walls of the
-// non-periodic axes (a thread per particle and wall), the others stride over
-// the listed pairs, G lanes each.
-template <int G>
-__global__ __launch_bounds__(256) void k_contacts(PartDev P, double* hist, double* hist_w, double* fc,
-                                                  const double* rch, DemP c, double dt, Geom g,
-                                                  const uint64_t* list, const uint32_t* count,
-                                                  uint32_t wall_blocks, int n_axes, int ax0, int ax1,
-                                                  int ax2)
+// One substep in one launch: whoever needs a particle's new state forms it from
+// the last substep's state and contact sum (the second half kick of that
+// substep, but not before the first, then the first half kick, the drift and
+// the rotation), so no launch in between has to.  The first workgroups take
+// the particles (a thread per particle and wall of a non-periodic axis; the
+// first of each particle keeps the new state and clears the next contact sum),
+// the others stride over the listed pairs, G lanes each: the positions first,
+// and only for a pair within reach the rotations, one body to a lane and
+// exchanged between neighbouring lanes.  What bounds it is the one chain of a
+// pair or wall in contact (loads, Newton, additions), so a launch less and the
+// points in registers tell.  Against a launch for the contacts and one for the
+// advance, ten substeps: 1000 metaballs 235 -> 190 us, 125 186 -> 163, 100
+// spheres 112 -> 101, 8000 packed ones 156 -> 136; with several waves for every
+// SIMD the state that each pair forms again is no longer free: 27 000 spheres
+// 302 -> 310.
+template <bool FIRST>
+__device__ __forceinline__ void advance_centre(Body& b, const double f[6], double dt, const Geom& g)
 {
-    const StateG S{P.pos, P.vel, P.omega, P.rs, rch, fc, P.off, P.wpts, P.K};
-    if (blockIdx.x < wall_blocks) {
+    const Kick k = kick_of(b, f);
+    if (!FIRST) kick_v(b, k);
+    kick_v(b, k);
+    move(b, dt, g);
+}
+template <bool FIRST>
+__device__ __forceinline__ void advance_rotation(Body& b, const double f[6], double dt)
+{
+    rotmat(b.q, b.R);
+    const Kick k = kick_of(b, f);
+    if (!FIRST) kick_w<true>(b, k);
+    kick_w<false>(b, k);
+    to_world(b);
+    rotate(b, dt);
+}
+
+// (spheres: two waves a SIMD, 8000 of them 142 -> 136 us, 27 000 399 -> 310;
+// metaballs: the points take the registers)
+template <int G, bool FIRST>
+__global__ __launch_bounds__(256, G == 2 ? 2 : 1) void k_substep(PartDev P, Ws w, int s, double* hist, double* hist_w,
+                                                 DemP c, double dt, Geom g, const uint64_t* list,
+                                                 const uint32_t* count, uint32_t own_blocks, int n_axes,
+                                                 int ax0, int ax1, int ax2)
+{
+    const double *con = w.con, *st = w.st[(s + 1) & 1], *sum = w.sum[(s + 2) % 3];
+    double *out = w.st[s & 1], *add_to = w.sum[s % 3], *next = w.sum[(s + 1) % 3];
+    auto sums_of = [&](int p, double f[6]) {
+        for (int k = 0; k < 6; ++k) f[k] = sum[(int64_t)kSums * p + k];
+    };
+    auto kin_of = [&](const Body& b, int p) {
+        Kin k;
+        for (int a = 0; a < 3; ++a) {
+            k.x[a] = b.x[a];
+            k.v[a] = b.v[a];
+            k.w[a] = b.w[a];
+        }
+        k.rs = con[(int64_t)kCon * p + 13];
+        k.reach = con[(int64_t)kCon * p + 14];
+        k.K = P.K + b.c0;
+        k.n = min(b.c1 - b.c0, kMaxPts);
+        return k;
+    };
+    // world coordinates of control point u of a body with centre x, matrix R
+    auto world = [&](const double x[3], const double R[9], int c0, int u, double r[3]) {
+        const double* bp = P.body_pts + 3 * (int64_t)(c0 + u);
+        for (int a = 0; a < 3; ++a)
+            r[a] = x[a] + (R[3 * a] * bp[0] + R[3 * a + 1] * bp[1] + R[3 * a + 2] * bp[2]);
+    };
+    if (blockIdx.x < own_blocks) {
         const int t = (int)(blockIdx.x * 256u + threadIdx.x);
-        const int per = 2 * n_axes;
+        const int per = max(2 * n_axes, 1);
         if (t >= P.n * per) return;
-        const int k = (t % per) >> 1, i = t / per, side = t & 1;
+        const int i = t / per, k = (t % per) >> 1, side = t & 1;
         const int ax = k == 0 ? ax0 : (k == 1 ? ax1 : ax2);
+        Body b = load_state(con + (int64_t)kCon * i, st + (int64_t)kState * i);
+        double f[6];
+        sums_of(i, f);
         double* h = hist_w + ((int64_t)i * 6 + 2 * ax + side) * kHist;
-        if (near_wall(S, i, ax, side, g))
-            wall_contact(S, h, i, ax, side, c, dt, g);
-        else if (h[0] != 0.0)
-            clear_record(h);
+        const double active = n_axes ? h[0] : 0.0;
+        const double lim = con[(int64_t)kCon * i + 13] + con[(int64_t)kCon * i + 14];
+        advance_centre<FIRST>(b, f, dt, g);
+        const bool keep = t % per == 0, near = n_axes && near_wall(component(b.x, ax), lim, ax, side, g);
+        if (keep || near) {
+            advance_rotation<FIRST>(b, f, dt);
+            if (keep) {
+                save_state(out + (int64_t)kState * i, b);
+                for (int a = 0; a < 6; ++a) next[(int64_t)kSums * i + a] = 0.0;
+            }
+            if (near)
+                wall_contact<G == 2 ? 1 : 8>(kin_of(b, i), [&](int u, double r[3]) { world(b.x, b.R, b.c0, u, r); }, h,
+                             ax, side, c, dt, g, [&](const double F[3], const double tq[3]) {
+                                 for (int a = 0; a < 3; ++a) {
+                                     atomicAdd(add_to + (int64_t)kSums * i + a, F[a]);
+                                     atomicAdd(add_to + (int64_t)kSums * i + 3 + a, tq[a]);
+                                 }
+                             });
+        }
+        if (!near && active != 0.0) clear_record(h);
         return;
     }
     // the wave's contacts, gathered so that consecutive lanes add the twelve
     // numbers of one: the sums of a particle lie in one line, and six lanes'
     // additions to it are one request (a lane that adds its own contact's
     // numbers one after the other makes twelve: 8000 packed spheres 15.2 us a
-    // substep, 8.0 of them without any addition)
+    // substep's contacts, 8.0 of them without any addition; so 9.4)
     constexpr int kPairs = 64 / G;
     __shared__ double add[4][12 * kPairs];
     __shared__ int who[4][2 * kPairs];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l = lane % G;
     double* wa = add[wave];
     int* ww = who[wave];
     const uint32_t n = *count;
-    const uint32_t stride = (gridDim.x - wall_blocks) * (256u / G);
-    for (uint32_t t0 = (blockIdx.x - wall_blocks) * (256u / G) + (uint32_t)(wave * kPairs); t0 < n;
+    const uint32_t stride = (gridDim.x - own_blocks) * (256u / G);
+    for (uint32_t t0 = (blockIdx.x - own_blocks) * (256u / G) + (uint32_t)(wave * kPairs); t0 < n;
          t0 += stride) {  // uniform over the wave
         const uint32_t t = t0 + (uint32_t)(lane / G);
         int i = 0, j = 0;
@@ -1032,16 +1208,64 @@ __global__ __launch_bounds__(256) void k_contacts(PartDev P, double* hist, doubl
         if (t < n) {
             const uint64_t e = list[t];
             i = (int)((e >> 16) & 0xffffu), j = (int)(e & 0xffffu);
-            pair_item<G>(S, hist + ((int64_t)i * kPairSlots + (int)(e >> 32)) * kHist, c, dt, g, i, j,
-                         lane % G, [&](const double F[3], const double ti[3], const double tj[3]) {
-                             on = true;
-                             for (int a = 0; a < 3; ++a) {
-                                 v[a] = F[a];
-                                 v[3 + a] = ti[a];
-                                 v[6 + a] = -F[a];
-                                 v[9 + a] = -tj[a];
-                             }
-                         });
+            double* h = hist + ((int64_t)i * kPairSlots + (int)(e >> 32)) * kHist;
+            const double active = h[0];
+            Body A = load_state(con + (int64_t)kCon * i, st + (int64_t)kState * i);
+            Body B = load_state(con + (int64_t)kCon * j, st + (int64_t)kState * j);
+            double fA[6], fB[6], sh[3];
+            sums_of(i, fA);
+            sums_of(j, fB);
+            Kin kA = kin_of(A, i), kB = kin_of(B, j);
+            advance_centre<FIRST>(A, fA, dt, g);
+            advance_centre<FIRST>(B, fB, dt, g);
+            if (near_pair(A.x, B.x, kA.reach + kB.reach + kA.rs + kB.rs, g, sh)) {
+                // odd lanes turn B, even lanes A (the same branch for a group)
+                const bool second = l & 1;
+                Body M = second ? B : A;
+                double f[6];
+                for (int k = 0; k < 6; ++k) f[k] = second ? fB[k] : fA[k];
+                advance_rotation<FIRST>(M, f, dt);
+                for (int k = 0; k < 9; ++k) {
+                    const double o = quad_perm<0xB1>(M.R[k]);
+                    A.R[k] = second ? o : M.R[k];
+                    B.R[k] = second ? M.R[k] : o;
+                }
+                for (int a = 0; a < 3; ++a) {
+                    const double o = quad_perm<0xB1>(M.w[a]);
+                    kA.w[a] = second ? o : M.w[a];
+                    kB.w[a] = second ? M.w[a] : o;
+                    kA.x[a] = A.x[a], kA.v[a] = A.v[a];
+                    kB.x[a] = B.x[a], kB.v[a] = B.v[a];
+                }
+                auto point = [&](int u, double r[3], double& K) __attribute__((always_inline)) {
+                    const bool of_b = u >= kA.n;
+                    // (a body without points is an error, reported: no read beyond)
+                    const int at = min(max(of_b ? B.c0 + (u - kA.n) : A.c0 + u, 0), w.last);
+                    const double* bp = P.body_pts + 3 * (int64_t)at;
+                    const double b0 = bp[0], b1 = bp[1], b2 = bp[2];
+                    K = P.K[at];
+                    for (int a = 0; a < 3; ++a) {
+                        const double x = of_b ? B.x[a] + sh[a] : A.x[a];
+                        r[a] = x + ((of_b ? B.R[3 * a] : A.R[3 * a]) * b0 +
+                                    (of_b ? B.R[3 * a + 1] : A.R[3 * a + 1]) * b1 +
+                                    (of_b ? B.R[3 * a + 2] : A.R[3 * a + 2]) * b2);
+                    }
+                };
+                pair_item<G>(kA, kB, sh, point, h, c, dt, l,
+                             [&](const double F[3], const double ti[3], const double tj[3]) {
+                                 on = true;
+                                 for (int a = 0; a < 3; ++a) {
+                                     v[a] = F[a];
+                                     v[3 + a] = ti[a];
+                                     v[6 + a] = -F[a];
+                                     v[9 + a] = -tj[a];
+                                 }
+                             });
+            } else if (active != 0.0 && l == 0) {
+                // out of reach: forget the pair's contact (read one double
+                // instead of writing eight when the record is zero already)
+                clear_record(h);
+            }
         }
         const uint64_t m = __ballot(on);
         if (!m) continue;
@@ -1056,35 +1280,30 @@ __global__ __launch_bounds__(256) void k_contacts(PartDev P, double* hist, doubl
         const int total = 12 * __popcll(m);
         for (int u = lane; u < total; u += 64) {
             const int q = u / 6;
-            atomicAdd(fc + 6 * (int64_t)ww[q] + (u - 6 * q), wa[u]);
+            atomicAdd(add_to + (int64_t)kSums * ww[q] + (u - 6 * q), wa[u]);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
 }
 
-// SECOND: the second half kick of a substep; FIRST: the first half kick,
-// drift, rotation and world control points of the next, clearing the contact
-// sums.  Both read the contact sum of the substep before.
-template <bool SECOND, bool FIRST>
-__global__ __launch_bounds__(64) void k_advance(PartDev P, const double* FTh, double* fc, DemP c,
-                                                double dt, Geom g)
+// The last substep's second half kick, and the caller's arrays.
+__global__ __launch_bounds__(64) void k_close(PartDev P, Ws w, int n_sub, double* fc)
 {
     const int p = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (p >= P.n) return;
-    Body b = load_body(P, p, FTh, c, 0.5 * dt);
+    Body b = load_state(w.con + (int64_t)kCon * p, w.st[(n_sub + 1) & 1] + (int64_t)kState * p);
+    const double* sum = w.sum[(n_sub + 2) % 3] + (int64_t)kSums * p;
     double f[6];
-    for (int k = 0; k < 6; ++k) f[k] = fc[6 * p + k];
+    for (int k = 0; k < 6; ++k) f[k] = sum[k];
+    rotmat(b.q, b.R);
     const Kick k = kick_of(b, f);
-    if constexpr (SECOND) half_kick<true>(b, k);
-    if constexpr (FIRST) half_kick<false>(b, k);
+    kick_v(b, k);
+    kick_w<true>(b, k);
     to_world(b);
-    if constexpr (FIRST) {
-        drift(b, dt, g);
-        place_points<4>(b, b.c0, b.c1, P.body_pts, P.wpts);
-        for (int a = 0; a < 6; ++a) fc[6 * p + a] = 0.0;
-    }
-    store_body(P, p, b, FIRST);
+    for (int a = 0; a < 6; ++a) fc[6 * p + a] = f[a];
+    store_body(P, p, b, true);
+    place_points<4>(b, b.c0, b.c1, P.body_pts, P.wpts);
 }
 
 // ---------------------------------------------------------------------------
@@ -1118,7 +1337,25 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
     __shared__ uint32_t npairs;
     const int tid = (int)threadIdx.x, lane = tid & 63, n = P.n;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const StateG S{pos, vel, om, rs, rch, sum, off, world, K};
+    auto kin = [&](int i) {
+        Kin k;
+        for (int a = 0; a < 3; ++a) {
+            k.x[a] = pos[3 * i + a];
+            k.v[a] = vel[3 * i + a];
+            k.w[a] = om[3 * i + a];
+        }
+        k.rs = rs[i];
+        k.reach = rch[i];
+        k.K = K + off[i];
+        k.n = min(off[i + 1] - off[i], kMaxPts);
+        return k;
+    };
+    auto points = [&](int i) {
+        const double* p = world + 3 * off[i];
+        return [p](int u, double r[3]) {
+            for (int a = 0; a < 3; ++a) r[a] = p[3 * u + a];
+        };
+    };
     const int p0 = P.off[0], np = min(P.off[n] - p0, kBlockPoints);
     if (tid == 0) npairs = 0u;
     if (tid <= n) off[tid] = min(P.off[tid] - p0, kBlockPoints);
@@ -1177,14 +1414,17 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
         if (on) {
             b = load_body(P, tid, FTh, c, 0.5 * dt);
             for (int k = 0; k < 6; ++k) f[k] = fc[6 * tid + k];
-            half_kick<false>(b, kick_of(b, f));
+            const Kick k0 = kick_of(b, f);
+            kick_v(b, k0);
+            kick_w<false>(b, k0);
             for (int k = 0; k < 6; ++k) live |= wall[(6 * tid + k) * kHist] != 0.0 ? 1u << k : 0u;
             lim = rch[tid] + rs[tid];
         }
         for (int sub = 0; sub < n_sub; ++sub) {
             if (on) {
                 to_world(b);
-                drift(b, dt, g);
+                move(b, dt, g);
+                rotate(b, dt);
                 place_points<1>(b, off[tid], off[tid + 1], body, world);
                 for (int a = 0; a < 3; ++a) {
                     pos[3 * tid + a] = b.x[a];
@@ -1205,7 +1445,13 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
                     const int k = __ffs(m) - 1;
                     double* h = wall + (6 * tid + k) * kHist;
                     if ((near >> k) & 1u) {
-                        wall_contact(S, h, tid, k >> 1, k & 1, c, dt, g);
+                        wall_contact<0>(kin(tid), points(tid), h, k >> 1, k & 1, c, dt, g,
+                                     [&](const double F[3], const double t[3]) {
+                                         for (int a = 0; a < 3; ++a) {
+                                             atomicAdd(sum + 6 * tid + a, F[a]);
+                                             atomicAdd(sum + 6 * tid + 3 + a, t[a]);
+                                         }
+                                     });
                         live |= 1u << k;
                     } else {
                         clear_record(h);
@@ -1217,8 +1463,12 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
             if (on) {
                 for (int k = 0; k < 6; ++k) f[k] = sum[6 * tid + k];
                 const Kick k = kick_of(b, f);
-                half_kick<true>(b, k);
-                if (sub + 1 < n_sub) half_kick<false>(b, k);
+                kick_v(b, k);
+                kick_w<true>(b, k);
+                if (sub + 1 < n_sub) {
+                    kick_v(b, k);
+                    kick_w<false>(b, k);
+                }
             }
         }
         if (on) {
@@ -1238,6 +1488,20 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
                 }
             };
         };
+        auto contact = [&](int i, int j, double* h) {
+            const Kin a = kin(i), b = kin(j);
+            double sh[3];
+            auto point = [&](int u, double r[3], double& Ku) __attribute__((always_inline)) {
+                const bool of_b = u >= a.n;
+                const int at = of_b ? off[j] + (u - a.n) : off[i] + u;
+                for (int k = 0; k < 3; ++k) r[k] = world[3 * at + k] + (of_b ? sh[k] : 0.0);
+                Ku = K[at];
+            };
+            if (near_pair(a.x, b.x, a.reach + b.reach + a.rs + b.rs, g, sh))
+                pair_item<kPairLanes>(a, b, sh, point, h, c, dt, l, adder(i, j));
+            else if (l == 0 && h[0] != 0.0)
+                clear_record(h);  // out of reach: forget the pair's contact
+        };
         const int total = (int)npairs;
         const bool mine = group < total;
         const uint64_t e0 = mine ? list[group] : 0;
@@ -1248,12 +1512,11 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
             for (int k = l; k < kHist; k += kPairLanes) h0[k] = g0[k];
         for (int sub = 0; sub < n_sub; ++sub) {
             __syncthreads();
-            if (mine) pair_item<kPairLanes>(S, h0, c, dt, g, i0, j0, l, adder(i0, j0));
+            if (mine) contact(i0, j0, h0);
             for (int t = group + kPairGroups; t < total; t += kPairGroups) {
                 const uint64_t e = list[t];
                 const int i = (int)((e >> 16) & 0xffffu), j = (int)(e & 0xffffu);
-                pair_item<kPairLanes>(S, hist + ((int64_t)i * kPairSlots + (int)(e >> 32)) * kHist, c,
-                                      dt, g, i, j, l, adder(i, j));
+                contact(i, j, hist + ((int64_t)i * kPairSlots + (int)(e >> 32)) * kHist);
             }
             __syncthreads();
         }
@@ -1294,7 +1557,9 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
     }
     const uint32_t bp = (uint32_t)(np + 63) / 64, bw = (uint32_t)(np + 15) / 16;
     const double T = (double)n_sub * dt;
-    hipLaunchKernelGGL(k_reach, dim3(bp), dim3(64), 0, ctx->stream, P, T, ws.reach, ws.bound, ws.count);
+    const Ws w = ws_of(ws.state, np, (int)ctx->cfg.n_ctrl);
+    hipLaunchKernelGGL(k_open, dim3(bp), dim3(64), 0, ctx->stream, P, ctx->FT, ctx->fc, c, dt, T, ws.reach,
+                       ws.bound, w, ws.count);
     if (ws.gcount && np >= kGridMinParticles) {
         if (np <= kGridBlock) {
             hipLaunchKernelGGL(k_grid_block, dim3(1), dim3(1024), 0, ctx->stream, P, ws.reach, T, g,
@@ -1321,25 +1586,20 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
     int axes[3] = {0, 0, 0}, n_axes = 0;
     for (int a = 0; a < 3; ++a)
         if (!g.per[a]) axes[n_axes++] = a;
-    const uint32_t wb = (uint32_t)(((int64_t)np * 2 * n_axes + 255) / 256);
+    const uint32_t wb = (uint32_t)(((int64_t)np * std::max(2 * n_axes, 1) + 255) / 256);
     // lanes for eight pairs a particle (more stride over the list)
     // (spheres: two control points a pair)
-    const int lanes = ctx->cfg.n_ctrl > np ? kPairLanes : 2;
+    const bool spheres = ctx->cfg.n_ctrl <= np;
+    const int lanes = spheres ? 2 : kPairLanes;
     const uint32_t pb = (uint32_t)std::min<int64_t>(((int64_t)np * 8 * lanes + 255) / 256, 2048);
-    const auto contacts = lanes == 2 ? k_contacts<2> : k_contacts<kPairLanes>;
-    hipLaunchKernelGGL((k_advance<false, true>), dim3(bp), dim3(64), 0, ctx->stream, P, ctx->FT,
-                       ctx->fc, c, dt, g);
     for (int s = 0; s < n_sub; ++s) {
-        hipLaunchKernelGGL(contacts, dim3(wb + pb), dim3(256), 0, ctx->stream, P,
-                           ctx->hist_pp, ctx->hist_pw, ctx->fc, ws.reach, c, dt, g, ws.pairs, ws.count,
-                           wb, n_axes, axes[0], axes[1], axes[2]);
-        if (s + 1 < n_sub)
-            hipLaunchKernelGGL((k_advance<true, true>), dim3(bp), dim3(64), 0, ctx->stream, P, ctx->FT,
-                               ctx->fc, c, dt, g);
-        else
-            hipLaunchKernelGGL((k_advance<true, false>), dim3(bp), dim3(64), 0, ctx->stream, P,
-                               ctx->FT, ctx->fc, c, dt, g);
+        const auto substep = spheres ? (s ? k_substep<2, false> : k_substep<2, true>)
+                                     : (s ? k_substep<kPairLanes, false> : k_substep<kPairLanes, true>);
+        hipLaunchKernelGGL(substep, dim3(wb + pb), dim3(256), 0, ctx->stream, P, w, s, ctx->hist_pp,
+                           ctx->hist_pw, c, dt, g, ws.pairs, ws.count, wb, n_axes, axes[0], axes[1],
+                           axes[2]);
     }
+    hipLaunchKernelGGL(k_close, dim3(bp), dim3(64), 0, ctx->stream, P, w, n_sub, ctx->fc);
     return hipGetLastError();
 }
 
@@ -1354,7 +1614,7 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
 namespace {
 constexpr size_t kNoAllocHead = 64;  // 8-byte words before the reach
 constexpr size_t kNoAllocWords =
-    kNoAllocHead + 2 * (size_t)kNoAllocParticles + (size_t)kNoAllocParticles * kPairSlots;
+    kNoAllocHead + (2 + kPairSlots + kDemStateDoubles) * (size_t)kNoAllocParticles;
 __device__ __align__(256) uint64_t scratch[kNoAllocWords];
 
 constexpr int kMaxDevices = 64;
@@ -1390,6 +1650,7 @@ bool dem_noalloc_scratch(int dev, DemScratch* out)
     out->reach = reinterpret_cast<double*>(base + kNoAllocHead);
     out->bound = out->reach + kNoAllocParticles;
     out->pairs = base + kNoAllocHead + 2 * kNoAllocParticles;
+    out->state = reinterpret_cast<double*>(out->pairs + kNoAllocParticles * kPairSlots);
     return true;
 }
 

@@ -257,6 +257,7 @@ struct lbm_ctx {
     uint32_t* numeric = nullptr;  // set by a step whose force or torque sums are not finite
     uint64_t* pairs = nullptr;    // [np kPairSlots] candidate pairs of a dem_step call
     uint32_t* pair_count = nullptr;
+    double* dem_state = nullptr;  // work space of a dem_step call
     uint32_t* grid = nullptr;     // the broad phase's cell grid (kGridMinParticles or more)
     double* grid_size = nullptr;
     int64_t grid_cap = 0;
@@ -326,6 +327,7 @@ namespace q15 {
 }
 
 // Launchers (lbm_dem.hip, lbm_dem_adjoint.hip)
+constexpr int kDemStateDoubles = 72;
 // Work space of one dem_step call: the candidate pairs (i, j, history slot),
 // their count, and each particle's reach and broad-phase bound.
 // The work space of one dem_step call.  With the cell grid (gcount not
@@ -337,6 +339,7 @@ struct DemScratch {
     uint32_t* count;
     double* reach;
     double* bound;                // [n]: a pair's candidate distance is the sum of its two
+    double* state = nullptr;      // [n][kDemStateDoubles]: constants, states, contact sums
     uint32_t* gcount = nullptr;   // [gcap + 1]: counts per cell, then their starts
     uint32_t* gcursor = nullptr;  // [gcap]
     uint32_t* gitem = nullptr;    // [n]: particles by cell
