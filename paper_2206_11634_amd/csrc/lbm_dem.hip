@@ -1607,9 +1607,9 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
 // The allocation-free work space of dem_step_noalloc: one static array per
 // device (module-scope device memory, loaded with the code object), laid out
 // as the pair count (first 512 bytes), the reach and the candidate bound of up
-// to kNoAllocParticles particles, then up to kNoAllocParticles * kPairSlots pair entries.  Host
-// code never uses the array's name as an address: the device address is
-// looked up once per device and kept.
+// to kNoAllocParticles particles, then up to kNoAllocParticles * kPairSlots pair
+// entries and the particles' states and sums.  Host code never uses the array's
+// name as an address: the device address is looked up once per device and kept.
 // ---------------------------------------------------------------------------
 namespace {
 constexpr size_t kNoAllocHead = 64;  // 8-byte words before the reach
