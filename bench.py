@@ -27,8 +27,8 @@ METRIC = "MLUPS + % HBM roofline (FP32/FP16-store vs plain), drag err; adjoint s
 # WRITE_SIZE passes (scaled by a copy kernel of known size; see profiles/),
 # valid only for the kernel source they were taken on.
 MEASURED_TRAFFIC = {
-    ("c4_sediment_512cube_1000p", "f32"): dict(source_sha256_16="a244481d9894da87",
-                                              read=10.294e9, written=12.348e9),
+    ("c4_sediment_512cube_1000p", "f32"): dict(source_sha256_16="8140312bcf1913e5",
+                                              read=10.352e9, written=12.348e9),
 }
 HBM_PEAK_GBS = 8000.0
 BYTES = {"f64": 8, "f32": 4, "f16": 2}

@@ -334,7 +334,7 @@ __global__ __launch_bounds__(256) void k_begin(PartDev P, int h, double* ball, u
 // Which nodes are visited.  If every control point lies farther than
 // rho = sqrt(sum_i K_i / c0) from a node, M_p < c0 there, so p's body lies
 // in the union of the balls (x_i, rho); it also lies in the ball (x_p, R) of
-// k_boxes.  One workgroup takes one z plane of p's box: for every row y of the
+// k_begin.  One workgroup takes one z plane of p's box: for every row y of the
 // plane it takes the x range of the union's hull on that row intersected with
 // the centre ball, cuts it into segments of 8 nodes, lists them in LDS (a
 // prefix sum over the rows places them) and hands them to its lanes, so a lane
@@ -809,7 +809,7 @@ __global__ __launch_bounds__(256, FINISH ? 5 : 6) void k_links(const uint32_t* _
     }
 }
 
-// The same as k_finish over the whole lattice (four consecutive nodes per
+// Flags and refill list from the whole lattice (four consecutive nodes per
 // thread, 16-byte owner loads), used when the balls cover most of the lattice
 // and a coalesced sweep is cheaper.
 __global__ __launch_bounds__(256) void k_finish_all(const uint32_t* __restrict__ err, const uint32_t* own_prev,
@@ -855,7 +855,7 @@ __global__ __launch_bounds__(256) void k_finish_all(const uint32_t* __restrict__
     }
 }
 
-// Dense mode, bodies moved less than the guard of k_boxes: the flags of the
+// Dense mode, bodies moved less than the guard of k_begin: the flags of the
 // nodes that left a body and the refill list, from the previous
 // classification's candidate lists (a node solid then and fluid now was
 // within reach of the old surface, hence a candidate).  New solid nodes got
