@@ -27,7 +27,7 @@ METRIC = "MLUPS + % HBM roofline (FP32/FP16-store vs plain), drag err; adjoint s
 # WRITE_SIZE passes (scaled by a copy kernel of known size; see profiles/),
 # valid only for the kernel source they were taken on.
 MEASURED_TRAFFIC = {
-    ("c4_sediment_512cube_1000p", "f32"): dict(source_sha256_16="8140312bcf1913e5",
+    ("c4_sediment_512cube_1000p", "f32"): dict(source_sha256_16="780bff85a0cc6656",
                                               read=10.352e9, written=12.348e9),
 }
 HBM_PEAK_GBS = 8000.0
@@ -113,7 +113,7 @@ def _stream_source_hash():
             return fh.read()
 
     stream = read("lbm_stream.hip")
-    k = re.search(r"template <int S>\n__global__[^\n]*k_stream_collide\(.*?\n}\n", stream, re.S)
+    k = re.search(r"template <int S, bool NT>\n__global__[^\n]*k_stream_collide\(.*?\n}\n", stream, re.S)
     m = re.search(r"__device__ __forceinline__ uint32_t xcd_block\(\).*?\n}\n", stream, re.S)
     internal = read("lbm_internal.h")
     parts = [k.group(0) if k else stream, m.group(0) if m else stream, read("lbm_kernels.h"),

@@ -30,6 +30,7 @@ struct St<LBM_STORE_F64> {
     // as stored, without the scale of half deviations
     static __device__ __forceinline__ double raw(const double* p) { return *p; }
     static __device__ __forceinline__ void put(double* p, double v) { *p = v; }
+    static __device__ __forceinline__ void put_nt(double* p, double v) { __builtin_nontemporal_store(v, p); }
     static constexpr bool scaled = false;
     static __device__ __forceinline__ void st_mom(M* p, double d, double x, double y, double z, float)
     {
@@ -52,6 +53,7 @@ struct St<LBM_STORE_F32> {
     static __device__ __forceinline__ void st(float* p, float v, float) { *p = v; }
     static __device__ __forceinline__ float raw(const float* p) { return *p; }
     static __device__ __forceinline__ void put(float* p, float v) { *p = v; }
+    static __device__ __forceinline__ void put_nt(float* p, float v) { __builtin_nontemporal_store(v, p); }
     static constexpr bool scaled = false;
     static __device__ __forceinline__ void st_mom(M* p, float d, float x, float y, float z, float)
     {
@@ -80,6 +82,10 @@ struct St<LBM_STORE_F16> {
     }
     static __device__ __forceinline__ float raw(const __half* p) { return __half2float(*p); }
     static __device__ __forceinline__ void put(__half* p, float v) { *p = __float2half_rn(v); }
+    static __device__ __forceinline__ void put_nt(__half* p, float v)
+    {
+        __builtin_nontemporal_store((_Float16)v, reinterpret_cast<_Float16*>(p));
+    }
     static constexpr bool scaled = true;
     static __device__ __forceinline__ void st_mom(M* p, float d, float x, float y, float z, float sc)
     {
@@ -356,7 +362,7 @@ __device__ __forceinline__ void pull_node(const typename St<S>::T* __restrict__ 
 // The populations of node first + threadIdx.x into every plane of dst (a
 // scalar base address and one vector offset for all planes); half deviations
 // come scaled.
-template <int S>
+template <int S, bool NT>
 __device__ __forceinline__ void store_node(typename St<S>::T* __restrict__ dst, const Geom& g,
                                            uint32_t first, const typename St<S>::A f[kQ])
 {
@@ -366,7 +372,10 @@ __device__ __forceinline__ void store_node(typename St<S>::T* __restrict__ dst, 
 #pragma unroll
     for (int i = 0; i < kQ; ++i) {
         char* b = reinterpret_cast<char*>(b0 + (int64_t)i * g.stride);
-        St<S>::put(reinterpret_cast<T*>(b + o), f[i]);
+        if constexpr (NT)
+            St<S>::put_nt(reinterpret_cast<T*>(b + o), f[i]);
+        else
+            St<S>::put(reinterpret_cast<T*>(b + o), f[i]);
     }
 }
 

@@ -44,13 +44,16 @@ __device__ __forceinline__ uint32_t xcd_block()
 
 // ---------------------------------------------------------------------------
 // Bulk: one thread per node, pull f_i(x - e_i), collide, store.  Bound by HBM:
-// FP32 3.70-3.76 ms on 512^3 (153 + 16 B a node, 6.1 TB/s, the rate of a copy),
-// FP64 7.4 ms, FP32 D3Q15 3.0 ms; small lattices by the latency of the flag and
-// population loads (48x40x44: 4.8 us FP32, 7.2 us FP64).  With an address per
-// lane and direction (687 vector instructions a wave instead of about 200; FP64
-// 112 registers instead of 88) 3.83, 7.5, 3.0-3.3 ms, 5.5 and 7.7 us.
+// FP32 3.7-4.3 ms on 512^3 by where the buffers lie in memory (153 + 16 B a node,
+// 5.3-6.1 TB/s; fixed from their allocation on, a copy of the same buffers makes
+// 6.2), FP64 7.4-8.3 ms, FP32 D3Q15 3.0-3.4 ms; fewer workgroups a compute unit,
+// six waves a SIMD for FP64 and other runs of workgroups gained nothing that held.
+// Small lattices are bound by the latency of the flag and population loads
+// (48x40x44: 4.8 us FP32, 7.2 us FP64).  With an address per lane and direction
+// (687 vector instructions a wave instead of about 200; FP64 112 registers
+// instead of 88) 3.83 (where 3.75), 7.5 (7.4), 3.0-3.3 ms, 5.5 and 7.7 us.
 // ---------------------------------------------------------------------------
-template <int S>
+template <int S, bool NT>
 __global__ __launch_bounds__(256) void k_stream_collide(const typename St<S>::T* __restrict__ src,
                                                         typename St<S>::T* __restrict__ dst,
                                                         typename St<S>::M* __restrict__ mom,
@@ -89,7 +92,7 @@ __global__ __launch_bounds__(256) void k_stream_collide(const typename St<S>::T*
             collide<DEV, A, St<S>::scaled>(f, om, go, F, drho, ux, uy, uz, A(ph.inv_scale), A(ph.scale));
         }
     }
-    store_node<S>(dst, g, first, f);
+    store_node<S, NT>(dst, g, first, f);
     St<S>::st_mom(mom + cell, drho, ux, uy, uz, ph.scale);
 }
 
@@ -99,7 +102,7 @@ __global__ __launch_bounds__(256) void k_stream_collide(const typename St<S>::T*
 // are loaded per node.  The arithmetic per node is that of k_stream_collide.
 // Requires an even nx (pairs never straddle a row).  Addresses as pull_node's:
 // the wave's common offset in the scalar base, three vector offsets.  Bound by
-// HBM: 2.10 ms on 512^3 (77 + 8 B a node, 5.4 TB/s), 28.5 us on 128^3; with an
+// HBM: 2.1-2.26 ms on 512^3 (77 + 8 B a node, 5.0-5.4 TB/s), 28.5 us on 128^3; with an
 // address per lane and direction and a sum per direction in the collision
 // (1345 vector instructions a wave) 2.31 ms and 35 us.
 __device__ __forceinline__ void pull_pair(const __half* __restrict__ src, const Geom& g,
@@ -162,6 +165,7 @@ __device__ __forceinline__ void pull_pair(const __half* __restrict__ src, const 
     }
 }
 
+template <bool NT>
 __global__ __launch_bounds__(256, 6) void k_stream_collide_x2(const __half* __restrict__ src,
                                                            __half* __restrict__ dst,
                                                            Mom16* __restrict__ mom,
@@ -202,7 +206,12 @@ __global__ __launch_bounds__(256, 6) void k_stream_collide_x2(const __half* __re
 #pragma unroll
     for (int i = 0; i < kQ; ++i) {
         char* b = reinterpret_cast<char*>(dst + first + (int64_t)i * g.stride);
-        *reinterpret_cast<__half2*>(b + o) = __floats2half2_rn(f0[i], f1[i]);
+        typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+        const __half2 v = __floats2half2_rn(f0[i], f1[i]);
+        if constexpr (NT)
+            __builtin_nontemporal_store(*reinterpret_cast<const half2_t*>(&v), reinterpret_cast<half2_t*>(b + o));
+        else
+            *reinterpret_cast<__half2*>(b + o) = v;
     }
     struct alignas(16) M2 {
         Mom16 a, b;
@@ -621,13 +630,23 @@ struct RunSC {
     static hipError_t run(lbm_ctx* c, const void* src, void* dst)
     {
         const ForceSums sums{c->sums, c->FX, c->FT, 6u * (uint32_t)c->cfg.n_particles};
+        // Populations stored past the cache (non-temporal) where two levels and the
+        // moments do not fit the 256 MB memory-side cache: a level written through
+        // it only pushes out what the next step would find there.  Same buffers,
+        // cached and past it, us: below the line 112^3 FP32 36.3 and 43.0, 128^3
+        // FP16 28.7 and 38.4, 88^3 FP64 35.5 and 45.9; above, 128^3 FP32 71 and 67,
+        // 104^3 FP64 76.0 and 69.7, 152^3 FP16 67.2 and 62.0, 256^3 281.5 and
+        // 275.7, 512^3 2325 and 2258.  From twice the cache on it is even for FP32
+        // and FP64 (-3 to +2 % by the buffers' place), which stay cached.
+        const int64_t bytes = 2 * c->sizes.population_bytes + c->sizes.moment_bytes;
+        const bool nt = bytes > ((int64_t)1 << 28) && (S == LBM_STORE_F16 || bytes < ((int64_t)1 << 29));
         // FP16 only: for FP32 the pair kernel was measured slower (4.8 against
-        // 4.4 ms on 512^3), the single-node pass already runs at copy speed
+        // 4.4 ms on 512^3)
         if constexpr (S == LBM_STORE_F16) {
             if (c->geom.n[0] % 2 == 0) {
                 uint32_t nb = blocks_for(c->geom.ncell / 2);
                 nb = (nb + 7u) & ~7u;
-                hipLaunchKernelGGL(k_stream_collide_x2, dim3(nb), dim3(256), 0, c->stream,
+                hipLaunchKernelGGL((nt ? k_stream_collide_x2<true> : k_stream_collide_x2<false>), dim3(nb), dim3(256), 0, c->stream,
                                    (const typename St<S>::T*)src, (typename St<S>::T*)dst,
                                    (typename St<S>::M*)c->mom, c->flag, c->geom, c->phys, sums);
                 return hipGetLastError();
@@ -635,7 +654,7 @@ struct RunSC {
         }
         uint32_t nb = blocks_for(c->geom.ncell);
         nb = (nb + 7u) & ~7u;  // whole rounds over the 8 XCDs
-        hipLaunchKernelGGL(k_stream_collide<S>, dim3(nb), dim3(256), 0, c->stream,
+        hipLaunchKernelGGL((nt ? k_stream_collide<S, true> : k_stream_collide<S, false>), dim3(nb), dim3(256), 0, c->stream,
                            (const typename St<S>::T*)src, (typename St<S>::T*)dst,
                            (typename St<S>::M*)c->mom, c->flag, c->geom, c->phys, sums);
         return hipGetLastError();

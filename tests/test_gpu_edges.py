@@ -44,6 +44,33 @@ def test_stream_collide_at_wave_and_row_edges(storage, lattice, dims):
         gpu.close()
 
 
+@pytest.mark.parametrize("storage,dims", [
+    ("f32", (117, 117, 116)), ("f32", (117, 117, 117)), ("f32", (147, 147, 147)), ("f32", (148, 147, 147)),
+    ("f64", (92, 92, 94)), ("f64", (93, 93, 93)), ("f16", (146, 147, 147)), ("f16", (148, 147, 147)),
+    ("f16", (149, 147, 147))])
+def test_stream_collide_at_the_cache_line_of_its_stores(storage, dims):
+    """Two levels and the moments just below and just above 2^28 bytes, and for
+    float 2^29 (where populations are stored past the cache), two steps of
+    random populations against the oracle."""
+    rng = np.random.default_rng(6)
+    lat = W.LatticeSpec(*dims, periodic=(1, 0, 1), tau=0.62, body_force=(2e-4, -1e-4, 3e-4))
+    gpu, ora = B.Lattice(lat, storage=storage), O.Oracle(lat)
+    parts = B.DeviceParticles(NONE)
+    ora.classify(NONE)
+    _, w, _ = O.stencil(19)
+    f = w[:, None] * (1.0 + 0.04 * rng.uniform(-1, 1, (19, lat.ncell)))
+    if storage != "f64":
+        cut, s = (np.float32, 1.0) if storage == "f32" else (np.float16, 1024.0)
+        f = ((f - w[:, None]) * s).astype(cut).astype(np.float64) / s + w[:, None]
+    gpu.set_populations(f)
+    ora.f[:] = f
+    for _ in range(2):
+        gpu.step(parts)
+        ora.step(NONE)
+    assert np.abs(gpu.populations() - ora.f).max() <= BULK_TOL[storage]
+    gpu.close()
+
+
 @pytest.mark.parametrize("points", [1, 3, 6, 9])
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 130])
 def test_dem_paths_match_the_oracle(n, points):
