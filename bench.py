@@ -27,7 +27,7 @@ METRIC = "MLUPS + % HBM roofline (FP32/FP16-store vs plain), drag err; adjoint s
 # WRITE_SIZE passes (scaled by a copy kernel of known size; see profiles/),
 # valid only for the kernel source they were taken on.
 MEASURED_TRAFFIC = {
-    ("c4_sediment_512cube_1000p", "f32"): dict(source_sha256_16="780bff85a0cc6656",
+    ("c4_sediment_512cube_1000p", "f32"): dict(source_sha256_16="c88b89ef01f94656",
                                               read=10.352e9, written=12.348e9),
 }
 HBM_PEAK_GBS = 8000.0

@@ -323,10 +323,13 @@ __device__ __forceinline__ AdjCoef<A> adj_collide(const A lam[kQ], const A pre[k
 // entries its refilled nodes read.
 //
 // Bound by memory where the lattice exceeds the caches: f and lambda(n + 1)
-// read, lambda(n) written, owners, 3 x 76 + 8 bytes a node in FP32, 97 us at
-// 128^3 (5.1 TB/s; 105 before sums over opposite pairs took the place of 19
-// terms each); a small FP64 box (48 x 40 x 44) takes 12.4 us (14.0 before).
-template <int S>
+// read, lambda(n) written, owners, 3 x 76 + 8 bytes a node in FP32, 79 us at
+// 128^3 (6.3 TB/s; 97 with everything through the memory-side cache; 105 before
+// sums over opposite pairs took the place of 19 terms each).  NT: the taped
+// level is loaded and the planes with e_x = 0 are stored past that cache (the
+// shifted planes' lines, written by two waves, have to meet in a cache: 100 us
+// with all stores past it).  A small FP64 box (48 x 40 x 44) takes 12.4 us (14.0 before).
+template <int S, bool NT>
 __global__ __launch_bounds__(256) void k_adj_node(const typename St<S>::T* __restrict__ f,
                                                   const uint32_t* __restrict__ own0,
                                                   const uint32_t* __restrict__ own1,
@@ -368,7 +371,7 @@ __global__ __launch_bounds__(256) void k_adj_node(const typename St<S>::T* __res
 #pragma unroll
             for (int i = 0; i < kQ; ++i) {
                 lam[i] = lam1[(int64_t)i * g.stride + cell];
-                pre[i] = St<S>::ld(f + entry(i), ph.inv_scale);
+                pre[i] = NT ? St<S>::ld_nt(f + entry(i), ph.inv_scale) : St<S>::ld(f + entry(i), ph.inv_scale);
             }
             co = adj_collide<DEV, A>(lam, pre, ph, acc);
         }
@@ -377,8 +380,12 @@ __global__ __launch_bounds__(256) void k_adj_node(const typename St<S>::T* __res
             const A v = live ? co(j, lam[j]) : A(0);
             const int sx = 1 - cx(j), sy = 1 - cy(j), sz = 1 - cz(j);
             if (!(refilled && j > 0 && vx[sx] && vy[sy] && vz[sz] &&
-                  own0[ox[sx] + oy[sy] + oz[sz]] == kFluid))
-                lam0[entry(j)] = v;
+                  own0[ox[sx] + oy[sy] + oz[sz]] == kFluid)) {
+                if (NT && cx(j) == 0)
+                    __builtin_nontemporal_store(v, lam0 + entry(j));
+                else
+                    lam0[entry(j)] = v;
+            }
         }
     }
     // list the refilled nodes for k_adj_refill (one atomic per wave); the
@@ -763,8 +770,20 @@ struct RunAdj {
     {
         using T = typename St<S>::T;
         using A = typename St<S>::A;
+        // Where two adjoint fields and a taped level outgrow the 256 MB memory-side
+        // cache, the taped level, which nothing reads again, and the planes stored
+        // whole go past it, and lambda stays for the next step.  Node, refill and
+        // link kernels of a 16-step window of one body, cached and past it, us:
+        // below the line 104^3 FP32 69.0 and 71.9, 80^3 FP64 66.7 and 67.5, 112^3
+        // FP16 76.3 and 77.9; above 112^3 FP32 92.8 and 84.5, 128^3 127.7 and 108.9,
+        // 96^3 FP64 108.0 and 87.4, 128^3 226 and 211, 160^3 FP16 192 and 181; from
+        // four times the cache on even (200^3 FP32 441 and 456, FP16 359 and 361,
+        // 160^3 FP64 411 and 397), so cached there.
+        const int64_t bytes = (int64_t)sizeof(A) * 2 * kQ * c->geom.stride + (int64_t)c->sizes.population_bytes;
+        const bool nt = bytes > ((int64_t)1 << 28) && bytes < ((int64_t)1 << 30);
         if (parts & kAdjNode)
-            hipLaunchKernelGGL(k_adj_node<S>, dim3(blocks_for(c->geom.ncell)), dim3(256), 0,
+            hipLaunchKernelGGL((nt ? k_adj_node<S, true> : k_adj_node<S, false>),
+                               dim3(blocks_for(c->geom.ncell)), dim3(256), 0,
                                c->stream, (const T*)ts.f, ts.own_use, own1, (const A*)lam1, (A*)lam0,
                                c->geom, c->phys, grad, list);
         if (parts & kAdjRefill) {

@@ -26,6 +26,7 @@ struct St<LBM_STORE_F64> {
     using M = Mom64;
     static constexpr bool dev = false;
     static __device__ __forceinline__ double ld(const double* p, float) { return *p; }
+    static __device__ __forceinline__ double ld_nt(const double* p, float) { return __builtin_nontemporal_load(p); }
     static __device__ __forceinline__ void st(double* p, double v, float) { *p = v; }
     // as stored, without the scale of half deviations
     static __device__ __forceinline__ double raw(const double* p) { return *p; }
@@ -50,6 +51,7 @@ struct St<LBM_STORE_F32> {
     using M = float4;
     static constexpr bool dev = true;
     static __device__ __forceinline__ float ld(const float* p, float) { return *p; }
+    static __device__ __forceinline__ float ld_nt(const float* p, float) { return __builtin_nontemporal_load(p); }
     static __device__ __forceinline__ void st(float* p, float v, float) { *p = v; }
     static __device__ __forceinline__ float raw(const float* p) { return *p; }
     static __device__ __forceinline__ void put(float* p, float v) { *p = v; }
@@ -75,6 +77,10 @@ struct St<LBM_STORE_F16> {
     static __device__ __forceinline__ float ld(const __half* p, float inv)
     {
         return __half2float(*p) * inv;
+    }
+    static __device__ __forceinline__ float ld_nt(const __half* p, float inv)
+    {
+        return (float)__builtin_nontemporal_load(reinterpret_cast<const _Float16*>(p)) * inv;
     }
     static __device__ __forceinline__ void st(__half* p, float v, float sc)
     {

@@ -181,6 +181,20 @@ def test_link_adjoint_on_both_sides_of_the_wave_split():
 # with few planes (a workgroup each) and with many (a wave each), planes of more
 # segments and more candidates than are listed at a time, squares around the
 # ball of 1, 2 and 3 tiles
+@pytest.mark.parametrize("dims", [(84, 84, 83), (84, 84, 84), (133, 133, 133), (134, 133, 133)])
+def test_node_adjoint_at_the_cache_line_of_its_stores(dims):
+    """Two FP64 adjoint fields and a taped level just below and above 2^28 and
+    2^30 bytes (between them the taped level and the whole planes go past the
+    cache): the dot products of a step with two moving bodies and a refill, to
+    the bound that the smaller lattices meet."""
+    from test_gpu_adjoint_dot import _Replay, _near_equilibrium, _one_body, _replay_case
+    _, ps = _one_body([[0.12, 0.03, -0.02], [-0.08, 0.05, 0.1]],
+                      [[0.01, -0.02, 0.015], [0.0, 0.01, -0.02]])
+    lat = W.LatticeSpec(*dims, (1, 0, 1), tau=0.6, body_force=(1e-5, 0.0, 0.0))
+    f0 = _near_equilibrium(lat, np.random.default_rng(4))
+    _replay_case(_Replay(lat, ps, 3), f0, 41, 1e-7)
+
+
 @pytest.mark.parametrize("n,d,dims,per,lattice",
                          [(1, 6.0, (33, 40, 35), (1, 1, 1), 15), (2, 29.0, (70, 64, 66), (0, 0, 0), 19),
                           (1, 31.6, (130, 64, 66), (1, 0, 0), 19), (1, 150.0, (160, 158, 156), (0, 0, 0), 19),
