@@ -525,9 +525,7 @@ int lbm_init(const lbm_config* cfg, const lbm_buffers* bufs, lbm_ctx** out)
     hipError_t e = carve_fixed(c);
     const size_t np1 = (size_t)std::max(np, 1);
     if (e == hipSuccess) {
-        c->refill_cursor = c->ctr + kCtrSet[0] + kSetRefill;
-        c->err = c->ctr + kCtrSet[0] + kSetErr;
-        c->inc = c->ctr + kCtrSet[0] + kSetIncremental;
+        c->use_counters(0);
         c->numeric = c->ctr + kCtrNumeric;
         c->link_cursor = c->ctr + kStageHead;
         c->cand_cursor = c->ctr + kStageHead + (size_t)kCursorPad * np1;
@@ -762,8 +760,14 @@ int lbm_classify_nodes(lbm_ctx* c, const lbm_particles* P, lbm_counts* out)
             rc = deferred_status(c, "lbm_classify_nodes");
             if (rc) return rc;
             const uint32_t* set = c->host_stage + kCtrSet[c->ctr_set];
-            if (set[kSetErr])
+            if (set[kSetErr]) {
+                // the set of the classification in force, with its refill count,
+                // is the current one again, and the rejected one's is clear
+                HIPCHK(c, hipMemsetAsync(c->ctr + kCtrSet[c->ctr_set], 0,
+                                         sizeof(uint32_t) * kSetWords, c->stream));
+                c->use_counters(c->ctr_set ^ 1);
                 return fail(c, LBM_EINVAL, "lbm_classify_nodes: " + err_text(set[kSetErr]));
+            }
             int64_t lmax = 0, ltot = 0, cmax = 0, ctot = 0;
             for (int p = 0; p < np; ++p) {
                 const int64_t v = link_counts[(size_t)p * kCursorPad];

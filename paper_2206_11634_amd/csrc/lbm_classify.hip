@@ -296,16 +296,16 @@ __device__ __forceinline__ void box_of(const PartDev& P, int p, int h, double* b
 }
 
 // The first kernel of a classification, a column of workgroups per particle:
-// the first of a column resets the particle's counters (the candidate counts of
-// the previous classification are kept for its lists) and finds its box, the
-// others, given a plane to clear, clear a z plane of its ball of two
-// classifications ago (also where the check of the boxes fails: that plane is
-// not in use, and the next attempt clears it again).  One launch for the chain
+// the first of a column resets the particle's candidate count (that of the
+// previous classification is kept for its lists) and finds its box, the others,
+// given a plane to clear, clear a z plane of its ball of two classifications ago
+// (also where the check of the boxes fails: that plane is not in use, and the
+// next attempt clears it again).  The link counts are those that lbm_step runs
+// by until the check has passed, so k_mark resets them.  One launch for the chain
 // of three that a small run waited 12 us for.
 __global__ __launch_bounds__(256) void k_begin(PartDev P, int h, double* ball, uint32_t* err, Geom g,
                                                const double* ball_prev, double* quat_prev,
-                                               uint32_t* inc_bad,
-                                               uint32_t* link_cursor, uint32_t* cand_cursor,
+                                               uint32_t* inc_bad, uint32_t* cand_cursor,
                                                uint32_t* cand_prev_count, uint32_t* own,
                                                const double* ball_clear)
 {
@@ -324,7 +324,6 @@ __global__ __launch_bounds__(256) void k_begin(PartDev P, int h, double* ball, u
         const int64_t at = (int64_t)p * kCursorPad;
         if (cand_prev_count) cand_prev_count[p] = cand_cursor[at];
         cand_cursor[at] = 0;
-        link_cursor[at] = 0;
     }
     box_of(P, p, h, ball, err, g, ball_prev, quat_prev, inc_bad);
 }
@@ -373,10 +372,14 @@ __global__ __launch_bounds__(256) void k_begin(PartDev P, int h, double* ball, u
 template <int T>
 __global__ __launch_bounds__(T, 8) void k_mark(const uint32_t* __restrict__ err, uint32_t* own, const double* ball, int h, PartDev P,
                                               Geom g, uint8_t* flag, int store_flag, uint32_t* cand,
-                                              int64_t cap, uint32_t* cursors, uint32_t* other_set)
+                                              int64_t cap, uint32_t* cursors, uint32_t* link_cursor,
+                                              uint32_t* other_set)
 {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kSetWords) other_set[threadIdx.x] = 0u;
-    if (*err) return;  // the boxes failed their check: leave every plane as it is
+    if (*err) return;  // the boxes failed their check: leave every plane and count as it is
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) link_cursor[(int64_t)blockIdx.y * kCursorPad] = 0u;
+        if (blockIdx.y == 0 && threadIdx.x < kSetWords) other_set[threadIdx.x] = 0u;
+    }
     constexpr int kSegs = 8 * T;           // segments of 8 nodes listed at a time
     constexpr uint32_t kCandBuf = 8 * T;
     __shared__ float4 sf[kMaxCtrl];
@@ -933,11 +936,7 @@ hipError_t launch_begin(lbm_ctx* c, const PartDev& P, int slot, int slot_prev, b
 {
     const int np = c->cfg.n_particles;
     if (np == 0) return hipSuccess;
-    c->ctr_set ^= 1;
-    uint32_t* set = c->ctr + kCtrSet[c->ctr_set];
-    c->refill_cursor = set + kSetRefill;
-    c->err = set + kSetErr;
-    c->inc = set + kSetIncremental;
+    c->use_counters(c->ctr_set ^ 1);
     if (own && c->dense) {
         const hipError_t e = hipMemsetAsync(own, 0xFF, sizeof(uint32_t) * (size_t)c->geom.ncell, c->stream);
         if (e != hipSuccess) return e;
@@ -946,7 +945,7 @@ hipError_t launch_begin(lbm_ctx* c, const PartDev& P, int slot, int slot_prev, b
     hipLaunchKernelGGL(k_begin, dim3(own ? 1 + c->box.S : 1, np), dim3(own ? 256 : 64), 0, c->stream, P,
                        c->box.h, c->ball_hist + (int64_t)slot * 4 * np, c->err, c->geom,
                        c->ball_hist + (int64_t)slot_prev * 4 * np, c->quat_prev,
-                       inc ? c->inc : nullptr, c->link_cursor, c->cand_cursor, c->cand_prev_count,
+                       inc ? c->inc : nullptr, c->cand_cursor, c->cand_prev_count,
                        own, c->ball_hist + (int64_t)slot_clear * 4 * np);
     return hipGetLastError();
 }
@@ -969,7 +968,7 @@ hipError_t launch_mark(lbm_ctx* c, uint32_t* own, const PartDev& P, int slot, bo
     hipLaunchKernelGGL(waves ? k_mark<64> : k_mark<256>, dim3(c->box.S, np), dim3(waves ? 64 : 256), 0,
                        c->stream, c->err, own, c->ball_hist + (int64_t)slot * 4 * np, c->box.h, P,
                        c->geom, c->flag, (c->dense && !inc) ? 0 : 1, c->cand, c->cand_cap,
-                       c->cand_cursor, c->ctr + kCtrSet[c->ctr_set ^ 1]);
+                       c->cand_cursor, c->link_cursor, c->ctr + kCtrSet[c->ctr_set ^ 1]);
     return hipGetLastError();
 }
 

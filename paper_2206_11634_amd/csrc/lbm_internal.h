@@ -242,6 +242,13 @@ struct lbm_ctx {
     int ctr_set = 0;              // the set of the last classification
     uint32_t* ctr = nullptr;      // the counter block: refill_cursor, err, inc, numeric,
                                   // link_cursor and cand_cursor point into it
+    void use_counters(int set)
+    {
+        ctr_set = set;
+        refill_cursor = ctr + mdlbm::kCtrSet[set] + mdlbm::kSetRefill;
+        err = ctr + mdlbm::kCtrSet[set] + mdlbm::kSetErr;
+        inc = ctr + mdlbm::kCtrSet[set] + mdlbm::kSetIncremental;
+    }
     double* FT = nullptr;         // [np][6] force, torque of the last step
     // the sums of the step under way, zero between steps: [np][6] doubles, or
     // [np][6][lo, hi] exact (LBM_FORCE_SUM_EXACT); the bulk pass moves them to FT
