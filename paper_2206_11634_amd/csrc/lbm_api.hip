@@ -654,6 +654,9 @@ int classify_enqueue(lbm_ctx* c, const PartDev& Pd, const ClassifyPlan& cp, Repo
         }
         std::swap(c->cand, c->cand_prev);
         std::swap(c->cand_cap, c->cand_prev_cap);
+        // should this call fail, the lists and orientations kept are not those
+        // of the classification in force (classify_commit takes this back)
+        c->inc_ok = false;
     }
     {
         PhaseTimer tm(c, LBM_PHASE_CLASSIFY);

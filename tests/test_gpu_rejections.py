@@ -70,3 +70,27 @@ def test_steps_and_snapshots_after_a_rejected_classification(classify, why, last
     for k in range(2):
         _step(gpu, ora, parts, P, (why, k))
     gpu.close()
+
+
+@pytest.mark.parametrize("classify", ["balls", "sweep"])
+@pytest.mark.parametrize("rejections", [1, 2, 3])
+def test_classification_after_a_rejected_one(classify, rejections):
+    """Bodies that moved little since the classification in force (the sweep mode
+    then works from its candidate lists): flags, through the populations of the
+    nodes that left a body, and refills of the next classifications match the
+    oracle's."""
+    gpu, ora = B.Lattice.for_particles(LAT, PS, storage="f64", classify=classify), O.Oracle(LAT)
+    parts, refilled = B.DeviceParticles(PS), 0
+    for n in range(6):
+        P = W.prescribed_state(PS, LAT, float(n))
+        if n in (2, 4):
+            for _ in range(rejections):
+                _reject(gpu, P, "weight")
+        parts.set_state(P)
+        gpu.classify(parts)
+        ora.classify(P)
+        _compare_geometry(gpu, ora, n)
+        refilled += len(ora.refill_nodes) if n in (2, 4) else 0
+        _step(gpu, ora, parts, P, n)
+    assert refilled > 0
+    gpu.close()
