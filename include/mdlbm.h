@@ -108,7 +108,9 @@ typedef struct {
     int32_t storage;       /* lbm_storage */
     int32_t treatments;    /* bitmask of lbm_treatment */
     int32_t n_particles;   /* number of particles (0 allowed) */
-    int32_t n_ctrl;        /* total control points over all particles */
+    int32_t n_ctrl;        /* total control points over all particles; below n_particles:
+                              not stated (the adjoints' pose gradients need it; dem_step
+                              reads ctrl_off and only picks its path by this) */
     int32_t box_half;      /* h: each particle's nodes lie within distance h-1 of its
                               centre; bounds the per-particle node box */
     double h16_scale;      /* scale of FP16 deviations (0: default 1024) */
@@ -290,7 +292,9 @@ int lbm_particle_forces(const lbm_ctx* ctx, double* F_dev, double* T_dev);
  * partners in one call (centres within the bodies' reach plus the call's
  * displacement) has the extra pairs left out; that is latched and reported
  * as ECAPACITY, with the context failed, by the next lbm_synchronize or
- * lbm_classify_nodes.  Allocates nothing.  Asynchronous. */
+ * lbm_classify_nodes.  So is, for up to 64 particles, a lbm_config.n_ctrl of
+ * at most 384 that ctrl_off[n] contradicts with more than 384 points.
+ * Allocates nothing.  Asynchronous. */
 int dem_step(lbm_ctx* ctx, lbm_particles* P, int n_sub, double dt, const dem_params* prm);
 
 /* lbm_step followed by dem_step in one call, with every argument checked

@@ -708,6 +708,10 @@ int deferred_status(lbm_ctx* c, const char* where)
                         std::string(where) + ": a particle had more than " +
                             std::to_string(kPairSlots) + " candidate contact partners in a "
                             "dem_step call; contacts beyond them were left out");
+        if (def & kDeferredPoints)
+            return fail(c, LBM_ECAPACITY,
+                        std::string(where) + ": a dem_step call had more control points than "
+                        "lbm_config.n_ctrl states; those beyond its work space were left out");
         if (def & kDeferredOverflow)
             return fail(c, LBM_ECAPACITY,
                         std::string(where) + ": an asynchronous classification outgrew its "

@@ -700,12 +700,10 @@ struct Ws {
     double* con;
     double* st[2];
     double* sum[3];
-    int last;  // the last control point
 };
-inline Ws ws_of(double* at, int n, int n_ctrl)
+inline Ws ws_of(double* at, int n)
 {
     Ws w;
-    w.last = n_ctrl - 1;
     w.con = at;
     w.st[0] = at + (int64_t)kCon * n;
     w.st[1] = w.st[0] + (int64_t)kState * n;
@@ -1218,7 +1216,8 @@ __global__ __launch_bounds__(256, G == 2 ? 2 : 1) void k_substep(PartDev P, Ws w
             Kin kA = kin_of(A, i), kB = kin_of(B, j);
             advance_centre<FIRST>(A, fA, dt, g);
             advance_centre<FIRST>(B, fB, dt, g);
-            if (near_pair(A.x, B.x, kA.reach + kB.reach + kA.rs + kB.rs, g, sh)) {
+            // (a body without points is an error, reported: it touches nothing)
+            if (near_pair(A.x, B.x, kA.reach + kB.reach + kA.rs + kB.rs, g, sh) && kA.n > 0 && kB.n > 0) {
                 // odd lanes turn B, even lanes A (the same branch for a group)
                 const bool second = l & 1;
                 Body M = second ? B : A;
@@ -1239,8 +1238,7 @@ __global__ __launch_bounds__(256, G == 2 ? 2 : 1) void k_substep(PartDev P, Ws w
                 }
                 auto point = [&](int u, double r[3], double& K) __attribute__((always_inline)) {
                     const bool of_b = u >= kA.n;
-                    // (a body without points is an error, reported: no read beyond)
-                    const int at = min(max(of_b ? B.c0 + (u - kA.n) : A.c0 + u, 0), w.last);
+                    const int at = of_b ? B.c0 + (u - kA.n) : A.c0 + u;
                     const double* bp = P.body_pts + 3 * (int64_t)at;
                     const double b0 = bp[0], b1 = bp[1], b2 = bp[2];
                     K = P.K[at];
@@ -1357,7 +1355,10 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
         };
     };
     const int p0 = P.off[0], np = min(P.off[n] - p0, kBlockPoints);
-    if (tid == 0) npairs = 0u;
+    if (tid == 0) {
+        npairs = 0u;
+        if (P.off[n] - p0 > kBlockPoints) atomicOr(deferred, kDeferredPoints);
+    }
     if (tid <= n) off[tid] = min(P.off[tid] - p0, kBlockPoints);
     for (int i = tid; i < np; i += kBlockThreads) K[i] = P.K[p0 + i];
     for (int i = tid; i < 3 * np; i += kBlockThreads) body[i] = P.body_pts[3 * (int64_t)p0 + i];
@@ -1497,7 +1498,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
                 for (int k = 0; k < 3; ++k) r[k] = world[3 * at + k] + (of_b ? sh[k] : 0.0);
                 Ku = K[at];
             };
-            if (near_pair(a.x, b.x, a.reach + b.reach + a.rs + b.rs, g, sh))
+            if (near_pair(a.x, b.x, a.reach + b.reach + a.rs + b.rs, g, sh) && a.n > 0 && b.n > 0)
                 pair_item<kPairLanes>(a, b, sh, point, h, c, dt, l, adder(i, j));
             else if (l == 0 && h[0] != 0.0)
                 clear_record(h);  // out of reach: forget the pair's contact
@@ -1549,7 +1550,10 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
     c.rhof = prm.rho_f;
     uint32_t* deferred = ctx->ctr + kCtrDeferred;
     const Geom& g = ctx->geom;
-    if (np <= kBlockParticles && ctx->cfg.n_ctrl <= kBlockPoints) {
+    // lbm_config.n_ctrl picks the path; a context that does not state it (fewer
+    // points than particles) takes the launches, which go by ctrl_off alone
+    const int n_ctrl = ctx->cfg.n_ctrl;
+    if (np <= kBlockParticles && n_ctrl >= np && n_ctrl <= kBlockPoints) {
         hipLaunchKernelGGL(k_dem_block, dim3(1), dim3(kBlockThreads), 0, ctx->stream, P, ctx->hist_pp,
                            ctx->hist_pw, ctx->hist_key, ctx->FT, ctx->fc, ws.pairs, c, n_sub, dt, g,
                            deferred);
@@ -1557,7 +1561,7 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
     }
     const uint32_t bp = (uint32_t)(np + 63) / 64, bw = (uint32_t)(np + 15) / 16;
     const double T = (double)n_sub * dt;
-    const Ws w = ws_of(ws.state, np, (int)ctx->cfg.n_ctrl);
+    const Ws w = ws_of(ws.state, np);
     hipLaunchKernelGGL(k_open, dim3(bp), dim3(64), 0, ctx->stream, P, ctx->FT, ctx->fc, c, dt, T, ws.reach,
                        ws.bound, w, ws.count);
     if (ws.gcount && np >= kGridMinParticles) {
@@ -1589,7 +1593,7 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
     const uint32_t wb = (uint32_t)(((int64_t)np * std::max(2 * n_axes, 1) + 255) / 256);
     // lanes for eight pairs a particle (more stride over the list)
     // (spheres: two control points a pair)
-    const bool spheres = ctx->cfg.n_ctrl <= np;
+    const bool spheres = n_ctrl == np;
     const int lanes = spheres ? 2 : kPairLanes;
     const uint32_t pb = (uint32_t)std::min<int64_t>(((int64_t)np * 8 * lanes + 255) / 256, 2048);
     for (int s = 0; s < n_sub; ++s) {

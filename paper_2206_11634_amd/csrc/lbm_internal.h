@@ -47,6 +47,9 @@ constexpr int kSetWords = 3;
 // Latched by dem_step when a particle had more candidate contact partners
 // than its history slots (reported like the asynchronous classifications).
 constexpr uint32_t kDeferredSlots = 0x200u;
+// Latched by a dem_step in one workgroup when the particles have more control
+// points than its LDS holds, and so more than lbm_config.n_ctrl stated.
+constexpr uint32_t kDeferredPoints = 0x400u;
 // Pair contact histories: each particle i keeps kPairSlots records for its
 // partners j > i, keyed by j; a record lives while the pair stays a
 // broad-phase candidate.

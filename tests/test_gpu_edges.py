@@ -113,6 +113,61 @@ def test_dem_paths_match_the_oracle(n, points):
         assert np.abs(a - b).max() <= 1e-9 * max(1.0, np.abs(b).max()), key
 
 
+@pytest.mark.parametrize("stated", ["none", "one", "all"])
+@pytest.mark.parametrize("n,points", [(3, 6), (64, 7), (65, 1), (65, 6), (130, 9)])
+def test_dem_of_contexts_that_do_not_state_their_control_points(n, points, stated):
+    """dem_step goes by ctrl_off: with lbm_config.n_ctrl left at 0, or below the
+    number of bodies, the bodies move as where it is stated, against the oracle
+    within 1e-9 (above 64 bodies, and below with more points than a workgroup's
+    call holds)."""
+    rng = np.random.default_rng(10 * n + points)
+    if points == 1:
+        shape = W.sphere_shape(6.2, 0.2)
+    else:
+        pts = rng.uniform(-0.4, 0.4, (points, 3))
+        shape = W.metaball_shape(pts, rng.uniform(0.7, 1.3, points) * 0.9 / points, 0.2, d_eq=6.4,
+                                 samples_per_unit=2.0)
+    k = np.arange(n)
+    lat = W.LatticeSpec(36, max(6 * (-(-n // 6)), 40), 30, (1, 0, 0))
+    pos = np.stack([(k % 6) * 6.0 + 3.0, (k // 6) * 6.0 + 2.7, np.full(n, 2.5)], -1)
+    pos += rng.uniform(-0.1, 0.1, (n, 3))
+    quats = np.array([W.random_quaternion(rng) for _ in range(n)])
+    ps = W.make_particles([shape] * n, pos, quats, 1.5, vel=rng.normal(size=(n, 3)) * 0.02,
+                          omega=rng.normal(size=(n, 3)) * 0.004)
+    kw = W.dem_defaults(ps, gravity=(0.0, 0.0, -2e-4))
+    n_ctrl = {"none": 0, "one": n - 1, "all": len(ps.K)}[stated]
+    gpu = B.Lattice(lat, n_particles=n, n_ctrl=n_ctrl, box_half=ps.box_half(), storage="f32")
+    dem, parts, P = O.OracleDEM(ps, lat), B.DeviceParticles(ps), ps.copy()
+    zero = np.zeros((n, 3))
+    for _ in range(2):
+        gpu.dem(parts, 10, 0.1, B.DemParams.make(**kw))
+        dem.step(P, zero, zero, O.DemParams(**kw), 10, 0.1)
+    gpu.sync()
+    G = parts.to_host(ps)
+    gpu.close()
+    for key in ("pos", "vel", "omega", "quat", "world_pts"):
+        a, b = getattr(G, key), getattr(P, key)
+        assert np.abs(a - b).max() <= 1e-9 * max(1.0, np.abs(b).max()), key
+
+
+def test_dem_reports_more_control_points_than_stated():
+    """64 bodies of seven points in a context that states 384 of the 448: the next
+    synchronisation says so."""
+    rng = np.random.default_rng(2)
+    shape = W.metaball_shape(rng.uniform(-0.4, 0.4, (7, 3)), np.full(7, 0.13), 0.2, d_eq=6.4,
+                             samples_per_unit=2.0)
+    k = np.arange(64)
+    lat = W.LatticeSpec(40, 40, 160, (0, 0, 0))
+    pos = np.stack([(k % 4) * 9.0 + 5.0, (k // 4 % 4) * 9.0 + 5.0, (k // 16) * 30.0 + 20.0], -1)
+    ps = W.make_particles([shape] * 64, pos, np.tile([1.0, 0, 0, 0], (64, 1)), 1.5)
+    gpu = B.Lattice(lat, n_particles=64, n_ctrl=384, box_half=ps.box_half(), storage="f32")
+    gpu.dem(B.DeviceParticles(ps), 2, 0.1, B.DemParams.make(**W.dem_defaults(ps)))
+    with pytest.raises(B.LbmError) as e:
+        gpu.sync()
+    assert e.value.code == B.LBM_ECAPACITY
+    gpu.close()
+
+
 @pytest.mark.parametrize("n,spacing", [(2048, 3.0), (2050, 13.0), (16384, 3.0), (16385, 3.0)])
 def test_dem_cell_grids_match_the_oracle(n, spacing):
     """dem_step on the cell grid where its making moves from one workgroup to a
