@@ -377,8 +377,10 @@ __global__ __launch_bounds__(T, 8) void k_mark(const uint32_t* __restrict__ err,
 {
     if (*err) return;  // the boxes failed their check: leave every plane and count as it is
     if (blockIdx.x == 0) {
+        // (the lowest plane lies beyond the ball, whose radius is below h)
         if (threadIdx.x == 0) link_cursor[(int64_t)blockIdx.y * kCursorPad] = 0u;
         if (blockIdx.y == 0 && threadIdx.x < kSetWords) other_set[threadIdx.x] = 0u;
+        return;
     }
     constexpr int kSegs = 8 * T;           // segments of 8 nodes listed at a time
     constexpr uint32_t kCandBuf = 8 * T;
