@@ -1027,7 +1027,8 @@ hipError_t launch_finish_links(lbm_ctx* c, const uint32_t* own_prev, const uint3
 
 hipError_t launch_latch_deferred(lbm_ctx* c)
 {
-    hipLaunchKernelGGL(k_latch_deferred, dim3(1), dim3(256), 0, c->stream, counter_report(c, false));
+    hipLaunchKernelGGL(k_latch_deferred, dim3(blocks_for(std::max(c->cfg.n_particles, 1))), dim3(256), 0,
+                       c->stream, counter_report(c, false));
     return hipGetLastError();
 }
 

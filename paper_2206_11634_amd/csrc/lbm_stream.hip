@@ -437,11 +437,11 @@ __global__ __launch_bounds__(256) void k_boundary(typename St<S>::T* __restrict_
 // The count is read on the device (the list's cursor, at most cap), so the
 // launch needs no read-back; a grid of at most a few thousand waves strides over
 // the list (64 nodes a workgroup spread its gathers over more compute units than
-// 256: 200 bodies 20 -> 11 us, 1000 in 512^3 42 -> 23), and the last workgroup
-// reports the classification's counters.  Each node reads only the previous populations and
-// owners and writes only its own populations and moments, so running the
-// kernel again over a longer list (after the list has grown) gives the same
-// values at the nodes of the first run.  Bound by the latency of one node's
+// 256: 200 bodies 20 -> 11 us, 1000 in 512^3 42 -> 23), which also
+// reports the classification's counters.  Each node reads only the previous
+// populations and owners and writes only its own populations and moments, so
+// running the kernel again over a longer list (after the list has grown) gives
+// the same values at the nodes of the first run.  Bound by the latency of one node's
 // chain: each neighbour's owner and population load once (the bounce-back of
 // direction i reads what the streaming of opp(i) would), all before the first
 // use: 4.3-5.2 us for a few nodes, 10 us for 60 bodies in FP64, where 38
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(64) void k_refill(const typename St<S>::T* __restri
                                                 const uint32_t* __restrict__ own_prev, PartDev P,
                                                 Geom g, Phys ph, CounterReport report)
 {
-    if (report.ctr && blockIdx.x == gridDim.x - 1u) report_counters(report);
+    if (report.ctr) report_counters(report);
     if (*err) return;  // the classification's box check failed: nothing was listed
     const uint32_t cnt = min(*cursor, cap);
     for (uint32_t l = blockIdx.x * 64u + threadIdx.x; l < cnt; l += gridDim.x * 64u)

@@ -328,3 +328,37 @@ def test_force_sums_and_counters_between_steps(exact):
             same(("eager", n, 1))
         gpu.sync()
         gpu.close()
+
+
+@pytest.mark.parametrize("n", [1, 32, 33, 700, 4100])
+def test_counts_of_many_bodies_are_reported_and_latched(n):
+    """Every particle's counts reach the host, whichever workgroup reports them
+    (one wave for a few bodies, all of the refill's for many), on the first
+    classification and the next; and an asynchronous classification in which the
+    links of the first, a middle or the last body outgrow their list is latched."""
+    m = int(np.ceil(n ** (1 / 3)))
+    k = np.arange(n)
+    pos = np.stack([k % m, k // m % m, k // (m * m)], -1) * 14.0 + 8.0
+    pos += np.random.default_rng(n).uniform(-0.5, 0.5, (n, 3))
+    lat = W.LatticeSpec(14 * m + 6, 14 * m + 6, 14 * m + 6, (0, 0, 0))
+    big = W.make_particles([W.sphere_shape(11.6, 0.2)] * n, pos, np.tile([1.0, 0, 0, 0], (n, 1)), 1.5)
+    ps = W.make_particles([W.sphere_shape(5.8, 0.2)] * n, pos, np.tile([1.0, 0, 0, 0], (n, 1)), 1.5)
+    for j in sorted({0, n // 2, n - 1}):
+        gpu = B.Lattice(lat, n_particles=n, n_ctrl=n, box_half=big.box_half(), storage="f16",
+                        classify="balls")
+        parts = B.DeviceParticles(ps)
+        for _ in range(3):
+            c = gpu.classify(parts)
+            L = gpu.links()
+            per_body = np.bincount(L["part"], minlength=n)
+            assert c.n_links == len(L["node"]) and per_body.min() > 100
+            alone = np.unique(np.stack([L["node"], L["d"]]), axis=1).shape[1]
+            assert alone == len(L["node"])       # no record written over another
+        gpu.classify(parts, sync=False)
+        gpu.sync()
+        parts.t["K"][j] *= (11.6 / 5.8) ** 2
+        gpu.classify(parts, sync=False)
+        with pytest.raises(B.LbmError) as e:
+            gpu.sync()
+        assert e.value.code == B.LBM_ECAPACITY
+        gpu.close()
