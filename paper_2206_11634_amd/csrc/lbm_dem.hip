@@ -39,7 +39,7 @@ constexpr int kHist = 8;  // active, xi[3], warm start[3], pad
 constexpr int kMaxPts = 64;
 
 struct DemP {
-    double kn, etan, kt, etat, mu, ctol, ntol;
+    double kn, etan, kt, etat, mu, ctol, ntol2;
     int niter;
     double g[3];
     double rhof;
@@ -426,7 +426,7 @@ __device__ __forceinline__ void pair_item(const Kin& A, const Kin& B, const doub
         }
         if (!solve3(H, gg, dx)) break;
         for (int a = 0; a < 3; ++a) x[a] += dx[a];
-        if (dot3(dx, dx) < c.ntol * c.ntol) {
+        if (dot3(dx, dx) < c.ntol2) {
             conv = true;
             break;
         }
@@ -598,7 +598,7 @@ __device__ __forceinline__ void wall_contact(const Kin& A, PA&& pa, double* h, i
         const double d2 = s * (h11 * gr[2] - h12 * gr[1]);
         y1 += d1;
         y2 += d2;
-        if (d1 * d1 + d2 * d2 < c.ntol * c.ntol) {
+        if (d1 * d1 + d2 * d2 < c.ntol2) {
             conv = true;
             break;
         }
@@ -1544,7 +1544,7 @@ hipError_t launch_dem(lbm_ctx* ctx, const PartDev& P, int n_sub, double dt, cons
     c.etat = prm.eta_t;
     c.mu = prm.mu_s;
     c.ctol = prm.ctol;
-    c.ntol = prm.newton_tol;
+    c.ntol2 = step_tol2(prm.newton_tol);
     c.niter = prm.newton_iter;
     for (int a = 0; a < 3; ++a) c.g[a] = prm.gravity[a];
     c.rhof = prm.rho_f;

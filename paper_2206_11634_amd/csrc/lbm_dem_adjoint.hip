@@ -138,7 +138,7 @@ struct DemTape {
 };
 
 struct Consts {
-    double kn, etan, kt, etat, mu, ctol, ntol;
+    double kn, etan, kt, etat, mu, ctol, ntol2;
     int niter;
     double g[3];
     double rhof;
@@ -420,7 +420,7 @@ __device__ __forceinline__ void wall_item(const Shapes& S, Body& b, int ax, int 
         const double d2 = -(-h12 * gr[t1] + h11 * gr[t2]) / det;
         x[t1] += d1;
         x[t2] += d2;
-        if (d1 * d1 + d2 * d2 < c.ntol * c.ntol) {
+        if (d1 * d1 + d2 * d2 < c.ntol2) {
             conv = true;
             break;
         }
@@ -517,7 +517,7 @@ __device__ void pair_item(const Shapes& S, Body& A, Body& B, Rec& h, const Const
         for (int a = 0; a < 9; ++a) H[a] = HA[a] + HB[a];
         if (!solve3(H, gg, dx)) break;
         for (int a = 0; a < 3; ++a) x[a] += dx[a];
-        if (dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2] < c.ntol * c.ntol) {
+        if (dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2] < c.ntol2) {
             conv = true;
             break;
         }
@@ -867,7 +867,7 @@ hipError_t launch_dem_adjoint(lbm_ctx* c, const TapeStep& ts, const int32_t* key
     k.etat = prm.eta_t;
     k.mu = prm.mu_s;
     k.ctol = prm.ctol;
-    k.ntol = prm.newton_tol;
+    k.ntol2 = step_tol2(prm.newton_tol);
     k.niter = prm.newton_iter;
     for (int a = 0; a < 3; ++a) k.g[a] = prm.gravity[a];
     k.rhof = prm.rho_f;

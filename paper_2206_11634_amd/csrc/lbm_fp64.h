@@ -3,7 +3,17 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <limits>
+
 namespace mdlbm {
+
+// |d| < tol as d.d < step_tol2(tol): never for a tol that is not positive, and
+// for one whose square underflows still where d.d is zero.
+inline double step_tol2(double tol)
+{
+    return tol > 0.0 ? std::max(tol * tol, std::numeric_limits<double>::denorm_min()) : 0.0;
+}
 
 // 1/x and 1/sqrt(x): the hardware's estimate and two Newton steps (an ulp or
 // so; a third of the instructions of a division).  Not a number at 0.

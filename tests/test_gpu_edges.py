@@ -168,6 +168,33 @@ def test_dem_reports_more_control_points_than_stated():
     gpu.close()
 
 
+@pytest.mark.parametrize("n", [1, 70])
+@pytest.mark.parametrize("tol", [1e-12, 1e-100, 1e-170, 1e-300, 0.0, -1.0])
+def test_dem_newton_tolerances(n, tol):
+    """Spheres bouncing straight off the floor, whose contact point the search has
+    exactly from the start: any positive step tolerance finds it, also one whose
+    square underflows, and none that is not positive (no contact then), as the
+    oracle's search."""
+    k = np.arange(n)
+    lat = W.LatticeSpec(64, 80, 30, (0, 0, 0))
+    pos = np.stack([(k % 7) * 8.0 + 8.0, (k // 7) * 7.0 + 5.0, np.full(n, 2.55)], -1)
+    ps = W.make_particles([W.sphere_shape(6.0, 0.2)] * n, pos, np.tile([1.0, 0, 0, 0], (n, 1)), 1.5,
+                          vel=np.tile([0.0, 0.0, -0.05], (n, 1)))
+    kw = dict(W.dem_defaults(ps, gravity=(0.0, 0.0, -2e-4)), newton_tol=tol)
+    gpu, dem = B.Lattice.for_particles(lat, ps, storage="f32"), O.OracleDEM(ps, lat)
+    parts, P = B.DeviceParticles(ps), ps.copy()
+    zero = np.zeros((n, 3))
+    for _ in range(4):
+        gpu.dem(parts, 10, 0.1, B.DemParams.make(**kw))
+        dem.step(P, zero, zero, O.DemParams(**kw), 10, 0.1)
+    gpu.sync()
+    G = parts.to_host(ps)
+    gpu.close()
+    assert (P.vel[:, 2].min() > -0.045) == (tol > 0.0)   # the floor slowed them, or did not
+    for key in ("pos", "vel", "omega"):
+        assert np.abs(getattr(G, key) - getattr(P, key)).max() <= 1e-9 * max(1.0, np.abs(getattr(P, key)).max())
+
+
 @pytest.mark.parametrize("n,spacing", [(2048, 3.0), (2050, 13.0), (16384, 3.0), (16385, 3.0)])
 def test_dem_cell_grids_match_the_oracle(n, spacing):
     """dem_step on the cell grid where its making moves from one workgroup to a
