@@ -147,7 +147,8 @@ __device__ __forceinline__ void contact_force(const DemP& c, double delta, const
     for (int a = 0; a < 3; ++a) xi[a] = xi[a] - xin * n[a] + vt[a] * dt;
     for (int a = 0; a < 3; ++a) Ft[a] = -c.kt * xi[a] - c.etat * vt[a];
     const double ft2 = dot3(Ft, Ft), lim = c.mu * Fn;
-    if (ft2 > lim * lim && ft2 > 0.0) {
+    // |Ft| > lim, of either sign
+    if (ft2 > lim * fabs(lim) && ft2 > 0.0) {
         const double s = lim * fast_rsqrt(ft2), ik = 1.0 / c.kt;
         for (int a = 0; a < 3; ++a) {
             Ft[a] *= s;

@@ -195,6 +195,31 @@ def test_dem_newton_tolerances(n, tol):
         assert np.abs(getattr(G, key) - getattr(P, key)).max() <= 1e-9 * max(1.0, np.abs(getattr(P, key)).max())
 
 
+@pytest.mark.parametrize("n", [1, 70])
+@pytest.mark.parametrize("mu", [-0.2, 0.0, 0.3, float("inf")])
+def test_dem_friction_coefficients(n, mu):
+    """Spheres sliding over the floor: the Coulomb limit for friction coefficients
+    of every kind acts as the oracle's."""
+    k = np.arange(n)
+    lat = W.LatticeSpec(64, 80, 30, (0, 0, 0))
+    pos = np.stack([(k % 7) * 8.0 + 8.0, (k // 7) * 7.0 + 5.0, np.full(n, 2.48)], -1)
+    ps = W.make_particles([W.sphere_shape(6.0, 0.2)] * n, pos, np.tile([1.0, 0, 0, 0], (n, 1)), 1.5,
+                          vel=np.tile([0.02, -0.01, 0.0], (n, 1)))
+    kw = dict(W.dem_defaults(ps, gravity=(0.0, 0.0, -2e-4)), mu_s=mu)
+    gpu, dem = B.Lattice.for_particles(lat, ps, storage="f32"), O.OracleDEM(ps, lat)
+    parts, P = B.DeviceParticles(ps), ps.copy()
+    zero = np.zeros((n, 3))
+    for _ in range(3):
+        gpu.dem(parts, 10, 0.1, B.DemParams.make(**kw))
+        dem.step(P, zero, zero, O.DemParams(**kw), 10, 0.1)
+    gpu.sync()
+    G = parts.to_host(ps)
+    gpu.close()
+    assert (np.abs(P.omega).max() > 1e-5) == (mu != 0.0)   # friction turned them
+    for key in ("pos", "vel", "omega"):
+        assert np.abs(getattr(G, key) - getattr(P, key)).max() <= 1e-9 * max(1.0, np.abs(getattr(P, key)).max())
+
+
 @pytest.mark.parametrize("n,spacing", [(2048, 3.0), (2050, 13.0), (16384, 3.0), (16385, 3.0)])
 def test_dem_cell_grids_match_the_oracle(n, spacing):
     """dem_step on the cell grid where its making moves from one workgroup to a
