@@ -73,8 +73,8 @@ __device__ __forceinline__ D operator/(const D& a, const D& b)
 }
 __device__ __forceinline__ D dsqrt(const D& a)
 {
-    const double y = a.v > 0.0 ? fast_rsqrt(a.v) : 0.0;
-    return D(a.v * y, 0.5 * a.d * y);
+    const double y = a.v > 0.0 ? fast_rsqrt(a.v) : 0.0, r = a.v * y;
+    return D(fma(fma(-r, r, a.v), 0.5 * y, r), 0.5 * a.d * y);
 }
 // f(a) with f(a.v) = fv and f'(a.v) = fp
 __device__ __forceinline__ D chain(const D& a, double fv, double fp) { return D(fv, fp * a.d); }

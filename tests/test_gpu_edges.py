@@ -196,7 +196,7 @@ def test_dem_newton_tolerances(n, tol):
 
 
 @pytest.mark.parametrize("n", [1, 70])
-@pytest.mark.parametrize("mu", [-0.2, 0.0, 0.3, float("inf")])
+@pytest.mark.parametrize("mu", [-5.0, -0.2, 0.0, 0.3, float("inf")])
 def test_dem_friction_coefficients(n, mu):
     """Spheres sliding over the floor: the Coulomb limit for friction coefficients
     of every kind acts as the oracle's."""
@@ -215,7 +215,7 @@ def test_dem_friction_coefficients(n, mu):
     gpu.sync()
     G = parts.to_host(ps)
     gpu.close()
-    assert (np.abs(P.omega).max() > 1e-5) == (mu != 0.0)   # friction turned them
+    assert (np.abs(P.omega).max() > 1e-6) == (mu != 0.0)   # friction turned them
     for key in ("pos", "vel", "omega"):
         assert np.abs(getattr(G, key) - getattr(P, key)).max() <= 1e-9 * max(1.0, np.abs(getattr(P, key)).max())
 
