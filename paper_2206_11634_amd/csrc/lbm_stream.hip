@@ -437,7 +437,7 @@ __global__ __launch_bounds__(256) void k_boundary(typename St<S>::T* __restrict_
 // The count is read on the device (the list's cursor, at most cap), so the
 // launch needs no read-back; a grid of at most a few thousand waves strides over
 // the list (64 nodes a workgroup spread its gathers over more compute units than
-// 256: 200 bodies 20 -> 11 us, 1000 in 512^3 42 -> 23), which also
+// 256: 200 bodies 20 -> 11 us, 1000 in 512^3 42 -> 16), which also
 // reports the classification's counters.  Each node reads only the previous
 // populations and owners and writes only its own populations and moments, so
 // running the kernel again over a longer list (after the list has grown) gives

@@ -414,3 +414,36 @@ def test_counts_of_many_bodies_are_reported_and_latched(n):
             gpu.sync()
         assert e.value.code == B.LBM_ECAPACITY
         gpu.close()
+
+
+@pytest.mark.parametrize("n,points,width,mode", [(3, 64, 0.5, "balls"), (3, 64, 1.6, "sweep"), (70, 24, 0.9, "balls"),
+                                                 (400, 12, 0.9, "balls"), (400, 40, 0.3, "sweep")])
+def test_classification_of_many_point_bodies(n, points, width, mode):
+    """Owners, links with q and refills of bodies whose control points lie close
+    together or apart (few or many of the visited nodes interior), by four waves
+    and by one wave a plane, moved once, against the oracle bit for bit."""
+    from test_gpu_parity import _compare_geometry
+    rng = np.random.default_rng(points)
+    d, c0 = 10.0, 0.97
+    pts = rng.uniform(-width / 2, width / 2, (points, 3)) * d
+    pts -= pts.mean(0)
+    K = rng.uniform(0.7, 1.3, points) / points * (0.4 * d) ** 2
+    V = np.pi / 6 * d ** 3
+    shape = W.Shape(pts=pts, K=K, c0=c0, rs=0.2, volume=V, inertia_unit=np.full(3, 0.1 * V * d * d),
+                    radius=W.body_radius(pts, K, c0))
+    m, k, pitch = int(np.ceil(n ** (1 / 3))), np.arange(n), 1.7 * shape.radius
+    side = max(int(m * pitch) + 2, 2 * int(shape.radius) + 14)
+    lat = W.LatticeSpec(side, side + 1, side + 3, (1, 0, 0))
+    pos = np.stack([k % m, k // m % m, k // (m * m)], -1) * pitch + pitch / 2
+    pos = np.mod(pos + rng.uniform(-0.5, 0.5, (n, 3)), side)
+    ps = W.make_particles([shape] * n, pos, np.array([W.random_quaternion(rng) for _ in range(n)]), 1.5)
+    gpu = B.Lattice.for_particles(lat, ps, storage="f32", classify=mode)
+    ora = O.Oracle(lat)
+    for _ in range(2):
+        gpu.classify(B.DeviceParticles(ps))
+        ora.classify(ps)
+        _compare_geometry(gpu, ora, (n, points))
+        ps = ps.copy()
+        ps.pos = np.mod(ps.pos + rng.uniform(-0.4, 0.4, (n, 3)), side)
+        ps.refresh_world()
+    gpu.close()
