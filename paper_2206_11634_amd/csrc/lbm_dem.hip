@@ -10,22 +10,20 @@
 // particles at most), not HBM-bound.  Up to kBlockParticles particles one
 // workgroup runs the whole call: the broad phase and every substep, with
 // barriers where more particles take a launch; the first wave moves the
-// particles (a lane each) and takes their wall contacts, the other waves take
-// the candidate pairs (kPairLanes lanes each), and what a substep hands over
-// lies in LDS.  Beyond, a substep is two launches: the contacts (2 or kPairLanes
-// lanes per candidate pair, a thread per particle-wall pair, FP64 atomics into
-// the sums), then the second half kick, and the first half of the next substep
-// (a thread per particle).  Both half kicks around a substep's start act in the
-// body frame, with one rotation matrix a pose and Euler's terms as products of
-// two components; half angles come from their series.
+// particles (a lane each) and takes their wall contacts (a lane each), the other
+// waves take the candidate pairs (kPairLanes lanes each), and what a substep hands
+// over lies in LDS.  Beyond, k_open, the broad phase (on the cell grid from
+// kGridMinParticles on), one k_substep a substep and k_close.  Both half kicks
+// around a substep's start act in the body frame, with one rotation matrix a pose
+// and Euler's terms as products of two components; half angles come from their
+// series.
 // Measured, microseconds a call of ten substeps (in parentheses a thread per
 // pair, per pair test and per particle's cells, 23 launches whatever the count):
-//   1 sphere 13 (83), 2 flat metaballs 35 (153), 64 packed spheres 67 (173),
-//   1000 metaballs of the 512^3 run 235 (535), packed spheres 1000: 130 (226),
-//   2548: 136 (420), 8000: 156 (462), 27 000: 302 (745).
-// In one workgroup with the points and records in global memory, a matrix a
-// half kick and the library's division, square root and sincos the first three
-// took 32, 60 and 98.
+//   1 sphere 13.5 (83), 2 flat metaballs 36 (153), 64 packed spheres 69 (173),
+//   1000 metaballs of the 512^3 run 190 (535), packed spheres 1000: 121 (226),
+//   2548: 123 (420), 8000: 137 (462), 27 000: 310 (745); a body of 64 points in a
+//   corner of three walls 267 (752; 1063 with its wall contacts one after the
+//   other on the body's lane and their coordinates picked from all three).
 #include <algorithm>
 #include <mutex>
 
@@ -528,7 +526,8 @@ __device__ __forceinline__ bool near_wall(double xa, double lim, int ax, int sid
 
 // Contact of particle A with wall (ax, side) near it, record h: in-plane Newton
 // for the point of the wall plane where M is largest, the contact test and the
-// force; the force and its torque go to emit(F, t).
+// force; the force and its torque go to emit(F, t).  pa(u, r): point u along the
+// wall's normal axis and the two after it.
 template <int R, class PA, class Emit>
 __device__ __forceinline__ void wall_contact(const Kin& A, PA&& pa, double* h, int ax, int side,
                                              const DemP& c, double dt, const Geom& g, Emit&& emit)
@@ -544,9 +543,7 @@ __device__ __forceinline__ void wall_contact(const Kin& A, PA&& pa, double* h, i
     double pr[R ? R : 1][3], kr[R ? R : 1];
     const bool regs = R && ni <= R && ni > 0;
     auto load = [&](int u, double r[3], double& K) __attribute__((always_inline)) {
-        double p[3];
-        pa(u, p);
-        r[0] = component(p, ax), r[1] = component(p, t1), r[2] = component(p, t2);
+        pa(u, r);
         K = A.K[u];
     };
     if (regs) {
@@ -1174,8 +1171,15 @@ __global__ __launch_bounds__(256, G == 2 ? 2 : 1) void k_substep(PartDev P, Ws w
                 for (int a = 0; a < 6; ++a) next[(int64_t)kSums * i + a] = 0.0;
             }
             if (near)
-                wall_contact<G == 2 ? 1 : 8>(kin_of(b, i), [&](int u, double r[3]) { world(b.x, b.R, b.c0, u, r); }, h,
-                             ax, side, c, dt, g, [&](const double F[3], const double tq[3]) {
+                wall_contact<G == 2 ? 1 : 8>(kin_of(b, i),
+                             [&](int u, double r[3]) {
+                                 double p[3];
+                                 world(b.x, b.R, b.c0, u, p);
+                                 r[0] = component(p, ax);
+                                 r[1] = component(p, (ax + 1) % 3);
+                                 r[2] = component(p, (ax + 2) % 3);
+                             },
+                             h, ax, side, c, dt, g, [&](const double F[3], const double tq[3]) {
                                  for (int a = 0; a < 3; ++a) {
                                      atomicAdd(add_to + (int64_t)kSums * i + a, F[a]);
                                      atomicAdd(add_to + (int64_t)kSums * i + 3 + a, tq[a]);
@@ -1333,6 +1337,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
     __shared__ double wall[6 * kBlockParticles * kHist];  // the particles' wall records
     __shared__ double rec[kPairGroups * kHist];           // the groups' first pairs' records
     __shared__ int32_t off[kBlockParticles + 1];
+    __shared__ uint16_t items[6 * kBlockParticles];       // the first wave's wall contacts
     __shared__ uint32_t npairs;
     const int tid = (int)threadIdx.x, lane = tid & 63, n = P.n;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1349,10 +1354,10 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
         k.n = min(off[i + 1] - off[i], kMaxPts);
         return k;
     };
-    auto points = [&](int i) {
-        const double* p = world + 3 * off[i];
-        return [p](int u, double r[3]) {
-            for (int a = 0; a < 3; ++a) r[a] = p[3 * u + a];
+    auto points = [&](int i, int ax) {
+        const double *p = world + 3 * off[i], *p0 = p + ax, *p1 = p + (ax + 1) % 3, *p2 = p + (ax + 2) % 3;
+        return [=](int u, double r[3]) {
+            r[0] = p0[3 * u], r[1] = p1[3 * u], r[2] = p2[3 * u];
         };
     };
     const int p0 = P.off[0], np = min(P.off[n] - p0, kBlockPoints);
@@ -1436,30 +1441,46 @@ __global__ __launch_bounds__(kBlockThreads) void k_dem_block(PartDev P, double* 
                 for (int k = 0; k < 6; ++k) sum[6 * tid + k] = 0.0;
             }
             if (pairs) __syncthreads();
-            if (on) {
-                uint32_t near = 0;  // as near_wall
+            uint32_t near = 0;  // as near_wall
+            if (on)
                 for (int ax = 0; ax < 3; ++ax)
                     if (!g.per[ax]) {
                         if (!(b.x[ax] + 0.5 > lim)) near |= 1u << (2 * ax);
                         if (!((double)g.n[ax] - 0.5 - b.x[ax] > lim)) near |= 2u << (2 * ax);
                     }
-                for (uint32_t m = near | live; m; m &= m - 1u) {
-                    const int k = __ffs(m) - 1;
-                    double* h = wall + (6 * tid + k) * kHist;
-                    if ((near >> k) & 1u) {
-                        wall_contact<0>(kin(tid), points(tid), h, k >> 1, k & 1, c, dt, g,
+            const uint32_t todo = near | live;
+            live = near;
+            if (__any(todo != 0u)) {
+                // the wave's bodies and walls listed, one to a lane: a body in a
+                // corner waits for one contact, not for three one after the other
+                int total = 0;
+                for (int k = 0; k < 6; ++k) {
+                    const bool is = (todo >> k) & 1u;
+                    const uint64_t m = __ballot(is);
+                    if (is)
+                        items[total + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+                            (uint16_t)(tid << 4 | k << 1 | (int)((near >> k) & 1u));
+                    total += __popcll(m);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                for (int t = tid; t < total; t += 64) {
+                    const int i = items[t] >> 4, k = (items[t] >> 1) & 7;
+                    double* h = wall + (6 * i + k) * kHist;
+                    if (items[t] & 1)
+                        wall_contact<0>(kin(i), points(i, k >> 1), h, k >> 1, k & 1, c, dt, g,
                                      [&](const double F[3], const double t[3]) {
                                          for (int a = 0; a < 3; ++a) {
-                                             atomicAdd(sum + 6 * tid + a, F[a]);
-                                             atomicAdd(sum + 6 * tid + 3 + a, t[a]);
+                                             atomicAdd(sum + 6 * i + a, F[a]);
+                                             atomicAdd(sum + 6 * i + 3 + a, t[a]);
                                          }
                                      });
-                        live |= 1u << k;
-                    } else {
+                    else
                         clear_record(h);
-                        live &= ~(1u << k);
-                    }
                 }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
             }
             if (pairs) __syncthreads();
             if (on) {

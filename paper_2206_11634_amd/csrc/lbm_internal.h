@@ -359,8 +359,8 @@ struct DemScratch {
 };
 // Most particles whose whole dem_step call runs in one workgroup: a lane of
 // its first wave each, and a barrier costs less than a launch (a call of ten
-// substeps, launches in parentheses: 1 sphere 13 us (61), 2 flat metaballs 35
-// (86), 64 packed spheres 67 (114)).
+// substeps, launches in parentheses: 1 sphere 13.5 us (57), 2 flat metaballs 36
+// (86), 64 packed spheres 69 (114)).  lbm_config.n_ctrl has to state their points.
 constexpr int kBlockParticles = 64;
 // Particle counts from which dem_step uses the cell grid.
 constexpr int kGridMinParticles = 2048;

@@ -220,6 +220,42 @@ def test_dem_friction_coefficients(n, mu):
         assert np.abs(getattr(G, key) - getattr(P, key)).max() <= 1e-9 * max(1.0, np.abs(getattr(P, key)).max())
 
 
+@pytest.mark.parametrize("n,points", [(1, 1), (1, 64), (2, 20), (21, 6), (22, 6), (64, 1), (64, 6), (70, 6)])
+def test_dem_wall_contacts_of_bodies_in_a_channel(n, points):
+    """Bodies between two walls and on the floor, apart from each other, some next
+    to the end walls: up to 64 of them give a workgroup's first wave less and more
+    wall contacts than it has lanes.  Three calls of ten substeps against the
+    oracle, within 1e-9."""
+    rng = np.random.default_rng(n + points)
+    d = 6.2
+    if points == 1:
+        shape = W.sphere_shape(d, 0.2)
+    else:
+        pts = rng.uniform(-0.3, 0.3, (points, 3))
+        shape = W.metaball_shape(pts, rng.uniform(0.7, 1.3, points) * 0.9 / points, 0.2, d_eq=d,
+                                 samples_per_unit=2.0)
+    lat = W.LatticeSpec(max(9 * n, 20), 6, 30, (0, 0, 0))
+    k = np.arange(n)
+    pos = np.stack([np.where(k == 0, 2.5, 9.0 * k + 4.5), np.full(n, 2.5), np.full(n, 2.5)], -1)
+    pos += rng.uniform(-0.02, 0.02, (n, 3))
+    ps = W.make_particles([shape] * n, pos, np.array([W.random_quaternion(rng) for _ in range(n)]), 1.5,
+                          vel=rng.normal(size=(n, 3)) * 0.01, omega=rng.normal(size=(n, 3)) * 0.004)
+    kw = W.dem_defaults(ps, gravity=(0.0, 0.0, -2e-4))
+    gpu = B.Lattice(lat, n_particles=n, n_ctrl=len(ps.K), box_half=ps.box_half(), storage="f32")
+    dem, parts, P = O.OracleDEM(ps, lat), B.DeviceParticles(ps), ps.copy()
+    zero = np.zeros((n, 3))
+    for _ in range(3):
+        gpu.dem(parts, 10, 0.1, B.DemParams.make(**kw))
+        dem.step(P, zero, zero, O.DemParams(**kw), 10, 0.1)
+    gpu.sync()
+    G = parts.to_host(ps)
+    gpu.close()
+    assert (np.abs(P.vel - ps.vel)[:, 1:] > 1e-5).sum() >= n   # the walls acted
+    for key in ("pos", "vel", "omega", "quat", "world_pts"):
+        a, b = getattr(G, key), getattr(P, key)
+        assert np.abs(a - b).max() <= 1e-9 * max(1.0, np.abs(b).max()), key
+
+
 @pytest.mark.parametrize("n,spacing", [(2048, 3.0), (2050, 13.0), (16384, 3.0), (16385, 3.0)])
 def test_dem_cell_grids_match_the_oracle(n, spacing):
     """dem_step on the cell grid where its making moves from one workgroup to a
