@@ -312,7 +312,7 @@ hipError_t carve_fixed(lbm_ctx* c)
         put(c->dem_state, np * kDemStateDoubles);
         // counts and starts, cursors, the binned particles, the grid's shape
         put(c->grid, grid ? 2 * (size_t)c->grid_cap + 1 + np + 4 : 0);
-        put(c->grid_size, grid ? 4 : 0);
+        put(c->grid_size, grid ? 3 : 0);
     };
     carve();
     hipError_t e = hipMalloc(&c->slab, at);
@@ -496,8 +496,6 @@ int lbm_init(const lbm_config* cfg, const lbm_buffers* bufs, lbm_ctx** out)
     const int h = std::max(cfg->box_half, 2);
     c->box.h = h;
     c->box.S = 2 * h + 1;
-    c->box.vol = c->box.S * c->box.S * c->box.S;
-    c->box.tiles = (c->box.vol + 255) / 256;
     for (int i = 0; i < 2; ++i) {
         c->f[i] = c->fu[i] = bufs->f_dev[i];
         c->own[i] = bufs->owner_dev[i];

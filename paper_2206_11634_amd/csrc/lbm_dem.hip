@@ -944,7 +944,6 @@ __device__ __forceinline__ int grid_shape(const PartDev& P, const double* rch, d
             gdim[a] = nc[a];
             gsize[a] = (double)nc[a] / (double)g.n[a];
         }
-        gsize[3] = H;
         gdim[3] = (int32_t)total;
         ncell = (int)total;
     }

@@ -14,15 +14,16 @@
 
 namespace mdlbm {
 
-// Owner plane value of a fluid node (a solid node holds its particle index).
 // Largest per-particle box half-width h (the classification kernels keep a
 // table of the 2h + 1 rows of one box plane in LDS).
 constexpr int kMaxBoxHalf = 511;
+// Owner plane value of a fluid node (a solid node holds its particle index).
 constexpr uint32_t kFluid = 0xFFFFFFFFu;
-// Counters of one classification, in one device block mirrored by one pinned
-// host block so that a single copy reads them all: the refill count, the box
-// check, the non-finite force flag (one 128-byte line), then one line per
-// particle for its link count and one per particle for its candidate count.
+// Counters, in one device block mirrored by one pinned host block so that a
+// single copy reads them all: a head line of 128 bytes (the non-finite force
+// flag, the latched bits, the two sets that classifications count in), then
+// one line per particle for its link count and one per particle for its
+// candidate count.
 constexpr int kCtrNumeric = 2;
 // Latched by asynchronous classifications: the box check's bits (low byte)
 // and kDeferredOverflow when a list outgrew its capacity.
@@ -178,9 +179,9 @@ __device__ __forceinline__ void copy_segment(const CopySeg& g, uint64_t t, uint6
         g.dst[i] = g.src ? g.src[i] : (uint8_t)(g.word >> (8 * (i & 3)));
 }
 
-// Per-particle node box: origin (unwrapped) and edge S = 2h + 1.
+// Per-particle node box: half-width h and edge S = 2h + 1.
 struct BoxSpec {
-    int h, S, vol, tiles;  // tiles of 256 box cells
+    int h, S;
 };
 
 constexpr int kCursorPad = 32;  // one 128-byte line per per-particle counter
@@ -339,8 +340,7 @@ namespace q15 {
 // Launchers (lbm_dem.hip, lbm_dem_adjoint.hip)
 constexpr int kDemStateDoubles = 72;
 // Work space of one dem_step call: the candidate pairs (i, j, history slot),
-// their count, and each particle's reach and broad-phase bound.
-// The work space of one dem_step call.  With the cell grid (gcount not
+// their count, and each particle's reach and broad-phase bound.  With the cell grid (gcount not
 // null), the broad phase bins the particles into cells at least as wide as
 // the largest pair distance it can accept and tests each particle against
 // the 27 cells around its own, instead of all n^2 pairs.
@@ -354,7 +354,7 @@ struct DemScratch {
     uint32_t* gcursor = nullptr;  // [gcap]
     uint32_t* gitem = nullptr;    // [n]: particles by cell
     int32_t* gdim = nullptr;      // cells per axis, and their product
-    double* gsize = nullptr;      // cells per node, then H (the largest accepted distance)
+    double* gsize = nullptr;      // [3]: cells per node and axis
     int64_t gcap = 0;             // cells the arrays hold
 };
 // Most particles whose whole dem_step call runs in one workgroup: a lane of

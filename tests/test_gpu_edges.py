@@ -320,10 +320,6 @@ def test_link_adjoint_on_both_sides_of_the_wave_split():
         assert np.abs(a - b).max() <= 1e-12 * np.abs(a).max()
 
 
-# bodies, diameter, box, periodic axes: boxes below and above a wave of rows
-# with few planes (a workgroup each) and with many (a wave each), planes of more
-# segments and more candidates than are listed at a time, squares around the
-# ball of 1, 2 and 3 tiles
 @pytest.mark.parametrize("dims", [(84, 84, 83), (84, 84, 84), (133, 133, 133), (134, 133, 133)])
 def test_node_adjoint_at_the_cache_line_of_its_stores(dims):
     """Two FP64 adjoint fields and a taped level just below and above 2^28 and
@@ -338,6 +334,10 @@ def test_node_adjoint_at_the_cache_line_of_its_stores(dims):
     _replay_case(_Replay(lat, ps, 3), f0, 41, 1e-7)
 
 
+# bodies, diameter, box, periodic axes: boxes below and above a wave of rows
+# with few planes (a workgroup each) and with many (a wave each), planes of more
+# segments and more candidates than are listed at a time, squares around the
+# ball of 1, 2 and 3 tiles
 @pytest.mark.parametrize("n,d,dims,per,lattice",
                          [(1, 6.0, (33, 40, 35), (1, 1, 1), 15), (2, 29.0, (70, 64, 66), (0, 0, 0), 19),
                           (1, 31.6, (130, 64, 66), (1, 0, 0), 19), (1, 150.0, (160, 158, 156), (0, 0, 0), 19),
