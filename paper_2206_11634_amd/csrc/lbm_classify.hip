@@ -947,9 +947,9 @@ hipError_t launch_begin(lbm_ctx* c, const PartDev& P, int slot, int slot_prev, b
 
 // From 4096 planes a wave per plane fills the chip, and the preparation of a
 // plane is done by one wave, not four (200 bodies in 256^3: 12.4 us against 15.2,
-// 1000 in 512^3 with both kernels' other changes 317 against 354); below, four
-// waves share a plane's nodes (60 bodies: 8.9 us against 11.0, two 8.1 against
-// 11.6).  Boxes beyond 256 rows take four waves (a lane keeps four rows).
+// 1000 in 512^3 317 against 354, and 285 since the interior bound shares the
+// estimate's loop); below, four waves share a plane's nodes (60 bodies: 8.9 us
+// against 11.0, two 8.1 against 11.6).  Boxes beyond 256 rows take four waves (a lane keeps four rows).
 constexpr int64_t kWavePlanes = 4096;
 
 hipError_t launch_mark(lbm_ctx* c, uint32_t* own, const PartDev& P, int slot, bool inc)
